@@ -316,32 +316,36 @@ int pbit_profile_variant(pbit_ctx *ctx, int32_t *variant);
 int pbit_profile_graph(pbit_ctx *ctx, int64_t *captures, int64_t *launches);
 
 /* The cube path of the latest cube anneal on this context (0 before any): 1 = the
- * streaming stencil, one launch per half-sweep; 2 = the LDS-resident form, the
- * whole lattice of 16 replicas per workgroup for runs of sweeps, taken for
- * cubes of at most 8192 sites; 3 = the fields of 32 sites x 32 replicas as int8
- * MFMAs over blocks of neighbour sites, one launch per half-sweep, possible for
- * cubes whose colour classes split into tiles of 32 sites with at most 8
- * neighbour blocks each (every cube with Lx = 32, for one).  By default a cube of
- * more than 8192 and at most 2^21 sites that allows path 3 takes whichever of
- * paths 1 and 3 ran faster when the first anneal of that shape and replica count
- * (rounded up to 128) on this context timed four half-sweeps of each; without
- * allocation (pbit_anneal_dev_noalloc) there is no timing and path 3 is taken
- * for at most 1024 replicas.  When the context is created, PBIT_EA_STREAM=1
- * selects path 1 for every cube, PBIT_EA_MFMA=1 path 3 wherever it can run,
- * PBIT_EA_MFMA=0 never path 3 and a negative value keeps the default.  All give
- * the same spins.
+ * streaming stencil, one launch per half-sweep, or, for cubes of more than 8192
+ * sites with enough replicas, the same runs of sweeps in LDS as path 2 (the spins
+ * between launches are the stencil's rows); 2 = the LDS-resident form, the whole
+ * lattice of 4, 8 or 16 replicas per workgroup, one bit per spin, for runs of
+ * sweeps, taken for cubes of at most 8192 sites; 3 = the fields of 32 sites x 32
+ * replicas as int8 MFMAs over blocks of neighbour sites, one launch per half-sweep,
+ * possible for cubes whose colour classes split into tiles of 32 sites with at most
+ * 8 neighbour blocks each (every cube with Lx = 32, for one).  By default a cube of
+ * more than 8192 and at most 61 950 sites is held in LDS where that is faster by the
+ * measured costs of both forms; otherwise a cube of at most 2^21 sites that allows
+ * path 3 takes whichever of the stencil and path 3 ran faster when the first anneal
+ * of that shape and replica count (rounded up to 128) on this context timed four
+ * half-sweeps of each; without allocation (pbit_anneal_dev_noalloc) there is no
+ * timing and path 3 is taken for at most 1024 replicas.  When the context is
+ * created, PBIT_EA_STREAM=1 selects the stencil for every cube, PBIT_EA_MFMA=1 path 3
+ * wherever it can run, PBIT_EA_MFMA=0 never path 3 and a negative value keeps the
+ * default.  All give the same spins.
  * *path is written on success only. */
 int pbit_profile_ea_path(pbit_ctx *ctx, int32_t *path);
 
 /* The general-graph path of the latest graph anneal on this context (0 before
  * any): 1 = one launch per colour class (every site of the class, 16 replicas per
  * thread); 2 = the whole graph for a tile of 16, 8 or 4 replicas held in one
- * workgroup's LDS for runs of up to 1000 sweeps per launch, taken when the graph's
- * spins for 4 replicas fit (at most 39 936 spins), with the narrowest tile that
- * fits and leaves at most two workgroups per compute unit (else the widest that
- * fits).  When the context is created, PBIT_GRAPH_SLAB=0 keeps path 1 and
- * PBIT_GRAPH_SLAB=4, 8 or 16 forces that tile width where it fits.  Both paths give
- * the same spins.  *path is written on success only. */
+ * workgroup's LDS for runs of up to 1000 sweeps per launch, taken for graphs of at
+ * most 39 936 spins: as bits where every spin has at most 15 nonzero couplings and
+ * fields, with the tile width of least measured cost, else as bytes, with the
+ * narrowest tile that fits and leaves at most two workgroups per compute unit (else
+ * the widest that fits).  When the context is created, PBIT_GRAPH_SLAB=0 keeps path 1
+ * and PBIT_GRAPH_SLAB=4, 8 or 16 forces that tile width where it fits.  Both paths
+ * give the same spins.  *path is written on success only. */
 int pbit_profile_graph_path(pbit_ctx *ctx, int32_t *path);
 
 /* The ceilings the sweep kernels are measured against, each timed as a kernel of

@@ -25,10 +25,6 @@ struct EaView {
     const int8_t *J;       // [3][N] as given (for from-scratch energies)
     const int8_t *h;       // [N] or null
     bool dense;            // every coupling is nonzero
-    // for lattices the LDS-resident kernel takes: per colour c and class position j
-    // (x = 2 (j mod Lx/2) + parity, row j / (Lx/2)), the pair {site | wrap flags of
-    // the +x, -x, +y, -y, +z, -z neighbours << 16, site code}, [2][N / 2]; else null
-    const uint32_t *slab_sites;
     // the matrix-core half-sweep (ea_mfma.hip), where the cube's shape allows it: per
     // colour and tile of 32 class positions a 16-word record (first coupling fragment,
     // then the K block starts), per colour and position {site, 8 (h + sum J + 7)}, and
@@ -83,13 +79,9 @@ struct EaRow {
     uint64_t s[15];
 };
 EaRow ea_row(const uint32_t *host_trow, int width);
-// ny: lattice rows per workgroup (0 = choose); early_rng: draw the random words before the field
-// Sweeps [s_begin, s_end) of a cube of at most kEaSlabMaxSites sites held in LDS,
-// 16 replicas per workgroup; table row s is sweep s, its absolute index sweep0 + s.
+// cubes of at most this many sites run held in LDS (bits.h) whatever their replicas
 constexpr int kEaSlabMaxSites = 8192;
-bool ea_slab_fits(const EaView &p);
-hipError_t ea_slab(const EaView &p, int8_t *spins, int Rp, const uint32_t *table, int width, int s_begin, int s_end,
-                   uint32_t sweep0, uint32_t rq0, Key key, hipStream_t st);
+// ny: lattice rows per workgroup (0 = choose); early_rng: draw the random words before the field
 hipError_t ea_halfsweep(const EaView &p, int8_t *spins, int Rp, int colour, const EaRow &row, uint32_t sweep,
                         uint32_t rq0, Key key, hipStream_t st, int ny = 0, bool early_rng = true);
 hipError_t ea_energy(const EaView &p, const int8_t *spins, int Rp, int R, int32_t *E, hipStream_t st);

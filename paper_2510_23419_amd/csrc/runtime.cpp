@@ -21,6 +21,7 @@
 
 #include "../../include/pbit.h"
 #include "batch.h"
+#include "bits.h"
 #include "internal.h"
 #include "runtime_internal.h"
 
@@ -209,6 +210,20 @@ static int upload(pbit_ctx *ctx, Problem &p, const void *host, size_t bytes, voi
     return PBIT_OK;
 }
 
+// Records of the bit-held sweep (bits.h), where the problem can take it.
+static int upload_bits(pbit_ctx *ctx, Problem &p, const BitHost &b, const int8_t *dev_h)
+{
+    void *dg = nullptr, *dr = nullptr, *dw = nullptr, *dp = nullptr;
+    int rc = upload(ctx, p, b.groups.data(), sizeof(int32_t) * b.groups.size(), &dg);
+    if (rc == PBIT_OK) rc = upload(ctx, p, b.rec.data(), sizeof(uint32_t) * b.rec.size(), &dr);
+    if (rc == PBIT_OK && !b.wide.empty()) rc = upload(ctx, p, b.wide.data(), sizeof(uint32_t) * b.wide.size(), &dw);
+    if (rc == PBIT_OK) rc = upload(ctx, p, b.pos_site.data(), sizeof(uint16_t) * b.pos_site.size(), &dp);
+    if (rc != PBIT_OK) return rc;
+    p.bits = BitView{b.form, b.n, b.n_pos, b.n_groups, b.n_pairs, b.n_wide, b.max_pairs, (const int4 *)dg,
+                     (const uint4 *)dr, (const uint4 *)dw, (const uint16_t *)dp, dev_h};
+    return PBIT_OK;
+}
+
 static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
 {
     const int Lx = d->dims[0], Ly = d->dims[1], Lz = d->dims[2];
@@ -253,10 +268,10 @@ static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
     int rc = upload(ctx, p, code.data(), sizeof(uint32_t) * (size_t)N, &dc);
     if (rc == PBIT_OK) rc = upload(ctx, p, d->J, (size_t)(3 * N), &dJ);
     if (rc == PBIT_OK && d->h) rc = upload(ctx, p, d->h, (size_t)N, &dh);
-    EaView v{Lx, Ly, Lz, N, (const uint32_t *)dc, (const int8_t *)dJ, (const int8_t *)dh, dense, nullptr,
+    EaView v{Lx, Ly, Lz, N, (const uint32_t *)dc, (const int8_t *)dJ, (const int8_t *)dh, dense,
              nullptr, nullptr, nullptr, 0, 0};
     if (rc == PBIT_OK && N < 65536) {
-        // the LDS-resident kernels' site list: class position -> site, wrap flags, code
+        // the batched tiles' site list: class position -> site, wrap flags, code
         const int64_t half = N / 2, hx = Lx / 2;
         std::vector<uint32_t> sites((size_t)4 * half);
         for (int c = 0; c < 2; ++c)
@@ -272,7 +287,29 @@ static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
             }
         rc = upload(ctx, p, sites.data(), sizeof(uint32_t) * sites.size(), &ds);
         p.tile_sites = (const uint32_t *)ds;
-        if (ea_slab_fits(v)) v.slab_sites = (const uint32_t *)ds;
+    }
+    BitHost bits;
+    if (rc == PBIT_OK && N <= kBitMaxPositions) {
+        std::vector<int32_t> start((size_t)N + 1), nbr((size_t)6 * N);
+        std::vector<int8_t> Jn((size_t)6 * N);
+        std::vector<uint8_t> colour((size_t)N);
+        for (int z = 0, i = 0; z < Lz; ++z)
+            for (int y = 0; y < Ly; ++y)
+                for (int x = 0; x < Lx; ++x, ++i) {
+                    const int xp = x + 1 == Lx ? i + 1 - Lx : i + 1, xm = x == 0 ? i - 1 + Lx : i - 1;
+                    const int yp = y + 1 == Ly ? i + Lx - (int)plane : i + Lx, ym = y == 0 ? i - Lx + (int)plane : i - Lx;
+                    const int zp = z + 1 == Lz ? i + (int)(plane - N) : i + (int)plane;
+                    const int zm = z == 0 ? i + (int)(N - plane) : i - (int)plane;
+                    const int nb6[6] = {xp, xm, yp, ym, zp, zm};
+                    const int8_t J6[6] = {d->J[i], d->J[xm], d->J[N + i], d->J[N + ym], d->J[2 * N + i], d->J[2 * N + zm]};
+                    start[i] = 6 * i;
+                    std::copy(nb6, nb6 + 6, &nbr[(size_t)6 * i]);
+                    std::copy(J6, J6 + 6, &Jn[(size_t)6 * i]);
+                    colour[i] = (uint8_t)((x + y + z) & 1);
+                }
+        start[(size_t)N] = (int32_t)(6 * N);
+        if (bit_build((int)N, start.data(), nbr.data(), Jn.data(), d->h, colour.data(), 2, Lx, bits))
+            rc = upload_bits(ctx, p, bits, (const int8_t *)dh);
     }
     // the matrix-core half-sweep's tiles (about 24 bytes per site), where the shape
     // allows them and the path may run: every cube with PBIT_EA_MFMA=1; by default the
@@ -483,6 +520,16 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
         meta[(size_t)4 * j + 3] = base[i];
     }
 
+    std::vector<int32_t> nbr(word.size());
+    std::vector<int8_t> Jn(word.size());
+    for (size_t e = 0; e < word.size(); ++e) {
+        nbr[e] = (int32_t)(word[e] >> 2);
+        Jn[e] = (int8_t)((word[e] & 1u) ? ((word[e] & 2u) ? -1 : 1) : 0);
+    }
+    BitHost bits;
+    const bool bits_ok = n <= kBitMaxPositions &&
+                         bit_build(n, start.data(), nbr.data(), Jn.data(), d->h, p.colour.data(), ncol, 0, bits);
+
     void *dmeta = nullptr, *dadj = nullptr, *dbi = nullptr, *dbj = nullptr, *dbJ = nullptr, *dh = nullptr;
     int rc = upload(ctx, p, meta.data(), sizeof(int32_t) * meta.size(), &dmeta);
     if (rc == PBIT_OK && nb > 0) rc = upload(ctx, p, adj.data(), sizeof(uint32_t) * adj.size(), &dadj);
@@ -492,6 +539,7 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
     if (rc == PBIT_OK && d->h) rc = upload(ctx, p, d->h, (size_t)n, &dh);
     void *dcs = nullptr;
     if (rc == PBIT_OK) rc = upload(ctx, p, p.class_start.data(), sizeof(int32_t) * p.class_start.size(), &dcs);
+    if (rc == PBIT_OK && bits_ok) rc = upload_bits(ctx, p, bits, (const int8_t *)dh);
     if (rc != PBIT_OK) return rc;
     p.kind = PBIT_GRAPH;
     p.N = n;
@@ -500,7 +548,7 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
                         (const int32_t *)dbi, (const int32_t *)dbj, (const int8_t *)dbJ, (const int8_t *)dh,
                         (const int32_t *)dcs};
     // the cube's layout kernels (init, transposes) are reused with N = n
-    p.ea = EaView{0, 0, 0, (int64_t)n, nullptr, nullptr, nullptr, false, nullptr, nullptr, nullptr, nullptr, 0, 0};
+    p.ea = EaView{0, 0, 0, (int64_t)n, nullptr, nullptr, nullptr, false, nullptr, nullptr, nullptr, 0, 0};
     return PBIT_OK;
 }
 
@@ -653,7 +701,8 @@ struct DevState {
     int bits_rt = 0;  // replicas per tile of the bit kernel (0: its launcher's rule)
     int slab_rs = 0;  // replicas per slice of the LDS-resident biclique kernel (0: its launcher's rule)
     bool slab = false;        // cube, graph or small biclique held in LDS for runs of sweeps
-    int graph_rs = 0;         // replicas per workgroup of the LDS-resident graph sweep (graph_slab)
+    int tile_rs = 0;          // replicas per workgroup of the LDS-resident cube and graph sweeps
+    bool bit_tiles = false;   // they hold the spins as bits (bits.h)
     int32_t *graph_energy = nullptr;  // its per-replica energies (not used by the runtime)
     bool mfma = false;        // cube fields on the matrix cores (ea_mfma.hip), spins [2][Rp][N / 2]
     Arena *arena = nullptr;   // set: buffers are carved from it (no allocation, no kernel timing)
@@ -845,6 +894,44 @@ static int tune_cube(pbit_ctx *ctx, const Problem &P, int R, int8_t *spins, hipS
     return PBIT_OK;
 }
 
+static int compute_units(const pbit_ctx *ctx)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) cus = 256;
+    return cus;
+}
+
+// Microseconds per sweep of the bit-held tiles, up to a common factor of the rounds the
+// device needs for them: measured 0.58 ns per site and tile of 4 replicas (0.70 with
+// fields or zero couplings), 1.6 and 2.7 times that with 8 and 16, at 12^3 to 36^3.
+static double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
+{
+    const int tiles = Rp / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
+    const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
+    return ((tiles + slots - 1) / slots) * c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N;
+}
+
+// Replicas per tile: the width whose rounds cost least (the narrowest among equals, which
+// spreads few replicas over the most compute units).
+static int bit_pick_rs(const Problem &P, int Rp, int cus)
+{
+    int best = 4;
+    for (int rs : {8, 16})
+        if (bit_sweep_us(P, Rp, rs, cus) < bit_sweep_us(P, Rp, best, cus)) best = rs;
+    return best;
+}
+
+// Cubes too large for the tiles to win at any replica count: the faster of the two
+// one-launch-per-half-sweep kernels takes about 8 us + 0.5 ps per spin and sweep at least
+// (measured 24^3 to 36^3, 64 to 4096 replicas: 8.0 to 101 us), against which the tiles'
+// time is set.  At 32^3 the line lies between 512 replicas (17.2 against 18.8 us per
+// sweep in tiles) and 1024 (27.8 against 19.2).
+static bool bits_preferred(const Problem &P, int R, int cus)
+{
+    const int Rp = round_up(R, kEaRPad);
+    return bit_sweep_us(P, Rp, bit_pick_rs(P, Rp, cus), cus) < 8.0 + 0.5e-6 * (double)P.N * R;
+}
+
 static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, hipStream_t st, DevState &ds,
                    const void *dev_init)
 {
@@ -858,15 +945,18 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
             return fail(PBIT_E_UNSUPPORTED, "%lld spins x %d replicas exceed 4 GiB of int8 spins",
                         (long long)P.N, R);
         // cube paths: PBIT_EA_STREAM=1 takes the stencil; PBIT_EA_MFMA=1 the matrix cores
-        // wherever built; by default cubes that fit LDS stay there, and for larger ones
-        // the stencil and the matrix cores (where built) are timed against each other
-        // (PBIT_EA_MFMA=0: the stencil)
+        // wherever built; by default cubes of at most kEaSlabMaxSites sites, and larger ones
+        // with enough replicas, stay in LDS as bits, and for the others the stencil and the
+        // matrix cores (where built) are timed against each other (PBIT_EA_MFMA=0: the stencil)
         const bool cube = P.kind == PBIT_EA3D, tiles = cube && P.ea.mfma_tiles;
         bool tune = false;
         if (cube && !ctx->ea_stream_forced) {
             ds.mfma = tiles && ctx->ea_mfma == 1;
-            ds.slab = !ds.mfma && P.ea.slab_sites;
-            tune = !ds.mfma && !ds.slab && tiles && ctx->ea_mfma != 0 && d->n_sweeps > 0;
+            // (without allocation, large cubes keep the matrix cores at up to 1024 replicas)
+            ds.bit_tiles = !ds.mfma && P.bits.n_pos &&
+                           (P.N <= kEaSlabMaxSites || (!(ds.arena && tiles && R <= 1024) &&
+                                                       bits_preferred(P, R, compute_units(ctx))));
+            tune = !ds.mfma && !ds.bit_tiles && tiles && ctx->ea_mfma != 0 && d->n_sweeps > 0;
         }
         // the tuner times both layouts in one buffer: spins for replicas padded to 128
         ds.Rp = round_up(R, ds.mfma || tune ? kEaMfmaRPad : kEaRPad);
@@ -904,27 +994,36 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
             if (e != hipSuccess) return device_fail(ctx, e, "spin bit buffer clear");
         }
     }
-    if (P.kind == PBIT_GRAPH && ctx->graph_slab) {
-        // the whole graph for a tile of replicas in LDS, runs of sweeps per launch: the
-        // narrowest tile (4, 8 or 16 replicas) that fits and leaves at most two workgroups
-        // per compute unit, else the widest that fits.  Measured on the L = 14 dimerized
-        // cube: a workgroup's sweep costs about the same at any tile width up to two per
-        // CU, so narrow tiles spread small replica counts over more CUs, and past two per
-        // CU the wider tile wins.
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) cus = 256;
-        for (int rs : {4, 8, 16}) {
-            if (ds.Rp % rs != 0 || graph_tile_lds(P.N, rs) > kGraphSlabLds) continue;
-            if (ctx->graph_slab_rs && rs != ctx->graph_slab_rs) continue;
-            ds.graph_rs = rs;
-            if (ds.Rp / rs <= 2 * cus) break;
+    if (P.kind == PBIT_GRAPH && ctx->graph_slab && graph_tile_lds(P.N, 4) <= kGraphSlabLds) {
+        // the whole graph for a tile of replicas in LDS, runs of sweeps per launch
+        ds.bit_tiles = P.bits.n_pos > 0;
+        ds.slab = true;
+        if (!ds.bit_tiles) {
+            // bytes, for graphs with sites of more terms than the bit records hold: the
+            // narrowest tile (4, 8 or 16 replicas) that fits and leaves at most two
+            // workgroups per compute unit, else the widest that fits.  A workgroup's sweep
+            // costs about the same at any tile width up to two per CU, so narrow tiles
+            // spread small replica counts over more CUs, and past two per CU the wider
+            // tile wins.
+            const int cus = compute_units(ctx);
+            for (int rs : {4, 8, 16}) {
+                if (ds.Rp % rs != 0 || graph_tile_lds(P.N, rs) > kGraphSlabLds) continue;
+                if (ctx->graph_slab_rs && rs != ctx->graph_slab_rs) continue;
+                ds.tile_rs = rs;
+                if (ds.Rp / rs <= 2 * cus) break;
+            }
+            if (ds.tile_rs) {
+                rc = take(ctx, ds, Slot::Aux, sizeof(int32_t) * (size_t)ds.Rp, &v);
+                if (rc) return rc;
+                ds.graph_energy = (int32_t *)v;
+            }
+            ds.slab = ds.tile_rs != 0;
         }
-        if (ds.graph_rs) {
-            rc = take(ctx, ds, Slot::Aux, sizeof(int32_t) * (size_t)ds.Rp, &v);
-            if (rc) return rc;
-            ds.graph_energy = (int32_t *)v;
-            ds.slab = true;
-        }
+    }
+    if (ds.bit_tiles) {
+        ds.slab = true;
+        ds.tile_rs = P.kind == PBIT_GRAPH && ctx->graph_slab_rs ? ctx->graph_slab_rs
+                                                                : bit_pick_rs(P, ds.Rp, compute_units(ctx));
     }
     rc = take(ctx, ds, Slot::E32, sizeof(int32_t) * (size_t)ds.Rp, &v);
     if (rc) return rc;
@@ -951,7 +1050,8 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     }
     ds.bits = P.kind == PBIT_BICLIQUE && ds.variant == BqVariant::Bits;
     if (P.kind == PBIT_BICLIQUE && ds.variant == BqVariant::Slab) ds.slab = true;  // runs of sweeps per launch
-    if (P.kind == PBIT_EA3D && d->n_sweeps > 0) ctx->ea_last_path = ds.slab ? 2 : (ds.mfma ? 3 : 1);
+    if (P.kind == PBIT_EA3D && d->n_sweeps > 0)
+        ctx->ea_last_path = ds.slab && P.N <= kEaSlabMaxSites ? 2 : (ds.mfma ? 3 : 1);
     if (P.kind == PBIT_GRAPH && d->n_sweeps > 0) ctx->graph_last_path = ds.slab ? 2 : 1;
     if (P.kind == PBIT_BICLIQUE && d->n_sweeps > 0) ctx->bq_last_variant = (int)ds.variant;
 
@@ -1026,15 +1126,16 @@ static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, 
     if (e == hipSuccess) {
         if (P.kind == PBIT_BICLIQUE) {
             e = bq_slab(P.bq, ds.MA, ds.MB, ds.Rp, ds.table, ds.width, s0, s1, sweep0, rq0, key, st, ds.slab_rs);
-        } else if (P.kind == PBIT_GRAPH) {
+        } else if (ds.bit_tiles) {
+            BitJobDev jb{P.bits, ds.table, ds.spins, nullptr, ds.width, ds.tile_rs, ds.Rp, sweep0, rq0, key.k0, key.k1};
+            e = bit_slab(jb, ds.Rp / ds.tile_rs, s0, s1, st);
+        } else {
             const GraphView &g = P.graph;
             GraphJobDev jb{reinterpret_cast<const int4 *>(g.site_meta), g.adj, g.class_start_dev, g.bi, g.bj, g.bJ,
                            g.h, ds.table, ds.spins, ds.graph_energy, g.n, g.n_bonds, g.n_colours, ds.width,
-                           ds.graph_rs, sweep0, rq0, key.k0, key.k1};
+                           ds.tile_rs, sweep0, rq0, key.k0, key.k1};
             jb.row_stride = ds.Rp;
-            e = graph_slab(jb, ds.Rp / ds.graph_rs, s0, s1, st);
-        } else {
-            e = ea_slab(P.ea, ds.spins, ds.Rp, ds.table, ds.width, s0, s1, sweep0, rq0, key, st);
+            e = graph_slab(jb, ds.Rp / ds.tile_rs, s0, s1, st);
         }
     }
     if (e == hipSuccess && timed) {

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/pbit.h"
+#include "bits.h"
 #include "bq.h"
 #include "host.h"
 
@@ -21,6 +22,7 @@ struct Problem {
     EaView ea{};
     BqView bq{};
     GraphView graph{};
+    BitView bits{};  // n_pos = 0: the problem cannot take the bit-held sweep
     const uint32_t *tile_sites = nullptr;  // cube site list for the batched tiles (N < 65536), else null
     std::vector<int32_t> class_start;  // host copy behind graph.class_start
     std::vector<uint8_t> colour;       // colouring used (graph problems)

@@ -1,0 +1,115 @@
+"""The bit-held sweep on the GPU against the oracle, bit-exact, at the edges of its
+dispatch: every record form, tile width (4, 8 and 16 replicas) and unit of work
+(pairs, positions, four replicas of a position), groups that do not fill a wave,
+sites of 8 to 15 terms, runs across the threshold-row boundaries, saturated
+thresholds, and cubes of more than 8192 sites."""
+import os
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import oracle
+from paper_2510_23419_amd import pbit
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", params=["4", "8", "16"])
+def width_ctx(request):
+    old = os.environ.get("PBIT_GRAPH_SLAB")
+    os.environ["PBIT_GRAPH_SLAB"] = request.param
+    try:
+        c = pbit.Context(0)
+    finally:
+        if old is None:
+            del os.environ["PBIT_GRAPH_SLAB"]
+        else:
+            os.environ["PBIT_GRAPH_SLAB"] = old
+    yield c.ctx
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = pbit.Context(0)
+    yield c.ctx
+    c.close()
+
+
+def _graph(inst):
+    if inst["kind"] == "ea3d":
+        return oracle.ea_graph(inst["dims"], inst["J"], inst["h"])
+    return oracle.graph_from_bonds(inst["n"], inst["bond_i"], inst["bond_j"], inst["bond_J"], inst.get("h"))
+
+
+def _sampled(ctx, inst, beta, R, seed, **kw):
+    """Spins and energies of the first, a middle and the last replica group."""
+    prob = pbit.load_instance(ctx, inst)
+    print("bits", inst["kind"], inst.get("dims", inst.get("n")), "R", R, "S", len(beta), flush=True)
+    got = pbit.pbit_anneal(ctx, prob, beta, R, seed, **kw)
+    pbit.pbit_unload_problem(ctx, prob)
+    g = _graph(inst)
+    for q in sorted({0, (R // 4) // 2, (R - 1) // 4}):
+        cnt = min(4, R - 4 * q)
+        ref = oracle.anneal(g, beta, cnt, seed, replica_offset=4 * q)
+        assert np.array_equal(got.spins[4 * q:4 * q + cnt], ref.spins), q
+        assert np.array_equal(got.energies[4 * q:4 * q + cnt], ref.energies), q
+
+
+# tiles of 16, 8 and 4 replicas by the rule's choice at 4096, 2048 and 1024; pairs at 16^3, positions
+# at 10^3 and 6^3; the aligned and the unaligned form, and the general one
+@pytest.mark.parametrize("dims,R", [((16, 16, 16), 4096), ((16, 16, 16), 2048), ((16, 16, 16), 1024), ((10, 10, 10), 4096),
+                                    ((10, 10, 10), 2052), ((6, 6, 6), 4096), ((6, 4, 2), 8200), ((4, 4, 2), 20)])
+@pytest.mark.parametrize("field", ["zero", "uniform3"])
+def test_cubes(ctx, dims, R, field):
+    inst = synth.ea_instance(dims, seed=R, field=field)
+    _sampled(ctx, inst, synth.beta_geometric(0.1, 5.0, 70), R, 5)
+
+
+@pytest.mark.parametrize("S", [1, 2, 15, 16, 17, 31, 32, 33, 49])
+def test_threshold_row_runs(ctx, S):
+    inst = synth.ea_instance((8, 6, 4), seed=S, field="uniform3")
+    _sampled(ctx, inst, synth.beta_linear(0.2, 4.0, S), 10, 8, sweep_offset=0)
+
+
+# betas at which |I| >= 6, 4, 2 (and, with fields, odd ones) have zero thresholds
+@pytest.mark.parametrize("betas", [[1.9, 1.95, 2.9, 3.9], [5.8, 11.5, 2.3, 1.91, 0.0]])
+@pytest.mark.parametrize("field", ["zero", "uniform3"])
+def test_saturated_thresholds(ctx, betas, field):
+    inst = synth.ea_instance((8, 8, 8), seed=7, field=field)
+    _sampled(ctx, inst, np.array(betas * 6), 24, 3)
+
+
+def _hub_graph(n, degrees, seed):
+    rng = np.random.default_rng(seed)
+    pairs = set()
+    for a, t in enumerate(degrees):
+        for b in rng.choice(np.arange(len(degrees), n), size=t, replace=False):
+            pairs.add((a, int(b)))
+    for _ in range(n):
+        a, b = rng.integers(len(degrees), n, 2)
+        if a != b:
+            pairs.add((int(min(a, b)), int(max(a, b))))
+    pairs = sorted(pairs)
+    J = np.where(rng.random(len(pairs)) < 0.5, 1, -1).astype(np.int8)
+    return {"kind": "graph", "n": n, "bond_i": np.array([p[0] for p in pairs], np.int32),
+            "bond_j": np.array([p[1] for p in pairs], np.int32), "bond_J": J,
+            "h": rng.integers(-1, 2, size=n).astype(np.int8)}
+
+
+@pytest.mark.parametrize("n,degrees", [(3, [2]), (70, [14, 8, 7]), (400, [8] * 33), (3000, [14, 9] * 20), (600, [20])])
+@pytest.mark.parametrize("R", [1, 37])
+def test_graphs_at_each_width(width_ctx, n, degrees, R):
+    """Wide pairs (none, some, an odd number), one site per group, groups beyond one
+    workgroup's threads, and a degree past the records' 15 (byte tiles)."""
+    _sampled(width_ctx, _hub_graph(n, degrees, seed=n), synth.beta_geometric(0.1, 4.0, 40), R, 9)
+    assert pbit.pbit_profile_graph_path(width_ctx) == 2
+
+
+@pytest.mark.parametrize("dims,R", [((22, 22, 22), 16), ((24, 24, 24), 1024), ((32, 32, 32), 1024), ((32, 32, 32), 2048),
+                                    ((32, 32, 30), 4096)])
+def test_large_cubes(ctx, dims, R):
+    field = "uniform3" if dims[2] == 30 else "zero"
+    _sampled(ctx, synth.ea_instance(dims, seed=R, field=field), synth.beta_geometric(0.1, 5.0, 20), R, 2)
+    assert pbit.pbit_profile_ea_path(ctx) == 1
