@@ -1,7 +1,7 @@
 // batch.h — device descriptors of the persistent batched sweep (many jobs in
 // one launch).  A job is one anneal (problem, schedule, replicas, seed).  It is
-// cut into replica tiles that never need each other: a cube tile is 4, 8 or 16
-// replicas of the whole lattice, a biclique tile is 32, 64 or 128 replicas of
+// cut into replica tiles that never need each other: a cube or graph tile is 4, 8 or 16
+// replicas of every site, a biclique tile is 32, 64 or 128 replicas of
 // both sides.
 // A work item advances one tile over a range of sweeps; a persistent kernel
 // pulls items from a queue until the queue is empty.
@@ -10,20 +10,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace pbit {
+#include "bits.h"
 
-struct EaJobDev {
-    const uint2 *sites;     // [2][N / 2] class position -> {site | wrap flags << 16, code}
-    const uint32_t *table;  // [S][width] thresholds, row s = local sweep s
-    int8_t *state;          // [tiles][N][rs]: spins of a tile, replica fastest (rs = 4, 8 or 16)
-    int32_t *energy;        // [tiles * rs]: energies after the tile's last item
-    int Lx, Ly, Lz, width;
-    int rs;                 // replicas per tile: 4, 8 or 16
-    int dense;              // 1: every coupling is nonzero
-    uint32_t sweep0;        // absolute index of local sweep 0
-    uint32_t rq0;           // global replica group of tile 0 (replica_offset / 4)
-    uint32_t k0, k1;        // Philox key
-};
+namespace pbit {
 
 struct BqJobDev {
     const int8_t *J, *JT;     // int8 couplings [na_p][nb_p], [nb_p][na_p]
@@ -65,18 +54,14 @@ struct WorkItem {
     int32_t pad[3];
 };
 
-constexpr int kEaTileThreads = 512;
-// cube tiles with more than this many bytes of LDS rows run one workgroup per CU, as
-// kEaTileThreadsLarge threads (ea_tiles picks the form from the launch's LDS bytes)
-constexpr int kEaTileThreadsLarge = 1024;
-constexpr size_t kEaLargeTileLds = 80 * 1024;
 constexpr int kGraphTileThreads = 512;
 constexpr int kBqTileThreads = 512;
 
 // Launch a persistent kernel over `n_items` items; `counter` (device int,
 // zeroed by the caller) hands out item indices.
-hipError_t ea_tiles(const EaJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter,
-                    int grid, size_t lds_bytes, hipStream_t st);
+// Cube and graph tiles with their spins as bits: threads 256, 512 or 1024 per workgroup.
+hipError_t bit_tiles(const BitJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter,
+                     int grid, int threads, size_t lds_bytes, hipStream_t st);
 // operand modes of the biclique tiles
 constexpr int kTileInt8 = 0, kTileBits = 2;
 hipError_t bq_tiles(const BqJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter,
@@ -90,9 +75,9 @@ hipError_t graph_tiles(const GraphJobDev *jobs, const WorkItem *items, const int
 hipError_t graph_slab(const GraphJobDev &jb, int tiles, int s_begin, int s_end, hipStream_t st);
 
 // LDS a tile kernel needs for the given job shape.
-size_t ea_tile_lds(int64_t N, int rs);  // rs = 4, 8 or 16 replicas
-size_t graph_tile_lds(int64_t N, int rs);
+size_t graph_tile_lds(int64_t N, int rs);  // byte rows, rs = 4, 8 or 16 replicas
 size_t bq_tile_lds(int rs, int na_p, int nb_p, int width, int mode);
 hipError_t tiles_set_lds_limit();
+hipError_t bit_tiles_set_lds_limit();
 
 }  // namespace pbit

@@ -108,6 +108,13 @@ __device__ __forceinline__ void lds_put(uint32_t a, T v)
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// A load from memory that no kernel writes, at a wave-uniform address: a scalar load.
+template <typename T>
+__device__ __forceinline__ T load_const(const void *p)
+{
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
 // 16-bit half of x, times two: the byte address of an element index.
 __device__ __forceinline__ uint32_t addr_lo(uint32_t x)
 {
@@ -520,7 +527,10 @@ __device__ __forceinline__ void run(const BitJobDev &jb, int tile, int s_begin, 
     };
 
     const int G = TWO ? 2 : v.n_groups;
-    auto group = [&](int c) { return v.groups[c < G ? c : c - G]; };
+    auto group = [&](int c) {
+        const u32x4 g = load_const<u32x4>(v.groups + (c < G ? c : c - G));
+        return make_int4((int)g.x, (int)g.y, (int)g.z, (int)g.w);
+    };
     auto pair_of = [&](Unit u, int j) { return u == kPair ? j : u == kSite ? j >> 1 : j / (2 * RQ); };
     auto units_of = [&](Unit u, const int4 &g) { return g.w * (u == kPair ? 1 : u == kSite ? 2 : 2 * RQ); };
     // record of unit j of a group, its position selected
@@ -534,7 +544,7 @@ __device__ __forceinline__ void run(const BitJobDev &jb, int tile, int s_begin, 
         if (tid < units_of(u, g)) fetch_rec(u, g, tid, r);
     };
     Rec<FORM> keep[TWO ? 2 : 1];  // the first record of each group, or of the next group
-    int4 ga = group(0), gb = group(1);
+    int4 ga = group(0), gb = group(G > 1 ? 1 : 0);
     first(ga, keep[0]);
     if constexpr (TWO) {
         first(gb, keep[1]);

@@ -264,30 +264,12 @@ static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
                 code[(size_t)i] = c;
                 amax = std::max(amax, nnz + std::abs(hv));
             }
-    void *dc = nullptr, *dJ = nullptr, *dh = nullptr, *ds = nullptr;
+    void *dc = nullptr, *dJ = nullptr, *dh = nullptr;
     int rc = upload(ctx, p, code.data(), sizeof(uint32_t) * (size_t)N, &dc);
     if (rc == PBIT_OK) rc = upload(ctx, p, d->J, (size_t)(3 * N), &dJ);
     if (rc == PBIT_OK && d->h) rc = upload(ctx, p, d->h, (size_t)N, &dh);
     EaView v{Lx, Ly, Lz, N, (const uint32_t *)dc, (const int8_t *)dJ, (const int8_t *)dh, dense,
              nullptr, nullptr, nullptr, 0, 0};
-    if (rc == PBIT_OK && N < 65536) {
-        // the batched tiles' site list: class position -> site, wrap flags, code
-        const int64_t half = N / 2, hx = Lx / 2;
-        std::vector<uint32_t> sites((size_t)4 * half);
-        for (int c = 0; c < 2; ++c)
-            for (int64_t j = 0; j < half; ++j) {
-                const int kx = (int)(j % hx), row = (int)(j / hx);
-                const int y = row % Ly, z = row / Ly;
-                const int x = 2 * kx + ((c + y + z) & 1);
-                const int64_t i = x + (int64_t)Lx * y + plane * z;
-                const uint32_t wrap = (x + 1 == Lx ? 1u : 0u) | (x == 0 ? 2u : 0u) | (y + 1 == Ly ? 4u : 0u) |
-                                      (y == 0 ? 8u : 0u) | (z + 1 == Lz ? 16u : 0u) | (z == 0 ? 32u : 0u);
-                sites[(size_t)2 * (c * half + j)] = (uint32_t)i | wrap << 16;
-                sites[(size_t)2 * (c * half + j) + 1] = code[(size_t)i];
-            }
-        rc = upload(ctx, p, sites.data(), sizeof(uint32_t) * sites.size(), &ds);
-        p.tile_sites = (const uint32_t *)ds;
-    }
     BitHost bits;
     if (rc == PBIT_OK && N <= kBitMaxPositions) {
         std::vector<int32_t> start((size_t)N + 1), nbr((size_t)6 * N);
@@ -894,7 +876,7 @@ static int tune_cube(pbit_ctx *ctx, const Problem &P, int R, int8_t *spins, hipS
     return PBIT_OK;
 }
 
-static int compute_units(const pbit_ctx *ctx)
+int compute_units(const pbit_ctx *ctx)
 {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) cus = 256;
@@ -904,16 +886,16 @@ static int compute_units(const pbit_ctx *ctx)
 // Microseconds per sweep of the bit-held tiles, up to a common factor of the rounds the
 // device needs for them: measured 0.58 ns per site and tile of 4 replicas (0.70 with
 // fields or zero couplings), 1.6 and 2.7 times that with 8 and 16, at 12^3 to 36^3.
-static double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
+double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
 {
-    const int tiles = Rp / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
+    const int tiles = (Rp + rs - 1) / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
     const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
     return ((tiles + slots - 1) / slots) * c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N;
 }
 
 // Replicas per tile: the width whose rounds cost least (the narrowest among equals, which
 // spreads few replicas over the most compute units).
-static int bit_pick_rs(const Problem &P, int Rp, int cus)
+int bit_pick_rs(const Problem &P, int Rp, int cus)
 {
     int best = 4;
     for (int rs : {8, 16})

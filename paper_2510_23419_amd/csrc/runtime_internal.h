@@ -23,7 +23,6 @@ struct Problem {
     BqView bq{};
     GraphView graph{};
     BitView bits{};  // n_pos = 0: the problem cannot take the bit-held sweep
-    const uint32_t *tile_sites = nullptr;  // cube site list for the batched tiles (N < 65536), else null
     std::vector<int32_t> class_start;  // host copy behind graph.class_start
     std::vector<uint8_t> colour;       // colouring used (graph problems)
     std::vector<void *> allocs;
@@ -115,6 +114,9 @@ int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_
                int64_t *d_energies, hipStream_t st, Arena *arena);
 size_t anneal_dev_bytes(const pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d);
 int noalloc_setup(int device);
+int compute_units(const pbit_ctx *ctx);
+double bit_sweep_us(const Problem &P, int Rp, int rs, int cus);
+int bit_pick_rs(const Problem &P, int Rp, int cus);
 
 }  // namespace pbit
 

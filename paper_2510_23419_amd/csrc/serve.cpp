@@ -35,14 +35,16 @@ int spins_in_range(const int8_t *s, size_t n);  // runtime.cpp
 namespace {
 
 constexpr int kMaxLdsTile = 160 * 1024 - 4096;
-// tile kinds, one persistent launch and one stream each: cube tiles (4, 8 or 16
-// replicas, one launch); 128-, 64- and 32-replica biclique tiles; general-graph
-// tiles (4, 8 or 16 replicas, one launch); cube tiles whose rows need more than
-// kEaLargeTileLds of LDS (one workgroup per CU, launched with more threads; apart
-// from the small ones, whose launch then keeps several workgroups per CU)
-constexpr int kKinds = 6;
-constexpr int kGraphKind = 4;
-constexpr int kCubeLargeKind = 5;
+constexpr int64_t kMaxTileSites = kMaxLdsTile / 4;  // largest cube or graph of a batched job
+// tile kinds, one persistent launch and one stream each: cube and graph tiles held as bits,
+// by threads per workgroup (256, 512, 1024: four, two and one workgroups per CU); 128-, 64-
+// and 32-replica biclique tiles; graph tiles in bytes (sites of more terms than the bit
+// records hold)
+constexpr int kKinds = 7;
+constexpr int kBitKind256 = 0, kGraphKind = 4, kBitKind1024 = 5, kBitKind512 = 6;
+inline int kind_of_threads(int t) { return t == 256 ? kBitKind256 : t == 512 ? kBitKind512 : kBitKind1024; }
+inline int threads_of_kind(int k) { return k == kBitKind256 ? 256 : k == kBitKind512 ? 512 : 1024; }
+inline bool bit_kind(int k) { return k == kBitKind256 || k == kBitKind512 || k == kBitKind1024; }
 inline int kind_of_rs(int rs) { return rs == 128 ? 1 : (rs == 64 ? 2 : 3); }
 constexpr double kItemOps = 1.5e11;  // multiply-adds of one biclique tile over its anneal
 inline int rs_of_kind(int k) { return k == 1 ? 128 : (k == 2 ? 64 : 32); }
@@ -58,6 +60,7 @@ struct BJob : SchedJob {
     int kind = 0, N = 0, R = 0, S = 0;
     int rs = 4, tiles = 0, width = 1, chunk = 1;
     int mode = kTileInt8;  // biclique tile operands: int8 rows (default) or spin bits
+    bool bits = false;     // cube or graph tiles hold their spins as bits
     // device memory (released when the job finishes)
     void *d_table = nullptr, *d_state = nullptr, *d_energy = nullptr;
     size_t bytes = 0;
@@ -83,9 +86,9 @@ struct ServeState {
     std::vector<BJob *> round_jobs;
     std::vector<int> round_end;
     // device work lists (grown on demand)
-    void *d_ea_jobs = nullptr, *d_bq_jobs[3] = {}, *d_graph_jobs = nullptr;  // per tile kind
+    void *d_bit_jobs = nullptr, *d_bq_jobs[3] = {}, *d_graph_jobs = nullptr;  // per tile kind
     void *d_items[kKinds] = {};
-    size_t cap_ea_jobs = 0, cap_bq_jobs[3] = {}, cap_graph_jobs = 0, cap_items[kKinds] = {};
+    size_t cap_bit_jobs = 0, cap_bq_jobs[3] = {}, cap_graph_jobs = 0, cap_items[kKinds] = {};
     int32_t *d_meta = nullptr;  // counters[kKinds], n_items[kKinds]
     bool lds_ready = false;
     // tile autotuner: (kind, shape, threshold width, replicas rounded to a power of two,
@@ -144,7 +147,7 @@ void serve_shutdown(pbit_ctx *ctx)
         dev_free(ctx, j->d_energy);
         if (j->P) j->P->jobs--;
     }
-    dev_free(ctx, s->d_ea_jobs);
+    dev_free(ctx, s->d_bit_jobs);
     dev_free(ctx, s->d_graph_jobs);
     for (int k = 0; k < 3; ++k) dev_free(ctx, s->d_bq_jobs[k]);
     for (int k = 0; k < kKinds; ++k) dev_free(ctx, s->d_items[k]);
@@ -178,12 +181,36 @@ static int tile_mode(const pbit_ctx *ctx)
     return kTileInt8;
 }
 
+// Replicas of a bit job's state, an [N][stride] matrix of bytes (the per-instance layout).
+static int bit_stride(const BJob &j) { return (j.tiles * j.rs + 15) / 16 * 16; }
+
+// Threads per workgroup of a bit job's tiles: for 16-replica tiles enough for the largest
+// group's pairs (the fewest instructions per update: such jobs share a full device), for
+// narrower ones, which are taken to finish sooner, as the per-instance sweep.
+static int bit_job_threads(const BJob &j)
+{
+    const int t = j.rs == 16 ? j.P->bits.max_pairs : bit_threads(j.P->bits, j.rs);
+    return t <= 256 ? 256 : t <= 512 ? 512 : 1024;
+}
+
 static size_t tile_bytes(const BJob &j)
 {
     return j.kind != PBIT_BICLIQUE ? (size_t)j.rs * j.N : (size_t)j.rs * bq_row_bytes(j);
 }
 
 static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<int> &cands, int *pick);
+
+static size_t state_bytes(const BJob &j)
+{
+    return j.bits ? (size_t)j.N * bit_stride(j) : (size_t)j.tiles * tile_bytes(j);
+}
+
+static void size_job(BJob &j)
+{
+    j.tiles = (j.R + j.rs - 1) / j.rs;
+    j.bytes = sizeof(uint32_t) * (size_t)std::max(j.S, 1) * j.width + state_bytes(j) +
+              sizeof(int32_t) * (size_t)j.tiles * j.rs;
+}
 
 static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
 {
@@ -196,12 +223,21 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
     j.mode = tile_mode(ctx);
     std::vector<int> cands;  // tile sizes the job can take (the autotuner times them)
     if (j.width > kMaxTableWidth) return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
-    if (P.kind == PBIT_GRAPH) {
-        // the widest tile (16, 8 or 4 replicas of every site) that the job fills and the LDS holds
-        if (graph_tile_lds(P.N, 4) > (size_t)kMaxLdsTile)
-            return fail(PBIT_E_UNSUPPORTED, "graph of %lld spins is too large for a batched tile", (long long)P.N);
-        if (j.width > kGraphMaxDegree + 2)
-            return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
+    j.bits = P.kind != PBIT_BICLIQUE && P.bits.n_pos > 0;
+    if (P.kind != PBIT_BICLIQUE && P.N > kMaxTileSites)
+        return fail(PBIT_E_UNSUPPORTED, "%s of %lld spins is too large for a batched tile",
+                    P.kind == PBIT_GRAPH ? "graph" : "cube", (long long)P.N);
+    if (P.kind == PBIT_EA3D && (P.ea.Lx > 1024 || P.ea.Ly > 1024))
+        return fail(PBIT_E_UNSUPPORTED, "cube of %lld sites is too large for a batched tile", (long long)P.N);
+    if (P.kind == PBIT_GRAPH && j.width > kGraphMaxDegree + 2)
+        return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
+    if (j.bits) {
+        // by the jobs waiting and running: an equal share of the device for each
+        const int active = (int)(s.q.queue.size() + s.q.running.size());
+        j.rs = bit_pick_rs(P, j.R, std::max(1, compute_units(ctx) / (active + 1)));
+    } else if (P.kind == PBIT_GRAPH) {
+        // byte tiles: the widest tile (16, 8 or 4 replicas of every site) that the job fills
+        // and the LDS holds
         j.rs = 4;
         for (int rs : {16, 8})
             if (j.R >= rs && graph_tile_lds(P.N, rs) <= (size_t)kMaxLdsTile) {
@@ -210,21 +246,6 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
             }
         for (int rs : {16, 8, 4})
             if (rs <= std::max(j.R, 4) && graph_tile_lds(P.N, rs) <= (size_t)kMaxLdsTile) cands.push_back(rs);
-    } else if (P.kind == PBIT_EA3D) {
-        if (ea_tile_lds(P.N, 4) > (size_t)kMaxLdsTile || P.ea.Lx > 1024 || P.ea.Ly > 1024)
-            return fail(PBIT_E_UNSUPPORTED, "cube of %lld sites is too large for a batched tile", (long long)P.N);
-        // the widest tile (16, 8 or 4 replicas: a 16-, 8- or 4-byte row per site) that the
-        // job fills and the LDS holds
-        if (!P.tile_sites)
-            return fail(PBIT_E_UNSUPPORTED, "cube of %lld sites has no site list", (long long)P.N);
-        j.rs = 4;
-        for (int rs : {16, 8})
-            if (j.R >= rs && ea_tile_lds(P.N, rs) <= (size_t)kMaxLdsTile) {
-                j.rs = rs;
-                break;
-            }
-        for (int rs : {16, 8, 4})
-            if (rs <= std::max(j.R, 4) && ea_tile_lds(P.N, rs) <= (size_t)kMaxLdsTile) cands.push_back(rs);
     } else {
         // the largest tile that the replicas fill, the LDS holds and whose whole anneal
         // stays below kItemOps multiply-adds: larger tiles stream fewer coupling bytes
@@ -262,9 +283,7 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
             s.tile_tuned[key] = pick;
         }
     }
-    j.tiles = (j.R + j.rs - 1) / j.rs;
-    j.bytes = sizeof(uint32_t) * (size_t)std::max(j.S, 1) * j.width + (size_t)j.tiles * tile_bytes(j) +
-              sizeof(int32_t) * (size_t)j.tiles * j.rs;
+    size_job(j);
     const bool check = j.d.has_target || j.d.trace_every > 0;
     j.chunk = check ? (j.d.trace_every > 0 ? j.d.trace_every : PBIT_CHECK_SWEEPS) : std::max(j.S, 1);
     j.trace_cap = j.d.trace_every > 0 ? j.S / j.d.trace_every : 0;
@@ -276,7 +295,12 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
 static void rows_to_tiles(const BJob &j, const int8_t *rows, std::vector<int8_t> &tiles_out)
 {
     const Problem &P = *j.P;
-    if (P.kind != PBIT_BICLIQUE) {  // cubes and graphs: [tile][site][replica in tile]
+    if (j.bits) {  // [site][replica]
+        const size_t st = bit_stride(j);
+        tiles_out.assign(state_bytes(j), 1);
+        for (int r = 0; r < j.R; ++r)
+            for (int i = 0; i < j.N; ++i) tiles_out[i * st + r] = rows[(size_t)r * j.N + i];
+    } else if (P.kind != PBIT_BICLIQUE) {  // byte graph tiles and graphs: [tile][site][replica in tile]
         tiles_out.assign((size_t)j.tiles * j.rs * j.N, 1);
         for (int r = 0; r < j.R; ++r)
             for (int i = 0; i < j.N; ++i)
@@ -302,29 +326,36 @@ static void rows_to_tiles(const BJob &j, const int8_t *rows, std::vector<int8_t>
 static void tiles_to_rows(const BJob &j, const int8_t *tl, int8_t *rows)
 {
     const Problem &P = *j.P;
-    if (P.kind != PBIT_BICLIQUE) {
+    if (j.bits) {
+        const size_t st = bit_stride(j);
+        for (int r = 0; r < j.R; ++r)
+            for (int i = 0; i < j.N; ++i) rows[(size_t)r * j.N + i] = tl[i * st + r];
+    } else if (P.kind != PBIT_BICLIQUE) {
         for (int r = 0; r < j.R; ++r)
             for (int i = 0; i < j.N; ++i)
                 rows[(size_t)r * j.N + i] = tl[((size_t)(r / j.rs) * j.N + i) * j.rs + (r % j.rs)];
     } else {
         const int Pw = bq_row_bytes(j);
-        for (int r = 0; r < j.R; ++r)
+        for (int r = 0; r < j.R; ++r) {
+            const int8_t *row = tl + ((size_t)(r / j.rs) * j.rs + (r % j.rs)) * Pw;
+            int8_t *out = rows + (size_t)r * j.N;
+            if (j.mode != kTileBits) {
+                std::memcpy(out, row, (size_t)P.bq.na);
+                std::memcpy(out + P.bq.na, row + P.bq.na_p, (size_t)P.bq.nb);
+                continue;
+            }
             for (int i = 0; i < j.N; ++i) {
                 const int col = i < P.bq.na ? i : P.bq.na_p + (i - P.bq.na);
-                const size_t row = (size_t)(r / j.rs) * j.rs + (r % j.rs);
-                if (j.mode == kTileBits) {
-                    rows[(size_t)r * j.N + i] = ((uint8_t)tl[row * Pw + col / 8] >> (col % 8)) & 1 ? -1 : 1;
-                } else {
-                    rows[(size_t)r * j.N + i] = tl[row * Pw + col];
-                }
+                out[i] = ((uint8_t)row[col / 8] >> (col % 8)) & 1 ? -1 : 1;
             }
+        }
     }
 }
 
 static int admit(pbit_ctx *ctx, BJob &j)
 {
     int rc = dev_alloc(ctx, sizeof(uint32_t) * (size_t)std::max(j.S, 1) * j.width, &j.d_table);
-    if (rc == PBIT_OK) rc = dev_alloc(ctx, (size_t)j.tiles * tile_bytes(j), &j.d_state);
+    if (rc == PBIT_OK) rc = dev_alloc(ctx, state_bytes(j), &j.d_state);
     if (rc == PBIT_OK) rc = dev_alloc(ctx, sizeof(int32_t) * (size_t)j.tiles * j.rs, &j.d_energy);
     if (rc != PBIT_OK) {
         dev_free(ctx, j.d_table);
@@ -411,7 +442,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     launched = false;
     s.round_jobs.clear();
     s.round_end.clear();
-    std::vector<EaJobDev> ea;
+    std::vector<BitJobDev> bit;
     std::vector<GraphJobDev> gr;
     std::vector<BqJobDev> bq[3];
     std::vector<WorkItem> items[kKinds];
@@ -425,22 +456,17 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         s.round_jobs.push_back(j);
         s.round_end.push_back(s1);
         const Key key{(uint32_t)j->d.seed, (uint32_t)(j->d.seed >> 32)};
-        if (j->kind == PBIT_EA3D) {
-            const EaView &v = j->P->ea;
-            EaJobDev jd{reinterpret_cast<const uint2 *>(j->P->tile_sites),
-                        (const uint32_t *)j->d_table,
-                        (int8_t *)j->d_state,
-                        (int32_t *)j->d_energy,
-                        v.Lx, v.Ly, v.Lz, j->width, j->rs, v.dense ? 1 : 0,
-                        (uint32_t)j->d.sweep_offset, (uint32_t)j->d.replica_offset >> 2, key.k0, key.k1};
-            const int idx = (int)ea.size();
-            ea.push_back(jd);
-            const int k = ea_tile_lds(j->N, j->rs) > kEaLargeTileLds ? kCubeLargeKind : 0;
+        if (j->bits) {
+            const BitView &v = j->P->bits;
+            const int idx = (int)bit.size(), k = kind_of_threads(bit_job_threads(*j));
+            bit.push_back(BitJobDev{v, (const uint32_t *)j->d_table, (int8_t *)j->d_state, (int32_t *)j->d_energy,
+                                    j->width, j->rs, bit_stride(*j), (uint32_t)j->d.sweep_offset,
+                                    (uint32_t)j->d.replica_offset >> 2, key.k0, key.k1});
             for (int t = 0; t < j->tiles; ++t) {
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
-                cost[k].push_back((double)(s1 - s0) * j->N * j->rs);
+                cost[k].push_back((double)(s1 - s0) * bit_sweep_us(*j->P, j->rs, j->rs, 1));
             }
-            lds[k] = std::max(lds[k], ea_tile_lds(j->N, j->rs));
+            lds[k] = std::max(lds[k], bit_lds(v.n_pos));
         } else if (j->kind == PBIT_GRAPH) {
             const GraphView &v = j->P->graph;
             GraphJobDev jd{reinterpret_cast<const int4 *>(v.site_meta), v.adj, v.class_start_dev, v.bi, v.bj, v.bJ,
@@ -482,7 +508,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         for (size_t q = 0; q < ord.size(); ++q) sorted[q] = items[k][ord[q]];
         items[k].swap(sorted);
     }
-    int rc = grow(ctx, &s.d_ea_jobs, &s.cap_ea_jobs, sizeof(EaJobDev) * std::max<size_t>(ea.size(), 1));
+    int rc = grow(ctx, &s.d_bit_jobs, &s.cap_bit_jobs, sizeof(BitJobDev) * std::max<size_t>(bit.size(), 1));
     if (rc == PBIT_OK)
         rc = grow(ctx, &s.d_graph_jobs, &s.cap_graph_jobs, sizeof(GraphJobDev) * std::max<size_t>(gr.size(), 1));
     for (int k = 0; k < 3 && rc == PBIT_OK; ++k)
@@ -498,8 +524,8 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     int32_t meta[2 * kKinds] = {0};
     for (int k = 0; k < kKinds; ++k) meta[kKinds + k] = (int32_t)items[k].size();
     hipError_t e = hipMemcpy(s.d_meta, meta, sizeof meta, hipMemcpyHostToDevice);
-    if (e == hipSuccess && !ea.empty())
-        e = hipMemcpy(s.d_ea_jobs, ea.data(), sizeof(EaJobDev) * ea.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !bit.empty())
+        e = hipMemcpy(s.d_bit_jobs, bit.data(), sizeof(BitJobDev) * bit.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !gr.empty())
         e = hipMemcpy(s.d_graph_jobs, gr.data(), sizeof(GraphJobDev) * gr.size(), hipMemcpyHostToDevice);
     for (int k = 0; k < 3 && e == hipSuccess; ++k)
@@ -508,18 +534,16 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         if (!items[k].empty()) e = hipMemcpy(s.d_items[k], items[k].data(), sizeof(WorkItem) * items[k].size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return device_fail(ctx, e, "round upload");
 
-    hipDeviceProp_t prop;
-    e = hipGetDeviceProperties(&prop, ctx->device);
-    if (e != hipSuccess) return device_fail(ctx, e, "hipGetDeviceProperties");
-    const int cus = prop.multiProcessorCount;
+    const int cus = compute_units(ctx);
     for (int k = 0; k < kKinds; ++k) {
         if (items[k].empty()) continue;
         const size_t per_cu_lds = std::max<size_t>(lds[k] + 2048, 1);
-        const int per_cu = std::max(1, std::min(4, (int)((160 * 1024) / per_cu_lds)));
+        const int most = bit_kind(k) ? 1024 / threads_of_kind(k) : 4;
+        const int per_cu = std::max(1, std::min(most, (int)((160 * 1024) / per_cu_lds)));
         const int grid = std::max(1, std::min((int)items[k].size(), cus * per_cu));
-        if (k == 0 || k == kCubeLargeKind)
-            e = ea_tiles((const EaJobDev *)s.d_ea_jobs, (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
-                         s.d_meta + k, grid, lds[k], s.st[k]);
+        if (bit_kind(k))
+            e = bit_tiles((const BitJobDev *)s.d_bit_jobs, (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
+                          s.d_meta + k, grid, threads_of_kind(k), lds[k], s.st[k]);
         else if (k == kGraphKind)
             e = graph_tiles((const GraphJobDev *)s.d_graph_jobs, (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
                             s.d_meta + k, grid, lds[k], s.st[k]);
@@ -567,9 +591,8 @@ static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<in
         BJob t = j;  // the job's shape with this tile size
         t.rs = rs;
         const size_t state = tile_bytes(t);
-        const size_t lds = P.kind == PBIT_EA3D ? ea_tile_lds(P.N, rs)
-                           : P.kind == PBIT_GRAPH ? graph_tile_lds(P.N, rs)
-                                                  : bq_tile_lds(rs, P.bq.na_p, P.bq.nb_p, j.width, j.mode);
+        const size_t lds = P.kind == PBIT_GRAPH ? graph_tile_lds(P.N, rs)
+                                                : bq_tile_lds(rs, P.bq.na_p, P.bq.nb_p, j.width, j.mode);
         // scratch: job descriptor, item, counter and item count, energies, table, state
         const size_t off_item = 512, off_meta = off_item + 64, off_en = off_meta + 64,
                      off_tab = off_en + ((sizeof(int32_t) * rs + 255) & ~(size_t)255),
@@ -583,13 +606,7 @@ static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<in
         e = hipMemcpy(b + off_tab, tab.data(), sizeof(uint32_t) * tab.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(b + off_item, &item, sizeof item, hipMemcpyHostToDevice);
         if (e == hipSuccess) {
-            if (P.kind == PBIT_EA3D) {
-                const EaView &v = P.ea;
-                const EaJobDev jd{reinterpret_cast<const uint2 *>(P.tile_sites), (const uint32_t *)(b + off_tab),
-                                  (int8_t *)(b + off_state), (int32_t *)(b + off_en), v.Lx, v.Ly, v.Lz, j.width, rs,
-                                  v.dense ? 1 : 0, 0u, 0u, 0u, 0u};
-                e = hipMemcpy(b, &jd, sizeof jd, hipMemcpyHostToDevice);
-            } else if (P.kind == PBIT_GRAPH) {
+            if (P.kind == PBIT_GRAPH) {
                 const GraphView &v = P.graph;
                 const GraphJobDev jd{reinterpret_cast<const int4 *>(v.site_meta), v.adj, v.class_start_dev, v.bi,
                                      v.bj, v.bJ, v.h, (const uint32_t *)(b + off_tab), (int8_t *)(b + off_state),
@@ -611,9 +628,7 @@ static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<in
             if (e == hipSuccess) {
                 const WorkItem *it = (const WorkItem *)(b + off_item);
                 int32_t *ctr = (int32_t *)(b + off_meta);
-                if (P.kind == PBIT_EA3D)
-                    e = ea_tiles((const EaJobDev *)b, it, ctr + 1, ctr, 1, lds, st);
-                else if (P.kind == PBIT_GRAPH)
+                if (P.kind == PBIT_GRAPH)
                     e = graph_tiles((const GraphJobDev *)b, it, ctr + 1, ctr, 1, lds, st);
                 else
                     e = bq_tiles((const BqJobDev *)b, it, ctr + 1, ctr, rs, j.mode, 1, lds, st);
@@ -739,8 +754,26 @@ static int new_job(pbit_ctx *ctx, ServeState &s, uint64_t problem, const pbit_an
 // Copy a finished job's results out and release its device memory.
 static int fill_result(pbit_ctx *ctx, BJob &j, pbit_result *res)
 {
-    if (res && res->spins && j.d_state) {
-        std::vector<int8_t> tl((size_t)j.tiles * tile_bytes(j));
+    if (res && res->spins && j.d_state && j.bits) {
+        // transposed on the device where the staging rows fit the budget
+        void *rows = nullptr;
+        const size_t bytes = (size_t)j.R * j.N;
+        const int rc = scratch(ctx, Slot::Stage, bytes, &rows);
+        if (rc == PBIT_OK) {
+            hipError_t e = ea_to_rows(j.P->ea, (const int8_t *)j.d_state, bit_stride(j), (int8_t *)rows, j.R, ctx->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(res->spins, rows, bytes, hipMemcpyDeviceToHost, ctx->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+            if (e != hipSuccess) return device_fail(ctx, e, "spin readback");
+        } else if (rc != PBIT_E_NOMEM) {
+            return rc;
+        } else {
+            std::vector<int8_t> tl(state_bytes(j));
+            hipError_t e = hipMemcpy(tl.data(), j.d_state, tl.size(), hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return device_fail(ctx, e, "spin readback");
+            tiles_to_rows(j, tl.data(), res->spins);
+        }
+    } else if (res && res->spins && j.d_state) {
+        std::vector<int8_t> tl(state_bytes(j));
         hipError_t e = hipMemcpy(tl.data(), j.d_state, tl.size(), hipMemcpyDeviceToHost);
         if (e != hipSuccess) return device_fail(ctx, e, "spin readback");
         tiles_to_rows(j, tl.data(), res->spins);
@@ -876,6 +909,36 @@ extern "C" int pbit_profile_tiles(pbit_ctx *ctx, int64_t *tunings, int32_t *shap
     return PBIT_OK;
 }
 
+namespace pbit {
+
+// Tile widths of a batch's cube and graph jobs: each job gets the share of the compute
+// units that its work is of the batch's, and the width of least cost on that share, so
+// that a small batch spreads over the device and a full one takes the widest tiles.
+// Work in microseconds of one compute unit: measured for tiles of 16 replicas, and 33 us
+// per sweep for 32 replicas of a 1024 x 1024 biclique.
+static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
+{
+    double total = 0.0;
+    std::vector<double> work;
+    for (const BJob *j : js) {
+        const double us = j->bits ? bit_sweep_us(*j->P, 16, 16, 1) * j->R / 16.0
+                          : j->kind == PBIT_BICLIQUE
+                              ? 33.0 * ((double)j->P->bq.na_p * j->P->bq.nb_p / (1 << 20)) * j->R / 32.0
+                              : 1e-3 * j->N * j->R / 4.0;
+        work.push_back(us * std::max(j->S, 1));
+        total += work.back();
+    }
+    const int cus = compute_units(ctx);
+    for (size_t q = 0; q < js.size(); ++q) {
+        BJob &j = *js[q];
+        if (!j.bits) continue;
+        j.rs = bit_pick_rs(*j.P, j.R, std::max(1, (int)(cus * work[q] / total)));
+        size_job(j);
+    }
+}
+
+}  // namespace pbit
+
 extern "C" int pbit_anneal_batch(pbit_ctx *ctx, const pbit_batch_job *jobs, int32_t n_jobs)
 {
     try {
@@ -902,6 +965,7 @@ extern "C" int pbit_anneal_batch(pbit_ctx *ctx, const pbit_batch_job *jobs, int3
             j->user = jobs[k].result;
             mine.push_back(j);
         }
+        share_device(ctx, mine);
         prebuild_tables(mine);
         int frc = PBIT_OK;
         for (;;) {
