@@ -42,7 +42,8 @@ constexpr int kMaxTableWidth = 4096;  // threshold-row entries a biclique kernel
 // of 256); Slab: sides of
 // at most 512 sites, couplings and 16- or 8-replica slices held in LDS for runs of
 // sweeps in one launch (bq_slab).
-enum class BqVariant : int { Auto = 0, Small = 1, Dma = 2, Bits = 3, Slab = 4 };
+// Cluster: couplings in registers across an XCD for runs of sweeps (bq_cluster).
+enum class BqVariant : int { Auto = 0, Small = 1, Dma = 2, Bits = 3, Slab = 4, Cluster = 5 };
 // The LDS-resident form for small sides: sweeps [s_begin, s_end) (table rows), absolute
 // index sweep0 + s, of all Rp replicas (Rp / rs workgroups of rs-replica slices) on MA / MB
 // in place.  rs is 16 or 8; 0 picks 16 when that gives a workgroup to every compute unit,
@@ -51,6 +52,16 @@ int bq_slab_rs(int Rp, int rs);
 bool bq_slab_supported(const BqView &p, int Rp, int width, int rs = 0);
 hipError_t bq_slab(const BqView &p, int8_t *MA, int8_t *MB, int Rp, const uint32_t *table, int width, int s_begin,
                    int s_end, uint32_t sweep0, uint32_t rq0, Key key, hipStream_t st, int rs = 0);
+// The form whose couplings stay in registers across an XCD (bq_cluster.hip), for sides of at
+// most 1024 sites and threshold rows of at most 256 entries: sweeps [s_begin, s_end) of
+// replicas [0, R) on MA / MB in place, with `work` (bq_cluster_bytes) as exchange memory and a
+// workgroup on each of `cus` compute units.  work[1] is 0 afterwards if the sweeps ran, 1
+// if the workgroups could not be resident together (MA / MB untouched), 2 after a lost flag.
+bool bq_cluster_supported(const BqView &p, int width);
+size_t bq_cluster_bytes(const BqView &p, int R);
+hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
+                      int s_begin, int s_end, uint32_t sweep0, uint32_t rq0, Key key, void *work, int cus,
+                      hipStream_t st);
 hipError_t bq_init(const BqView &p, int8_t *MA, int8_t *MB, int R, uint32_t rq0, Key key, hipStream_t st);
 hipError_t bq_from_rows(const BqView &p, const int8_t *src_rn, int R, int8_t *MA, int8_t *MB, hipStream_t st);
 hipError_t bq_to_rows(const BqView &p, const int8_t *MA, const int8_t *MB, int8_t *dst_rn, int R, hipStream_t st);

@@ -1,0 +1,401 @@
+// bq_cluster.hip — bicliques whose couplings stay in the registers of one XCD's compute
+// units for a whole run of sweeps.
+//
+// A half-sweep of a mid-sized biclique is a few hundred nanoseconds of matrix work, far
+// below what a launch costs, and its couplings do not fit one compute unit.  Here the 32
+// compute units of an XCD form a cluster that anneals row tiles of 32 replicas: workgroup
+// c of a cluster owns sites 32 c .. 32 c + 31 of both sides and keeps their coupling rows
+// as MFMA operands in registers (one wave per SIMD, so 512 of them; 256 hold the couplings
+// at 1024 sites per side).  Each of its four waves takes one row tile, and the waves with
+// the same row tile in the other workgroups are all it ever talks to: after an update a
+// wave stores its 32 x 32 new spins as 32 words and raises its flag, and before one it
+// waits for the flags of the other side's blocks and reads their words, all within the
+// XCD's own L2.  No other synchronisation takes place inside a run.
+//
+// What bounds it: a serial chain per half-sweep, with one wave per SIMD.  At 1024 sites per
+// side, 32 dependent MFMAs with the widening of their spin bits (about 1.6 k cycles), 16
+// decisions (1 k), the store, flag, poll and load through the L2 (1.5 k) and the random
+// words, which are drawn in the shadow of the stores.  4.4 us a sweep at 1024 x 1024 sites
+// and 1024 replicas, against 13.3 us for the bit kernel's launch per half-sweep and a
+// matrix floor of 0.9 us; 4.3 against 21.5 us with 16 replicas; 3.6 against 4.5 us at
+// 512 x 512 for the LDS-resident kernel, which wins below 256 (2.2 against 2.9 at 32).
+// Stores with agent scope, which the protocol does not need inside one L2, made it 9.2 us;
+// threshold rows loaded every sweep instead of 16 at a time, and a table of carry words
+// rebuilt every sweep instead of the rows themselves, cost 0.5 and 0.3 us.
+//
+// The workgroups have to be resident together, and spread evenly over the XCDs: they
+// meet before touching anything, and if they do not all arrive in time or an XCD has too
+// few of them, all leave and the caller runs the sweeps another way.
+//
+// Arithmetic, counters and decisions are the bit kernel's (bq_kernels.hip): spin bits
+// widened for the int8 MFMA, exact int32 sums, carry words S(I).
+#include <algorithm>
+#include <type_traits>
+
+#include "bq.h"
+#include "device.h"
+
+namespace pbit {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+constexpr int kXcds = 8;
+constexpr uint32_t kAbort = 0x80000000u;
+constexpr uint64_t kMeetTicks = 200000;  // 2 ms of the 100 MHz clock; an idle device takes some 10 us
+constexpr int kMaxWidth = 256;            // threshold row entries
+constexpr int kRows = 16;                 // threshold rows held per wave
+constexpr int kBias = 1 << 24;            // far above 4 |h2| + 8 sum |J|: accumulators stay positive
+constexpr int kPollLimit = 1 << 21;       // a second or so: never reached by resident workgroups
+
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+struct Args {
+    const int8_t *J[2];     // Jb, JTb: coupling rows of side A's and side B's sites
+    const int32_t *h2[2];   // field plus coupling sum
+    int8_t *M[2];           // int8 spins [Rp][n_p]
+    uint32_t *X[2];         // spin words [row tile][block / 4][32 replicas][4]
+    uint32_t *flags;        // [2][row tiles][32]: updates a block has published
+    uint32_t *ctl;          // arrivals, status, 8 per-XCD counts
+    const uint32_t *table;
+    int n[2], n_p[2], blocks[2];
+    int width, tiles, s_begin, s_end, members;
+    uint32_t sweep0, rq0, k0, k1;
+};
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t agent_add(uint32_t *p, uint32_t v)
+{
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// All workgroups arrive, or none proceeds: a workgroup that waited too long marks the
+// arrival count (only while it is incomplete), and whoever sees the mark leaves.
+__device__ bool meet(uint32_t *ctl, uint32_t groups, uint32_t members, uint32_t xcc, uint32_t &slot)
+{
+    slot = agent_add(ctl + 2 + (xcc & (kXcds - 1)), 1u);
+    uint32_t seen = agent_add(ctl, 1u) + 1u;
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    while (seen < groups) {  // the mark makes it larger
+        if (__builtin_amdgcn_s_memrealtime() - t0 > kMeetTicks) {
+            uint32_t expect = seen;
+            if (__hip_atomic_compare_exchange_strong(ctl, &expect, seen | kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return false;
+            seen = expect;
+            continue;
+        }
+        __builtin_amdgcn_s_sleep(2);
+        seen = agent_add(ctl, 0u);
+    }
+    if (seen & kAbort) return false;
+    bool ok = xcc < kXcds;
+    for (int k = 0; k < kXcds; ++k) ok = ok && agent_add(ctl + 2 + k, 0u) >= members;
+    return ok;
+}
+
+// |a - b| + c
+__device__ __forceinline__ uint32_t sad(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Exchange words of one side and row tile as a buffer of whole quads (reads past them give 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int quads)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, 512 * quads, 0x00027000);
+}
+
+// KS: K steps of 32 sites a side may have (the couplings take 8 KS registers).
+template <int KS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_bq_cluster(Args g)
+{
+    extern __shared__ uint32_t lds[];  // per wave kRows threshold rows; starts at LDS address 0
+    uint32_t *joined = lds;            // before the rows are loaded
+    if (threadIdx.x == 0) {
+        const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (31 << 11)) & 15u;  // HW_REG_XCC_ID
+        uint32_t slot = 0u;
+        const bool ok = meet(g.ctl, gridDim.x, (uint32_t)g.members, xcc, slot);
+        joined[0] = ok;
+        joined[1] = xcc;
+        joined[2] = slot;
+        if (!ok) __hip_atomic_store(g.ctl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    const int ok = __builtin_amdgcn_readfirstlane((int)joined[0]);
+    const int cluster = __builtin_amdgcn_readfirstlane((int)joined[1]);
+    const int c = __builtin_amdgcn_readfirstlane((int)joined[2]);
+    __syncthreads();
+    if (!ok || c >= g.members) return;
+
+    const int lane = threadIdx.x & 63, ln = lane & 31, kg = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool has[2] = {c < g.blocks[0], c < g.blocks[1]};
+    // coupling operands: row 32 c + ln, 16 bytes of K step u at 32 u + 16 kg; zero past the row
+    v4i_t jr[2][KS];
+    int h2[2];
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const int ko = g.n_p[1 - side];
+        const int8_t *row = g.J[side] + (size_t)(32 * c + ln) * ko + 16 * kg;
+#pragma unroll
+        for (int u = 0; u < KS; ++u)
+            jr[side][u] = has[side] && 32 * u < ko ? *reinterpret_cast<const v4i_t *>(row + 32 * u) : v4i_t{0, 0, 0, 0};
+        h2[side] = has[side] ? g.h2[side][32 * c + ln] : 0;
+    }
+    const int top = g.width - 1;
+    // The products start at kBias, so an accumulator holds kBias + 8 sum_k J b = mid - 4 I
+    // with mid = kBias + 4 h2 (both positive), and |4 I| is the byte offset of Tm(|I|).
+    v16i bias;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) bias[j] = kBias;
+    const uint32_t mid[2] = {(uint32_t)(kBias + 4 * h2[0]), (uint32_t)(kBias + 4 * h2[1])};
+    const uint32_t rows = (uint32_t)wave * kRows * 4u * (uint32_t)g.width;  // LDS address of this wave's threshold rows
+
+    for (int t = cluster + kXcds * wave; t < g.tiles; t += kXcds * kWaves) {
+        uint32_t *flag[2] = {g.flags + 32 * t, g.flags + 32 * (g.tiles + t)};
+        const int quads[2] = {(g.blocks[0] + 3) / 4, (g.blocks[1] + 3) / 4};  // blocks / 4 of a side
+        uint32_t *xt[2] = {g.X[0] + (size_t)t * quads[0] * 128, g.X[1] + (size_t)t * quads[1] * 128};
+        int out[2] = {0, 0};  // lane r: this block's word of replica r
+        // random words of one update: two of the four blocks at a time
+        uint32_t w[16];
+        auto draw = [&](int side, uint32_t sweep, int q0) {
+            const uint32_t site = (uint32_t)(side ? g.n[0] : 0) + 32u * (uint32_t)c + (uint32_t)ln;
+#pragma unroll
+            for (int q = q0; q < q0 + 2; ++q) {
+                const Block4 b = philox(site, sweep, g.rq0 + (uint32_t)(8 * t + 2 * q + kg), kDomainSweep, g.k0, g.k1);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) w[4 * q + p] = b.w[p];
+            }
+#pragma unroll
+            for (int j = 4 * q0; j < 4 * q0 + 8; ++j) asm volatile("" : "+v"(w[j]));  // drawn here, not where they are used
+        };
+        // publish the own block (sequence number seq of its side), drawing the next update's
+        // words (side ns, sweep next) while the stores travel and the first look at the flags
+        // that update waits for is under way
+        uint32_t peek = 0u;
+        auto publish = [&](int side, uint32_t seq, int ns, uint32_t next) {
+            if (lane < 32)
+                __hip_atomic_store(xt[side] + (((c >> 2) * 32 + lane) * 4 + (c & 3)), (uint32_t)out[side],
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __builtin_amdgcn_sched_barrier(0);
+            draw(ns, next, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the words are in L2
+            asm volatile("" ::: "memory");
+            if (lane == 0)
+                __hip_atomic_store(flag[side] + c, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            peek = agent_load(flag[1 - ns] + ln);
+            __builtin_amdgcn_sched_barrier(0);
+            draw(ns, next, 2);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const int first = has[0] ? 0 : 1;  // the side this block updates first in a sweep
+        // initial spins of the own block of both sides
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+            if (has[side]) {
+                const int8_t *m = g.M[side] + (size_t)(32 * t + 16 * kg) * g.n_p[side] + 32 * c + ln;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const uint64_t b = __ballot(m[(size_t)r * g.n_p[side]] < 0);
+                    out[side] = lane_write((int)(uint32_t)b, r, out[side]);
+                    out[side] = lane_write((int)(uint32_t)(b >> 32), r + 16, out[side]);
+                }
+            }
+        if (has[1])
+            publish(1, 1u, first, g.sweep0 + (uint32_t)g.s_begin);
+        else {
+            draw(first, g.sweep0 + (uint32_t)g.s_begin, 0);
+            draw(first, g.sweep0 + (uint32_t)g.s_begin, 2);
+            peek = agent_load(flag[1 - first] + ln);
+        }
+
+        bool lost = false;
+        const __amdgpu_buffer_rsrc_t xr[2] = {rsrc(xt[0], quads[0]), rsrc(xt[1], quads[1])};
+        auto half = [&](auto side_c, uint32_t row, uint32_t need, uint32_t seq, int ns, uint32_t next) {
+            constexpr int side = decltype(side_c)::value;
+            const uint32_t *f = flag[1 - side] + ln;
+            const bool watch = ln < g.blocks[1 - side];
+            int polls = 0;
+            while (!__all(!watch || peek >= need)) {
+                if (++polls > kPollLimit) {
+                    lost = true;
+                    return;
+                }
+                peek = agent_load(f);
+            }
+            asm volatile("" ::: "memory");
+            // words of replica ln, four blocks a load: the even quads in lanes 0-31 and the odd
+            // ones in lanes 32-63 (reads past the last quad return zero)
+            v4i_t v[(KS + 7) / 8];
+#pragma unroll
+            for (int k = 0; k < (KS + 7) / 8; ++k)
+                v[k] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(xr[1 - side], 512 * kg + 16 * ln,
+                                                                                      1024 * k, 16 /* sc1 */));
+            v16i acc = bias;
+            v4i_t a = v4i_t{0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < (KS + 7) / 8; ++k)
+                if (2 * k < quads[1 - side]) {
+                    // both quads to all lanes, shifted by four bits in lanes 32-63 as widened there
+                    uint32_t x[8];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)v[k][u], (uint32_t)v[k][u] >> 4, false, false);
+                        x[u] = p[0];
+                        x[4 + u] = p[1];
+                    }
+                    a = widen_bits(x[0], 0);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const v4i_t cur = a;
+                        if (u < 7) a = widen_bits(x[u + 1], 0);
+                        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, jr[side][8 * k + u], acc, 0, 0, 0);
+                    }
+                }
+            uint32_t T[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                // |acc - mid| + row, at most the row's last entry
+                const uint32_t at = min(sad((uint32_t)acc[j], mid[side], row), row + 4u * (uint32_t)top);
+                T[j] = *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)at;
+            }
+            uint64_t minus[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                // -1 exactly when w + T carries (I >= 0), or w >= T (I < 0)
+                const uint64_t up = __ballot((uint32_t)acc[j] <= mid[side]);
+                const uint64_t carry = __ballot(w[j] > ~T[j]), above = __ballot(w[j] >= T[j]);
+                minus[j] = (up & carry) | (~up & above);
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int r = 8 * (j >> 2) + (j & 3);
+                out[side] = lane_write((int)(uint32_t)minus[j], r, out[side]);
+                out[side] = lane_write((int)(uint32_t)(minus[j] >> 32), r + 4, out[side]);
+            }
+            publish(side, seq, ns, next);
+        };
+
+        // kRows sweeps' threshold rows at a time in LDS (a row loaded every sweep would put a
+        // memory latency into every wait below), then each sweep's decision words
+        for (int s = g.s_begin; s < g.s_end; ++s) {
+            const int k = (s - g.s_begin) % kRows;
+            if (k == 0) {
+                const int count = min(kRows, g.s_end - s) * g.width;
+                const uint32_t *src = g.table + (size_t)s * g.width;
+                for (int e = 0; e < count; e += 64)
+                    if (e + lane < count)
+                        __builtin_amdgcn_global_load_lds(src + e + lane, lds + wave * kRows * g.width + e, 4, 0, 0);
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                asm volatile("" ::: "memory");
+            }
+            const uint32_t row = rows + 4u * (uint32_t)(k * g.width);
+            const uint32_t done = (uint32_t)(s - g.s_begin);
+            const uint32_t sweep = g.sweep0 + (uint32_t)s;
+            if (has[0])
+                half(std::integral_constant<int, 0>{}, row, done + 1u, done + 1u, has[1] ? 1 : 0, has[1] ? sweep : sweep + 1u);
+            if (lost) break;
+            if (has[1]) half(std::integral_constant<int, 1>{}, row, done + 1u, done + 2u, first, sweep + 1u);
+            if (lost) break;
+        }
+        if (lost) {
+            if (lane == 0) __hip_atomic_store(g.ctl + 1, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        // spins out, zero at padding sites
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+            if (has[side]) {
+                int8_t *m = g.M[side] + (size_t)(32 * t + 16 * kg) * g.n_p[side] + 32 * c + ln;
+                const bool real = 32 * c + ln < g.n[side];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(out[side], r);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(out[side], r + 16);
+                    const uint32_t b = ((kg ? hi : lo) >> ln) & 1u;
+                    m[(size_t)r * g.n_p[side]] = real ? (b ? (int8_t)-1 : (int8_t)1) : (int8_t)0;
+                }
+            }
+    }
+}
+
+constexpr int kMaxBlocks = 32;
+constexpr size_t kCtlWords = 16;
+
+int blocks_of(int n) { return (n + 31) / 32; }
+
+template <int KS>
+hipError_t launch(const Args &g, int cus, size_t lds, hipStream_t st)
+{
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bq_cluster<KS>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(k_bq_cluster<KS>, dim3((unsigned)cus), dim3(kThreads), lds, st, g);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool bq_cluster_supported(const BqView &p, int width)
+{
+    return p.Jb && blocks_of(p.na) <= kMaxBlocks && blocks_of(p.nb) <= kMaxBlocks && width >= 1 && width <= kMaxWidth;
+}
+
+size_t bq_cluster_bytes(const BqView &p, int R)
+{
+    const size_t tiles = (size_t)(R + 31) / 32;
+    const size_t quads = (size_t)(blocks_of(p.na) + 3) / 4 + (size_t)(blocks_of(p.nb) + 3) / 4;
+    return 4 * (kCtlWords + 2 * tiles * 32 + tiles * quads * 128);
+}
+
+hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
+                      int s_begin, int s_end, uint32_t sweep0, uint32_t rq0, Key key, void *work, int cus,
+                      hipStream_t st)
+{
+    const int tiles = (R + 31) / 32;
+    if (!bq_cluster_supported(p, width) || s_end < s_begin || 32 * tiles > Rp || cus < kXcds) return hipErrorInvalidValue;
+    if (s_end == s_begin) return hipSuccess;
+    uint32_t *w = static_cast<uint32_t *>(work);
+    hipError_t e = fill_i32((int32_t *)w, (int64_t)(bq_cluster_bytes(p, R) / 4), 0, st);
+    if (e != hipSuccess) return e;
+    Args g{};
+    g.J[0] = p.Jb;
+    g.J[1] = p.JTb;
+    g.h2[0] = p.hA2;
+    g.h2[1] = p.hB2;
+    g.M[0] = MA;
+    g.M[1] = MB;
+    g.ctl = w;
+    g.flags = w + kCtlWords;
+    g.X[0] = g.flags + 2 * tiles * 32;
+    g.X[1] = g.X[0] + (size_t)tiles * ((blocks_of(p.na) + 3) / 4) * 128;
+    g.table = table;
+    g.n[0] = p.na;
+    g.n[1] = p.nb;
+    g.n_p[0] = p.na_p;
+    g.n_p[1] = p.nb_p;
+    g.blocks[0] = blocks_of(p.na);
+    g.blocks[1] = blocks_of(p.nb);
+    g.members = g.blocks[0] > g.blocks[1] ? g.blocks[0] : g.blocks[1];
+    g.width = width;
+    g.tiles = tiles;
+    g.s_begin = s_begin;
+    g.s_end = s_end;
+    g.sweep0 = sweep0;
+    g.rq0 = rq0;
+    g.k0 = key.k0;
+    g.k1 = key.k1;
+    const size_t lds = sizeof(uint32_t) * (size_t)std::max(kRows * width * kWaves, 4);
+    if (g.members <= 8) return launch<8>(g, cus, lds, st);
+    return g.members <= 16 ? launch<16>(g, cus, lds, st) : launch<32>(g, cus, lds, st);
+}
+
+}  // namespace pbit

@@ -45,14 +45,30 @@ namespace pbit {
 
 static std::atomic<uint32_t> g_ctx_serial{1};
 
+// The cluster kernel's exchange memory is the one buffer an anneal can do without: it is
+// given back, between anneals, before an allocation is refused.
+static bool give_back_work(pbit_ctx *ctx)
+{
+    Scratch &w = ctx->scratch[(int)Slot::Work];
+    if (!w.ptr || ctx->work_busy) return false;
+    dev_free(ctx, w.ptr);
+    w = Scratch{};
+    return true;
+}
+
 int dev_alloc(pbit_ctx *ctx, size_t bytes, void **out)
 {
     *out = nullptr;
     if (bytes == 0) return PBIT_OK;
+    if (ctx->budget && ctx->in_use + bytes > ctx->budget) give_back_work(ctx);
     if (ctx->budget && ctx->in_use + bytes > ctx->budget)
         return fail(PBIT_E_NOMEM, "device budget exhausted: %llu in use + %llu requested > %llu",
                     (unsigned long long)ctx->in_use, (unsigned long long)bytes, (unsigned long long)ctx->budget);
     hipError_t e = hipMalloc(out, bytes);
+    if (e == hipErrorOutOfMemory && give_back_work(ctx)) {
+        (void)hipGetLastError();
+        e = hipMalloc(out, bytes);
+    }
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         *out = nullptr;
@@ -127,9 +143,9 @@ extern "C" int pbit_create(pbit_ctx **out, int device, uint64_t hbm_budget_bytes
     if (!ctx) return fail(PBIT_E_NOMEM, "pbit_create: host allocation failed");
     ctx->device = device;
     ctx->budget = hbm_budget_bytes;
-    if (const char *v = std::getenv("PBIT_BQ_VARIANT")) {  // tuning override: 1..4 (see BqVariant)
+    if (const char *v = std::getenv("PBIT_BQ_VARIANT")) {  // tuning override: 1..5 (see BqVariant)
         const int k = std::atoi(v);
-        if (k >= 1 && k <= 4) ctx->bq_forced = (BqVariant)k;
+        if (k >= 1 && k <= 5) ctx->bq_forced = (BqVariant)k;
     }
     if (const char *v = std::getenv("PBIT_BQ_BITS_RT")) ctx->bq_bits_rt = std::atoi(v);  // tuning override
     if (const char *v = std::getenv("PBIT_GRAPH_SLAB")) {  // tuning override: 0 off, 4 / 8 / 16 a tile width
@@ -687,7 +703,15 @@ struct DevState {
     bool bit_tiles = false;   // they hold the spins as bits (bits.h)
     int32_t *graph_energy = nullptr;  // its per-replica energies (not used by the runtime)
     bool mfma = false;        // cube fields on the matrix cores (ea_mfma.hip), spins [2][Rp][N / 2]
+    void *cluster_work = nullptr;  // exchange memory of the biclique cluster kernel
+    int chunk = 1;            // sweeps per launch
     Arena *arena = nullptr;   // set: buffers are carved from it (no allocation, no kernel timing)
+};
+
+// Marks the cluster kernel's exchange memory idle when an anneal ends.
+struct WorkRelease {
+    pbit_ctx *ctx;
+    ~WorkRelease() { ctx->work_busy = false; }
 };
 
 // Device buffers of an anneal: carved from the arena when there is one, else the
@@ -705,13 +729,49 @@ static int take(pbit_ctx *ctx, DevState &ds, Slot slot, size_t bytes, void **out
 }
 
 constexpr int kSlabChunk = 1000;  // sweeps per launch of the LDS-resident cube, graph and biclique kernels
+constexpr int kClusterChunk = 20000;  // and of the biclique cluster kernel
+constexpr int kClusterSkip = 64;      // anneals that do not try it after it could not run
 constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
+
+// Whether the cluster kernel can run a biclique's sweeps.  It has to report back whether its
+// workgroups were resident together, so not from a graph or in static scratch, and not for the
+// next anneals after it once was not.  A launch starts by loading couplings and ends in that
+// report, 25-40 us together: runs of 16 sweeps carry that against kernels of 13-21 us a sweep
+// (sides over 512), and against the LDS-resident kernel's 2-4.5 us runs of 64.  That one costs
+// 2.0 us + 4.7 ns per site a sweep and this one 2.9 us + 1.5 ns for each pass of 1024
+// replicas, so beside it only sides over 256 in one pass are worth timing.  Above 8192
+// replicas it would make eight passes of what the bit tile does in one.
+static bool cluster_possible(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, bool slab_ok)
+{
+    const int run = d->trace_every > 0 ? d->trace_every : d->has_target ? 1 : d->n_sweeps;
+    const bool forced = ctx->bq_forced == BqVariant::Cluster;
+    if (ds.arena || ctx->use_graph || (!forced && ctx->bq_forced != BqVariant::Auto) || ds.R > 8192 ||
+        (!forced && std::min(run, d->n_sweeps) < (slab_ok ? 64 : 16)) ||
+        (!forced && slab_ok && (std::max(P.bq.na, P.bq.nb) <= 256 || ds.R > 1024)) || !bq_cluster_supported(P.bq, ds.width))
+        return false;
+    if (ctx->bq_cluster_skip > 0) {
+        --ctx->bq_cluster_skip;
+        return false;
+    }
+    // what the rest of the anneal may yet allocate (staged rows) comes first
+    const size_t bytes = bq_cluster_bytes(P.bq, ds.R), rest = 2 * (size_t)ds.R * P.N + 65536;
+    if (ctx->budget && ctx->in_use + bytes + rest > ctx->budget) return false;
+    ctx->work_busy = true;
+    return scratch(ctx, Slot::Work, bytes, &ds.cluster_work) == PBIT_OK;
+}
+
+static hipError_t cluster_status(const DevState &ds, hipStream_t st, int *status)
+{
+    hipError_t e = hipMemcpyAsync(status, (int *)ds.cluster_work + 1, sizeof *status, hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+}
 
 // Pick the biclique kernel variant for this shape: the forced one, a cached
 // choice, or the fastest of the candidates timed here on the (not yet
 // initialised) spin buffers, whose contents do not affect the timing.
-static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStream_t st, int n_sweeps)
+static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, hipStream_t st)
 {
+    const int n_sweeps = d->n_sweeps;
     // the DMA and bit tiles need sides padded to 128 (and the bit tiles a bit copy of
     // the spins, made where the replicas pad to 256); the LDS-resident form sides of
     // at most 512 and its decision words in LDS
@@ -725,14 +785,19 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
         ds.variant = f;  // a forced kernel the shape cannot take falls back to the tuned choice
         return PBIT_OK;
     }
-    const std::array<int, 4> shape{P.bq.na_p, P.bq.nb_p, ds.Rp, slab_ok ? 1 : 0};
+    const bool cluster_ok = cluster_possible(ctx, P, d, ds, slab_ok);
+    if (cluster_ok && f == BqVariant::Cluster) {
+        ds.variant = f;
+        return PBIT_OK;
+    }
+    const std::array<int, 4> shape{P.bq.na_p, P.bq.nb_p, ds.Rp, (slab_ok ? 1 : 0) + (cluster_ok ? 2 : 0)};
     auto it = ctx->bq_tuned.find(shape);
     if (it != ctx->bq_tuned.end()) {
         ds.variant = it->second.first;
         (ds.variant == BqVariant::Slab ? ds.slab_rs : ds.bits_rt) = it->second.second;
         return PBIT_OK;
     }
-    if (!large && !slab_ok) {
+    if (!large && !slab_ok && !cluster_ok) {
         ds.variant = BqVariant::Small;
         ctx->bq_tuned[shape] = {ds.variant, 0};
         return PBIT_OK;
@@ -744,7 +809,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
         ds.variant = slab_ok ? BqVariant::Slab : ds.MAb ? BqVariant::Bits : large ? BqVariant::Dma : BqVariant::Small;
         return PBIT_OK;
     }
-    const BqVariant cand[] = {BqVariant::Small, BqVariant::Dma, BqVariant::Bits, BqVariant::Slab};
+    const BqVariant cand[] = {BqVariant::Small, BqVariant::Dma, BqVariant::Bits, BqVariant::Slab, BqVariant::Cluster};
     hipEvent_t e0, e1;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -758,7 +823,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
     float best_ms = 0.f;
     BqVariant best = BqVariant::Small;
     int best_rt = 0;
-    bool have = false;
+    bool have = false, cache = true;
     int rt = 0;  // the bit kernel's replica tile or the LDS-resident kernel's slice being timed
     // one warm-up pass, then the best of three (a profiler's tracing stretches single launches)
     auto time_it = [&](BqVariant v, int slab_sweeps, float *best_pass) {
@@ -770,6 +835,10 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
                 if (e == hipSuccess)
                     e = bq_slab(P.bq, ds.MA, ds.MB, ds.Rp, ds.table, ds.width, 0, slab_sweeps, 0u, 0u, key, st,
                                 rt);
+            } else if (v == BqVariant::Cluster) {
+                if (e == hipSuccess)
+                    e = bq_cluster(P.bq, ds.MA, ds.MB, ds.R, ds.Rp, ds.table, ds.width, 0, slab_sweeps, 0u, 0u, key,
+                                   ds.cluster_work, compute_units(ctx), st);
             } else {
                 for (int k = 0; k < 4 && e == hipSuccess; ++k)
                     e = v == BqVariant::Bits
@@ -789,7 +858,8 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
     // larger ones read the couplings fewer times or use more of the MFMA's rows
     std::vector<std::pair<BqVariant, int>> runs;
     for (BqVariant v : cand) {
-        if ((v == BqVariant::Dma && !large) || (v == BqVariant::Bits && !ds.MAb) || (v == BqVariant::Slab && !slab_ok))
+        if ((v == BqVariant::Dma && !large) || (v == BqVariant::Bits && !ds.MAb) || (v == BqVariant::Slab && !slab_ok) ||
+            (v == BqVariant::Cluster && !cluster_ok))
             continue;  // the shape cannot take it
         if (v == BqVariant::Bits && ds.bits_rt == 0) {
             for (int w : {256, 128, 64})
@@ -805,13 +875,23 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
         const BqVariant v = run.first;
         rt = run.second;
         float ms = 0.f;
-        if (v == BqVariant::Slab) {
+        if (v == BqVariant::Slab || v == BqVariant::Cluster) {
             float t1 = 0.f, t2 = 0.f;
             time_it(v, 1, &t1);
+            if (v == BqVariant::Cluster && e == hipSuccess) {
+                int status = 0;
+                e = cluster_status(ds, st, &status);
+                if (status != 0) {  // not resident together: no candidate now
+                    ctx->bq_cluster_skip = kClusterSkip;
+                    cache = false;
+                    continue;
+                }
+            }
             if (m > 0) time_it(v, 1 + m, &t2);
             const double per_sweep = m > 0 ? std::max(0.0, (double)(t2 - t1) / m) : t1;
             const double load = m > 0 ? std::max(0.0, t1 - per_sweep) : 0.0;
-            const double total = (double)((S + kSlabChunk - 1) / kSlabChunk) * load + S * per_sweep;
+            const int chunk = v == BqVariant::Slab ? kSlabChunk : kClusterChunk;
+            const double total = (double)((S + chunk - 1) / chunk) * load + S * per_sweep;
             ms = (float)(total * 2.0 / S);  // per four half-sweeps, as the others
         } else {
             time_it(v, 0, &ms);
@@ -830,7 +910,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStrea
     ds.variant = best;
     if (best == BqVariant::Bits) ds.bits_rt = best_rt;
     if (best == BqVariant::Slab) ds.slab_rs = best_rt;
-    ctx->bq_tuned[shape] = {ds.variant, best == BqVariant::Slab ? ds.slab_rs : ds.bits_rt};
+    if (cache) ctx->bq_tuned[shape] = {ds.variant, best == BqVariant::Slab ? ds.slab_rs : ds.bits_rt};
     return PBIT_OK;
 }
 
@@ -912,6 +992,21 @@ static bool bits_preferred(const Problem &P, int R, int cus)
 {
     const int Rp = round_up(R, kEaRPad);
     return bit_sweep_us(P, Rp, bit_pick_rs(P, Rp, cus), cus) < 8.0 + 0.5e-6 * (double)P.N * R;
+}
+
+// The kernel that runs a biclique's sweeps when the cluster kernel's workgroups could not be
+// resident together (MA and MB hold the spins): as without timing.
+static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStream_t st)
+{
+    ctx->bq_cluster_skip = kClusterSkip;
+    const bool large = P.bq.na_p % 128 == 0 && P.bq.nb_p % 128 == 0;
+    ds.variant = bq_slab_supported(P.bq, ds.Rp, ds.width, 0) ? BqVariant::Slab
+                 : ds.MAb ? BqVariant::Bits : large ? BqVariant::Dma : BqVariant::Small;
+    ds.slab = ds.variant == BqVariant::Slab;
+    ds.bits = ds.variant == BqVariant::Bits;
+    ds.chunk = ds.slab ? kSlabChunk : 1;
+    ctx->bq_last_variant = (int)ds.variant;
+    return ds.bits ? bqb_pack(P.bq, ds.MA, ds.MB, ds.MAb, ds.MBb, ds.Rp, st) : hipSuccess;
 }
 
 static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, hipStream_t st, DevState &ds,
@@ -1027,11 +1122,13 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     if (e != hipSuccess) return device_fail(ctx, e, "hipMemcpyAsync (table)");
 
     if (P.kind == PBIT_BICLIQUE && d->n_sweeps > 0) {
-        rc = tune_biclique(ctx, P, ds, st, d->n_sweeps);
+        rc = tune_biclique(ctx, P, d, ds, st);
         if (rc) return rc;
     }
     ds.bits = P.kind == PBIT_BICLIQUE && ds.variant == BqVariant::Bits;
-    if (P.kind == PBIT_BICLIQUE && ds.variant == BqVariant::Slab) ds.slab = true;  // runs of sweeps per launch
+    // runs of sweeps per launch
+    if (P.kind == PBIT_BICLIQUE) ds.slab = ds.variant == BqVariant::Slab || ds.variant == BqVariant::Cluster;
+    ds.chunk = !ds.slab ? 1 : ds.variant == BqVariant::Cluster ? kClusterChunk : kSlabChunk;
     if (P.kind == PBIT_EA3D && d->n_sweeps > 0)
         ctx->ea_last_path = ds.slab && P.N <= kEaSlabMaxSites ? 2 : (ds.mfma ? 3 : 1);
     if (P.kind == PBIT_GRAPH && d->n_sweeps > 0) ctx->graph_last_path = ds.slab ? 2 : 1;
@@ -1095,6 +1192,25 @@ static hipError_t sweep(pbit_ctx *ctx, const Problem &P, DevState &ds, int s, ui
 static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, int s1, uint32_t sweep0,
                          uint32_t rq0, Key key, hipStream_t st)
 {
+    if (ds.variant == BqVariant::Cluster) {
+        const bool timed = ctx->prof_every > 0 && ctx->prof_open < 0;
+        hipError_t e = timed ? prof_begin(ctx, P.kind, st) : hipSuccess;
+        if (e == hipSuccess)
+            e = bq_cluster(P.bq, ds.MA, ds.MB, ds.R, ds.Rp, ds.table, ds.width, s0, s1, sweep0, rq0, key,
+                           ds.cluster_work, compute_units(ctx), st);
+        if (e == hipSuccess && timed) {
+            ctx->prof_launches.back() += 2 * (s1 - s0);
+            e = prof_close(ctx, st);
+        }
+        int status = 0;
+        if (e == hipSuccess) e = cluster_status(ds, st, &status);
+        if (e != hipSuccess || status == 0) return e;
+        if (status != 1) return hipErrorLaunchFailure;
+        e = cluster_fallback(ctx, P, ds, st);
+        for (int s = s0; s < s1 && e == hipSuccess; s += ds.chunk)
+            e = sweeps(ctx, P, ds, s, std::min(s1, s + ds.chunk), sweep0, rq0, key, st);
+        return e;
+    }
     if (!ds.slab) {
         for (int s = s0; s < s1; ++s) {
             hipError_t e = sweep(ctx, P, ds, s, sweep0 + (uint32_t)s, rq0, key, st);
@@ -1232,6 +1348,7 @@ int run_blocking(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, pbi
 {
     const hipStream_t st = ctx->stream;
     DevState ds;
+    const WorkRelease release{ctx};
     int rc = prepare(ctx, P, d, st, ds, nullptr);
     if (rc) return rc;
     const Key key{(uint32_t)d->seed, (uint32_t)(d->seed >> 32)};
@@ -1247,7 +1364,7 @@ int run_blocking(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, pbi
     }
     for (int s = 0; s < d->n_sweeps && !hit;) {
         // up to the next energy check (every sweep on the per-half-sweep path)
-        int s1 = ds.slab ? std::min(d->n_sweeps, s + kSlabChunk) : s + 1;
+        int s1 = std::min(d->n_sweeps, s + ds.chunk);
         if (check > 0) s1 = std::min(s1, (s / check + 1) * check);
         hipError_t e = sweeps(ctx, P, ds, s, s1, (uint32_t)d->sweep_offset, rq0, key, st);
         if (e != hipSuccess) return device_fail(ctx, e, "sweep launch");
@@ -1354,6 +1471,7 @@ int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_
                int64_t *d_energies, hipStream_t st, Arena *arena)
 {
     DevState ds;
+    const WorkRelease release{ctx};
     ds.arena = arena;
     int rc = prepare(ctx, P, d, st, ds, spins_in ? d_spins : nullptr);
     if (rc) return rc;
@@ -1361,7 +1479,7 @@ int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_
     const uint32_t rq0 = (uint32_t)d->replica_offset >> 2;
     auto loop = [&]() -> hipError_t {
         for (int s = 0; s < d->n_sweeps;) {
-            const int s1 = ds.slab ? std::min(d->n_sweeps, s + kSlabChunk) : s + 1;
+            const int s1 = std::min(d->n_sweeps, s + ds.chunk);
             hipError_t e = sweeps(ctx, P, ds, s, s1, (uint32_t)d->sweep_offset, rq0, key, st);
             if (e != hipSuccess) return e;
             s = s1;

@@ -29,7 +29,7 @@ struct Problem {
     int jobs = 0;  // serving jobs that still reference the problem
 };
 
-enum class Slot : int { Spins = 0, Table, E32, Stage, Aux, Snap, Hit, Count };
+enum class Slot : int { Spins = 0, Table, E32, Stage, Aux, Snap, Hit, Work, Count };
 
 struct Scratch {
     void *ptr = nullptr;
@@ -74,6 +74,8 @@ struct pbit_ctx {
     // biclique kernel variant: forced (PBIT_BQ_VARIANT) or autotuned per shape
     pbit::BqVariant bq_forced = pbit::BqVariant::Auto;
     int bq_last_variant = 0;  // biclique half-sweep variant of the latest biclique anneal (0: none yet)
+    bool work_busy = false;   // an anneal uses Slot::Work
+    int bq_cluster_skip = 0;  // anneals until the cluster kernel is tried again, after it could not be resident
     int bq_bits_rt = 0;       // replicas per tile of the bit kernel (PBIT_BQ_BITS_RT: 64, 128, 256; 0 = by size)
     int bq_slab_rs = 0;       // replicas per slice of the LDS-resident kernel (PBIT_BQ_SLAB_RS: 16, 8; 0 = timed)
     bool ea_stream_forced = false;  // cubes always take the streaming stencil (PBIT_EA_STREAM=1)
