@@ -18,7 +18,7 @@ struct BqJobDev {
     const int8_t *J, *JT;     // int8 couplings [na_p][nb_p], [nb_p][na_p]
     const int8_t *Jb, *JTb;   // couplings in the widened-bit column order, scaled (bit tiles)
     const int32_t *hA2, *hB2; // field plus coupling sum per site (bit tiles)
-    const uint32_t *J2, *JT2; // J + 1 as two-bit codes in fragment order (int8 tiles)
+    const uint32_t *J2;       // both sides' couplings as two-bit codes in fragment order (FP4 tiles)
     const int8_t *hA, *hB;    // [na_p], [nb_p]
     const uint32_t *table;    // [S][width]
     uint8_t *state;           // [tiles][RS][row]: row r = side A then side B, as int8 (na_p + nb_p
@@ -56,6 +56,9 @@ struct WorkItem {
 
 constexpr int kGraphTileThreads = 512;
 constexpr int kBqTileThreads = 512;
+
+// Sweeps whose threshold rows a biclique tile holds at a time (16 KiB of them, or one).
+constexpr int bq_tile_rows(int width) { return width >= 4096 ? 1 : width <= 256 ? 16 : 4096 / width; }
 
 // Launch a persistent kernel over `n_items` items; `counter` (device int,
 // zeroed by the caller) hands out item indices.

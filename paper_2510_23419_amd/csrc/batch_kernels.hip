@@ -235,40 +235,19 @@ __global__ __launch_bounds__(kGraphTileThreads) void k_graph_slab(GraphJobDev jb
 
 // ---------------------------------------------------------------- biclique tiles
 
-// A tile holds RB x 32 replicas of both sides in LDS, one row per replica:
-// side A in columns [0, na_p), side B in [na_p, na_p + nb_p), padding zero.
+// A tile holds RB x 32 replicas of both sides in LDS, one row per replica, padding zero.
 // Each half-sweep is an MFMA product of the LDS spin rows with the couplings
 // streamed from global memory (L2-resident, shared by all tiles of the job),
 // followed by the decision epilogue writing the new side into LDS.
-constexpr int kRing = 4;  // K-units of J fragments in flight per site block
+constexpr int kRing = 4;      // K-units of J fragments in flight per site block (bit tiles)
+constexpr int kCodeRing = 4;  // K steps of coupling codes in flight per site block (FP4 tiles)
 
-// 4 x 4 byte transpose across a quad of lanes: lane u holds bytes M[u][0..3]
-// and receives M[0..3][u].  Two exchanges (partners u ^ 1, then u ^ 2), each a
-// DPP quad permutation and one byte permute.
-__device__ __forceinline__ uint32_t quad_transpose(uint32_t d, int u)
+// The FP4 operand (32 K values of a lane) of two words of coupling codes: nibble i of dword
+// 2 d + e is bits 3 - e (sign) and 1 - e (set: +-1, else 0) of nibble i of word d.
+__device__ __forceinline__ v4i widen_codes(v2i_t x, uint32_t mask)
 {
-    // v_perm_b32 selects bytes of {src0:src1} as a 64-bit value: selector byte
-    // values 0..3 pick src1 bytes, 4..7 pick src0 bytes
-    const uint32_t t = (uint32_t)__builtin_amdgcn_mov_dpp((int)d, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
-    // even u: (d0, t0, d2, t2); odd u: (t1, d1, t3, d3); here src0 = t, src1 = d
-    const uint32_t d1 = __builtin_amdgcn_perm(t, d, (u & 1) ? 0x03070105u : 0x06020400u);
-    const uint32_t t2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)d1, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
-    // u < 2: (d1_0, d1_1, t2_0, t2_1); u >= 2: (t2_2, t2_3, d1_2, d1_3)
-    return __builtin_amdgcn_perm(t2, d1, (u & 2) ? 0x03020706u : 0x05040100u);
-}
-
-// Four dwords of int8 K bytes from one word of two-bit codes: byte i of dword j is
-// the code at bits 2 j, 2 j + 1 of byte i (the value J + 1 in {0, 1, 2}).
-__device__ __forceinline__ v4i widen_codes(uint32_t x)
-{
-    return v4i{(int)(x & 0x03030303u), (int)((x >> 2) & 0x03030303u), (int)((x >> 4) & 0x03030303u),
-               (int)((x >> 6) & 0x03030303u)};
-}
-
-// Sum of the four bytes of x.
-__device__ __forceinline__ int byte_sum(uint32_t x)
-{
-    return (int)((x & 0xFFu) + ((x >> 8) & 0xFFu) + ((x >> 16) & 0xFFu) + (x >> 24));
+    const int m = (int)mask;
+    return v4i{x[0] & m, (x[0] << 1) & m, x[1] & m, (x[1] << 1) & m};
 }
 
 // Biclique tiles with the spins held as bits in LDS: row r holds one bit per site (set = -1), 32 sites per word, side A
@@ -280,7 +259,7 @@ __device__ __forceinline__ int byte_sum(uint32_t x)
 // 8 sum_k J_sk b_k and the field is I = (h + sum_k J) - (acc >> 2), exact.
 // A bit row is an eighth of an int8 row, so 128 replicas fit LDS at any side
 // length and each coupling fragment feeds RB MFMAs: couplings reach the CU at
-// 1 / (32 RB) bytes per multiply-add.  Decisions as in the int8 tiles; the 64
+// 1 / (32 RB) bytes per multiply-add.  The 64
 // decisions of a wave for one (replica group, p) form a ballot mask, and the
 // words of the 32 replicas of a block are written by one lane each.
 template <int RB>
@@ -441,30 +420,38 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles_bits(const BqJobDev
     }
 }
 
-// A tile holds RB x 32 replicas of both sides in LDS, one row per replica:
-// side A first, then side B, zero padding.  With int8 operands a row holds one
-// byte per site and the half-sweep is the int8 MFMA with int32
-// accumulation; the couplings stream as two-bit codes of J + 1 (a quarter of
-// the int8 bytes: these tiles are bound by how fast a CU pulls couplings from
-// L2), widened to bytes in registers, and the field is the product minus the
-// replica's sum over the other side's spins.  Each half-sweep multiplies the LDS rows by the
-// couplings streamed from global memory (L2-resident, shared by all tiles of
-// the job); each coupling fragment feeds RB MFMAs, so larger tiles stream
-// fewer bytes per replica.  The decision epilogue writes the new side into LDS.
-template <int RB>
-__global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles(const BqJobDev *__restrict__ jobs,
+// A tile holds RB x 32 replicas of both sides in LDS, one row per replica, side A first:
+// four bits a site, +1, -1 or (padding) 0 as E2M1 numbers, 32 sites in 16 bytes with site
+// 4 i + j at nibble i of dword j.  A half-sweep multiplies the rows by the couplings on the
+// FP4 MFMA, 64 sites a step: products are -1, 0 or 1 and the float sums stay below 2^20 from
+// a start of 1.5 x 2^21, where the accumulator's bits are kFieldBase + 4 sum exactly, so |4 I| is
+// one v_sad away and indexes the sweep's threshold row.  Couplings stream from the L2 (shared
+// by all tiles of the job) as two-bit codes, two instructions from the MFMA's operand, and
+// each fragment feeds RB MFMAs.
+//
+// What bounds it: instruction issue.  A block of 32 sites x 32 replicas takes about 140 vector
+// instructions for its random words and as many for its decisions, and each K step an MFMA of
+// 32 cycles and 6 instructions for the codes, which do not overlap (56 cycles a step); the
+// sum of these is the measured 13.5 us a sweep of a tile at 1022 sites per side.  A tile of 32
+// replicas alone on a compute unit took 33 us there with int8 operands (27 against 11 at 876,
+// where 16 waves against 8 gave 15 to 19): half the MFMA time, an eighth of the LDS reads.
+// Deeper rings than four steps changed nothing at 16 waves.
+template <int RB, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_bq_tiles(const BqJobDev *__restrict__ jobs,
                                                              const WorkItem *__restrict__ items,
                                                              const int32_t *__restrict__ n_items_p,
-                                                             int32_t *__restrict__ counter, uint32_t one)
+                                                             int32_t *__restrict__ counter, uint32_t)
 {
     constexpr int RS = 32 * RB;
     extern __shared__ uint4 dyn[];
     __shared__ int32_t eacc[RS];
-    __shared__ int32_t mag[RS];  // sum of the other side's spins per replica
     __shared__ int slot;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6, ln = lane & 31, kg = lane >> 5;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), ln = lane & 31, kg = lane >> 5;
     const int n_items = *n_items_p;
+    v16f_t bias;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) bias[j] = __uint_as_float(kFieldBase);
 
     for (;;) {
         const int it = take_item(counter, &slot);
@@ -472,174 +459,153 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles(const BqJobDev *__r
         const WorkItem w = items[it];
         const BqJobDev jb = jobs[w.job];
         const int na = jb.na, nb = jb.nb, na_p = jb.na_p, nb_p = jb.nb_p;
-        const int pa = na_p, pb = nb_p;  // bytes of each side in a row
-        const int PR = pa + pb, pitch = PR + 16;
+        const int PR = na_p + nb_p, pitch = PR / 2 + 16;  // sites of a row, bytes between rows (an odd number of 16)
         uint8_t *sp = reinterpret_cast<uint8_t *>(dyn);
-        // decision words of the sweep: S(I) = Tm(|I|) for I >= 0, 2^32 - Tm(|I|) for I < 0,
-        // I in [-top, top] (RS * pitch is a multiple of 16, so the words are aligned)
-        uint64_t *Sw = reinterpret_cast<uint64_t *>(sp + (size_t)RS * pitch);
-        const char *Sb = reinterpret_cast<const char *>(Sw);
+        uint32_t *rows = reinterpret_cast<uint32_t *>(sp + (size_t)RS * pitch);  // threshold rows of some sweeps
+        const int n_rows = bq_tile_rows(jb.width);
+        int8_t *fields = reinterpret_cast<int8_t *>(rows + n_rows * jb.width);  // of both sides
         uint8_t *gst = jb.state + (size_t)w.tile * RS * PR;
         const uint32_t rg0 = jb.rq0 + (uint32_t)(w.tile * (RS / 4));
+        // the dword and bit of a site (side B's from na_p on) in its row
+        auto dword = [&](int r, int i) { return reinterpret_cast<uint32_t *>(sp + r * pitch) + 4 * (i >> 5) + (i & 3); };
+        auto shift = [](int i) { return (i & 28); };
 
         if (w.init) {
-            for (int k = tid; k < RS * pitch / 16; k += kBqTileThreads) dyn[k] = make_uint4(0, 0, 0, 0);
+            for (int k = tid; k < RS * pitch / 16; k += THREADS) dyn[k] = make_uint4(0, 0, 0, 0);
             __syncthreads();
-            // thread (byte column, replica group): one byte in each of four rows
-            for (int k = tid; k < PR * (RS / 4); k += kBqTileThreads) {
-                const int g = k % (RS / 4), pi = k / (RS / 4);
-                const bool A = pi < pa;
-                const int s0 = A ? pi : pi - pa, n = A ? na : nb;
-                if (s0 >= n) continue;
-                const uint32_t i0 = (uint32_t)(A ? s0 : na + s0);
-                const Block4 b0 = philox(i0, 0u, rg0 + (uint32_t)g, kDomainInit, jb.k0, jb.k1);
+            // thread (site, replica group): one nibble in each of four rows
+            for (int k = tid; k < (na + nb) * (RS / 4); k += THREADS) {
+                const int g = k % (RS / 4), i = k / (RS / 4);
+                const int at = i < na ? i : na_p + (i - na);
+                const Block4 b = philox((uint32_t)i, 0u, rg0 + (uint32_t)g, kDomainInit, jb.k0, jb.k1);
 #pragma unroll
-                for (int p = 0; p < 4; ++p) sp[(4 * g + p) * pitch + pi] = (uint8_t)init_spin(b0.w[p]);
+                for (int p = 0; p < 4; ++p)
+                    atomicOr(dword(4 * g + p, at), (init_spin(b.w[p]) < 0 ? 0xAu : 0x2u) << shift(at));
             }
         } else {
-            for (int k = tid; k < RS * (PR / 16); k += kBqTileThreads) {
+            // 16 int8 spins of a row to a halfword in each of four dwords
+            for (int k = tid; k < RS * (PR / 16); k += THREADS) {
                 const int r = k / (PR / 16), c16 = k % (PR / 16);
-                *reinterpret_cast<uint4 *>(sp + r * pitch + 16 * c16) =
-                    *reinterpret_cast<const uint4 *>(gst + (size_t)r * PR + 16 * c16);
+                const uint4 x = *reinterpret_cast<const uint4 *>(gst + (size_t)r * PR + 16 * c16);
+                const uint32_t y[4] = {x.x, x.y, x.z, x.w};
+                uint32_t h[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t t = ((y[i] >> 4) & 0x08080808u) | ((y[i] & 0x01010101u) << 1);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) h[j] |= ((t >> (8 * j)) & 15u) << (4 * i);
+                }
+                uint16_t *d = reinterpret_cast<uint16_t *>(dword(r, 16 * c16)) + (c16 & 1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[2 * j] = (uint16_t)h[j];
             }
         }
         if (tid < RS) eacc[tid] = 0;
+        for (int k = tid; k < PR; k += THREADS) fields[k] = k < na_p ? jb.hA[k] : jb.hB[k - na_p];
+
+        // coupling codes of both sides, read by a uniform offset and the lane's own
+        const int side_b = na_p * nb_p / 4;
+        const __amdgpu_buffer_rsrc_t codes = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint32_t *>(jb.J2), 0, (uint32_t)(2 * side_b), 0x00027000);  // reads past the end give zero
+        constexpr int kUnit = 512;  // bytes from one K step to the next
+        constexpr int kStep = THREADS / 64;
+        auto fetch = [&](int from, int u) {
+            return __builtin_bit_cast(v2i_t, __builtin_amdgcn_raw_buffer_load_b64(codes, 8 * lane + kUnit * u, from, 0));
+        };
+        v2i_t ring[kCodeRing];
+#pragma unroll
+        for (int u = 0; u < kCodeRing; ++u) ring[u] = fetch(kUnit * (nb_p / 64) * wave, u);
 
         for (int s = w.s_begin; s < w.s_end; ++s) {
-            __syncthreads();
-            const uint32_t *trow = jb.table + (size_t)s * jb.width;
-            const int top = jb.width - 1;
-            for (int e = tid; e <= 2 * top; e += kBqTileThreads) {
-                const int I = e - top;
-                const uint32_t Tm = load_global<uint32_t>(trow + (I >= 0 ? I : -I));
-                Sw[e] = I >= 0 ? (uint64_t)Tm : ((uint64_t)1 << 32) - Tm;
+            const int kr = (s - w.s_begin) % n_rows;
+            if (kr == 0) {
+                __syncthreads();
+                const uint32_t *trow = jb.table + (size_t)s * jb.width;
+                const int count = min(n_rows, w.s_end - s) * jb.width;
+                for (int e = tid; e < count; e += THREADS) rows[e] = load_global<uint32_t>(trow + e);
+                __syncthreads();
             }
-            __syncthreads();
+            const uint32_t row = lds_address(rows) + 4u * (uint32_t)(kr * jb.width);
+            const uint32_t row_end = row + 4u * (uint32_t)(jb.width - 1);
             const uint32_t t = jb.sweep0 + (uint32_t)s;
             const bool last = s + 1 == w.s_end;
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
-                const int ns_p = side == 0 ? na_p : nb_p;
                 const int ns = side == 0 ? na : nb;
-                const int ko = side == 0 ? pb : pa;         // bytes per coupling row (the other side)
-                const int in_col = side == 0 ? pa : 0;      // bytes of the other side (A operand)
-                const int out_col = side == 0 ? 0 : pa;     // bytes of this side
-                const uint8_t *Jx = reinterpret_cast<const uint8_t *>(side == 0 ? jb.J2 : jb.JT2);
-                const int8_t *hs = side == 0 ? jb.hA : jb.hB;
+                const int no = side == 0 ? nb : na, no_p = side == 0 ? nb_p : na_p;  // the other side
+                const uint8_t *in = sp + (side == 0 ? na_p / 2 : 0) + ln * pitch + 16 * kg;
+                uint8_t *out = sp + (side == 0 ? 0 : na_p / 2);
                 const uint32_t site_base = side == 0 ? 0u : (uint32_t)na;
-                // one 32-site block per wave at a time; its coupling fragments stream
-                // from global memory through a ring kRing K-units (32 bytes) ahead.
-                // Past the end of a block the ring fills with the first units of the
-                // wave's next block, so that they arrive during this block's epilogue.
-                const int nku = ko / 32;
-                constexpr int kStep = kBqTileThreads / 64;
-                const int nblk = ns_p / 32;
-                {
-                    // the other side's spin sum per replica, padding sites included (their
-                    // codes are 1): T threads per row, bytewise
-                    // counts of nonzero and of -1 spins (at most 72 per byte for the
-                    // row lengths that fit LDS), then a sum over the T lanes
-                    constexpr int T = kBqTileThreads / RS;
-                    const int r = tid / T, part = tid % T;
-                    const uint4 *row = reinterpret_cast<const uint4 *>(sp + r * pitch + in_col);
-                    uint32_t nz = 0u, neg = 0u;
-#pragma unroll 4
-                    for (int d = part; d < ko / 16; d += T) {
-                        const uint4 x = row[d];
-                        nz += (x.x & 0x01010101u) + (x.y & 0x01010101u) + (x.z & 0x01010101u) + (x.w & 0x01010101u);
-                        neg += ((x.x >> 7) & 0x01010101u) + ((x.y >> 7) & 0x01010101u) + ((x.z >> 7) & 0x01010101u) +
-                               ((x.w >> 7) & 0x01010101u);
-                    }
-                    int v = byte_sum(nz) - 2 * byte_sum(neg);
+                // one 32-site block per wave at a time; its coupling codes stream from global
+                // memory through a ring kCodeRing K steps ahead.  Past the end of a block the
+                // ring fills with the first steps of the wave's next block, of the other side
+                // after the last one, so that they arrive during the decisions and the barrier.
+                const int nku = (no + 63) / 64, nblk = (ns + 31) / 32;
+                const int per_block = kUnit * (no_p / 64);
+                const int start = side == 0 ? 0 : side_b, other = side == 0 ? side_b : 0;
+                const int other_start = other + kUnit * ((side == 0 ? na_p : nb_p) / 64) * wave;
+                if (wave >= nblk)
 #pragma unroll
-                    for (int off = T / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-                    if (part == 0) mag[r] = v;
-                    __syncthreads();
-                }
-                // coupling fragments: [K step][site block] of one word of codes per lane,
-                // 64 words per K step and block
-                using Frag = uint32_t;
-                auto frag_ptr = [&](int blk) -> const uint8_t * {
-                    return Jx + 4 * (((size_t)blk * nku * 2 + kg) * 32 + ln);
-                };
-                constexpr int kUnit = 256;  // bytes from one K step of a fragment to the next
-                Frag ring[kRing];
-                if (wave < nblk) {
-                    const uint8_t *br0 = frag_ptr(wave);
-#pragma unroll
-                    for (int u = 0; u < kRing; ++u)
-                        ring[u] = load_global<Frag>(br0 + (size_t)kUnit * min(u, nku - 1));
-                }
+                    for (int u = 0; u < kCodeRing; ++u) ring[u] = fetch(other_start, u);
                 for (int blk = wave; blk < nblk; blk += kStep) {
                     const int site = blk * 32 + ln;
-                    const uint8_t *br = frag_ptr(blk);
-                    // the next block of this wave, or this one again when there is none
-                    const uint8_t *bn = blk + kStep < nblk ? frag_ptr(blk + kStep) : br;
-                    v16i acc[RB];
+                    const int br = start + per_block * blk;
+                    const int bn = blk + kStep < nblk ? br + per_block * kStep : other_start;
+                    const int hval = fields[(side == 0 ? 0 : na_p) + site];  // padded fields are zero
+                    v16f_t acc[RB];
 #pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) acc[rb] = v16i{0};
-                    const uint8_t *abase = sp + ln * pitch + in_col + 16 * kg;
-                    for (int kb = 0; kb < nku; kb += kRing) {
+                    for (int rb = 0; rb < RB; ++rb) acc[rb] = bias;
+                    for (int kb = 0; kb < nku; kb += kCodeRing) {
+                        const int ahead = br + kUnit * (kb + kCodeRing);
+                        v4i a[kCodeRing][RB];
 #pragma unroll
-                        for (int u = 0; u < kRing; ++u) {
-                            const int ku = kb + u;
-                            if (ku < nku) {
-                                const v4i b = widen_codes(ring[u]);
-                                // slot u takes unit ku + kRing of this block, or, after this
-                                // block's last unit of its residue class, unit u of the next block
-                                const int kn = ku + kRing;
-                                ring[u] = load_global<Frag>(kn < nku ? br + (size_t)kUnit * kn
-                                                                     : bn + (size_t)kUnit * min(u, nku - 1));
+                        for (int u = 0; u < kCodeRing; ++u)
 #pragma unroll
-                                for (int rb = 0; rb < RB; ++rb) {
-                                    const v4i a = *reinterpret_cast<const v4i *>(abase + rb * 32 * pitch + 32 * ku);
-                                    acc[rb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[rb], 0, 0, 0);
-                                }
-                            }
+                            for (int rb = 0; rb < RB; ++rb)
+                                a[u][rb] = *reinterpret_cast<const v4i *>(in + rb * 32 * pitch + 32 * (kb + u));
+#pragma unroll
+                        for (int u = 0; u < kCodeRing; ++u) {
+                            const v4i b = widen_codes(ring[u], kb + u < nku ? 0xAAAAAAAAu : 0u);
+                            // slot u takes the step a ring ahead in this block, or, after this
+                            // block's last step of its residue class, step u of the next block
+                            ring[u] = fetch(kb + kCodeRing + u < nku ? ahead : bn, u);
+#pragma unroll
+                            for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma_fp4(a[u][rb], b, acc[rb]);
                         }
                     }
-                    // decisions: the field F of a replica and site indexes S(F + h)
-                    // (clamped to [-top, top]); the sign bits of a group's four
-                    // replicas become spin codes, one per byte, transposed across the
-                    // lane quad (sites s .. s + 3) so that each lane writes four
-                    // consecutive sites of one replica row.
-                    // Padding sites may take any value: their couplings and fields are
-                    // zero and they are never returned.
-                    const int hval = load_global<int8_t>(hs + site);  // site < ns_p: padded fields are zero
-                    const bool site_ok = site < ns;
-                    const int flo = -top - hval, fhi = top - hval;  // F range whose F + h is in [-top, top]
-                    const int base8 = 8 * (hval + top);
-                    const int u4 = ln & 3;
-                    const int quad_col = out_col + site - u4;
+                    const uint32_t mid = kFieldBase - 4u * (uint32_t)hval;  // the accumulator at I = 0
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
+                        uint32_t x[16], T[16];
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) {
+                            x[j] = __float_as_uint(acc[rb][j]);
+                            T[j] = lds_word(min(sad(x[j], mid, row), row_end));  // at most its last entry
+                        }
+                        __builtin_amdgcn_sched_barrier(0);  // the reads go out together, before the random words
+                        uint32_t outw = 0u;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             const int r4 = rb * 32 + 8 * q + 4 * kg;  // first replica of the group in the tile
                             const Block4 b = philox(site_base + (uint32_t)site, t, rg0 + (uint32_t)(r4 >> 2),
                                                     kDomainSweep, jb.k0, jb.k1);
-                            uint32_t sgn[4];  // 1: the replica's new spin is -1
 #pragma unroll
                             for (int p = 0; p < 4; ++p) {
-                                // an exact integer; with codes of J + 1 the product exceeds the
-                                // field by the replica's spin sum over the other side
-                                const int F = (int)acc[rb][4 * q + p] - mag[r4 + p];
-                                const int Fc = min(max(F, flo), fhi);
-                                const uint64_t S = *static_cast<const uint64_t *>(
-                                    __builtin_assume_aligned(Sb + 8 * Fc + base8, 8));
-                                sgn[p] = (uint32_t)(((uint64_t)b.w[p] * one + S) >> 32);
+                                const uint64_t m = heat_bath(b.w[p], T[4 * q + p], x[4 * q + p], mid);
                                 // energy after the last side-B update: E = -sum_b m_b I_b - sum_a h_a m_a
-                                if (side == 1 && last && site_ok)
-                                    atomicAdd(&eacc[r4 + p], (sgn[p] ? 1 : -1) * (F + hval));
+                                if (side == 1 && last && site < ns) {
+                                    const int I = (int)(x[4 * q + p] - mid) >> 2;
+                                    atomicAdd(&eacc[r4 + p], (m >> lane) & 1u ? I : -I);
+                                }
+                                const int L = 8 * q + p;
+                                outw = (uint32_t)lane_write((int)(uint32_t)m, L, (int)outw);
+                                outw = (uint32_t)lane_write((int)(uint32_t)(m >> 32), L + 4, (int)outw);
                             }
-                            const uint32_t lo = __builtin_amdgcn_perm(sgn[1], sgn[0], 0x0C0C0400u);
-                            const uint32_t hi = __builtin_amdgcn_perm(sgn[3], sgn[2], 0x0C0C0400u);
-                            // sign bit 0 -> +1, 1 -> -1: 0x01 / 0xFF bytes
-                            const uint32_t packed = __builtin_amdgcn_perm(0u, 0xFF01u,
-                                                                          __builtin_amdgcn_perm(hi, lo, 0x05040100u));
-                            const uint32_t x = quad_transpose(packed, u4);  // four sites, one byte each
-                            *reinterpret_cast<uint32_t *>(sp + (r4 + u4) * pitch + quad_col) = x;
                         }
+                        // lane r: the 32 new spins of replica r (padding sites take any value:
+                        // their couplings and fields are zero and they are never returned)
+                        if (lane < 32)
+                            *reinterpret_cast<v4i *>(out + (rb * 32 + lane) * pitch + 16 * blk) = spin_nibbles(outw);
                     }
                 }
                 __syncthreads();
@@ -647,19 +613,28 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles(const BqJobDev *__r
         }
 
         // field part of side A, then the energies and the spins go back to global memory
-        for (int k = tid; k < RS * na; k += kBqTileThreads) {
+        __syncthreads();
+        for (int k = tid; k < RS * na; k += THREADS) {
             const int r = k / na, a = k % na;
-            const int m = (int)(int8_t)sp[r * pitch + a];
-            const int v = (int)jb.hA[a] * m;
-            if (v != 0) atomicAdd(&eacc[r], -v);
+            const int v = (int)jb.hA[a];
+            if (v != 0) atomicAdd(&eacc[r], (*dword(r, a) >> shift(a)) & 8u ? v : -v);
         }
         __syncthreads();
         if (tid < RS) jb.energy[w.tile * RS + tid] = eacc[tid];
-        for (int k = tid; k < RS * (PR / 16); k += kBqTileThreads) {
+        for (int k = tid; k < RS * (PR / 16); k += THREADS) {
             const int r = k / (PR / 16), c16 = k % (PR / 16);
-            *reinterpret_cast<uint4 *>(gst + (size_t)r * PR + 16 * c16) =
-                *reinterpret_cast<const uint4 *>(sp + r * pitch + 16 * c16);
+            const uint16_t *d = reinterpret_cast<const uint16_t *>(dword(r, 16 * c16)) + (c16 & 1);
+            uint32_t y[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t n = (uint32_t)d[2 * j] >> (4 * i);
+                    y[i] |= (n & 2u ? (n & 8u ? 0xFFu : 1u) : 0u) << (8 * j);
+                }
+            *reinterpret_cast<uint4 *>(gst + (size_t)r * PR + 16 * c16) = make_uint4(y[0], y[1], y[2], y[3]);
         }
+        __syncthreads();
     }
 }
 
@@ -671,10 +646,10 @@ size_t bq_tile_lds(int rs, int na_p, int nb_p, int width, int mode)
 {
     // spin rows, then one 64-bit decision word per field value in [-(width - 1), width - 1]
     size_t rows;
-    if (mode == kTileBits)
-        rows = sizeof(uint32_t) * (size_t)((rs * ((na_p + nb_p) / 32 + 1) + 1) & ~1);
-    else
-        rows = (size_t)rs * ((size_t)(na_p + nb_p) + 16);
+    if (mode != kTileBits)  // four bits a site, threshold rows of some sweeps, fields
+        return (size_t)rs * ((size_t)(na_p + nb_p) / 2 + 16) + sizeof(uint32_t) * (size_t)(bq_tile_rows(width) * width) +
+               (size_t)(na_p + nb_p);
+    rows = sizeof(uint32_t) * (size_t)((rs * ((na_p + nb_p) / 32 + 1) + 1) & ~1);
     return rows + sizeof(uint64_t) * (size_t)(2 * width - 1);
 }
 
@@ -710,8 +685,8 @@ hipError_t tiles_set_lds_limit()
     const void *bq_kernels[] = {reinterpret_cast<const void *>(&k_bq_tiles_bits<1>),
                                 reinterpret_cast<const void *>(&k_bq_tiles_bits<2>),
                                 reinterpret_cast<const void *>(&k_bq_tiles_bits<4>),
-                                reinterpret_cast<const void *>(&k_bq_tiles<1>),
-                                reinterpret_cast<const void *>(&k_bq_tiles<2>)};
+                                reinterpret_cast<const void *>(&k_bq_tiles<1, 1024>),
+                                reinterpret_cast<const void *>(&k_bq_tiles<2, 512>)};
     for (const void *k : bq_kernels)
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
     return e;
@@ -728,17 +703,17 @@ hipError_t graph_tiles(const GraphJobDev *jobs, const WorkItem *items, const int
 hipError_t bq_tiles(const BqJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter, int rs,
                     int mode, int grid, size_t lds_bytes, hipStream_t st)
 {
-#define PBIT_BQ_TILES(K)                                                                                        \
-    hipLaunchKernelGGL(K, dim3((unsigned)grid), dim3(kBqTileThreads), lds_bytes, st, jobs, items, n_items, counter, 1u)
+#define PBIT_BQ_TILES(K, THREADS)                                                                                        \
+    hipLaunchKernelGGL(K, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, jobs, items, n_items, counter, 1u)
     const int rb = rs == 128 ? 4 : rs == 64 ? 2 : rs == 32 ? 1 : 0;
     if (rb == 0 || (mode != kTileInt8 && mode != kTileBits)) return hipErrorInvalidValue;
     if (mode == kTileBits) {
-        if (rb == 4) PBIT_BQ_TILES((k_bq_tiles_bits<4>)); else if (rb == 2) PBIT_BQ_TILES((k_bq_tiles_bits<2>));
-        else PBIT_BQ_TILES((k_bq_tiles_bits<1>));
+        if (rb == 4) PBIT_BQ_TILES((k_bq_tiles_bits<4>), kBqTileThreads); else if (rb == 2) PBIT_BQ_TILES((k_bq_tiles_bits<2>), kBqTileThreads);
+        else PBIT_BQ_TILES((k_bq_tiles_bits<1>), kBqTileThreads);
     } else {
-        // int8 rows come in 32- and 64-replica tiles (a 128-replica int8 tile spills registers)
+        // FP4 rows come in 32- and 64-replica tiles (128 replicas would spill registers)
         if (rb == 4) return hipErrorInvalidValue;
-        if (rb == 2) PBIT_BQ_TILES((k_bq_tiles<2>)); else PBIT_BQ_TILES((k_bq_tiles<1>));
+        if (rb == 2) PBIT_BQ_TILES((k_bq_tiles<2, 512>), 512); else PBIT_BQ_TILES((k_bq_tiles<1, 1024>), 1024);
     }
 #undef PBIT_BQ_TILES
     return hipGetLastError();

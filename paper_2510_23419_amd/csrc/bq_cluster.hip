@@ -98,14 +98,6 @@ __device__ bool meet(uint32_t *ctl, uint32_t groups, uint32_t members, uint32_t 
     return ok;
 }
 
-// |a - b| + c
-__device__ __forceinline__ uint32_t sad(uint32_t a, uint32_t b, uint32_t c)
-{
-    uint32_t r;
-    asm("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // Exchange words of one side and row tile as a buffer of whole quads (reads past them give 0).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int quads)
 {

@@ -86,6 +86,59 @@ __device__ __forceinline__ T load_global(const void *p)
 }
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
+typedef int v2i_t __attribute__((ext_vector_type(2)));
+typedef int v8i_t __attribute__((ext_vector_type(8)));
+typedef float v16f_t __attribute__((ext_vector_type(16)));
+
+// ---- biclique fields on the FP4 matrix cores
+//
+// Spins (+-1 or bits) and couplings (-1, 0, 1) are exact E2M1 numbers, so their products
+// are and a float sum of them is up to 2^24 in size.  Accumulators start at kFieldBase =
+// 1.5 x 2^21, whose last place is 1/4: their bits are then kFieldBase + 4 sum while the sum
+// stays within 2^20, and 4 |I|, the byte offset of a threshold, is a difference of bits.
+constexpr uint32_t kFieldBase = 0x4A400000u;
+
+// acc + A B over 64 K values, 32 (four registers) in each lane half; any K order that A and
+// B share.
+__device__ __forceinline__ v16f_t mfma_fp4(v4i_t a, v4i_t b, v16f_t acc)
+{
+    const v8i_t x = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, y = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, acc, 4, 4, 0, 127, 0, 127);  // both E2M1, scales 1
+}
+
+// 32 spin bits (set = -1) as E2M1 numbers +-1: bit 4 i + j to nibble i of dword j.
+__device__ __forceinline__ v4i_t spin_nibbles(uint32_t w)
+{
+    constexpr uint32_t one = 0x22222222u, sign = 0x88888888u;
+    return v4i_t{(int)(one | ((w << 3) & sign)), (int)(one | ((w << 2) & sign)), (int)(one | ((w << 1) & sign)),
+                 (int)(one | (w & sign))};
+}
+
+// |a - b| + c
+__device__ __forceinline__ uint32_t sad(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_sad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+__device__ __forceinline__ uint32_t lds_word(uint32_t address)
+{
+    return *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)address;
+}
+
+// The wave's heat-bath decisions as a mask, set where the new spin is -1: w + Tm(|I|)
+// carries for I >= 0 (accumulator bits x from `mid` on), w >= Tm(|I|) for I < 0.
+__device__ __forceinline__ uint64_t heat_bath(uint32_t w, uint32_t Tm, uint32_t x, uint32_t mid)
+{
+    constexpr int kUgt = 34, kUge = 35;  // wave-wide comparisons; as plain ones the first becomes an add, a select and a test
+    const uint64_t up = __builtin_amdgcn_uicmp(x, mid, kUge);
+    return (up & __builtin_amdgcn_uicmp(w, ~Tm, kUgt)) | (~up & __builtin_amdgcn_uicmp(w, Tm, kUge));
+}
 
 // Spin bits widened for the int8 MFMA: the K bytes that lane half g of a 32x32x32
 // fragment holds (dword j byte i = K position 16 g + 4 j + i) from a word w of

@@ -59,7 +59,7 @@ struct BJob : SchedJob {
     std::vector<uint32_t> table;  // threshold rows built ahead of admission (batch calls), else empty
     int kind = 0, N = 0, R = 0, S = 0;
     int rs = 4, tiles = 0, width = 1, chunk = 1;
-    int mode = kTileInt8;  // biclique tile operands: int8 rows (default) or spin bits
+    int mode = kTileInt8;  // biclique tile states: int8 spins (default) or spin bits
     bool bits = false;     // cube or graph tiles hold their spins as bits
     // device memory (released when the job finishes)
     void *d_table = nullptr, *d_state = nullptr, *d_energy = nullptr;
@@ -170,11 +170,9 @@ static int bq_row_bytes(const BJob &j)
     return j.mode == kTileBits ? n / 8 : n;
 }
 
-// Operand mode of a context's biclique tiles: int8 rows unless the bit variant is
-// forced.  Bit rows let 128 replicas share each coupling fragment at any
-// side length, but on the bag's sides (n <= 1024) a tile's Philox draws and
-// decisions cost about as much as its MFMAs, and the int8 rows' smaller tiles
-// spread a job over more CUs: measured, int8 rows are the faster default there.
+// Mode of a context's biclique tiles: int8 spins, run on the FP4 matrix cores, unless the
+// bit variant is forced (int8 MFMAs on widened bits, up to 128 replicas a tile): half the
+// matrix time and a quarter of the coupling bytes make the first the faster one.
 static int tile_mode(const pbit_ctx *ctx)
 {
     if (ctx->bq_forced == BqVariant::Bits) return kTileBits;
@@ -253,8 +251,13 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
         // is cut into more, smaller tiles that run side by side
         const int na_p = P.bq.na_p, nb_p = P.bq.nb_p;
         j.rs = 0;
+        // a batched job's largest sides: what 32 replicas took of the LDS as bytes
+        const bool takes = j.mode == kTileBits ||
+                           (size_t)32 * ((size_t)(na_p + nb_p) + 16) + sizeof(uint64_t) * (size_t)(2 * j.width - 1) <=
+                               (size_t)kMaxLdsTile;
         for (int rs : {128, 64, 32}) {
-            if (rs == 128 && j.mode != kTileBits) continue;  // int8 rows: 64 and 32 replicas
+            if (!takes) break;
+            if (rs == 128 && j.mode != kTileBits) continue;  // the FP4 tiles: 64 and 32 replicas
             if (bq_tile_lds(rs, na_p, nb_p, j.width, j.mode) > (size_t)kMaxLdsTile) continue;
             j.rs = rs;  // the smallest that fits, if none passes the tests below
             const double item = 2.0 * na_p * nb_p * rs * std::max(j.S, 1);
@@ -484,7 +487,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         } else {
             const BqView &v = j->P->bq;
             const int k = kind_of_rs(j->rs);
-            BqJobDev jd{v.J, v.JT, v.Jb, v.JTb, v.hA2, v.hB2, v.J2, v.JT2, v.hA, v.hB,
+            BqJobDev jd{v.J, v.JT, v.Jb, v.JTb, v.hA2, v.hB2, v.J2, v.hA, v.hB,
                         (const uint32_t *)j->d_table, (uint8_t *)j->d_state,
                         (int32_t *)j->d_energy, v.na, v.nb, v.na_p, v.nb_p, j->width,
                         (uint32_t)j->d.sweep_offset, (uint32_t)j->d.replica_offset >> 2, key.k0, key.k1};
@@ -615,7 +618,7 @@ static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<in
                 e = hipMemcpy(b, &jd, sizeof jd, hipMemcpyHostToDevice);
             } else {
                 const BqView &v = P.bq;
-                const BqJobDev jd{v.J, v.JT, v.Jb, v.JTb, v.hA2, v.hB2, v.J2, v.JT2, v.hA, v.hB,
+                const BqJobDev jd{v.J, v.JT, v.Jb, v.JTb, v.hA2, v.hB2, v.J2, v.hA, v.hB,
                                   (const uint32_t *)(b + off_tab), (uint8_t *)(b + off_state),
                                   (int32_t *)(b + off_en), v.na, v.nb, v.na_p, v.nb_p, j.width, 0u, 0u, 0u, 0u};
                 e = hipMemcpy(b, &jd, sizeof jd, hipMemcpyHostToDevice);
