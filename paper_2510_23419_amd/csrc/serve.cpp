@@ -1,8 +1,8 @@
 // serve.cpp — batched anneals and the serving scheduler (continuous batching).
 //
 // Jobs are cut into replica tiles; a round advances every running job by one
-// chunk of sweeps with one persistent kernel per tile kind (cube tiles, and
-// biclique tiles of 64 or 32 replicas), each on its own stream so the kinds
+// chunk of sweeps with one persistent kernel per tile kind (cube and graph tiles, and
+// biclique tiles of 64 or 32 replicas), on several streams so the kinds
 // overlap on the device.  Between rounds the scheduler harvests energies
 // (traces, targets), retires finished jobs, and admits queued ones when their
 // device memory fits the context's budget.  A job's arithmetic and random
@@ -36,11 +36,12 @@ namespace {
 
 constexpr int kMaxLdsTile = 160 * 1024 - 4096;
 constexpr int64_t kMaxTileSites = kMaxLdsTile / 4;  // largest cube or graph of a batched job
-// tile kinds, one persistent launch and one stream each: cube and graph tiles held as bits,
+// tile kinds, one persistent launch each: cube and graph tiles held as bits,
 // by threads per workgroup (256, 512, 1024: four, two and one workgroups per CU); 128-, 64-
 // and 32-replica biclique tiles; graph tiles in bytes (sites of more terms than the bit
 // records hold)
 constexpr int kKinds = 7;
+constexpr int kQueues = 4;  // hardware queues a process has by default
 constexpr int kBitKind256 = 0, kGraphKind = 4, kBitKind1024 = 5, kBitKind512 = 6;
 inline int kind_of_threads(int t) { return t == 256 ? kBitKind256 : t == 512 ? kBitKind512 : kBitKind1024; }
 inline int threads_of_kind(int k) { return k == kBitKind256 ? 256 : k == kBitKind512 ? 512 : 1024; }
@@ -80,8 +81,10 @@ struct ServeState {
     std::map<uint64_t, std::unique_ptr<BJob>> jobs;
     uint64_t next_id = 1;
     int max_queue = 4096, round_sweeps = 500;
-    // one stream per tile kind
-    hipStream_t st[kKinds] = {};
+    // One stream per hardware queue.  The runtime gives a new stream the queue with the fewest
+    // streams: the default stream and the context's have taken two, two spares take the others,
+    // and the next four are spread over all (they were found to share two without the spares).
+    hipStream_t spare[2] = {}, st[kQueues] = {};
     hipEvent_t fork = nullptr, join[kKinds] = {};
     std::vector<BJob *> round_jobs;
     std::vector<int> round_end;
@@ -122,7 +125,8 @@ static int serve_init(pbit_ctx *ctx)
     std::unique_ptr<ServeState> s(new (std::nothrow) ServeState());
     if (!s) return fail(PBIT_E_NOMEM, "serving state: host allocation failed");
     hipError_t e = hipSuccess;
-    for (int k = 0; k < kKinds && e == hipSuccess; ++k) e = hipStreamCreateWithFlags(&s->st[k], hipStreamNonBlocking);
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipStreamCreateWithFlags(&s->spare[k], hipStreamNonBlocking);
+    for (int k = 0; k < kQueues && e == hipSuccess; ++k) e = hipStreamCreateWithFlags(&s->st[k], hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
     for (int k = 0; k < kKinds && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
     if (e != hipSuccess) return device_fail(ctx, e, "serving streams");
@@ -152,8 +156,11 @@ void serve_shutdown(pbit_ctx *ctx)
     for (int k = 0; k < 3; ++k) dev_free(ctx, s->d_bq_jobs[k]);
     for (int k = 0; k < kKinds; ++k) dev_free(ctx, s->d_items[k]);
     dev_free(ctx, s->d_meta);
+    for (hipStream_t x : s->spare)
+        if (x) (void)hipStreamDestroy(x);
+    for (hipStream_t x : s->st)
+        if (x) (void)hipStreamDestroy(x);
     for (int k = 0; k < kKinds; ++k) {
-        if (s->st[k]) (void)hipStreamDestroy(s->st[k]);
         if (s->join[k]) (void)hipEventDestroy(s->join[k]);
     }
     if (s->fork) (void)hipEventDestroy(s->fork);
@@ -440,6 +447,8 @@ static void release(pbit_ctx *ctx, BJob &j)
 
 // ---------------------------------------------------------------- rounds
 
+static double tile_us(const BJob &j, int rs, int *per_cu);
+
 static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> &running, bool &launched)
 {
     launched = false;
@@ -449,7 +458,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     std::vector<GraphJobDev> gr;
     std::vector<BqJobDev> bq[3];
     std::vector<WorkItem> items[kKinds];
-    std::vector<double> cost[kKinds];
+    std::vector<double> cost[kKinds];  // microseconds
     size_t lds[kKinds] = {};
     for (BJob *j : running) {
         if (j->finished) continue;
@@ -459,6 +468,8 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         s.round_jobs.push_back(j);
         s.round_end.push_back(s1);
         const Key key{(uint32_t)j->d.seed, (uint32_t)(j->d.seed >> 32)};
+        int per_cu = 1;
+        const double us = tile_us(*j, j->rs, &per_cu);
         if (j->bits) {
             const BitView &v = j->P->bits;
             const int idx = (int)bit.size(), k = kind_of_threads(bit_job_threads(*j));
@@ -467,7 +478,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
                                     (uint32_t)j->d.replica_offset >> 2, key.k0, key.k1});
             for (int t = 0; t < j->tiles; ++t) {
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
-                cost[k].push_back((double)(s1 - s0) * bit_sweep_us(*j->P, j->rs, j->rs, 1));
+                cost[k].push_back((s1 - s0) * us);
             }
             lds[k] = std::max(lds[k], bit_lds(v.n_pos));
         } else if (j->kind == PBIT_GRAPH) {
@@ -481,7 +492,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
             const int k = kGraphKind;
             for (int t = 0; t < j->tiles; ++t) {
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
-                cost[k].push_back((double)(s1 - s0) * ((double)j->N + 2.0 * v.n_bonds) * j->rs);
+                cost[k].push_back((s1 - s0) * us);
             }
             lds[k] = std::max(lds[k], graph_tile_lds(j->N, j->rs));
         } else {
@@ -495,7 +506,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
             bq[k - 1].push_back(jd);
             for (int t = 0; t < j->tiles; ++t) {
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
-                cost[k].push_back((double)(s1 - s0) * (double)v.na_p * v.nb_p * j->rs);
+                cost[k].push_back((s1 - s0) * us);
             }
             lds[k] = std::max(lds[k], bq_tile_lds(j->rs, v.na_p, v.nb_p, j->width, j->mode));
         }
@@ -503,6 +514,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     if (s.round_jobs.empty()) return PBIT_OK;
 
     // longest items first, so that the persistent workgroups finish together
+    double longest[kKinds] = {};
     for (int k = 0; k < kKinds; ++k) {
         std::vector<size_t> ord(items[k].size());
         for (size_t q = 0; q < ord.size(); ++q) ord[q] = q;
@@ -510,7 +522,14 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         std::vector<WorkItem> sorted(items[k].size());
         for (size_t q = 0; q < ord.size(); ++q) sorted[q] = items[k][ord[q]];
         items[k].swap(sorted);
+        if (!ord.empty()) longest[k] = cost[k][ord[0]];
     }
+    // the kinds with the longest first, each on its own stream, the shortest ones one after
+    // another on the last: streams beyond the device's four queues share one anyway, where a
+    // short launch would hold up a long one
+    int kinds[kKinds];
+    for (int k = 0; k < kKinds; ++k) kinds[k] = k;
+    std::stable_sort(kinds, kinds + kKinds, [&](int a, int b) { return longest[a] > longest[b]; });
     int rc = grow(ctx, &s.d_bit_jobs, &s.cap_bit_jobs, sizeof(BitJobDev) * std::max<size_t>(bit.size(), 1));
     if (rc == PBIT_OK)
         rc = grow(ctx, &s.d_graph_jobs, &s.cap_graph_jobs, sizeof(GraphJobDev) * std::max<size_t>(gr.size(), 1));
@@ -537,23 +556,67 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         if (!items[k].empty()) e = hipMemcpy(s.d_items[k], items[k].data(), sizeof(WorkItem) * items[k].size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return device_fail(ctx, e, "round upload");
 
+    // Compute units per stream: all that its workgroups fill, or, where the streams together
+    // want more than there are, a share by their work.  A persistent launch that took every
+    // unit would keep the other kinds' tiles, and the longest among them, waiting for its last.
     const int cus = compute_units(ctx);
-    for (int k = 0; k < kKinds; ++k) {
+    int per_cu[kKinds] = {};
+    double work[kQueues] = {}, want[kQueues] = {}, all_work = 0.0, all_want = 0.0;
+    for (int q = 0; q < kKinds; ++q) {
+        const int k = kinds[q], i = std::min(q, kQueues - 1);
+        const int by_threads = bit_kind(k) ? 1024 / threads_of_kind(k) : k == kGraphKind ? 2 : 1;
+        per_cu[k] = std::max(1, std::min(by_threads, (int)((160 * 1024) / (lds[k] + 2048))));
+        double sum = 0.0;
+        for (double c : cost[k]) sum += c;
+        work[i] += sum / per_cu[k];
+        want[i] = std::max(want[i], (double)items[k].size() / per_cu[k]);
+    }
+    for (int i = 0; i < kQueues; ++i) {
+        all_work += work[i];
+        all_want += want[i];
+    }
+    double units[kQueues];
+    for (int i = 0; i < kQueues; ++i) units[i] = want[i];
+    if (all_want > cus) {
+        // streams that want an eighth or less get it all (their tiles share compute units with
+        // others and run at half speed or less there, so a small share would end last), the
+        // rest share what is left
+        double left = cus;
+        bool full[kQueues] = {};
+        for (int i = 0; i < kQueues; ++i)
+            if (want[i] <= cus / 8.0) {
+                full[i] = true;
+                left -= want[i];
+                all_work -= work[i];
+            }
+        for (bool again = true; again;) {
+            again = false;
+            for (int i = 0; i < kQueues; ++i)
+                if (!full[i] && all_work > 0.0 && want[i] <= left * work[i] / all_work) {
+                    full[i] = again = true;
+                    left -= want[i];
+                    all_work -= work[i];
+                }
+        }
+        for (int i = 0; i < kQueues; ++i)
+            if (!full[i] && all_work > 0.0) units[i] = left * work[i] / all_work;
+    }
+    for (int q = 0; q < kKinds; ++q) {
+        const int k = kinds[q];
         if (items[k].empty()) continue;
-        const size_t per_cu_lds = std::max<size_t>(lds[k] + 2048, 1);
-        const int most = bit_kind(k) ? 1024 / threads_of_kind(k) : 4;
-        const int per_cu = std::max(1, std::min(most, (int)((160 * 1024) / per_cu_lds)));
-        const int grid = std::max(1, std::min((int)items[k].size(), cus * per_cu));
+        const int i = std::min(q, kQueues - 1);
+        const hipStream_t st = s.st[i];
+        const int grid = std::max(1, std::min((int)items[k].size(), (int)(units[i] * per_cu[k] + 0.999)));
         if (bit_kind(k))
             e = bit_tiles((const BitJobDev *)s.d_bit_jobs, (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
-                          s.d_meta + k, grid, threads_of_kind(k), lds[k], s.st[k]);
+                          s.d_meta + k, grid, threads_of_kind(k), lds[k], st);
         else if (k == kGraphKind)
             e = graph_tiles((const GraphJobDev *)s.d_graph_jobs, (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
-                            s.d_meta + k, grid, lds[k], s.st[k]);
+                            s.d_meta + k, grid, lds[k], st);
         else
             e = bq_tiles((const BqJobDev *)s.d_bq_jobs[k - 1], (const WorkItem *)s.d_items[k], s.d_meta + kKinds + k,
-                         s.d_meta + k, rs_of_kind(k), tile_mode(ctx), grid, lds[k], s.st[k]);
-        if (e == hipSuccess) e = hipEventRecord(s.join[k], s.st[k]);
+                         s.d_meta + k, rs_of_kind(k), tile_mode(ctx), grid, lds[k], st);
+        if (e == hipSuccess) e = hipEventRecord(s.join[k], st);
         if (e != hipSuccess) return device_fail(ctx, e, "tile kernel launch");
     }
     launched = true;
@@ -669,7 +732,7 @@ static bool round_done(ServeState &s)
 static int harvest(pbit_ctx *ctx, ServeState &s)
 {
     hipError_t e = hipSuccess;
-    for (int k = 0; k < kKinds && e == hipSuccess; ++k) e = hipStreamSynchronize(s.st[k]);
+    for (int k = 0; k < kQueues && e == hipSuccess; ++k) e = hipStreamSynchronize(s.st[k]);
     if (e != hipSuccess) return device_fail(ctx, e, "round");
     std::vector<int32_t> tile_e;
     for (size_t q = 0; q < s.round_jobs.size(); ++q) {
@@ -807,7 +870,7 @@ static void withdraw(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> &mi
 {
     if (s.q.in_flight) {
         if (harvest(ctx, s) != PBIT_OK)
-            for (int k = 0; k < kKinds; ++k) (void)hipStreamSynchronize(s.st[k]);
+            for (int k = 0; k < kQueues; ++k) (void)hipStreamSynchronize(s.st[k]);
         s.q.in_flight = false;
         s.q.running.erase(std::remove_if(s.q.running.begin(), s.q.running.end(), [](BJob *j) { return j->finished; }),
                           s.q.running.end());
@@ -914,29 +977,75 @@ extern "C" int pbit_profile_tiles(pbit_ctx *ctx, int64_t *tunings, int32_t *shap
 
 namespace pbit {
 
-// Tile widths of a batch's cube and graph jobs: each job gets the share of the compute
-// units that its work is of the batch's, and the width of least cost on that share, so
-// that a small batch spreads over the device and a full one takes the widest tiles.
-// Work in microseconds of one compute unit: measured for tiles of 16 replicas, and 33 us
-// per sweep for 32 replicas of a 1024 x 1024 biclique.
+// Microseconds a compute unit needs for one sweep of one tile, and how many such tiles it
+// runs in that time.  Biclique tiles of 32 replicas measured 1.6 us at 193 sites per side,
+// 4.2 at 428, 8 at 689, 11 at 876 and 13 at 1022; of 64 replicas 1.8 times that.
+static double tile_us(const BJob &j, int rs, int *per_cu)
+{
+    *per_cu = 1;
+    if (j.bits) {
+        *per_cu = bit_tiles_per_cu(j.P->bits, rs);
+        return bit_sweep_us(*j.P, rs, rs, 1);
+    }
+    if (j.kind != PBIT_BICLIQUE) return 2.5e-4 * j.N * rs;
+    const double n = j.P->bq.na + j.P->bq.nb;
+    return (1.0 + n / 128.0 * (0.47 + 1.8e-4 * n)) * (rs == 32 ? 1.0 : rs / 36.0);
+}
+
+// Tile widths of a batch.  Wide tiles take the least work and narrow ones end soonest, and
+// the batch ends when its work is done and its longest tile too.  So a time limit for a
+// tile is sought: with each job in its widest tiles within the limit, the larger of that
+// limit and the work spread over the device is to be least.  For an eighth of the mixed bag
+// (32 jobs) that is 46 ms in tiles of 8 replicas for its 24^3 cubes, which alone took 78 ms
+// in tiles of 16. 
+// Bicliques take tiles of 32 replicas: those of 64 need a tenth less work, but a launch of
+// their own beside three others ended later (101 against 79 ms).
 static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
 {
-    double total = 0.0;
-    std::vector<double> work;
-    for (const BJob *j : js) {
-        const double us = j->bits ? bit_sweep_us(*j->P, 16, 16, 1) * j->R / 16.0
-                          : j->kind == PBIT_BICLIQUE
-                              ? 33.0 * ((double)j->P->bq.na_p * j->P->bq.nb_p / (1 << 20)) * j->R / 32.0
-                              : 1e-3 * j->N * j->R / 4.0;
-        work.push_back(us * std::max(j->S, 1));
-        total += work.back();
-    }
-    const int cus = compute_units(ctx);
+    struct Option {
+        int rs;
+        double us, load;  // of a tile's whole run; of all tiles in compute-unit time
+    };
+    std::vector<std::vector<Option>> options(js.size());  // widest first
+    double longest = 0.0;
     for (size_t q = 0; q < js.size(); ++q) {
-        BJob &j = *js[q];
-        if (!j.bits) continue;
-        j.rs = bit_pick_rs(*j.P, j.R, std::max(1, (int)(cus * work[q] / total)));
-        size_job(j);
+        const BJob &j = *js[q];
+        auto add = [&](int rs) {
+            int per_cu = 1;
+            const double us = tile_us(j, rs, &per_cu) * std::max(j.S, 1);
+            options[q].push_back({rs, us, us * ((j.R + rs - 1) / rs) / per_cu});
+        };
+        if (j.bits) {
+            for (int rs : {16, 8, 4})
+                if (rs == 4 || j.R > rs / 2) add(rs);
+        } else {
+            add(j.kind == PBIT_BICLIQUE && j.mode == kTileInt8 ? 32 : j.rs);
+        }
+        longest = std::max(longest, options[q][0].us);
+    }
+    const double cus = compute_units(ctx);
+    auto width_within = [&](size_t q, double limit) -> const Option & {
+        for (const Option &o : options[q])
+            if (o.us <= limit) return o;
+        return options[q].back();
+    };
+    double best = 0.0, best_limit = longest;
+    for (double limit = longest; limit > longest / 16.0; limit *= 0.9) {
+        double load = 0.0, last = 0.0;
+        for (size_t q = 0; q < js.size(); ++q) {
+            const Option &o = width_within(q, limit);
+            load += o.load;
+            last = std::max(last, o.us);
+        }
+        const double ends = std::max(last, load / (0.8 * cus));  // tiles of several lengths do not pack fully
+        if (best == 0.0 || ends < best) {
+            best = ends;
+            best_limit = limit;
+        }
+    }
+    for (size_t q = 0; q < js.size(); ++q) {
+        js[q]->rs = width_within(q, best_limit).rs;
+        size_job(*js[q]);
     }
 }
 
