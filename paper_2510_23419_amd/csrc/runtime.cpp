@@ -825,10 +825,11 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     int best_rt = 0;
     bool have = false, cache = true;
     int rt = 0;  // the bit kernel's replica tile or the LDS-resident kernel's slice being timed
-    // one warm-up pass, then the best of three (a profiler's tracing stretches single launches)
+    // one warm-up pass, then the best of three (a profiler's tracing stretches single launches;
+    // of one for the cluster kernel, whose passes take the device to themselves)
     auto time_it = [&](BqVariant v, int slab_sweeps, float *best_pass) {
         *best_pass = 0.f;
-        for (int rep = 0; rep < 4 && e == hipSuccess; ++rep) {
+        for (int rep = 0; rep < (v == BqVariant::Cluster ? 2 : 4) && e == hipSuccess; ++rep) {
             float one_pass = 0.f, *ms = &one_pass;
             e = hipEventRecord(e0, st);
             if (v == BqVariant::Slab) {
@@ -963,14 +964,17 @@ int compute_units(const pbit_ctx *ctx)
     return cus;
 }
 
-// Microseconds per sweep of the bit-held tiles, up to a common factor of the rounds the
-// device needs for them: measured 0.58 ns per site and tile of 4 replicas (0.70 with
-// fields or zero couplings), 1.6 and 2.7 times that with 8 and 16, at 12^3 to 36^3.
+// Microseconds per sweep of the bit-held tiles in the rounds the device needs for them:
+// measured 0.58 ns per site and tile of 4 replicas (0.70 with fields or zero couplings), 1.6
+// and 2.7 times that with 8 and 16, at 12^3 to 36^3, and what an update group costs at least
+// (4^3 to 8^3 cubes; graphs of 64 to 500 sites).
 double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
 {
     const int tiles = (Rp + rs - 1) / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
     const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
-    return ((tiles + slots - 1) / slots) * c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N;
+    const double group = P.bits.form == kBitGeneral && P.bits.n_groups != 2 ? 0.65 : 0.28;
+    return ((tiles + slots - 1) / slots) *
+           (group * P.bits.n_groups + c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N);
 }
 
 // Replicas per tile: the width whose rounds cost least (the narrowest among equals, which
@@ -981,6 +985,22 @@ int bit_pick_rs(const Problem &P, int Rp, int cus)
     for (int rs : {8, 16})
         if (bit_sweep_us(P, Rp, rs, cus) < bit_sweep_us(P, Rp, best, cus)) best = rs;
     return best;
+}
+
+// Whether a graph's sweeps are faster with its spins as bits than as bytes.  An update group
+// of the bit tiles costs 0.75 us at least (1.25 with a site of more than 7 terms), of the byte
+// tiles 0.35 us and 0.1 for every bond of a site, and 1 ns for every site: with about 4 bonds
+// a site the lines lie near 1000 sites (500: 3.1 against 2.6 us per sweep in bytes, 1500: 3.7
+// against 4.0), and with wide sites near 2500 (1500: 7.7 against 6.7, 2200: 8.9 against 8.8,
+// 4000: 8.5 against 12.1) or, with more replicas than one round of narrow tiles takes, 1000;
+// with 6 bonds bits win at any size (185: 4.3 against 4.9) or, with wide sites, from 400 on
+// (185: 7.6 against 6.4, 500: 7.5 against 7.3, 1500: 8.8 against 9.6).
+bool graph_bits_preferred(const Problem &P, int R)
+{
+    if (P.bits.n_groups == 2) return true;  // their records stay in registers
+    const bool sparse = 2 * (int64_t)P.graph.n_bonds <= 5 * P.N, wide = P.bits.n_wide > 0;
+    if (!sparse) return !wide || P.N >= 400;
+    return P.N >= (wide && R <= 1024 ? 2500 : 1000);
 }
 
 // Cubes too large for the tiles to win at any replica count: the faster of the two
@@ -1073,11 +1093,10 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     }
     if (P.kind == PBIT_GRAPH && ctx->graph_slab && graph_tile_lds(P.N, 4) <= kGraphSlabLds) {
         // the whole graph for a tile of replicas in LDS, runs of sweeps per launch
-        ds.bit_tiles = P.bits.n_pos > 0;
+        ds.bit_tiles = P.bits.n_pos > 0 && (ctx->graph_slab_rs != 0 || graph_bits_preferred(P, R));
         ds.slab = true;
         if (!ds.bit_tiles) {
-            // bytes, for graphs with sites of more terms than the bit records hold: the
-            // narrowest tile (4, 8 or 16 replicas) that fits and leaves at most two
+            // bytes: the narrowest tile (4, 8 or 16 replicas) that fits and leaves at most two
             // workgroups per compute unit, else the widest that fits.  A workgroup's sweep
             // costs about the same at any tile width up to two per CU, so narrow tiles
             // spread small replica counts over more CUs, and past two per CU the wider

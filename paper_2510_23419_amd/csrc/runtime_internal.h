@@ -117,6 +117,7 @@ int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_
 size_t anneal_dev_bytes(const pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d);
 int noalloc_setup(int device);
 int compute_units(const pbit_ctx *ctx);
+bool graph_bits_preferred(const Problem &P, int R);
 double bit_sweep_us(const Problem &P, int Rp, int rs, int cus);
 int bit_pick_rs(const Problem &P, int Rp, int cus);
 
