@@ -252,14 +252,13 @@ __device__ __forceinline__ v4i widen_codes(v2i_t x, uint32_t mask)
 
 // Biclique tiles with the spins held as bits in LDS: row r holds one bit per site (set = -1), 32 sites per word, side A
 // in words [0, na_p / 32), side B after it, with an odd row pitch so that the 32
-// rows a fragment read touches sit on distinct banks.  A K step of 32 sites is
-// one word per replica, widened in registers to the bytes bit * 2^j (dword j)
-// and multiplied on the int8 MFMA with int32 sums by the couplings stored in
-// the widened-bit column order and scaled by 2^(3 - j) (Jb, JTb): the sum is
-// 8 sum_k J_sk b_k and the field is I = (h + sum_k J) - (acc >> 2), exact.
+// rows a fragment read touches sit on distinct banks.  A K step of 64 sites is two words per
+// replica, one in each lane half, widened in registers to four-bit numbers and multiplied on
+// the FP4 MFMA by the couplings stored in the same order (J4, JT4): the sum is
+// 2 sum_k J_sk b_k and the field is I = (h + sum_k J) - the sum, exact.
 // A bit row is an eighth of an int8 row, so 128 replicas fit LDS at any side
 // length and each coupling fragment feeds RB MFMAs: couplings reach the CU at
-// 1 / (32 RB) bytes per multiply-add.  The 64
+// 1 / (64 RB) bytes per multiply-add.  The 64
 // decisions of a wave for one (replica group, p) form a ballot mask, and the
 // words of the 32 replicas of a block are written by one lane each.
 template <int RB>
@@ -331,29 +330,31 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles_bits(const BqJobDev
                 const int ko = side == 0 ? nb_p : na_p;  // coupling bytes per row (the other side)
                 const int in_w = side == 0 ? wa : 0;     // word column of the other side
                 const int out_w = side == 0 ? 0 : wa;    // word column of this side
-                const uint8_t *Jx = reinterpret_cast<const uint8_t *>(side == 0 ? jb.Jb : jb.JTb);
+                const uint8_t *Jx = side == 0 ? jb.J4 : jb.JT4;
                 const int32_t *hs2 = side == 0 ? jb.hA2 : jb.hB2;
                 const uint32_t site_base = side == 0 ? 0u : (uint32_t)na;
                 // one 32-site block per wave at a time; its coupling fragments stream
                 // from global memory through a ring kRing K-units (32 bytes) ahead,
                 // which past the end of a block fills with the wave's next block
-                const int nku = ko / 32;
+                const int nku = ko / 64, row = bq_row_bytes(ko);
                 constexpr int kStep = kBqTileThreads / 64;
                 const int nblk = ns_p / 32;
                 v4i ring[kRing];
                 if (wave < nblk) {
-                    const uint8_t *br0 = Jx + (size_t)(wave * 32 + ln) * ko + 16 * kg;
+                    const uint8_t *br0 = Jx + (size_t)(wave * 32 + ln) * row + 16 * kg;
 #pragma unroll
                     for (int u = 0; u < kRing; ++u) ring[u] = load_global<v4i>(br0 + 32 * min(u, nku - 1));
                 }
                 for (int blk = wave; blk < nblk; blk += kStep) {
                     const int site = blk * 32 + ln;
-                    const uint8_t *br = Jx + (size_t)site * ko + 16 * kg;
-                    const uint8_t *bn = blk + kStep < nblk ? br + (size_t)kStep * 32 * ko : br;
-                    v16i acc[RB];
+                    const uint8_t *br = Jx + (size_t)site * row + 16 * kg;
+                    const uint8_t *bn = blk + kStep < nblk ? br + (size_t)kStep * 32 * row : br;
+                    v16f_t acc[RB];
 #pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) acc[rb] = v16i{0};
-                    const uint32_t *abase = sw + ln * pitch + in_w;
+                    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) acc[rb][j] = __uint_as_float(kFieldBase);
+                    const uint32_t *abase = sw + ln * pitch + in_w + kg;
                     for (int kb = 0; kb < nku; kb += kRing) {
 #pragma unroll
                         for (int u = 0; u < kRing; ++u) {
@@ -364,8 +365,8 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles_bits(const BqJobDev
                                 ring[u] = load_global<v4i>(kn < nku ? br + 32 * kn : bn + 32 * min(u, nku - 1));
 #pragma unroll
                                 for (int rb = 0; rb < RB; ++rb) {
-                                    const v4i a = widen_bits(abase[rb * 32 * pitch + ku], kg);
-                                    acc[rb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[rb], 0, 0, 0);
+                                    const v4i a = spin_bits_fp4(abase[rb * 32 * pitch + 2 * ku]);
+                                    acc[rb] = mfma_fp4(a, b, acc[rb]);
                                 }
                             }
                         }
@@ -384,7 +385,8 @@ __global__ __launch_bounds__(kBqTileThreads) void k_bq_tiles_bits(const BqJobDev
                                                     kDomainSweep, jb.k0, jb.k1);
 #pragma unroll
                             for (int p = 0; p < 4; ++p) {
-                                const int I = h2 - (acc[rb][4 * q + p] >> 2);  // the accumulator holds 8 sum J b
+                                // the accumulator's bits are kFieldBase + 8 sum J b
+                                const int I = h2 - ((int)(__float_as_uint(acc[rb][4 * q + p]) - kFieldBase) >> 2);
                                 const int Ic = min(max(I, -top), top);
                                 const uint64_t S = *static_cast<const uint64_t *>(
                                     __builtin_assume_aligned(Sb + 8 * (Ic + top), 8));

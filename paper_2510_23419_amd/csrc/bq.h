@@ -13,12 +13,11 @@ struct BqView {
     const int8_t *JT;  // [nb_p][na_p]
     const int8_t *hA;  // [na_p]
     const int8_t *hB;  // [nb_p]
-    // for the kernels on spin bits: the couplings with the columns of every group of
-    // 32 in the order the widened bits take, scaled by 2^(3 - j) for the bit's
-    // position j in its byte lane, [na_p][nb_p] and [nb_p][na_p], and each site's
-    // field plus its coupling sum
-    const int8_t *Jb;
-    const int8_t *JTb;
+    // for the kernels on spin bits: the couplings as E2M1 numbers in the order the widened
+    // bits take (spin_bits_fp4), scaled so that every product is 2 J b, rows of
+    // bq_row_bytes(nb_p) and bq_row_bytes(na_p), and each site's field plus its coupling sum
+    const uint8_t *J4;
+    const uint8_t *JT4;
     const int32_t *hA2;  // [na_p]
     const int32_t *hB2;  // [nb_p]
     // for the batched FP4 tiles: couplings as two-bit codes, 16 per word, in MFMA fragment
@@ -26,6 +25,9 @@ struct BqView {
     const uint32_t *J2;
 };
 
+// Bytes of a row of four-bit couplings: whole stages of 256 sites for the per-launch bit kernel
+// (zeros past ko_p) where it can take the side.
+constexpr int bq_row_bytes(int ko_p) { return ko_p % 128 == 0 ? (ko_p + 255) / 256 * 128 : ko_p / 2; }
 constexpr int kBqPad = 64;       // site padding of small biclique sides (MFMA K and N tiles)
 constexpr int kBqPadLarge = 128; // site padding of sides with at least kBqLargeSide sites
 constexpr int kBqLargeSide = 512;
@@ -37,7 +39,7 @@ constexpr int kMaxTableWidth = 4096;  // threshold-row entries a biclique kernel
 // global memory (any padding); Dma: 128 x 128 tiles with K stages of 128 bytes
 // moved by the global-to-LDS DMA into a ring of 4 stages (sides padded to 128,
 // Rp a multiple of 128); Bits: tiles of 64 sites x 256, 128 or 64 replicas on spins
-// held as bits, widened for the int8 MFMA (bqb_*; sides padded to 128, Rp a multiple
+// held as bits, widened for the FP4 MFMA (bqb_*; sides padded to 128, Rp a multiple
 // of 256); Slab: sides of
 // at most 512 sites, couplings and 16- or 8-replica slices held in LDS for runs of
 // sweeps in one launch (bq_slab).

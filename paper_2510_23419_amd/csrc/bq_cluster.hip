@@ -46,16 +46,13 @@ constexpr uint32_t kAbort = 0x80000000u;
 constexpr uint64_t kMeetTicks = 200000;  // 2 ms of the 100 MHz clock; an idle device takes some 10 us
 constexpr int kMaxWidth = 256;            // threshold row entries
 constexpr int kRows = 16;                 // threshold rows held per wave
-constexpr int kBias = 1 << 24;            // far above 4 |h2| + 8 sum |J|: accumulators stay positive
 constexpr int kPollLimit = 1 << 21;       // a second or so: never reached by resident workgroups
 
-typedef int v16i __attribute__((ext_vector_type(16)));
-
 struct Args {
-    const int8_t *J[2];     // Jb, JTb: coupling rows of side A's and side B's sites
+    const uint8_t *J[2];    // J4, JT4: coupling rows of side A's and side B's sites
     const int32_t *h2[2];   // field plus coupling sum
     int8_t *M[2];           // int8 spins [Rp][n_p]
-    uint32_t *X[2];         // spin words [row tile][block / 4][32 replicas][4]
+    uint32_t *X[2];         // spin words [row tile][block / 8][block % 2][32 replicas][block / 2 % 4]
     uint32_t *flags;        // [2][row tiles][32]: updates a block has published
     uint32_t *ctl;          // arrivals, status, 8 per-XCD counts
     const uint32_t *table;
@@ -98,13 +95,14 @@ __device__ bool meet(uint32_t *ctl, uint32_t groups, uint32_t members, uint32_t 
     return ok;
 }
 
-// Exchange words of one side and row tile as a buffer of whole quads (reads past them give 0).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int quads)
+// Exchange words of one side and row tile as a buffer of whole octets of blocks (reads past
+// them give 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int octets)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(p, 0, 512 * quads, 0x00027000);
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, 1024 * octets, 0x00027000);
 }
 
-// KS: K steps of 32 sites a side may have (the couplings take 8 KS registers).
+// KS: K steps of 64 sites a side may have (the couplings take 8 KS registers).
 template <int KS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_bq_cluster(Args g)
 {
@@ -135,25 +133,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const int ko = g.n_p[1 - side];
-        const int8_t *row = g.J[side] + (size_t)(32 * c + ln) * ko + 16 * kg;
+        const uint8_t *row = g.J[side] + (size_t)(32 * c + ln) * bq_row_bytes(ko) + 16 * kg;
 #pragma unroll
         for (int u = 0; u < KS; ++u)
-            jr[side][u] = has[side] && 32 * u < ko ? *reinterpret_cast<const v4i_t *>(row + 32 * u) : v4i_t{0, 0, 0, 0};
+            jr[side][u] = has[side] && 64 * u < ko ? *reinterpret_cast<const v4i_t *>(row + 32 * u) : v4i_t{0, 0, 0, 0};
         h2[side] = has[side] ? g.h2[side][32 * c + ln] : 0;
     }
     const int top = g.width - 1;
-    // The products start at kBias, so an accumulator holds kBias + 8 sum_k J b = mid - 4 I
-    // with mid = kBias + 4 h2 (both positive), and |4 I| is the byte offset of Tm(|I|).
-    v16i bias;
+    // An accumulator's bits are kFieldBase + 4 (2 sum_k J b) = mid - 4 I with mid =
+    // kFieldBase + 4 h2, and |4 I| is the byte offset of Tm(|I|).
+    v16f_t bias;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) bias[j] = kBias;
-    const uint32_t mid[2] = {(uint32_t)(kBias + 4 * h2[0]), (uint32_t)(kBias + 4 * h2[1])};
+    for (int j = 0; j < 16; ++j) bias[j] = __uint_as_float(kFieldBase);
+    const uint32_t mid[2] = {kFieldBase + 4u * (uint32_t)h2[0], kFieldBase + 4u * (uint32_t)h2[1]};
     const uint32_t rows = (uint32_t)wave * kRows * 4u * (uint32_t)g.width;  // LDS address of this wave's threshold rows
 
     for (int t = cluster + kXcds * wave; t < g.tiles; t += kXcds * kWaves) {
         uint32_t *flag[2] = {g.flags + 32 * t, g.flags + 32 * (g.tiles + t)};
-        const int quads[2] = {(g.blocks[0] + 3) / 4, (g.blocks[1] + 3) / 4};  // blocks / 4 of a side
-        uint32_t *xt[2] = {g.X[0] + (size_t)t * quads[0] * 128, g.X[1] + (size_t)t * quads[1] * 128};
+        const int octets[2] = {(g.blocks[0] + 7) / 8, (g.blocks[1] + 7) / 8};  // blocks / 8 of a side
+        uint32_t *xt[2] = {g.X[0] + (size_t)t * octets[0] * 256, g.X[1] + (size_t)t * octets[1] * 256};
         int out[2] = {0, 0};  // lane r: this block's word of replica r
         // random words of one update: two of the four blocks at a time
         uint32_t w[16];
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         uint32_t peek = 0u;
         auto publish = [&](int side, uint32_t seq, int ns, uint32_t next) {
             if (lane < 32)
-                __hip_atomic_store(xt[side] + (((c >> 2) * 32 + lane) * 4 + (c & 3)), (uint32_t)out[side],
+                __hip_atomic_store(xt[side] + (((c >> 3) * 2 + (c & 1)) * 128 + 4 * lane + ((c >> 1) & 3)), (uint32_t)out[side],
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_sched_barrier(0);
             draw(ns, next, 0);
@@ -210,7 +208,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         }
 
         bool lost = false;
-        const __amdgpu_buffer_rsrc_t xr[2] = {rsrc(xt[0], quads[0]), rsrc(xt[1], quads[1])};
+        const __amdgpu_buffer_rsrc_t xr[2] = {rsrc(xt[0], octets[0]), rsrc(xt[1], octets[1])};
         auto half = [&](auto side_c, uint32_t row, uint32_t need, uint32_t seq, int ns, uint32_t next) {
             constexpr int side = decltype(side_c)::value;
             const uint32_t *f = flag[1 - side] + ln;
@@ -224,49 +222,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
                 peek = agent_load(f);
             }
             asm volatile("" ::: "memory");
-            // words of replica ln, four blocks a load: the even quads in lanes 0-31 and the odd
-            // ones in lanes 32-63 (reads past the last quad return zero)
-            v4i_t v[(KS + 7) / 8];
+            // words of replica ln, of four even blocks a load in lanes 0-31 and of four odd ones
+            // in lanes 32-63: the halves of four K steps (reads past the last octet return zero)
+            constexpr int KO = (KS + 3) / 4;
+            v4i_t v[KO];
 #pragma unroll
-            for (int k = 0; k < (KS + 7) / 8; ++k)
+            for (int k = 0; k < KO; ++k)
                 v[k] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(xr[1 - side], 512 * kg + 16 * ln,
                                                                                       1024 * k, 16 /* sc1 */));
-            v16i acc = bias;
-            v4i_t a = v4i_t{0, 0, 0, 0};
+            v16f_t acc = bias;
 #pragma unroll
-            for (int k = 0; k < (KS + 7) / 8; ++k)
-                if (2 * k < quads[1 - side]) {
-                    // both quads to all lanes, shifted by four bits in lanes 32-63 as widened there
-                    uint32_t x[8];
+            for (int k = 0; k < KO; ++k)
+                if (k < octets[1 - side]) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)v[k][u], (uint32_t)v[k][u] >> 4, false, false);
-                        x[u] = p[0];
-                        x[4 + u] = p[1];
-                    }
-                    a = widen_bits(x[0], 0);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const v4i_t cur = a;
-                        if (u < 7) a = widen_bits(x[u + 1], 0);
-                        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, jr[side][8 * k + u], acc, 0, 0, 0);
-                    }
+                    for (int u = 0; u < 4; ++u)
+                        acc = mfma_fp4(spin_bits_fp4((uint32_t)v[k][u]), jr[side][4 * k + u], acc);
                 }
-            uint32_t T[16];
+            uint32_t x[16], T[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                // |acc - mid| + row, at most the row's last entry
-                const uint32_t at = min(sad((uint32_t)acc[j], mid[side], row), row + 4u * (uint32_t)top);
-                T[j] = *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)at;
+                x[j] = __float_as_uint(acc[j]);
+                T[j] = lds_word(min(sad(x[j], mid[side], row), row + 4u * (uint32_t)top));  // at most the last entry
             }
             uint64_t minus[16];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                // -1 exactly when w + T carries (I >= 0), or w >= T (I < 0)
-                const uint64_t up = __ballot((uint32_t)acc[j] <= mid[side]);
-                const uint64_t carry = __ballot(w[j] > ~T[j]), above = __ballot(w[j] >= T[j]);
-                minus[j] = (up & carry) | (~up & above);
-            }
+            for (int j = 0; j < 16; ++j) minus[j] = heat_bath(w[j], T[j], mid[side], x[j]);  // I >= 0 up to mid
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int r = 8 * (j >> 2) + (j & 3);
@@ -338,14 +318,14 @@ hipError_t launch(const Args &g, int cus, size_t lds, hipStream_t st)
 
 bool bq_cluster_supported(const BqView &p, int width)
 {
-    return p.Jb && blocks_of(p.na) <= kMaxBlocks && blocks_of(p.nb) <= kMaxBlocks && width >= 1 && width <= kMaxWidth;
+    return p.J4 && blocks_of(p.na) <= kMaxBlocks && blocks_of(p.nb) <= kMaxBlocks && width >= 1 && width <= kMaxWidth;
 }
 
 size_t bq_cluster_bytes(const BqView &p, int R)
 {
     const size_t tiles = (size_t)(R + 31) / 32;
-    const size_t quads = (size_t)(blocks_of(p.na) + 3) / 4 + (size_t)(blocks_of(p.nb) + 3) / 4;
-    return 4 * (kCtlWords + 2 * tiles * 32 + tiles * quads * 128);
+    const size_t octets = (size_t)(blocks_of(p.na) + 7) / 8 + (size_t)(blocks_of(p.nb) + 7) / 8;
+    return 4 * (kCtlWords + 2 * tiles * 32 + tiles * octets * 256);
 }
 
 hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
@@ -359,8 +339,8 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     hipError_t e = fill_i32((int32_t *)w, (int64_t)(bq_cluster_bytes(p, R) / 4), 0, st);
     if (e != hipSuccess) return e;
     Args g{};
-    g.J[0] = p.Jb;
-    g.J[1] = p.JTb;
+    g.J[0] = p.J4;
+    g.J[1] = p.JT4;
     g.h2[0] = p.hA2;
     g.h2[1] = p.hB2;
     g.M[0] = MA;
@@ -368,7 +348,7 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.ctl = w;
     g.flags = w + kCtlWords;
     g.X[0] = g.flags + 2 * tiles * 32;
-    g.X[1] = g.X[0] + (size_t)tiles * ((blocks_of(p.na) + 3) / 4) * 128;
+    g.X[1] = g.X[0] + (size_t)tiles * ((blocks_of(p.na) + 7) / 8) * 256;
     g.table = table;
     g.n[0] = p.na;
     g.n[1] = p.nb;
@@ -386,8 +366,8 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.k0 = key.k0;
     g.k1 = key.k1;
     const size_t lds = sizeof(uint32_t) * (size_t)std::max(kRows * width * kWaves, 4);
-    if (g.members <= 8) return launch<8>(g, cus, lds, st);
-    return g.members <= 16 ? launch<16>(g, cus, lds, st) : launch<32>(g, cus, lds, st);
+    if (g.members <= 8) return launch<4>(g, cus, lds, st);
+    return g.members <= 16 ? launch<8>(g, cus, lds, st) : launch<16>(g, cus, lds, st);
 }
 
 }  // namespace pbit

@@ -387,21 +387,16 @@ __global__ __launch_bounds__(kThreads) void k_bq_field_energy(const int8_t *__re
 //
 // Spins are +-1, so a replica fits one bit per site: bit b of spin word w of a
 // replica is set when site 32 w + b holds -1.  The words of a side are stored
-// by blocks of 128 sites: word w of replica r at ((w / 4) Rp + r) 4 + w % 4, so
-// that the 16 bytes of one block of consecutive replicas are contiguous.
+// by blocks of 128 sites, even words first: word w of replica r at
+// ((w / 4) Rp + r) 4 + word_at(w), so that the 16 bytes of one block of consecutive
+// replicas are contiguous and a lane half reads its words of two K steps as one.
 // With b_k the bit of site k, m_k = 1 - 2 b_k and the field of a site s is
 //     I_s = h_s + sum_k J_sk m_k = (h_s + sum_k J_sk) - 2 sum_k J_sk b_k,
-// whose last sum runs on the int8 MFMA with int32 accumulation, the bits
-// widened to bytes in registers.  The spins cross from L2 at one eighth of
-// the int8 bytes, which is what bounds the int8 tiles of large bicliques.
-//
-// Widening: lane half g (lanes 32 g .. 32 g + 31) of an MFMA fragment holds 16
-// K bytes, dword j byte i at K position 16 g + 4 j + i.  From a spin word w,
-// x = w >> 4 g, the dword x & (0x01010101 << j) holds bit 8 i + 4 g + j of w in
-// byte i, as the value 0 or 2^j: one AND per dword.  The couplings are stored
-// with their columns in that order inside every group of 32 and scaled by
-// 2^(3 - j) (Jb, JTb, values in [-8, 8]), so every product is 8 J b and the
-// accumulator holds 8 sum_k J_sk b_k exactly.
+// whose last sum runs on the FP4 MFMA, the bits widened to four-bit numbers in registers
+// (five instructions for 64 sites) and met by couplings in the same order whose scale makes
+// every product 2 J b.  The spins cross from L2 at one eighth of their int8 bytes and the
+// couplings at half, which is what bounds the int8 tiles of large bicliques; the matrix
+// work is half that of int8 operands.
 //
 // Tile: 64 sites x RT replicas per workgroup, RT = 256 on large bicliques.  The
 // bytes that reach a CU per multiply-add, 1 / RT for the couplings plus 1 / 512
@@ -414,33 +409,32 @@ __global__ __launch_bounds__(kThreads) void k_bq_field_energy(const int8_t *__re
 // work stays near 2.5 instructions per MFMA (an MFMA holds the wave's VALU issue
 // for about half of its 32 cycles) and the LDS fragment reads under the
 // matrix-core time of a stage.
-// Stages of KT = 128 or 256 K move by the global-to-LDS DMA into a ring: 64
-// coupling rows of KT bytes (chunk c of row r at position c ^ swzb(r)), then the
-// RT replicas' 16 bytes (four spin words) per 128-site block of the stage.
+// Stages of 256 sites move by the global-to-LDS DMA into a ring: 64 coupling rows of 128
+// bytes (chunk c of row r at position c ^ swzb(r)), then the RT replicas' 16 bytes (four
+// spin words) per 128-site block of the stage.
 //
-// Decisions through 64-bit words in LDS, one per clamped field value:
-// S(I) = Tm(|I|) for I >= 0, 2^32 - Tm(|I|) for I < 0; the new spin is -1
-// exactly when w + S(I) carries into bit 32 (the heat-bath rule with the
-// uniform word w), so a lane's decision is one multiply-add and one compare,
-// and a wave's 64 decisions form one ballot mask.
+// Decisions: an accumulator's bits lie 4 |I| from those at I = 0, which is the byte offset of
+// Tm(|I|) in the threshold row in LDS; three comparisons give a wave's 64 decisions as one
+// mask.
 
 constexpr int kBitsST = 64;     // sites per tile
+// place of spin word w in its block's four
+__host__ __device__ constexpr int word_at(int w) { return (w & 1) * 2 + ((w >> 1) & 1); }
 constexpr int kBitsRT = 256;    // replicas per tile of the full-size form; Rp is a multiple of it
 constexpr int kBitsBlock = 128; // sites per block of the spin-word layout (four words)
 constexpr int kBitsWaves = 8;   // waves per workgroup of the full-size form (32 replicas each, two per SIMD)
 constexpr int kBitsMinGroups = 256;  // workgroups (one per CU) below which the default tile shrinks
 
-// KT: K per stage, 128 (an 8-stage ring) or 256 (a 4-stage ring, half the
-// barriers per launch, for sides that are multiples of 256).  RT: replicas per
-// tile, 32 per wave; tiles of 128 and 64 replicas (four and two waves) give a
-// launch more workgroups where sides of 1024 or 2048 would fill only a quarter or
+// RT: replicas per tile, 32 per wave; tiles of 128 and 64 replicas (four and two waves)
+// give a launch more workgroups where sides of 1024 or 2048 would fill only a quarter or
 // half of the CUs with 256.
-template <int WAVES, int KT, int RT>
+template <int WAVES, int RT>
 struct BitsGeom {
     static constexpr int threads = 64 * WAVES;
-    static constexpr int NS = KT == 256 ? 4 : 8;          // stages in the ring
+    static constexpr int NS = 8;                           // stages in the ring
+    static constexpr int KT = 128;                         // bytes of a coupling row in a stage (256 sites)
     static constexpr int jbytes = kBitsST * KT;            // coupling rows of one stage
-    static constexpr int bbytes = RT * KT / 8;             // spin words of one stage (KT / 128 blocks)
+    static constexpr int bbytes = RT * KT / 4;             // spin words of one stage (two blocks)
     static constexpr int bblock = 16 * RT;                 // bytes of one 128-site block of the stage's spin words
     static constexpr int stage = jbytes + bbytes;
     static constexpr int j_per_wave = jbytes / 1024 / WAVES;          // 16-byte-lane DMA instructions per wave
@@ -457,27 +451,27 @@ struct BitsGeom {
                   "whole DMA instructions");
 };
 
-template <int WAVES, int KT, int RT>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(BitsGeom<WAVES, KT, RT>::waves_per_eu,
-                                                                              BitsGeom<WAVES, KT, RT>::waves_per_eu))) void
-k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__ Jb, const int32_t *__restrict__ hs2,
+template <int WAVES, int RT>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(BitsGeom<WAVES, RT>::waves_per_eu,
+                                                                              BitsGeom<WAVES, RT>::waves_per_eu))) void
+k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const uint8_t *__restrict__ J4, const int32_t *__restrict__ hs2,
                     uint32_t *__restrict__ Msb, const uint32_t *__restrict__ trow, int width, int Ko, int Rp,
                     int tiles_s, int xcd_bands, uint32_t site_base, uint32_t sweep, uint32_t rq0, uint32_t k0,
-                    uint32_t k1, uint32_t one)
+                    uint32_t k1)
 {
-    using G = BitsGeom<WAVES, KT, RT>;
-    constexpr int NS = G::NS;
+    using G = BitsGeom<WAVES, RT>;
+    constexpr int NS = G::NS, KT = G::KT;
     constexpr int CH = KT / 16;       // 16-byte chunks per coupling row
-    constexpr int kSubs = KT / 32;    // K steps per stage
-    constexpr int KB = KT / kBitsBlock;  // spin-word blocks per stage
+    constexpr int kSubs = KT / 32;    // K steps (64 sites, 32 bytes of a row) per stage
+    constexpr int KB = 2;             // spin-word blocks per stage
     constexpr int BI = G::bi;         // replica blocks of 32 per wave
     constexpr int RW = 32 * BI;       // replicas per wave
 
     extern __shared__ uint4 smem[];
     int8_t *ring = reinterpret_cast<int8_t *>(smem);
-    uint64_t *Sw = reinterpret_cast<uint64_t *>(ring + G::ring);  // [2 top + 1]
+    uint32_t *row = reinterpret_cast<uint32_t *>(ring + G::ring);  // thresholds [width]
     const int top = width - 1;
-    // the threshold row goes to registers now and into the LDS decision words after
+    // the threshold row goes to registers now and into LDS after
     // the K loop, so that its load overlaps the DMA stages instead of preceding them:
     // thread x holds Tm(x + threads k), k < kTv
     constexpr int kTv = (kMaxTableWidth + G::threads - 1) / G::threads;
@@ -507,47 +501,38 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
     // stage, from a wave-uniform base plus a 32-bit lane offset.  Row r of a stage keeps
     // chunk c at position c ^ swzb(r), with a swizzle of r mod 32 only, so that the two
     // site blocks of a fragment read sit at a fixed distance.  Rows of 128 bytes span
-    // half the banks: the swizzle spreads 8 even and 8 odd rows; rows of 256 bytes
-    // span all of them: it spreads 16 rows.
-    auto swzb = [](int r) { return CH == 8 ? ((r ^ ((r >> 3) & 3)) & 7) : (r & 15); };
-    uint32_t offJl[4], offBl[4];
-    static_assert(G::j_per_wave <= 4 && G::b_per_wave <= 4 && kSubs <= 8, "fixed array bounds");
+    // half the banks: the swizzle spreads 8 even and 8 odd rows.
+    auto swzb = [](int r) { return (r ^ ((r >> 3) & 3)) & 7; };
+    const int row_bytes = bq_row_bytes(Ko);
+    uint32_t offJl[4], offBl;
+    static_assert(G::j_per_wave <= 4 && G::b_per_wave == 1 && G::bsz == 16 && kSubs <= 8, "fixed array bounds");
 #pragma unroll
     for (int j = 0; j < G::j_per_wave; ++j) {
         const int S = 64 * (G::j_per_wave * wave + j) + lane;
         const int r = S / CH, c = (S % CH) ^ swzb(S / CH);
-        offJl[j] = (uint32_t)(r * Ko + 16 * c);
+        offJl[j] = (uint32_t)(r * row_bytes + 16 * c);
     }
-    // spin words: byte o of a stage's spin area is byte o % bblock of block o / bblock of the
-    // stage (its replicas' 16 bytes each, contiguous in the block layout)
-#pragma unroll
-    for (int j = 0; j < G::b_per_wave; ++j) {
-        const uint32_t o = (uint32_t)(G::bsz * (64 * (G::b_per_wave * wave + j) + lane));
-        offBl[j] = (o / (uint32_t)G::bblock) * 16u * (uint32_t)Rp + o % (uint32_t)G::bblock;
-    }
-    const int8_t *Jt0 = Jb + (size_t)s0 * Ko;
+    // spin words: a wave fills 1024 bytes of a stage's spin area, of one of its two blocks
+    // (its replicas' 16 bytes each, contiguous in the block layout); past the side's last
+    // block, whose couplings are zero, of that block again
+    const int wave_block = 1024 * wave / G::bblock;
+    offBl = (uint32_t)((1024 * wave) % G::bblock + 16 * lane);
+    const int blocks = Ko / kBitsBlock;
+    const uint8_t *Jt0 = J4 + (size_t)s0 * row_bytes;
     const char *Bt0 = reinterpret_cast<const char *>(Mob + (size_t)r0 * 4);
-    const int nk = Ko / KT;
+    const int nk = row_bytes / KT;
     const int ln = lane & 31, kg = lane >> 5;
     // the fields of this lane's two sites (field plus coupling sum; zero at padding sites),
     // loaded before the DMA so that the stage waits also cover them
     const int h2v[2] = {hs2[s0 + ln], hs2[s0 + 32 + ln]};
     auto issue = [&](int t) {
         int8_t *dJ = ring + (t % NS) * G::stage + 1024 * G::j_per_wave * wave;
-        int8_t *dB = ring + (t % NS) * G::stage + G::jbytes + 64 * G::bsz * G::b_per_wave * wave;
-        const int8_t *Jt = Jt0 + (size_t)t * KT;
-        const char *Bt = Bt0 + (size_t)t * KB * 16 * Rp;
+        int8_t *dB = ring + (t % NS) * G::stage + G::jbytes + 1024 * wave;
+        const uint8_t *Jt = Jt0 + (size_t)t * KT;
+        const char *Bt = Bt0 + (size_t)min(t * KB + wave_block, blocks - 1) * 16 * Rp;
 #pragma unroll
         for (int j = 0; j < G::j_per_wave; ++j) __builtin_amdgcn_global_load_lds(Jt + offJl[j], dJ + 1024 * j, 16, 0, 0);
-        // size and LDS step as literals: with a template-dependent LDS offset, the
-        // compiler's host pass rejects the 16-byte form and silently drops the kernel
-#pragma unroll
-        for (int j = 0; j < G::b_per_wave; ++j) {
-            if constexpr (G::bsz == 16)
-                __builtin_amdgcn_global_load_lds(Bt + offBl[j], dB + 1024 * j, 16, 0, 0);
-            else
-                __builtin_amdgcn_global_load_lds(Bt + offBl[j], dB + 256 * j, 4, 0, 0);
-        }
+        __builtin_amdgcn_global_load_lds(Bt + offBl, dB, 16, 0, 0);
     };
     // the threshold row and field loads above are older than every DMA below, so each
     // wait for a stage also covers them
@@ -558,17 +543,19 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
     int offJ[8];
 #pragma unroll
     for (int sub = 0; sub < kSubs; ++sub) offJ[sub] = KT * ln + 16 * ((2 * sub + kg) ^ swzb(ln));
-    const int offB = G::jbytes + 16 * (RW * wave + ln);  // spin words of replica rows RW wave + 32 bi + ln
-    v16i acc[BI][2];  // [replica block][site block]
+    const int offB = G::jbytes + 16 * (RW * wave + ln) + 8 * kg;  // spin words of replica rows RW wave + 32 bi + ln
+    v16f_t acc[BI][2];  // [replica block][site block]
 #pragma unroll
-    for (int bi = 0; bi < BI; ++bi) acc[bi][0] = acc[bi][1] = v16i{0};
+    for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[bi][0][j] = acc[bi][1][j] = __uint_as_float(kFieldBase);
     uint32_t words[8 * BI][4];
 
     // the fragments of one stage in registers: the next stage's are read from LDS
     // while the MFMAs run on the current one's (a barrier before the reads would
     // otherwise leave the matrix cores idle for the LDS latency at every stage)
     struct Frag {
-        v4i w[BI][KB];     // spin words of replica rows 32 bi + ln, one per K step of a block
+        v2i_t w[BI][KB];   // spin words of replica rows 32 bi + ln: this lane half's of a block's two K steps
         v4i b[kSubs][2];   // coupling fragments [K step][site block]
     };
     auto load = [&](int t, Frag &f) {
@@ -580,7 +567,7 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
         for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
-                f.w[bi][kb] = *reinterpret_cast<const v4i *>(st + offB + G::bblock * kb + 16 * 32 * bi);
+                f.w[bi][kb] = *reinterpret_cast<const v2i_t *>(st + offB + G::bblock * kb + 16 * 32 * bi);
 #pragma unroll
         for (int sub = 0; sub < kSubs; ++sub)
 #pragma unroll
@@ -592,10 +579,9 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
         for (int sub = 0; sub < kSubs; ++sub)
 #pragma unroll
             for (int bi = 0; bi < BI; ++bi) {
-                const v4i a = widen_bits((uint32_t)f.w[bi][sub / 4][sub % 4], kg);
+                const v4i a = spin_bits_fp4((uint32_t)f.w[bi][sub / 2][sub % 2]);
 #pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    acc[bi][bj] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, f.b[sub][bj], acc[bi][bj], 0, 0, 0);
+                for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = mfma_fp4(a, f.b[sub][bj], acc[bi][bj]);
             }
     };
     // an empty statement that takes the fragments as its outputs: called where they are
@@ -672,22 +658,19 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
     // block, half 1: row 8 q + 4 + p); lane L of out[bj] collects the word of
     // replica row L of the wave for site block bj.  Padding sites and replicas
     // take bits that nothing reads (their couplings and fields are zero).
-    // decision words for I = +-x from Tm(x): Tm for I >= 0, 2^32 - Tm for I < 0; built
-    // here, where no DMA is in flight, so that waiting for the row costs nothing
+    // the threshold row goes to LDS here, where no DMA is in flight, so that waiting for it
+    // costs nothing
 #pragma unroll
     for (int k = 0; k < kTv; ++k) {
         const int x = (int)threadIdx.x + G::threads * k;
-        if (x <= top) {
-            Sw[top + x] = (uint64_t)tv[k];
-            Sw[top - x] = ((uint64_t)1 << 32) - tv[k];
-        }
+        if (x <= top) row[x] = tv[k];
     }
     __syncthreads();
-    const char *Sb = reinterpret_cast<const char *>(Sw);
+    const uint32_t row0 = lds_address(row), row_end = row0 + 4u * (uint32_t)top;
     uint32_t out[2] = {0u, 0u};
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
-        const int h2 = h2v[bj];
+        const uint32_t mid = kFieldBase + 4u * (uint32_t)h2v[bj];  // the accumulator at I = 0
 #pragma unroll
         for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
@@ -695,21 +678,21 @@ k_bq_halfsweep_bits(const uint32_t *__restrict__ Mob, const int8_t *__restrict__
                 const int blk = (bj * BI + bi) * 4 + q;
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
-                    const int I = h2 - (acc[bi][bj][4 * q + p] >> 2);  // the accumulator holds 8 sum J b
-                    const int Ic = min(max(I, -top), top);
-                    const uint64_t S =
-                        *static_cast<const uint64_t *>(__builtin_assume_aligned(Sb + 8 * (Ic + top), 8));
-                    const uint64_t m = __ballot((((uint64_t)words[blk][p] * one + S) >> 32) != 0);
+                    const uint32_t x = __float_as_uint(acc[bi][bj][4 * q + p]);  // kFieldBase + 8 sum J b
+                    const uint32_t T = lds_word(min(sad(x, mid, row0), row_end));
+                    const uint64_t m = heat_bath(words[blk][p], T, mid, x);
                     const int L = bi * 32 + 8 * q + p;
                     out[bj] = (uint32_t)lane_write((int)(uint32_t)m, L, (int)out[bj]);
                     out[bj] = (uint32_t)lane_write((int)(uint32_t)(m >> 32), L + 4, (int)out[bj]);
                 }
             }
     }
-    // words s0 / 32 and + 1 of replica row RW wave + lane: an aligned pair in a block of four
-    if (lane < RW)
-        *reinterpret_cast<uint2 *>(Msb + ((size_t)(s0 / kBitsBlock) * Rp + r0 + RW * wave + lane) * 4 + (s0 / 32) % 4) =
-            make_uint2(out[0], out[1]);
+    // words s0 / 32 (an even one) and + 1 of replica row RW wave + lane
+    if (lane < RW) {
+        uint32_t *to = Msb + ((size_t)(s0 / kBitsBlock) * Rp + r0 + RW * wave + lane) * 4 + word_at(s0 / 32);
+        to[0] = out[0];
+        to[2] = out[1];
+    }
 }
 
 // int8 rows [Rp][cols] <-> spin words by blocks of 128 sites; one thread per word
@@ -722,7 +705,7 @@ __global__ __launch_bounds__(kThreads) void k_bq_bits(int8_t *__restrict__ M, ui
     if (k >= (int64_t)Rp * nw) return;
     const int r = (int)(k / nw), w = (int)(k % nw);
     uint4 *row = reinterpret_cast<uint4 *>(M + (size_t)r * cols + 32 * w);
-    uint32_t *word = Mb + ((size_t)(w / 4) * Rp + r) * 4 + w % 4;
+    uint32_t *word = Mb + ((size_t)(w / 4) * Rp + r) * 4 + word_at(w);
     if (PACK) {
         const uint4 v0 = row[0], v1 = row[1];
         const uint32_t d[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -841,7 +824,7 @@ hipError_t bqb_unpack(const BqView &p, const uint32_t *MAb, const uint32_t *MBb,
 
 bool bqb_supported(const BqView &p, int Rp)
 {
-    return p.Jb && p.na_p % kBitsST == 0 && p.nb_p % kBitsST == 0 && p.na_p % kBitsBlock == 0 &&
+    return p.J4 && p.na_p % kBitsST == 0 && p.nb_p % kBitsST == 0 && p.na_p % kBitsBlock == 0 &&
            p.nb_p % kBitsBlock == 0 && Rp % kBitsRT == 0;
 }
 
@@ -855,21 +838,21 @@ static int bits_rt(int tiles_s, int Rp, int rt)
     return Rp % 128 == 0 ? 128 : 64;
 }
 
-template <int WAVES, int KT, int RT>
-static hipError_t bits_launch(const uint32_t *Mob, const int8_t *Jb, const int32_t *hs2, uint32_t *Msb,
+template <int WAVES, int RT>
+static hipError_t bits_launch(const uint32_t *Mob, const uint8_t *J4, const int32_t *hs2, uint32_t *Msb,
                               const uint32_t *trow, int width, int Ko, int Rp, int tiles_s, uint32_t site_base,
                               uint32_t sweep, uint32_t rq0, Key key, hipStream_t st)
 {
-    using G = BitsGeom<WAVES, KT, RT>;
+    using G = BitsGeom<WAVES, RT>;
     static const hipError_t lds_attr = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&k_bq_halfsweep_bits<WAVES, KT, RT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-        G::ring + (int)sizeof(uint64_t) * (2 * kMaxTableWidth - 1));
+        reinterpret_cast<const void *>(&k_bq_halfsweep_bits<WAVES, RT>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        G::ring + (int)sizeof(uint32_t) * kMaxTableWidth);
     if (lds_attr != hipSuccess) return lds_attr;
     const int bands = tiles_s % 8 == 0 ? 1 : 0;
-    const size_t tab = sizeof(uint64_t) * (size_t)(2 * width - 1);
+    const size_t tab = sizeof(uint32_t) * (size_t)width;
     const dim3 grid((unsigned)(tiles_s * (Rp / RT)));
-    hipLaunchKernelGGL((k_bq_halfsweep_bits<WAVES, KT, RT>), grid, dim3(G::threads), G::ring + tab, st, Mob, Jb, hs2,
-                       Msb, trow, width, Ko, Rp, tiles_s, bands, site_base, sweep, rq0, key.k0, key.k1, 1u);
+    hipLaunchKernelGGL((k_bq_halfsweep_bits<WAVES, RT>), grid, dim3(G::threads), G::ring + tab, st, Mob, J4, hs2,
+                       Msb, trow, width, Ko, Rp, tiles_s, bands, site_base, sweep, rq0, key.k0, key.k1);
     return hipGetLastError();
 }
 
@@ -880,27 +863,19 @@ hipError_t bqb_halfsweep(const BqView &p, int side, uint32_t *MAb, uint32_t *MBb
     const bool A = side == 0;
     const int Ns_p = A ? p.na_p : p.nb_p, Ko = A ? p.nb_p : p.na_p;
     const uint32_t *Mob = A ? MBb : MAb;
-    const int8_t *Jb = A ? p.Jb : p.JTb;
+    const uint8_t *J4 = A ? p.J4 : p.JT4;
     const int32_t *hs2 = A ? p.hA2 : p.hB2;
     uint32_t *Msb = A ? MAb : MBb;
     const uint32_t site_base = A ? 0u : (uint32_t)p.na;
     const int tiles_s = Ns_p / kBitsST;
-    // two waves cannot take a 256-deep stage (its DMA needs more than four 16-byte
-    // loads per lane), so 64-replica tiles always stage 128
     switch (bits_rt(tiles_s, Rp, rt)) {
     case 256:
-        return Ko % 256 == 0 ? bits_launch<kBitsWaves, 256, 256>(Mob, Jb, hs2, Msb, trow, width, Ko, Rp, tiles_s,
-                                                                  site_base, sweep, rq0, key, st)
-                             : bits_launch<kBitsWaves, 128, 256>(Mob, Jb, hs2, Msb, trow, width, Ko, Rp, tiles_s,
-                                                                  site_base, sweep, rq0, key, st);
+        return bits_launch<kBitsWaves, 256>(Mob, J4, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base, sweep, rq0, key,
+                                            st);
     case 128:
-        return Ko % 256 == 0 ? bits_launch<4, 256, 128>(Mob, Jb, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base,
-                                                         sweep, rq0, key, st)
-                             : bits_launch<4, 128, 128>(Mob, Jb, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base,
-                                                         sweep, rq0, key, st);
+        return bits_launch<4, 128>(Mob, J4, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base, sweep, rq0, key, st);
     default:
-        return bits_launch<2, 128, 64>(Mob, Jb, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base, sweep, rq0, key,
-                                       st);
+        return bits_launch<2, 64>(Mob, J4, hs2, Msb, trow, width, Ko, Rp, tiles_s, site_base, sweep, rq0, key, st);
     }
 }
 

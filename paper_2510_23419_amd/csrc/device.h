@@ -114,6 +114,13 @@ __device__ __forceinline__ v4i_t spin_nibbles(uint32_t w)
                  (int)(one | (w & sign))};
 }
 
+// 32 spin bits for a product with couplings scaled to match: bit 4 i + j at nibble i of
+// dword j, as 0 or (an E2M1 number) 1/2, 1, 2, 1/2 for j = 0 .. 3.
+__device__ __forceinline__ v4i_t spin_bits_fp4(uint32_t w)
+{
+    return v4i_t{(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u), (int)((w >> 3) & 0x11111111u)};
+}
+
 // |a - b| + c
 __device__ __forceinline__ uint32_t sad(uint32_t a, uint32_t b, uint32_t c)
 {
@@ -138,22 +145,6 @@ __device__ __forceinline__ uint64_t heat_bath(uint32_t w, uint32_t Tm, uint32_t 
     constexpr int kUgt = 34, kUge = 35;  // wave-wide comparisons; as plain ones the first becomes an add, a select and a test
     const uint64_t up = __builtin_amdgcn_uicmp(x, mid, kUge);
     return (up & __builtin_amdgcn_uicmp(w, ~Tm, kUgt)) | (~up & __builtin_amdgcn_uicmp(w, Tm, kUge));
-}
-
-// Spin bits widened for the int8 MFMA: the K bytes that lane half g of a 32x32x32
-// fragment holds (dword j byte i = K position 16 g + 4 j + i) from a word w of
-// 32 spin bits (set = -1): byte i of dword j holds bit 8 i + 4 g + j of w as the
-// value 0 or 2^j.  Couplings stored in that site order and scaled by 2^(3 - j)
-// make every product 8 J b.
-__device__ __forceinline__ v4i_t widen_bits(uint32_t w, int g)
-{
-    const uint32_t x = w >> (4 * g);
-    v4i_t a;
-    a[0] = (int)(x & 0x01010101u);
-    a[1] = (int)(x & 0x02020202u);
-    a[2] = (int)(x & 0x04040404u);
-    a[3] = (int)(x & 0x08080808u);
-    return a;
 }
 
 // Initial spin from a domain-1 word.

@@ -373,25 +373,26 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
     if (rc == PBIT_OK) rc = upload(ctx, p, JT.data(), JT.size(), &dJT);
     if (rc == PBIT_OK) rc = upload(ctx, p, hA.data(), hA.size(), &dhA);
     if (rc == PBIT_OK) rc = upload(ctx, p, hB.data(), hB.size(), &dhB);
-    void *dJb = nullptr, *dJTb = nullptr, *dhA2 = nullptr, *dhB2 = nullptr;
+    void *dJ4 = nullptr, *dJT4 = nullptr, *dhA2 = nullptr, *dhB2 = nullptr;
     if (rc == PBIT_OK) {
-        // the kernels on spin bits (per-instance half-sweep and batched tiles): K byte p = 16 g + 4 j + i of every group of 32
-        // columns holds column 8 i + 4 g + j of the group times 2^(3 - j) (the spin
-        // byte it meets holds the bit times 2^j), and each field carries the coupling
-        // sum of its site
-        auto permute = [](const std::vector<int8_t> &M, int rows, int cols, std::vector<int8_t> &out) {
-            out.assign(M.size(), 0);
+        // the kernels on spin bits (per-instance half-sweep, cluster and batched tiles): 32
+        // columns in 16 bytes, column 4 i + j at nibble i of dword j, times 4, 2, 1, 4 for
+        // j = 0 .. 3 (the spin bit it meets counts 1/2, 1, 2, 1/2) as an E2M1 number; and each
+        // field carries the coupling sum of its site
+        auto pack4 = [](const std::vector<int8_t> &M, int rows, int cols, std::vector<uint32_t> &out) {
+            static const uint32_t size[4] = {6u, 4u, 2u, 6u};
+            const size_t words = (size_t)bq_row_bytes(cols) / 4;
+            out.assign((size_t)rows * words, 0u);
             for (int r = 0; r < rows; ++r)
-                for (int c0 = 0; c0 < cols; c0 += 32)
-                    for (int q = 0; q < 32; ++q) {
-                        const int g = q >> 4, j = (q >> 2) & 3, i = q & 3;
-                        out[(size_t)r * cols + c0 + q] =
-                            (int8_t)(M[(size_t)r * cols + c0 + 8 * i + 4 * g + j] * (1 << (3 - j)));
-                    }
+                for (int c = 0; c < cols; ++c) {
+                    const int v = M[(size_t)r * cols + c], j = c % 4;
+                    if (v != 0)
+                        out[r * words + (size_t)(c / 32) * 4 + j] |= (size[j] | (v < 0 ? 8u : 0u)) << (4 * (c % 32 / 4));
+                }
         };
-        std::vector<int8_t> Jb, JTb;
-        permute(J, na_p, nb_p, Jb);
-        permute(JT, nb_p, na_p, JTb);
+        std::vector<uint32_t> J4, JT4;
+        pack4(J, na_p, nb_p, J4);
+        pack4(JT, nb_p, na_p, JT4);
         std::vector<int32_t> hA2(na_p, 0), hB2(nb_p, 0);
         for (int a = 0; a < na; ++a) {
             hA2[a] = hA[a];
@@ -401,8 +402,8 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
             hB2[b] = hB[b];
             for (int a = 0; a < na; ++a) hB2[b] += JT[(size_t)b * na_p + a];
         }
-        rc = upload(ctx, p, Jb.data(), Jb.size(), &dJb);
-        if (rc == PBIT_OK) rc = upload(ctx, p, JTb.data(), JTb.size(), &dJTb);
+        rc = upload(ctx, p, J4.data(), sizeof(uint32_t) * J4.size(), &dJ4);
+        if (rc == PBIT_OK) rc = upload(ctx, p, JT4.data(), sizeof(uint32_t) * JT4.size(), &dJT4);
         if (rc == PBIT_OK) rc = upload(ctx, p, hA2.data(), sizeof(int32_t) * hA2.size(), &dhA2);
         if (rc == PBIT_OK) rc = upload(ctx, p, hB2.data(), sizeof(int32_t) * hB2.size(), &dhB2);
     }
@@ -434,7 +435,7 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
     p.N = (int64_t)na + nb;
     p.amax = amax;
     p.bq = BqView{na, nb, na_p, nb_p, (const int8_t *)dJ, (const int8_t *)dJT, (const int8_t *)dhA,
-                  (const int8_t *)dhB, (const int8_t *)dJb, (const int8_t *)dJTb, (const int32_t *)dhA2, (const int32_t *)dhB2,
+                  (const int8_t *)dhB, (const uint8_t *)dJ4, (const uint8_t *)dJT4, (const int32_t *)dhA2, (const int32_t *)dhB2,
                   (const uint32_t *)dJ2};
     return PBIT_OK;
 }
@@ -1071,7 +1072,7 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
         // int8 spins, plus a bit copy where the sides are padded to 128 and the replicas to 256
         // (the tuner then times the bit kernel, whose tiles hold 256 replicas: a forced bit
         // kernel pads to that)
-        const bool bits_forced = ctx->bq_forced == BqVariant::Bits && P.bq.Jb;
+        const bool bits_forced = ctx->bq_forced == BqVariant::Bits && P.bq.J4;
         ds.Rp = round_up(R, bits_forced ? 256 : kBqRPad);
         const size_t a = (size_t)ds.Rp * P.bq.na_p, b = (size_t)ds.Rp * P.bq.nb_p;
         rc = take(ctx, ds, Slot::Spins, a + b, &v);
@@ -1531,7 +1532,7 @@ size_t anneal_dev_bytes(const pbit_ctx *ctx, const Problem &P, const pbit_anneal
     const size_t R = (size_t)d->n_replicas;
     size_t spins, Rp;
     if (P.kind == PBIT_BICLIQUE) {
-        const bool bits = ctx->bq_forced == BqVariant::Bits && P.bq.Jb;
+        const bool bits = ctx->bq_forced == BqVariant::Bits && P.bq.J4;
         Rp = (R + (bits ? 255 : kBqRPad - 1)) / (bits ? 256 : kBqRPad) * (bits ? 256 : kBqRPad);
         const size_t ab = Rp * (size_t)(P.bq.na_p + P.bq.nb_p);
         spins = ab + (bqb_supported(P.bq, (int)Rp) ? ab / 8 + 256 : 0);
