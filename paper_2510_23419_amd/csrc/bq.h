@@ -54,7 +54,7 @@ bool bq_slab_supported(const BqView &p, int Rp, int width, int rs = 0);
 hipError_t bq_slab(const BqView &p, int8_t *MA, int8_t *MB, int Rp, const uint32_t *table, int width, int s_begin,
                    int s_end, uint32_t sweep0, uint32_t rq0, Key key, hipStream_t st, int rs = 0);
 // The form whose couplings stay in registers across an XCD (bq_cluster.hip), for sides of at
-// most 1024 sites and threshold rows of at most 256 entries: sweeps [s_begin, s_end) of
+// most 2048 sites and threshold rows of at most 256 entries: sweeps [s_begin, s_end) of
 // replicas [0, R) on MA / MB in place, with `work` (bq_cluster_bytes) as exchange memory and a
 // workgroup on each of `cus` compute units.  work[1] is 0 afterwards if the sweeps ran, 1
 // if the workgroups could not be resident together (MA / MB untouched), 2 after a lost flag.

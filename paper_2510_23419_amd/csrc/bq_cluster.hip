@@ -46,6 +46,7 @@ constexpr uint32_t kAbort = 0x80000000u;
 constexpr uint64_t kMeetTicks = 200000;  // 2 ms of the 100 MHz clock; an idle device takes some 10 us
 constexpr int kMaxWidth = 256;            // threshold row entries
 constexpr int kRows = 16;                 // threshold rows held per wave
+constexpr int kMaxBlocks = 64;            // a wave's lanes watch one flag each
 constexpr int kPollLimit = 1 << 21;       // a second or so: never reached by resident workgroups
 
 struct Args {
@@ -53,7 +54,7 @@ struct Args {
     const int32_t *h2[2];   // field plus coupling sum
     int8_t *M[2];           // int8 spins [Rp][n_p]
     uint32_t *X[2];         // spin words [row tile][block / 8][block % 2][32 replicas][block / 2 % 4]
-    uint32_t *flags;        // [2][row tiles][32]: updates a block has published
+    uint32_t *flags;        // [2][row tiles][kMaxBlocks]: updates a block has published
     uint32_t *ctl;          // arrivals, status, 8 per-XCD counts
     const uint32_t *table;
     int n[2], n_p[2], blocks[2];
@@ -102,8 +103,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int octets)
     return __builtin_amdgcn_make_buffer_rsrc(p, 0, 1024 * octets, 0x00027000);
 }
 
-// KS: K steps of 64 sites a side may have (the couplings take 8 KS registers).
-template <int KS>
+// KS: K steps of 64 sites a side may have (the couplings take 8 KS registers).  BPW: blocks of
+// a workgroup, one a wave: all four waves on one block, each with a row tile of its own, or
+// two waves on each of two.
+template <int KS, int BPW>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_bq_cluster(Args g)
 {
     extern __shared__ uint32_t lds[];  // per wave kRows threshold rows; starts at LDS address 0
@@ -120,13 +123,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     __syncthreads();
     const int ok = __builtin_amdgcn_readfirstlane((int)joined[0]);
     const int cluster = __builtin_amdgcn_readfirstlane((int)joined[1]);
-    const int c = __builtin_amdgcn_readfirstlane((int)joined[2]);
+    const int slot = __builtin_amdgcn_readfirstlane((int)joined[2]);
     __syncthreads();
-    if (!ok || c >= g.members) return;
+    if (!ok || slot >= g.members) return;
 
     const int lane = threadIdx.x & 63, ln = lane & 31, kg = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = BPW * slot + wave % BPW;  // this wave's block
     const bool has[2] = {c < g.blocks[0], c < g.blocks[1]};
+    if (!has[0] && !has[1]) return;
     // coupling operands: row 32 c + ln, 16 bytes of K step u at 32 u + 16 kg; zero past the row
     v4i_t jr[2][KS];
     int h2[2];
@@ -148,8 +153,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     const uint32_t mid[2] = {kFieldBase + 4u * (uint32_t)h2[0], kFieldBase + 4u * (uint32_t)h2[1]};
     const uint32_t rows = (uint32_t)wave * kRows * 4u * (uint32_t)g.width;  // LDS address of this wave's threshold rows
 
-    for (int t = cluster + kXcds * wave; t < g.tiles; t += kXcds * kWaves) {
-        uint32_t *flag[2] = {g.flags + 32 * t, g.flags + 32 * (g.tiles + t)};
+    for (int t = cluster + kXcds * (wave / BPW); t < g.tiles; t += kXcds * (kWaves / BPW)) {
+        uint32_t *flag[2] = {g.flags + kMaxBlocks * t, g.flags + kMaxBlocks * (g.tiles + t)};
         const int octets[2] = {(g.blocks[0] + 7) / 8, (g.blocks[1] + 7) / 8};  // blocks / 8 of a side
         uint32_t *xt[2] = {g.X[0] + (size_t)t * octets[0] * 256, g.X[1] + (size_t)t * octets[1] * 256};
         int out[2] = {0, 0};  // lane r: this block's word of replica r
@@ -181,7 +186,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             asm volatile("" ::: "memory");
             if (lane == 0)
                 __hip_atomic_store(flag[side] + c, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            peek = agent_load(flag[1 - ns] + ln);
+            peek = agent_load(flag[1 - ns] + lane);
             __builtin_amdgcn_sched_barrier(0);
             draw(ns, next, 2);
             __builtin_amdgcn_sched_barrier(0);
@@ -204,15 +209,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         else {
             draw(first, g.sweep0 + (uint32_t)g.s_begin, 0);
             draw(first, g.sweep0 + (uint32_t)g.s_begin, 2);
-            peek = agent_load(flag[1 - first] + ln);
+            peek = agent_load(flag[1 - first] + lane);
         }
 
         bool lost = false;
         const __amdgpu_buffer_rsrc_t xr[2] = {rsrc(xt[0], octets[0]), rsrc(xt[1], octets[1])};
         auto half = [&](auto side_c, uint32_t row, uint32_t need, uint32_t seq, int ns, uint32_t next) {
             constexpr int side = decltype(side_c)::value;
-            const uint32_t *f = flag[1 - side] + ln;
-            const bool watch = ln < g.blocks[1 - side];
+            const uint32_t *f = flag[1 - side] + lane;
+            const bool watch = lane < g.blocks[1 - side];
             int polls = 0;
             while (!__all(!watch || peek >= need)) {
                 if (++polls > kPollLimit) {
@@ -299,18 +304,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     }
 }
 
-constexpr int kMaxBlocks = 32;
 constexpr size_t kCtlWords = 16;
 
 int blocks_of(int n) { return (n + 31) / 32; }
 
-template <int KS>
+template <int KS, int BPW>
 hipError_t launch(const Args &g, int cus, size_t lds, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bq_cluster<KS>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bq_cluster<KS, BPW>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(k_bq_cluster<KS>, dim3((unsigned)cus), dim3(kThreads), lds, st, g);
+    hipLaunchKernelGGL((k_bq_cluster<KS, BPW>), dim3((unsigned)cus), dim3(kThreads), lds, st, g);
     return hipGetLastError();
 }
 
@@ -325,7 +329,7 @@ size_t bq_cluster_bytes(const BqView &p, int R)
 {
     const size_t tiles = (size_t)(R + 31) / 32;
     const size_t octets = (size_t)(blocks_of(p.na) + 7) / 8 + (size_t)(blocks_of(p.nb) + 7) / 8;
-    return 4 * (kCtlWords + 2 * tiles * 32 + tiles * octets * 256);
+    return 4 * (kCtlWords + 2 * tiles * kMaxBlocks + tiles * octets * 256);
 }
 
 hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
@@ -347,7 +351,7 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.M[1] = MB;
     g.ctl = w;
     g.flags = w + kCtlWords;
-    g.X[0] = g.flags + 2 * tiles * 32;
+    g.X[0] = g.flags + 2 * tiles * kMaxBlocks;
     g.X[1] = g.X[0] + (size_t)tiles * ((blocks_of(p.na) + 7) / 8) * 256;
     g.table = table;
     g.n[0] = p.na;
@@ -356,7 +360,8 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.n_p[1] = p.nb_p;
     g.blocks[0] = blocks_of(p.na);
     g.blocks[1] = blocks_of(p.nb);
-    g.members = g.blocks[0] > g.blocks[1] ? g.blocks[0] : g.blocks[1];
+    const int blocks = std::max(g.blocks[0], g.blocks[1]);
+    g.members = blocks <= 32 ? blocks : (blocks + 1) / 2;
     g.width = width;
     g.tiles = tiles;
     g.s_begin = s_begin;
@@ -366,8 +371,9 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.k0 = key.k0;
     g.k1 = key.k1;
     const size_t lds = sizeof(uint32_t) * (size_t)std::max(kRows * width * kWaves, 4);
-    if (g.members <= 8) return launch<4>(g, cus, lds, st);
-    return g.members <= 16 ? launch<8>(g, cus, lds, st) : launch<16>(g, cus, lds, st);
+    if (blocks <= 8) return launch<4, 1>(g, cus, lds, st);
+    if (blocks <= 16) return launch<8, 1>(g, cus, lds, st);
+    return blocks <= 32 ? launch<16, 1>(g, cus, lds, st) : launch<32, 2>(g, cus, lds, st);
 }
 
 }  // namespace pbit

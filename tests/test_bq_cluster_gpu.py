@@ -61,10 +61,12 @@ def _sampled(ctx, inst, beta, R, seed, **kw):
     return variant
 
 
-# block counts at the edges of the three operand sizes (8, 16 and 32 blocks), blocks of one side only
+# block counts at the edges of the four operand sizes (8, 16, 32 and 64 blocks), blocks of one side
+# only, an odd count of blocks in pairs
 @pytest.mark.parametrize("na,nb,R,S", [
     (1, 1, 1, 3), (33, 1, 5, 20), (1, 65, 33, 20), (32, 32, 32, 33), (256, 256, 64, 17), (257, 31, 40, 17),
     (129, 512, 31, 18), (513, 480, 70, 16), (100, 1024, 36, 9), (1024, 993, 128, 40), (64, 96, 1100, 12),
+    (1025, 1100, 70, 9), (2048, 2017, 33, 6), (40, 1800, 300, 17), (1056, 30, 600, 5),
 ])
 def test_cluster_sides_and_replicas(forced, na, nb, R, S):
     inst = synth.biclique_instance(na, seed=na + 5 * nb, nb=nb)
