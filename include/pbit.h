@@ -297,7 +297,7 @@ int pbit_profile_read(pbit_ctx *ctx, int32_t kind, double *total_ms, int64_t *la
  * tiles staged in LDS by the global-to-LDS DMA (sides padded to 128), 3 = spins
  * held as bits, tiles of 64 sites x 256, 128 or 64 replicas (sides padded to 128,
  * replicas to 256), 4 = sides of at most 512 held in LDS with their couplings for
- * runs of sweeps per launch, in slices of 16 or 8 replicas, 5 = sides of at most 1024
+ * runs of sweeps per launch, in slices of 16 or 8 replicas, 5 = sides of at most 2048
  * with couplings in the registers of each XCD's compute units for runs of sweeps
  * (runs of 16 sweeps or more, at most 8192 replicas, and the whole device free at the
  * launch: where its workgroups cannot be resident together another kernel runs the

@@ -4,31 +4,36 @@
 // A half-sweep of a mid-sized biclique is a few hundred nanoseconds of matrix work, far
 // below what a launch costs, and its couplings do not fit one compute unit.  Here the 32
 // compute units of an XCD form a cluster that anneals row tiles of 32 replicas: workgroup
-// c of a cluster owns sites 32 c .. 32 c + 31 of both sides and keeps their coupling rows
-// as MFMA operands in registers (one wave per SIMD, so 512 of them; 256 hold the couplings
-// at 1024 sites per side).  Each of its four waves takes one row tile, and the waves with
+// c of a cluster owns sites 32 c .. 32 c + 31 of both sides (two such blocks where a side has
+// more than 1024) and keeps their coupling rows as MFMA operands in registers (one wave per
+// SIMD, so 512 of them; 256 hold a block's couplings at 2048 sites per side, four bits each).
+// Each of its four waves takes row tiles of its own, and the waves with
 // the same row tile in the other workgroups are all it ever talks to: after an update a
 // wave stores its 32 x 32 new spins as 32 words and raises its flag, and before one it
 // waits for the flags of the other side's blocks and reads their words, all within the
 // XCD's own L2.  No other synchronisation takes place inside a run.
 //
 // What bounds it: a serial chain per half-sweep, with one wave per SIMD.  At 1024 sites per
-// side, 32 dependent MFMAs with the widening of their spin bits (about 1.6 k cycles), 16
-// decisions (1 k), the store, flag, poll and load through the L2 (1.5 k) and the random
-// words, which are drawn in the shadow of the stores.  4.4 us a sweep at 1024 x 1024 sites
-// and 1024 replicas, against 13.3 us for the bit kernel's launch per half-sweep and a
-// matrix floor of 0.9 us; 4.3 against 21.5 us with 16 replicas; 3.6 against 4.5 us at
-// 512 x 512 for the LDS-resident kernel, which wins below 256 (2.2 against 2.9 at 32).
-// Stores with agent scope, which the protocol does not need inside one L2, made it 9.2 us;
-// threshold rows loaded every sweep instead of 16 at a time, and a table of carry words
-// rebuilt every sweep instead of the rows themselves, cost 0.5 and 0.3 us.
+// side, 16 MFMAs with the widening of their spin bits (55 cycles each, not overlapped), 16
+// decisions and the random words (some 1.5 k cycles), the store, flag, poll and load
+// through the L2 (1.5 k), behind which half of the random words are drawn.
+//
+// Measured, us per sweep, the kernel it was taken for (a launch per half-sweep, or the
+// LDS-resident form at 512) and this one:
+//   2048 x 2048, 1024 replicas   17.9 ->  8.5 (9.2 with the two row tiles of a wave in turn)
+//   1024 x 1024, 1024 replicas   13.3 ->  3.8 (4.4 with int8 operands)
+//   1024 x 1024, 16 replicas     21.5 ->  3.7
+//    512 x 512, 1024 replicas     4.5 ->  3.3; below 256 sites the LDS-resident form wins
+// Stores with agent scope, which the protocol does not need inside one L2, made 1024 x 1024
+// 9.2 us; threshold rows loaded every sweep instead of 16 at a time, and a table of carry
+// words rebuilt every sweep instead of the rows themselves, cost 0.5 and 0.3 us.
 //
 // The workgroups have to be resident together, and spread evenly over the XCDs: they
 // meet before touching anything, and if they do not all arrive in time or an XCD has too
 // few of them, all leave and the caller runs the sweeps another way.
 //
 // Arithmetic, counters and decisions are the bit kernel's (bq_kernels.hip): spin bits
-// widened for the int8 MFMA, exact int32 sums, carry words S(I).
+// widened for the FP4 MFMA, exact sums, thresholds by |I|.
 #include <algorithm>
 #include <type_traits>
 
@@ -105,8 +110,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int octets)
 
 // KS: K steps of 64 sites a side may have (the couplings take 8 KS registers).  BPW: blocks of
 // a workgroup, one a wave: all four waves on one block, each with a row tile of its own, or
-// two waves on each of two.
-template <int KS, int BPW>
+// two waves on each of two.  TILES: row tiles a wave advances together, one's half-sweep in
+// the shadow of the other's exchange.
+template <int KS, int BPW, int TILES>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_bq_cluster(Args g)
 {
     extern __shared__ uint32_t lds[];  // per wave kRows threshold rows; starts at LDS address 0
@@ -153,78 +159,102 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     const uint32_t mid[2] = {kFieldBase + 4u * (uint32_t)h2[0], kFieldBase + 4u * (uint32_t)h2[1]};
     const uint32_t rows = (uint32_t)wave * kRows * 4u * (uint32_t)g.width;  // LDS address of this wave's threshold rows
 
-    for (int t = cluster + kXcds * (wave / BPW); t < g.tiles; t += kXcds * (kWaves / BPW)) {
-        uint32_t *flag[2] = {g.flags + kMaxBlocks * t, g.flags + kMaxBlocks * (g.tiles + t)};
+    auto each_tile = [](auto f) {
+        f(std::integral_constant<int, 0>{});
+        if constexpr (TILES > 1) f(std::integral_constant<int, 1>{});
+    };
+    constexpr int kStep = kXcds * (kWaves / BPW);
+    for (int t0 = cluster + kXcds * (wave / BPW); t0 < g.tiles; t0 += kStep * TILES) {
+        auto present = [&](int i) { return i == 0 || t0 + kStep * i < g.tiles; };
+        uint32_t *flag[TILES][2];
         const int octets[2] = {(g.blocks[0] + 7) / 8, (g.blocks[1] + 7) / 8};  // blocks / 8 of a side
-        uint32_t *xt[2] = {g.X[0] + (size_t)t * octets[0] * 256, g.X[1] + (size_t)t * octets[1] * 256};
-        int out[2] = {0, 0};  // lane r: this block's word of replica r
+        uint32_t *xt[TILES][2];
+        __amdgpu_buffer_rsrc_t xr[TILES][2];
+#pragma unroll
+        for (int i = 0; i < TILES; ++i)
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const size_t t = (size_t)(present(i) ? t0 + kStep * i : t0);
+                flag[i][side] = g.flags + kMaxBlocks * (side * (size_t)g.tiles + t);
+                xt[i][side] = g.X[side] + t * octets[side] * 256;
+                xr[i][side] = rsrc(xt[i][side], octets[side]);
+            }
+        int out[TILES][2] = {};  // lane r: this block's word of replica r
         // random words of one update: two of the four blocks at a time
-        uint32_t w[16];
-        auto draw = [&](int side, uint32_t sweep, int q0) {
+        uint32_t w[TILES][16];
+        auto draw = [&](auto ic, int side, uint32_t sweep, int q0) {
+            constexpr int i = decltype(ic)::value;
+            const int t = t0 + kStep * i;
             const uint32_t site = (uint32_t)(side ? g.n[0] : 0) + 32u * (uint32_t)c + (uint32_t)ln;
 #pragma unroll
             for (int q = q0; q < q0 + 2; ++q) {
                 const Block4 b = philox(site, sweep, g.rq0 + (uint32_t)(8 * t + 2 * q + kg), kDomainSweep, g.k0, g.k1);
 #pragma unroll
-                for (int p = 0; p < 4; ++p) w[4 * q + p] = b.w[p];
+                for (int p = 0; p < 4; ++p) w[i][4 * q + p] = b.w[p];
             }
 #pragma unroll
-            for (int j = 4 * q0; j < 4 * q0 + 8; ++j) asm volatile("" : "+v"(w[j]));  // drawn here, not where they are used
+            for (int j = 4 * q0; j < 4 * q0 + 8; ++j) asm volatile("" : "+v"(w[i][j]));  // drawn here, not where they are used
         };
         // publish the own block (sequence number seq of its side), drawing the next update's
         // words (side ns, sweep next) while the stores travel and the first look at the flags
         // that update waits for is under way
-        uint32_t peek = 0u;
-        auto publish = [&](int side, uint32_t seq, int ns, uint32_t next) {
+        uint32_t peek[TILES] = {};
+        auto publish = [&](auto ic, int side, uint32_t seq, int ns, uint32_t next) {
+            constexpr int i = decltype(ic)::value;
             if (lane < 32)
-                __hip_atomic_store(xt[side] + (((c >> 3) * 2 + (c & 1)) * 128 + 4 * lane + ((c >> 1) & 3)), (uint32_t)out[side],
+                __hip_atomic_store(xt[i][side] + (((c >> 3) * 2 + (c & 1)) * 128 + 4 * lane + ((c >> 1) & 3)), (uint32_t)out[i][side],
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_sched_barrier(0);
-            draw(ns, next, 0);
+            draw(ic, ns, next, 0);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the words are in L2
             asm volatile("" ::: "memory");
             if (lane == 0)
-                __hip_atomic_store(flag[side] + c, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            peek = agent_load(flag[1 - ns] + lane);
+                __hip_atomic_store(flag[i][side] + c, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            peek[i] = agent_load(flag[i][1 - ns] + lane);
             __builtin_amdgcn_sched_barrier(0);
-            draw(ns, next, 2);
+            draw(ic, ns, next, 2);
             __builtin_amdgcn_sched_barrier(0);
         };
         const int first = has[0] ? 0 : 1;  // the side this block updates first in a sweep
         // initial spins of the own block of both sides
+        auto start = [&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if (!present(i)) return;
 #pragma unroll
-        for (int side = 0; side < 2; ++side)
-            if (has[side]) {
-                const int8_t *m = g.M[side] + (size_t)(32 * t + 16 * kg) * g.n_p[side] + 32 * c + ln;
+            for (int side = 0; side < 2; ++side)
+                if (has[side]) {
+                    const int8_t *m = g.M[side] + (size_t)(32 * (t0 + kStep * i) + 16 * kg) * g.n_p[side] + 32 * c + ln;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint64_t b = __ballot(m[(size_t)r * g.n_p[side]] < 0);
-                    out[side] = lane_write((int)(uint32_t)b, r, out[side]);
-                    out[side] = lane_write((int)(uint32_t)(b >> 32), r + 16, out[side]);
+                    for (int r = 0; r < 16; ++r) {
+                        const uint64_t b = __ballot(m[(size_t)r * g.n_p[side]] < 0);
+                        out[i][side] = lane_write((int)(uint32_t)b, r, out[i][side]);
+                        out[i][side] = lane_write((int)(uint32_t)(b >> 32), r + 16, out[i][side]);
+                    }
                 }
+            if (has[1]) {
+                publish(ic, 1, 1u, first, g.sweep0 + (uint32_t)g.s_begin);
+            } else {
+                draw(ic, first, g.sweep0 + (uint32_t)g.s_begin, 0);
+                draw(ic, first, g.sweep0 + (uint32_t)g.s_begin, 2);
+                peek[i] = agent_load(flag[i][1 - first] + lane);
             }
-        if (has[1])
-            publish(1, 1u, first, g.sweep0 + (uint32_t)g.s_begin);
-        else {
-            draw(first, g.sweep0 + (uint32_t)g.s_begin, 0);
-            draw(first, g.sweep0 + (uint32_t)g.s_begin, 2);
-            peek = agent_load(flag[1 - first] + lane);
-        }
+        };
+        each_tile(start);
 
         bool lost = false;
-        const __amdgpu_buffer_rsrc_t xr[2] = {rsrc(xt[0], octets[0]), rsrc(xt[1], octets[1])};
-        auto half = [&](auto side_c, uint32_t row, uint32_t need, uint32_t seq, int ns, uint32_t next) {
-            constexpr int side = decltype(side_c)::value;
-            const uint32_t *f = flag[1 - side] + lane;
+        auto half = [&](auto ic, auto side_c, uint32_t row, uint32_t need, uint32_t seq, int ns, uint32_t next) {
+            constexpr int i = decltype(ic)::value, side = decltype(side_c)::value;
+            if (!present(i)) return;
+            const uint32_t *f = flag[i][1 - side] + lane;
             const bool watch = lane < g.blocks[1 - side];
             int polls = 0;
-            while (!__all(!watch || peek >= need)) {
+            while (!__all(!watch || peek[i] >= need)) {
                 if (++polls > kPollLimit) {
                     lost = true;
                     return;
                 }
-                peek = agent_load(f);
+                peek[i] = agent_load(f);
             }
             asm volatile("" ::: "memory");
             // words of replica ln, of four even blocks a load in lanes 0-31 and of four odd ones
@@ -233,7 +263,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             v4i_t v[KO];
 #pragma unroll
             for (int k = 0; k < KO; ++k)
-                v[k] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(xr[1 - side], 512 * kg + 16 * ln,
+                v[k] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(xr[i][1 - side], 512 * kg + 16 * ln,
                                                                                       1024 * k, 16 /* sc1 */));
             v16f_t acc = bias;
 #pragma unroll
@@ -251,14 +281,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             }
             uint64_t minus[16];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) minus[j] = heat_bath(w[j], T[j], mid[side], x[j]);  // I >= 0 up to mid
+            for (int j = 0; j < 16; ++j) minus[j] = heat_bath(w[i][j], T[j], mid[side], x[j]);  // I >= 0 up to mid
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int r = 8 * (j >> 2) + (j & 3);
-                out[side] = lane_write((int)(uint32_t)minus[j], r, out[side]);
-                out[side] = lane_write((int)(uint32_t)(minus[j] >> 32), r + 4, out[side]);
+                out[i][side] = lane_write((int)(uint32_t)minus[j], r, out[i][side]);
+                out[i][side] = lane_write((int)(uint32_t)(minus[j] >> 32), r + 4, out[i][side]);
             }
-            publish(side, seq, ns, next);
+            publish(ic, side, seq, ns, next);
         };
 
         // kRows sweeps' threshold rows at a time in LDS (a row loaded every sweep would put a
@@ -278,9 +308,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             const uint32_t done = (uint32_t)(s - g.s_begin);
             const uint32_t sweep = g.sweep0 + (uint32_t)s;
             if (has[0])
-                half(std::integral_constant<int, 0>{}, row, done + 1u, done + 1u, has[1] ? 1 : 0, has[1] ? sweep : sweep + 1u);
+                each_tile([&](auto ic) {
+                    half(ic, std::integral_constant<int, 0>{}, row, done + 1u, done + 1u, has[1] ? 1 : 0,
+                         has[1] ? sweep : sweep + 1u);
+                });
             if (lost) break;
-            if (has[1]) half(std::integral_constant<int, 1>{}, row, done + 1u, done + 2u, first, sweep + 1u);
+            if (has[1])
+                each_tile([&](auto ic) {
+                    half(ic, std::integral_constant<int, 1>{}, row, done + 1u, done + 2u, first, sweep + 1u);
+                });
             if (lost) break;
         }
         if (lost) {
@@ -288,19 +324,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             return;
         }
         // spins out, zero at padding sites
+        each_tile([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if (!present(i)) return;
 #pragma unroll
-        for (int side = 0; side < 2; ++side)
-            if (has[side]) {
-                int8_t *m = g.M[side] + (size_t)(32 * t + 16 * kg) * g.n_p[side] + 32 * c + ln;
-                const bool real = 32 * c + ln < g.n[side];
+            for (int side = 0; side < 2; ++side)
+                if (has[side]) {
+                    int8_t *m = g.M[side] + (size_t)(32 * (t0 + kStep * i) + 16 * kg) * g.n_p[side] + 32 * c + ln;
+                    const bool real = 32 * c + ln < g.n[side];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(out[side], r);
-                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(out[side], r + 16);
-                    const uint32_t b = ((kg ? hi : lo) >> ln) & 1u;
-                    m[(size_t)r * g.n_p[side]] = real ? (b ? (int8_t)-1 : (int8_t)1) : (int8_t)0;
+                    for (int r = 0; r < 16; ++r) {
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(out[i][side], r);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(out[i][side], r + 16);
+                        const uint32_t b = ((kg ? hi : lo) >> ln) & 1u;
+                        m[(size_t)r * g.n_p[side]] = real ? (b ? (int8_t)-1 : (int8_t)1) : (int8_t)0;
+                    }
                 }
-            }
+        });
     }
 }
 
@@ -308,14 +348,22 @@ constexpr size_t kCtlWords = 16;
 
 int blocks_of(int n) { return (n + 31) / 32; }
 
+template <int KS, int BPW, int TILES>
+hipError_t launch_tiles(const Args &g, int cus, size_t lds, hipStream_t st)
+{
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bq_cluster<KS, BPW, TILES>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((k_bq_cluster<KS, BPW, TILES>), dim3((unsigned)cus), dim3(kThreads), lds, st, g);
+    return hipGetLastError();
+}
+
 template <int KS, int BPW>
 hipError_t launch(const Args &g, int cus, size_t lds, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bq_cluster<KS, BPW>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k_bq_cluster<KS, BPW>), dim3((unsigned)cus), dim3(kThreads), lds, st, g);
-    return hipGetLastError();
+    // two row tiles a wave wherever some wave has two
+    if (g.tiles > kXcds * (kWaves / BPW)) return launch_tiles<KS, BPW, 2>(g, cus, lds, st);
+    return launch_tiles<KS, BPW, 1>(g, cus, lds, st);
 }
 
 }  // namespace

@@ -739,8 +739,8 @@ constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph til
 // next anneals after it once was not.  A launch starts by loading couplings and ends in that
 // report, 25-40 us together: runs of 16 sweeps carry that against kernels of 13-21 us a sweep
 // (sides over 512), and against the LDS-resident kernel's 2-4.5 us runs of 64.  That one costs
-// 2.0 us + 4.7 ns per site a sweep and this one 2.9 us + 1.5 ns for each pass of 1024
-// replicas, so beside it only sides over 256 in one pass are worth timing.  Above 8192
+// 2.0 us + 4.7 ns per site a sweep and this one 2.8 us + 1 ns for each 1024 replicas, so
+// beside it only sides over 256 with up to 1024 replicas are worth timing.  Above 8192
 // replicas it would make eight passes of what the bit tile does in one.
 static bool cluster_possible(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, bool slab_ok)
 {
