@@ -29,6 +29,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 INT8_MFMA_PEAK_TOPS = 5000.0   # MI355X dense int8 MFMA, published (TOP/s)
+FP4_MFMA_PEAK_TOPS = 10000.0   # dense FP4 (E2M1) MFMA: twice the K of an int8 one in the same cycles
+FP4_VARIANTS = (3, 5)          # biclique kernels whose operands (bits and couplings, exact) are FP4
 # biclique half-sweep kernels by variant number (pbit_profile_variant)
 BQ_KERNELS = {1: "k_bq_halfsweep", 2: "k_bq_halfsweep_dma", 3: "k_bq_halfsweep_bits", 4: "k_bq_slab", 5: "k_bq_cluster"}
 VALU_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12  # 32-bit vector lane-ops/s: CUs x SIMDs x lanes x clock
@@ -194,8 +196,8 @@ def measured_traffic(workload, kernel=None):
 
 
 def _bag_dtype():
-    """Arithmetic of the batched tiles: int8 spins and couplings, biclique fields as
-    int8 MFMA products with int32 sums."""
+    """Data of the batched tiles: int8 spins and couplings (cubes as bits, biclique fields
+    as exact FP4 MFMA products)."""
     return "int8"
 
 
@@ -528,10 +530,13 @@ def main():
     # roofline of the half-sweep kernel
     avg_ms = kern_ms / launches if launches else float("inf")
     ea_path = pbit.pbit_profile_ea_path(ctx.ctx) if w["kind"] == "ea3d" else 0
-    if ea_path == 2:
+    # a run of sweeps in LDS is one timed launch counted as its half-sweeps: all of them; of the
+    # launches of one half-sweep, a window of eight in every --profile-every is timed
+    resident = ea_path == 1 and args.profile_every > 8 and launches == 2 * S * args.steps
+    if ea_path == 2 or resident:
         # the cube held in LDS for runs of sweeps: no HBM traffic per half-sweep, so the
         # vector ALU is the roof; lane-ops per update from the committed counter run
-        rec = profile_record(args.workload, "k_ea_slab")
+        rec = profile_record(args.workload, "k_bit_slab")
         lops = None
         if rec and rec.get("valu_insts_per_dispatch"):
             # the counter run's one launch holds all of its sweeps
@@ -539,7 +544,7 @@ def main():
             lops = float(rec["valu_insts_per_dispatch"]) * 64 / (N * R * sweeps)
         upd_per_s = (N * R / 2) / (avg_ms * 1e-3)  # updates per second inside the kernel
         roof = {"bound": "alu", "achieved": None if lops is None else upd_per_s * lops / 1e12,
-                "peak": VALU_PEAK_TLANEOPS, "unit": "Tlane-op/s", "traffic": None, "kernel": "k_ea_slab",
+                "peak": VALU_PEAK_TLANEOPS, "unit": "Tlane-op/s", "traffic": None, "kernel": "k_bit_slab",
                 "lane_ops_per_update": lops, "updates_per_s_in_kernel": upd_per_s,
                 "avg_halfsweep_us": avg_ms * 1e3, "halfsweeps_timed": launches}
     elif w["kind"] == "ea3d":
@@ -557,14 +562,14 @@ def main():
         # vector ALU is the roof, as for the cube in LDS; the window counts one launch per
         # colour class and sweep, so a "launch" is one class update on average
         groups = pbit.pbit_problem_colouring(ctx.ctx, prob)[1]
-        rec = profile_record(args.workload, "k_graph_slab")
+        rec = profile_record(args.workload, "k_bit_slab")
         lops = None
         if rec and rec.get("valu_insts_per_dispatch"):
             sweeps = rec.get("sweeps_per_dispatch") or rec["pmc_sweeps"]
             lops = float(rec["valu_insts_per_dispatch"]) * 64 / (N * R * sweeps)
         upd_per_s = (N * R / groups) / (avg_ms * 1e-3)  # updates per second inside the kernel
         roof = {"bound": "alu", "achieved": None if lops is None else upd_per_s * lops / 1e12,
-                "peak": VALU_PEAK_TLANEOPS, "unit": "Tlane-op/s", "traffic": None, "kernel": "k_graph_slab",
+                "peak": VALU_PEAK_TLANEOPS, "unit": "Tlane-op/s", "traffic": None, "kernel": "k_bit_slab",
                 "groups": groups, "lane_ops_per_update": lops, "updates_per_s_in_kernel": upd_per_s,
                 "avg_class_update_us": avg_ms * 1e3, "class_updates_timed": launches}
     elif w["kind"] == "graph":
@@ -577,9 +582,11 @@ def main():
         alg_ops = 2 * n * n * R  # one side's fields: n x n couplings times n x R spins
         # the kernel the library ran (autotuned unless PBIT_BQ_VARIANT forces one)
         variant = pbit.pbit_profile_variant(ctx.ctx)
+        fp4 = variant in FP4_VARIANTS
         roof = {"bound": "mfma", "achieved": alg_ops / (avg_ms * 1e-3) / 1e12,
-                "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "traffic": None,
-                "kernel": BQ_KERNELS.get(variant, "k_bq_halfsweep"), "variant": variant, "operands": "int8",
+                "peak": FP4_MFMA_PEAK_TOPS if fp4 else INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "traffic": None,
+                "kernel": BQ_KERNELS.get(variant, "k_bq_halfsweep"), "variant": variant,
+                "operands": "fp4 (spin bits and couplings in {-1, 0, 1}, exact sums)" if fp4 else "int8",
                 "alg_ops_per_launch": alg_ops, "avg_launch_us": avg_ms * 1e3, "launches_timed": launches}
     if launches == 0:  # launch timing switched off (--profile-every 0)
         roof["achieved"] = None

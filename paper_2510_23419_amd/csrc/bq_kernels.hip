@@ -824,7 +824,8 @@ hipError_t bqb_unpack(const BqView &p, const uint32_t *MAb, const uint32_t *MBb,
 
 bool bqb_supported(const BqView &p, int Rp)
 {
-    return p.J4 && p.na_p % kBitsST == 0 && p.nb_p % kBitsST == 0 && p.na_p % kBitsBlock == 0 &&
+    // sides on which the accumulators are exact (device.h: |2 sum J b| stays below 2^20)
+    return p.J4 && p.na_p < 1 << 19 && p.nb_p < 1 << 19 && p.na_p % kBitsST == 0 && p.nb_p % kBitsST == 0 && p.na_p % kBitsBlock == 0 &&
            p.nb_p % kBitsBlock == 0 && Rp % kBitsRT == 0;
 }
 
