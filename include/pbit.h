@@ -234,8 +234,10 @@ typedef struct {
     pbit_result *result;      /* filled as by pbit_anneal (spin_trace is not supported) */
 } pbit_batch_job;
 
-/* Tile sizes of batched jobs.  Where a job's shape can take more than one tile
- * size, the library times one tile of each (a couple of the job's sweeps on
+/* Tile sizes of batched jobs.  Cube and graph tiles that hold their spins as bits take
+ * 4, 8 or 16 replicas, by the cost of each width (and, in pbit_anneal_batch, so that the
+ * longest tile and the work of the whole batch end together).  Where another job's shape
+ * can take more than one tile size, the library times one tile of each (a couple of the job's sweeps on
  * scratch memory) when the shape is first seen and no round is in flight, and
  * keeps the size whose tiles cost the least device time per job; the choice is
  * cached per (problem kind, sides or spins, threshold width, replicas rounded up

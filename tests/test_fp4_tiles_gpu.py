@@ -1,0 +1,59 @@
+"""Batched biclique tiles on the FP4 matrix cores against the oracle, bit-exact, where their
+loops end: K steps of 64 sites in every remainder of a ring of four, site blocks that fill no
+wave and more than the 16 waves, ragged sides, replicas past one tile, threshold rows past the
+16 held at a time, given spins, and fields at their largest."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import oracle
+from paper_2510_23419_amd import pbit
+from tests.test_bq_variants_gpu import _biclique_with_zeros
+from tests.test_parity_gpu import graph_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = pbit.Context(0)
+    yield c.ctx
+    c.close()
+
+
+def _check(ctx, inst, beta, R, seed, **kw):
+    print("tiles", inst["J"].shape, "R", R, "S", len(beta), flush=True)
+    prob = pbit.load_instance(ctx, inst)
+    got = pbit.pbit_anneal_batch(ctx, [dict(problem=prob, beta=beta, n_replicas=R, seed=seed, **kw)])[0]
+    pbit.pbit_unload_problem(ctx, prob)
+    ref = oracle.anneal(graph_of(inst), beta, R, seed, **kw)
+    assert np.array_equal(got.spins, ref.spins) and np.array_equal(got.energies, ref.energies)
+
+
+@pytest.mark.parametrize("na,nb,R,S", [(1, 1, 1, 2), (64, 65, 33, 17), (129, 192, 31, 33), (257, 300, 64, 5),
+                                       (321, 40, 70, 16), (600, 530, 40, 3), (31, 1100, 5, 4)])
+def test_tiles_at_their_edges(ctx, na, nb, R, S):
+    _check(ctx, _biclique_with_zeros(na, nb, seed=na + nb) if min(na, nb) > 8 else
+           synth.biclique_instance(na, seed=3, nb=nb), synth.beta_linear(0.05, 2.0, S), R, seed=na)
+
+
+def test_tiles_given_spins_and_offsets(ctx):
+    inst = _biclique_with_zeros(100, 90, seed=4)
+    _check(ctx, inst, synth.beta_linear(0.05, 2.0, 6), 40, seed=9, init_spins=synth.random_spins(40, 190, seed=2),
+           sweep_offset=7, replica_offset=8)
+
+
+@pytest.mark.parametrize("n", [700, 1500])
+def test_largest_fields_are_exact(ctx, n):
+    """All couplings +1 and all spins alike: |I| = n, through a batch and the per-instance call."""
+    inst = synth.ferro_biclique(n)
+    beta, R = np.full(16, 1e-4), 32
+    init = np.ones((R, 2 * n), np.int8)
+    init[1::2] = -1
+    ref = oracle.anneal(graph_of(inst), beta, R, 5, init_spins=init)
+    prob = pbit.load_instance(ctx, inst)
+    outs = [pbit.pbit_anneal(ctx, prob, beta, R, 5, init_spins=init),
+            pbit.pbit_anneal_batch(ctx, [dict(problem=prob, beta=beta, n_replicas=R, seed=5, init_spins=init)])[0]]
+    pbit.pbit_unload_problem(ctx, prob)
+    for got in outs:
+        assert np.array_equal(got.spins, ref.spins) and np.array_equal(got.energies, ref.energies)
