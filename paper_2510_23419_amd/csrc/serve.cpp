@@ -568,7 +568,10 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         per_cu[k] = std::max(1, std::min(by_threads, (int)((160 * 1024) / (lds[k] + 2048))));
         double sum = 0.0;
         for (double c : cost[k]) sum += c;
-        work[i] += sum / per_cu[k];
+        // tiles of fewer threads lie beside 1024-thread ones and run at a third of their pace
+        // there (256 mixed jobs: 350 ms of the others' tiles, and 633 and 698 ms of the 512- and
+        // 256-thread tiles with shares by their time alone)
+        work[i] += bit_kind(k) && per_cu[k] > 1 ? 1.5 * sum : sum / per_cu[k];
         want[i] = std::max(want[i], (double)items[k].size() / per_cu[k]);
     }
     for (int i = 0; i < kQueues; ++i) {
