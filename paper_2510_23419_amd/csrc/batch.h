@@ -15,7 +15,6 @@
 namespace pbit {
 
 struct BqJobDev {
-    const int8_t *J, *JT;     // int8 couplings [na_p][nb_p], [nb_p][na_p]
     const uint8_t *J4, *JT4;  // couplings as four-bit numbers in the widened bits' order (bit tiles)
     const int32_t *hA2, *hB2; // field plus coupling sum per site (bit tiles)
     const uint32_t *J2;       // both sides' couplings as two-bit codes in fragment order (FP4 tiles)

@@ -19,23 +19,7 @@ namespace pbit {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-
-// 8- and 16-byte global loads (vector types: uint2 and uint4 do not bind to an
-// address-space-qualified reference)
-__device__ __forceinline__ uint2 load_u2(const void *p)
-{
-    const v2u v = load_global<v2u>(p);
-    return make_uint2(v.x, v.y);
-}
-__device__ __forceinline__ uint4 load_u4(const void *p)
-{
-    const v4u v = load_global<v4u>(p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 
 __device__ __forceinline__ int take_item(int32_t *counter, int *slot)
 {
@@ -442,7 +426,7 @@ template <int RB, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_bq_tiles(const BqJobDev *__restrict__ jobs,
                                                              const WorkItem *__restrict__ items,
                                                              const int32_t *__restrict__ n_items_p,
-                                                             int32_t *__restrict__ counter, uint32_t)
+                                                             int32_t *__restrict__ counter)
 {
     constexpr int RS = 32 * RB;
     extern __shared__ uint4 dyn[];
@@ -705,17 +689,21 @@ hipError_t graph_tiles(const GraphJobDev *jobs, const WorkItem *items, const int
 hipError_t bq_tiles(const BqJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter, int rs,
                     int mode, int grid, size_t lds_bytes, hipStream_t st)
 {
-#define PBIT_BQ_TILES(K, THREADS)                                                                                        \
-    hipLaunchKernelGGL(K, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, jobs, items, n_items, counter, 1u)
+#define PBIT_BQ_TILES(K, THREADS, ...)                                                                             \
+    hipLaunchKernelGGL(K, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, jobs, items, n_items, counter, ##__VA_ARGS__)
     const int rb = rs == 128 ? 4 : rs == 64 ? 2 : rs == 32 ? 1 : 0;
     if (rb == 0 || (mode != kTileInt8 && mode != kTileBits)) return hipErrorInvalidValue;
     if (mode == kTileBits) {
-        if (rb == 4) PBIT_BQ_TILES((k_bq_tiles_bits<4>), kBqTileThreads); else if (rb == 2) PBIT_BQ_TILES((k_bq_tiles_bits<2>), kBqTileThreads);
-        else PBIT_BQ_TILES((k_bq_tiles_bits<1>), kBqTileThreads);
+        if (rb == 4) PBIT_BQ_TILES((k_bq_tiles_bits<4>), kBqTileThreads, 1u);
+        else if (rb == 2) PBIT_BQ_TILES((k_bq_tiles_bits<2>), kBqTileThreads, 1u);
+        else PBIT_BQ_TILES((k_bq_tiles_bits<1>), kBqTileThreads, 1u);
     } else {
-        // FP4 rows come in 32- and 64-replica tiles (128 replicas would spill registers)
+        // FP4 rows come in 32- and 64-replica tiles (128 replicas would spill registers); 16 waves
+        // hide more than 8 (12 against 15.5 us a sweep at 689 sites), but two replica blocks
+        // do not fit their registers
         if (rb == 4) return hipErrorInvalidValue;
-        if (rb == 2) PBIT_BQ_TILES((k_bq_tiles<2, 512>), 512); else PBIT_BQ_TILES((k_bq_tiles<1, 1024>), 1024);
+        if (rb == 2) PBIT_BQ_TILES((k_bq_tiles<2, 512>), 512);
+        else PBIT_BQ_TILES((k_bq_tiles<1, 1024>), 1024);
     }
 #undef PBIT_BQ_TILES
     return hipGetLastError();

@@ -142,9 +142,12 @@ __device__ __forceinline__ uint32_t lds_word(uint32_t address)
 // carries for I >= 0 (accumulator bits x from `mid` on), w >= Tm(|I|) for I < 0.
 __device__ __forceinline__ uint64_t heat_bath(uint32_t w, uint32_t Tm, uint32_t x, uint32_t mid)
 {
-    constexpr int kUgt = 34, kUge = 35;  // wave-wide comparisons; as plain ones the first becomes an add, a select and a test
+    constexpr int kUge = 35;  // wave-wide comparison
+    uint32_t sum;
+    uint64_t carry;  // as a mask, which the compiler would make of an add, a select and a test
+    asm("v_add_co_u32 %0, %1, %2, %3" : "=v"(sum), "=s"(carry) : "v"(w), "v"(Tm));
     const uint64_t up = __builtin_amdgcn_uicmp(x, mid, kUge);
-    return (up & __builtin_amdgcn_uicmp(w, ~Tm, kUgt)) | (~up & __builtin_amdgcn_uicmp(w, Tm, kUge));
+    return (up & carry) | (~up & __builtin_amdgcn_uicmp(w, Tm, kUge));
 }
 
 // Initial spin from a domain-1 word.

@@ -498,7 +498,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
         } else {
             const BqView &v = j->P->bq;
             const int k = kind_of_rs(j->rs);
-            BqJobDev jd{v.J, v.JT, v.J4, v.JT4, v.hA2, v.hB2, v.J2, v.hA, v.hB,
+            BqJobDev jd{v.J4, v.JT4, v.hA2, v.hB2, v.J2, v.hA, v.hB,
                         (const uint32_t *)j->d_table, (uint8_t *)j->d_state,
                         (int32_t *)j->d_energy, v.na, v.nb, v.na_p, v.nb_p, j->width,
                         (uint32_t)j->d.sweep_offset, (uint32_t)j->d.replica_offset >> 2, key.k0, key.k1};
@@ -684,7 +684,7 @@ static int tune_tile(pbit_ctx *ctx, ServeState &s, BJob &j, const std::vector<in
                 e = hipMemcpy(b, &jd, sizeof jd, hipMemcpyHostToDevice);
             } else {
                 const BqView &v = P.bq;
-                const BqJobDev jd{v.J, v.JT, v.J4, v.JT4, v.hA2, v.hB2, v.J2, v.hA, v.hB,
+                const BqJobDev jd{v.J4, v.JT4, v.hA2, v.hB2, v.J2, v.hA, v.hB,
                                   (const uint32_t *)(b + off_tab), (uint8_t *)(b + off_state),
                                   (int32_t *)(b + off_en), v.na, v.nb, v.na_p, v.nb_p, j.width, 0u, 0u, 0u, 0u};
                 e = hipMemcpy(b, &jd, sizeof jd, hipMemcpyHostToDevice);
