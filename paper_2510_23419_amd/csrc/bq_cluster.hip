@@ -20,7 +20,7 @@
 //
 // Measured, us per sweep, the kernel it was taken for (a launch per half-sweep, or the
 // LDS-resident form at 512) and this one:
-//   2048 x 2048, 1024 replicas   17.9 ->  8.5 (9.2 with the two row tiles of a wave in turn)
+//   2048 x 2048, 1024 replicas   17.9 ->  8.2 (9.2 with the two row tiles of a wave in turn)
 //   1024 x 1024, 1024 replicas   13.3 ->  3.8 (4.4 with int8 operands)
 //   1024 x 1024, 16 replicas     21.5 ->  3.7
 //    512 x 512, 1024 replicas     4.5 ->  3.3; below 256 sites the LDS-resident form wins
