@@ -528,7 +528,7 @@ __device__ __forceinline__ void run(const BitJobDev &jb, int tile, int s_begin, 
 
     const int G = TWO ? 2 : v.n_groups;
     auto group = [&](int c) {
-        const u32x4 g = load_const<u32x4>(v.groups + (c < G ? c : c - G));
+        const u32x4 g = load_const<u32x4>(v.groups + bit_group_at(c, G));
         return make_int4((int)g.x, (int)g.y, (int)g.z, (int)g.w);
     };
     auto pair_of = [&](Unit u, int j) { return u == kPair ? j : u == kSite ? j >> 1 : j / (2 * RQ); };

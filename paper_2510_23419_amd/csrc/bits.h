@@ -65,6 +65,10 @@ struct BitHost {
 bool bit_build(int n, const int32_t *start, const int32_t *nbr, const int8_t *J, const int8_t *h,
                const uint8_t *group, int n_groups, int cube_lx, BitHost &out);
 
+// Update group that a sweep's cursor c (up to two past the last of its `groups` groups) stands on:
+// the groups of the next sweep follow.
+constexpr __host__ __device__ int bit_group_at(int c, int groups) { return groups == 1 ? 0 : c < groups ? c : c - groups; }
+
 // One anneal's tiles: tile t holds replicas [rs t, rs t + rs).
 struct BitJobDev {
     BitView v;

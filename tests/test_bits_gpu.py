@@ -113,3 +113,21 @@ def test_large_cubes(ctx, dims, R):
     field = "uniform3" if dims[2] == 30 else "zero"
     _sampled(ctx, synth.ea_instance(dims, seed=R, field=field), synth.beta_geometric(0.1, 5.0, 20), R, 2)
     assert pbit.pbit_profile_ea_path(ctx) == 1
+
+
+@pytest.mark.parametrize("forced", [False, True])
+def test_one_update_group(ctx, width_ctx, forced):
+    """Sites without bonds form one group: its cursor stays on it over sweeps that one launch
+    runs, per instance and batched (1200 spins take the bit-held form by themselves)."""
+    n, R = (1200, 40) if not forced else (90, 21)
+    inst = {"kind": "graph", "n": n, "bond_i": np.zeros(0, np.int32), "bond_j": np.zeros(0, np.int32),
+            "bond_J": np.zeros(0, np.int8), "h": np.random.default_rng(n).integers(-1, 2, size=n).astype(np.int8)}
+    c = width_ctx if forced else ctx
+    beta = synth.beta_linear(0.1, 1.0, 40)
+    _sampled(c, inst, beta, R, 6)
+    prob = pbit.load_instance(c, inst)
+    assert pbit.pbit_problem_colouring(c, prob)[1] == 1
+    out = pbit.pbit_anneal_batch(c, [dict(problem=prob, beta=beta, n_replicas=R, seed=6)])[0]
+    ref = oracle.anneal(_graph(inst), beta, 4, 6)
+    assert np.array_equal(out.spins[:4], ref.spins) and np.array_equal(out.energies[:4], ref.energies)
+    pbit.pbit_unload_problem(c, prob)
