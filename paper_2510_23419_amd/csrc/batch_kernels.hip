@@ -224,7 +224,6 @@ __global__ __launch_bounds__(kGraphTileThreads) void k_graph_slab(GraphJobDev jb
 // streamed from global memory (L2-resident, shared by all tiles of the job),
 // followed by the decision epilogue writing the new side into LDS.
 constexpr int kRing = 4;      // K-units of J fragments in flight per site block (bit tiles)
-constexpr int kCodeRing = 4;  // K steps of coupling codes in flight per site block (FP4 tiles)
 
 // The FP4 operand (32 K values of a lane) of two words of coupling codes: nibble i of dword
 // 2 d + e is bits 3 - e (sign) and 1 - e (set: +-1, else 0) of nibble i of word d.
@@ -489,18 +488,19 @@ __global__ __launch_bounds__(THREADS) void k_bq_tiles(const BqJobDev *__restrict
         if (tid < RS) eacc[tid] = 0;
         for (int k = tid; k < PR; k += THREADS) fields[k] = k < na_p ? jb.hA[k] : jb.hB[k - na_p];
 
-        // coupling codes of both sides, read by a uniform offset and the lane's own
+        // coupling codes of both sides, read by a uniform offset and the lane's own (the uniform
+        // offset is outside the buffer's range check: every start is a block of the side)
         const int side_b = na_p * nb_p / 4;
         const __amdgpu_buffer_rsrc_t codes = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint32_t *>(jb.J2), 0, (uint32_t)(2 * side_b), 0x00027000);  // reads past the end give zero
-        constexpr int kUnit = 512;  // bytes from one K step to the next
+            const_cast<uint32_t *>(jb.J2), 0, (uint32_t)bq_code_bytes(na_p, nb_p), 0x00027000);
+        constexpr int kUnit = kCodeUnit;
         constexpr int kStep = THREADS / 64;
         auto fetch = [&](int from, int u) {
             return __builtin_bit_cast(v2i_t, __builtin_amdgcn_raw_buffer_load_b64(codes, 8 * lane + kUnit * u, from, 0));
         };
         v2i_t ring[kCodeRing];
 #pragma unroll
-        for (int u = 0; u < kCodeRing; ++u) ring[u] = fetch(kUnit * (nb_p / 64) * wave, u);
+        for (int u = 0; u < kCodeRing; ++u) ring[u] = fetch(bq_code_start(na_p, nb_p, 0, wave), u);
 
         for (int s = w.s_begin; s < w.s_end; ++s) {
             const int kr = (s - w.s_begin) % n_rows;
@@ -528,8 +528,8 @@ __global__ __launch_bounds__(THREADS) void k_bq_tiles(const BqJobDev *__restrict
                 // after the last one, so that they arrive during the decisions and the barrier.
                 const int nku = (no + 63) / 64, nblk = (ns + 31) / 32;
                 const int per_block = kUnit * (no_p / 64);
-                const int start = side == 0 ? 0 : side_b, other = side == 0 ? side_b : 0;
-                const int other_start = other + kUnit * ((side == 0 ? na_p : nb_p) / 64) * wave;
+                const int start = side == 0 ? 0 : side_b;
+                const int other_start = bq_code_start(na_p, nb_p, 1 - side, wave);
                 if (wave >= nblk)
 #pragma unroll
                     for (int u = 0; u < kCodeRing; ++u) ring[u] = fetch(other_start, u);

@@ -21,13 +21,28 @@ struct BqView {
     const int32_t *hA2;  // [na_p]
     const int32_t *hB2;  // [nb_p]
     // for the batched FP4 tiles: couplings as two-bit codes, 16 per word, in MFMA fragment
-    // order (see load_biclique), side A's sites (na_p * nb_p / 16 words), then side B's
+    // order (see load_biclique), side A's sites (na_p * nb_p / 16 words), then side B's, then
+    // the words that the tiles' rings read past them (bq_code_bytes)
     const uint32_t *J2;
 };
 
 // Bytes of a row of four-bit couplings: whole stages of 256 sites for the per-launch bit kernel
 // (zeros past ko_p) where it can take the side.
 constexpr int bq_row_bytes(int ko_p) { return ko_p % 128 == 0 ? (ko_p + 255) / 256 * 128 : ko_p / 2; }
+// Coupling codes of the batched FP4 tiles: bytes of one K step (64 sites of the other side) of a
+// block of 32 sites, K steps a wave reads ahead, where a block of a side starts (the block of a
+// wave past the side's last one is the last), and the bytes of both sides with what a ring that
+// starts on the last block reads past it.
+constexpr int kCodeUnit = 512, kCodeRing = 4;
+constexpr __host__ __device__ int bq_code_start(int na_p, int nb_p, int side, int wave)
+{
+    const int blocks = (side == 0 ? na_p : nb_p) / 32, per_block = kCodeUnit * ((side == 0 ? nb_p : na_p) / 64);
+    return (side == 0 ? 0 : na_p * nb_p / 4) + per_block * (wave < blocks ? wave : blocks - 1);
+}
+constexpr __host__ __device__ int64_t bq_code_bytes(int na_p, int nb_p)
+{
+    return (int64_t)na_p * nb_p / 2 + (kCodeRing - 1) * kCodeUnit;
+}
 constexpr int kBqPad = 64;       // site padding of small biclique sides (MFMA K and N tiles)
 constexpr int kBqPadLarge = 128; // site padding of sides with at least kBqLargeSide sites
 constexpr int kBqLargeSide = 512;

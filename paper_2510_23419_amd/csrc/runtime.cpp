@@ -415,7 +415,7 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
         // 64 u + 32 g + 4 i + j, as bits 3 - j % 2 (sign) and 1 - j % 2 (set) of nibble i of
         // word j / 2; side B's follow side A's
         const size_t words = (size_t)na_p * nb_p / 16;
-        std::vector<uint32_t> J2(2 * words, 0u);
+        std::vector<uint32_t> J2((size_t)bq_code_bytes(na_p, nb_p) / 4, 0u);
         auto pack2 = [](const std::vector<int8_t> &M, int rows, int cols, uint32_t *out) {
             const int nku = cols / 64;
             for (int r = 0; r < rows; ++r)

@@ -4,6 +4,7 @@
 #include <cstdlib>
 
 #include "bits.h"
+#include "bq.h"
 
 using namespace pbit;
 
@@ -31,9 +32,34 @@ static void group_cursor()
     }
 }
 
+// Reads of the FP4 tiles' coupling codes: a lane reads 8 bytes at 8 lane + a K step from the
+// uniform start of a wave's ring, the first block's or the next one's, in sides of every padding.
+static void coupling_codes()
+{
+    for (int na_p = 64; na_p <= 1152; na_p += 64)
+        for (int nb_p = 64; nb_p <= 1152; nb_p += 64)
+            for (int waves : {8, 16}) {
+                const int64_t bytes = bq_code_bytes(na_p, nb_p);
+                auto reads = [&](int64_t from, int steps) {
+                    CHECK(from >= 0 && from + (int64_t)kCodeUnit * (steps - 1) + 8 * 63 + 8 <= bytes);
+                };
+                for (int side = 0; side < 2; ++side) {
+                    const int blocks = (side == 0 ? na_p : nb_p) / 32, steps = (side == 0 ? nb_p : na_p) / 64;
+                    for (int wave = 0; wave < waves; ++wave) {
+                        reads(bq_code_start(na_p, nb_p, side, wave), kCodeRing);
+                        for (int blk = wave; blk < blocks; blk += waves) {
+                            const int64_t at = (side == 0 ? 0 : na_p * nb_p / 4) + (int64_t)kCodeUnit * steps * blk;
+                            reads(at, steps > kCodeRing ? steps : kCodeRing);
+                        }
+                    }
+                }
+            }
+}
+
 int main()
 {
     group_cursor();
+    coupling_codes();
     std::printf("rules ok\n");
     return 0;
 }
