@@ -43,6 +43,9 @@ constexpr __host__ __device__ int64_t bq_code_bytes(int na_p, int nb_p)
 {
     return (int64_t)na_p * nb_p / 2 + (kCodeRing - 1) * kCodeUnit;
 }
+// Exchange words of the cluster kernel come in octets of blocks; the octet that K steps 4 k to
+// 4 k + 3 of a side of `octets` octets read (the last one's past it, whose products are left out).
+constexpr __host__ __device__ int bq_octet(int k, int octets) { return k < octets ? k : octets - 1; }
 constexpr int kBqPad = 64;       // site padding of small biclique sides (MFMA K and N tiles)
 constexpr int kBqPadLarge = 128; // site padding of sides with at least kBqLargeSide sites
 constexpr int kBqLargeSide = 512;

@@ -101,8 +101,8 @@ __device__ bool meet(uint32_t *ctl, uint32_t groups, uint32_t members, uint32_t 
     return ok;
 }
 
-// Exchange words of one side and row tile as a buffer of whole octets of blocks (reads past
-// them give 0).
+// Exchange words of one side and row tile as a buffer of whole octets of blocks (its range check
+// leaves the uniform offset out: see bq_octet).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(uint32_t *p, int octets)
 {
     return __builtin_amdgcn_make_buffer_rsrc(p, 0, 1024 * octets, 0x00027000);
@@ -258,13 +258,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             }
             asm volatile("" ::: "memory");
             // words of replica ln, of four even blocks a load in lanes 0-31 and of four odd ones
-            // in lanes 32-63: the halves of four K steps (reads past the last octet return zero)
+            // in lanes 32-63: the halves of four K steps
             constexpr int KO = (KS + 3) / 4;
             v4i_t v[KO];
 #pragma unroll
             for (int k = 0; k < KO; ++k)
                 v[k] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(xr[i][1 - side], 512 * kg + 16 * ln,
-                                                                                      1024 * k, 16 /* sc1 */));
+                                                                                      1024 * bq_octet(k, octets[1 - side]),
+                                                                                      16 /* sc1 */));
             v16f_t acc = bias;
 #pragma unroll
             for (int k = 0; k < KO; ++k)

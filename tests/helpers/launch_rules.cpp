@@ -56,10 +56,25 @@ static void coupling_codes()
             }
 }
 
+// Reads of the cluster kernel's exchange words: octet by octet up to the widest side its operands
+// hold, within the octets the side has.
+static void exchange_octets()
+{
+    for (int steps : {4, 8, 16, 32})
+        for (int blocks = 1; blocks <= 2 * steps; ++blocks) {
+            const int octets = (blocks + 7) / 8;
+            for (int k = 0; k < (steps + 3) / 4; ++k) {
+                const int at = bq_octet(k, octets);
+                CHECK(at >= 0 && 1024 * at + 512 + 16 * 31 + 16 <= 1024 * octets && (k >= octets || at == k));
+            }
+        }
+}
+
 int main()
 {
     group_cursor();
     coupling_codes();
+    exchange_octets();
     std::printf("rules ok\n");
     return 0;
 }
