@@ -302,8 +302,8 @@ int pbit_profile_read(pbit_ctx *ctx, int32_t kind, double *total_ms, int64_t *la
  * runs of sweeps per launch, in slices of 16 or 8 replicas, 5 = sides of at most 2048
  * with couplings in the registers of each XCD's compute units for runs of sweeps
  * (runs of 16 sweeps or more, at most 8192 replicas, and the whole device free at the
- * launch: where its workgroups cannot be resident together another kernel runs the
- * sweeps).  The library times the
+ * launch: where its workgroups have not all met within PBIT_BQ_MEET_US microseconds, 2000
+ * by default, another kernel runs the sweeps).  The library times the
  * kernels the shape can take (kernel 3 in each replica tile that divides the padded
  * replica count, kernel 4 in both slice widths) on the first anneal of a shape and
  * keeps the fastest, unless PBIT_BQ_VARIANT (1..5) names a kernel, PBIT_BQ_BITS_RT

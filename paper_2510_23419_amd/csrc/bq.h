@@ -74,13 +74,15 @@ hipError_t bq_slab(const BqView &p, int8_t *MA, int8_t *MB, int Rp, const uint32
 // The form whose couplings stay in registers across an XCD (bq_cluster.hip), for sides of at
 // most 2048 sites and threshold rows of at most 256 entries: sweeps [s_begin, s_end) of
 // replicas [0, R) on MA / MB in place, with `work` (bq_cluster_bytes) as exchange memory and a
-// workgroup on each of `cus` compute units.  work[1] is 0 afterwards if the sweeps ran, 1
+// workgroup on each of `cus` compute units, which wait up to `meet_us` for each other
+// (kMeetUs: an idle device takes some 10 us).  work[1] is 0 afterwards if the sweeps ran, 1
 // if the workgroups could not be resident together (MA / MB untouched), 2 after a lost flag.
 bool bq_cluster_supported(const BqView &p, int width);
 size_t bq_cluster_bytes(const BqView &p, int R);
+constexpr int kMeetUs = 2000;
 hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
                       int s_begin, int s_end, uint32_t sweep0, uint32_t rq0, Key key, void *work, int cus,
-                      hipStream_t st);
+                      int meet_us, hipStream_t st);
 hipError_t bq_init(const BqView &p, int8_t *MA, int8_t *MB, int R, uint32_t rq0, Key key, hipStream_t st);
 hipError_t bq_from_rows(const BqView &p, const int8_t *src_rn, int R, int8_t *MA, int8_t *MB, hipStream_t st);
 hipError_t bq_to_rows(const BqView &p, const int8_t *MA, const int8_t *MB, int8_t *dst_rn, int R, hipStream_t st);

@@ -29,8 +29,8 @@
 // words rebuilt every sweep instead of the rows themselves, cost 0.5 and 0.3 us.
 //
 // The workgroups have to be resident together, and spread evenly over the XCDs: they
-// meet before touching anything, and if they do not all arrive in time or an XCD has too
-// few of them, all leave and the caller runs the sweeps another way.
+// meet before touching anything (meet.h), and if they do not all arrive in time or an XCD has
+// too few of them, all leave and the caller runs the sweeps another way.
 //
 // Arithmetic, counters and decisions are the bit kernel's (bq_kernels.hip): spin bits
 // widened for the FP4 MFMA, exact sums, thresholds by |I|.
@@ -39,6 +39,7 @@
 
 #include "bq.h"
 #include "device.h"
+#include "meet.h"
 
 namespace pbit {
 
@@ -46,9 +47,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kXcds = 8;
-constexpr uint32_t kAbort = 0x80000000u;
-constexpr uint64_t kMeetTicks = 200000;  // 2 ms of the 100 MHz clock; an idle device takes some 10 us
 constexpr int kMaxWidth = 256;            // threshold row entries
 constexpr int kRows = 16;                 // threshold rows held per wave
 constexpr int kMaxBlocks = 64;            // a wave's lanes watch one flag each
@@ -65,6 +63,7 @@ struct Args {
     int n[2], n_p[2], blocks[2];
     int width, tiles, s_begin, s_end, members;
     uint32_t sweep0, rq0, k0, k1;
+    uint64_t meet_ticks;  // longest wait for the other workgroups, of the 100 MHz clock
 };
 
 __device__ __forceinline__ uint32_t agent_load(const uint32_t *p)
@@ -76,30 +75,24 @@ __device__ __forceinline__ uint32_t agent_add(uint32_t *p, uint32_t v)
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// All workgroups arrive, or none proceeds: a workgroup that waited too long marks the
-// arrival count (only while it is incomplete), and whoever sees the mark leaves.
-__device__ bool meet(uint32_t *ctl, uint32_t groups, uint32_t members, uint32_t xcc, uint32_t &slot)
-{
-    slot = agent_add(ctl + 2 + (xcc & (kXcds - 1)), 1u);
-    uint32_t seen = agent_add(ctl, 1u) + 1u;
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    while (seen < groups) {  // the mark makes it larger
-        if (__builtin_amdgcn_s_memrealtime() - t0 > kMeetTicks) {
-            uint32_t expect = seen;
-            if (__hip_atomic_compare_exchange_strong(ctl, &expect, seen | kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT))
-                return false;
-            seen = expect;
-            continue;
-        }
-        __builtin_amdgcn_s_sleep(2);
-        seen = agent_add(ctl, 0u);
+// The meeting words (meet.h) in device memory.
+struct MeetDevice {
+    uint32_t *ctl;
+    uint64_t limit, t0;
+    __device__ uint32_t add(int word, uint32_t v) { return agent_add(ctl + word, v); }
+    __device__ uint32_t read(int word) { return agent_add(ctl + word, 0u); }
+    __device__ uint32_t arrive()
+    {
+        return __hip_atomic_fetch_add(ctl, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (seen & kAbort) return false;
-    bool ok = xcc < kXcds;
-    for (int k = 0; k < kXcds; ++k) ok = ok && agent_add(ctl + 2 + k, 0u) >= members;
-    return ok;
-}
+    __device__ bool swap(uint32_t &seen, uint32_t v)
+    {
+        return __hip_atomic_compare_exchange_strong(ctl, &seen, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ bool late() { return __builtin_amdgcn_s_memrealtime() - t0 > limit; }
+    __device__ void pause() { __builtin_amdgcn_s_sleep(2); }
+};
 
 // Exchange words of one side and row tile as a buffer of whole octets of blocks (its range check
 // leaves the uniform offset out: see bq_octet).
@@ -120,7 +113,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (threadIdx.x == 0) {
         const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (31 << 11)) & 15u;  // HW_REG_XCC_ID
         uint32_t slot = 0u;
-        const bool ok = meet(g.ctl, gridDim.x, (uint32_t)g.members, xcc, slot);
+        MeetDevice mem{g.ctl, g.meet_ticks, __builtin_amdgcn_s_memrealtime()};
+        const bool ok = meet(mem, gridDim.x, (uint32_t)g.members, xcc, slot);
         joined[0] = ok;
         joined[1] = xcc;
         joined[2] = slot;
@@ -131,7 +125,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     const int cluster = __builtin_amdgcn_readfirstlane((int)joined[1]);
     const int slot = __builtin_amdgcn_readfirstlane((int)joined[2]);
     __syncthreads();
-    if (!ok || slot >= g.members) return;
+    if (!ok || (uint32_t)slot >= (uint32_t)g.members) return;
 
     const int lane = threadIdx.x & 63, ln = lane & 31, kg = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -383,7 +377,7 @@ size_t bq_cluster_bytes(const BqView &p, int R)
 
 hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, const uint32_t *table, int width,
                       int s_begin, int s_end, uint32_t sweep0, uint32_t rq0, Key key, void *work, int cus,
-                      hipStream_t st)
+                      int meet_us, hipStream_t st)
 {
     const int tiles = (R + 31) / 32;
     if (!bq_cluster_supported(p, width) || s_end < s_begin || 32 * tiles > Rp || cus < kXcds) return hipErrorInvalidValue;
@@ -419,6 +413,7 @@ hipError_t bq_cluster(const BqView &p, int8_t *MA, int8_t *MB, int R, int Rp, co
     g.rq0 = rq0;
     g.k0 = key.k0;
     g.k1 = key.k1;
+    g.meet_ticks = 100u * (uint64_t)meet_us;
     const size_t lds = sizeof(uint32_t) * (size_t)std::max(kRows * width * kWaves, 4);
     if (blocks <= 8) return launch<4, 1>(g, cus, lds, st);
     if (blocks <= 16) return launch<8, 1>(g, cus, lds, st);

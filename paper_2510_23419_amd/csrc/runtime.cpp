@@ -157,6 +157,7 @@ extern "C" int pbit_create(pbit_ctx **out, int device, uint64_t hbm_budget_bytes
         const int k = std::atoi(v);
         ctx->bq_slab_rs = k == 16 || k == 8 ? k : 0;
     }
+    if (const char *v = std::getenv("PBIT_BQ_MEET_US")) ctx->bq_meet_us = std::max(0, std::atoi(v));  // tuning override
     if (const char *v = std::getenv("PBIT_EA_STREAM")) ctx->ea_stream_forced = std::atoi(v) != 0;
     if (const char *v = std::getenv("PBIT_EA_ROWS")) ctx->ea_rows = std::max(0, std::atoi(v));  // tuning override
     if (const char *v = std::getenv("PBIT_GRAPH")) ctx->use_graph = std::atoi(v) != 0;
@@ -840,7 +841,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
             } else if (v == BqVariant::Cluster) {
                 if (e == hipSuccess)
                     e = bq_cluster(P.bq, ds.MA, ds.MB, ds.R, ds.Rp, ds.table, ds.width, 0, slab_sweeps, 0u, 0u, key,
-                                   ds.cluster_work, compute_units(ctx), st);
+                                   ds.cluster_work, compute_units(ctx), ctx->bq_meet_us, st);
             } else {
                 for (int k = 0; k < 4 && e == hipSuccess; ++k)
                     e = v == BqVariant::Bits
@@ -1217,7 +1218,7 @@ static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, 
         hipError_t e = timed ? prof_begin(ctx, P.kind, st) : hipSuccess;
         if (e == hipSuccess)
             e = bq_cluster(P.bq, ds.MA, ds.MB, ds.R, ds.Rp, ds.table, ds.width, s0, s1, sweep0, rq0, key,
-                           ds.cluster_work, compute_units(ctx), st);
+                           ds.cluster_work, compute_units(ctx), ctx->bq_meet_us, st);
         if (e == hipSuccess && timed) {
             ctx->prof_launches.back() += 2 * (s1 - s0);
             e = prof_close(ctx, st);

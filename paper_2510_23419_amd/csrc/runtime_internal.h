@@ -76,6 +76,7 @@ struct pbit_ctx {
     int bq_last_variant = 0;  // biclique half-sweep variant of the latest biclique anneal (0: none yet)
     bool work_busy = false;   // an anneal uses Slot::Work
     int bq_cluster_skip = 0;  // anneals until the cluster kernel is tried again, after it could not be resident
+    int bq_meet_us = pbit::kMeetUs;  // longest wait of the cluster kernel's workgroups for each other (PBIT_BQ_MEET_US)
     int bq_bits_rt = 0;       // replicas per tile of the bit kernel (PBIT_BQ_BITS_RT: 64, 128, 256; 0 = by size)
     int bq_slab_rs = 0;       // replicas per slice of the LDS-resident kernel (PBIT_BQ_SLAB_RS: 16, 8; 0 = timed)
     bool ea_stream_forced = false;  // cubes always take the streaming stencil (PBIT_EA_STREAM=1)

@@ -2,9 +2,15 @@
 // for tests/test_launch_rules_cpu.py.  Prints "rules ok".
 #include <cstdio>
 #include <cstdlib>
+#include <mutex>
+#include <random>
+#include <thread>
+#include <utility>
+#include <vector>
 
 #include "bits.h"
 #include "bq.h"
+#include "meet.h"
 
 using namespace pbit;
 
@@ -70,11 +76,111 @@ static void exchange_octets()
         }
 }
 
+// Meeting words as memory that performs an unordered add as late as it may: after the thread's
+// next ordered operation, or, where arrivals order nothing (ordered = false), a while after it.
+struct MeetMemory {
+    std::mutex mu;
+    uint32_t word[10] = {};
+};
+struct MeetThread {
+    MeetMemory &m;
+    std::mt19937 rng;
+    bool ordered;
+    int patience;
+    std::vector<int> pending;
+    int until = 0;
+    void perform()
+    {
+        for (int w : pending) ++m.word[w];
+        pending.clear();
+    }
+    void operation()
+    {
+        if (--until <= 0) perform();
+    }
+    uint32_t add(int w, uint32_t)
+    {
+        std::lock_guard<std::mutex> lk(m.mu);
+        pending.push_back(w);
+        until = 20;
+        return m.word[w];  // (a slot is not used before the meeting ends)
+    }
+    uint32_t arrive()
+    {
+        std::lock_guard<std::mutex> lk(m.mu);
+        if (ordered) perform();
+        return m.word[0]++;
+    }
+    uint32_t read(int w)
+    {
+        std::lock_guard<std::mutex> lk(m.mu);
+        operation();
+        return m.word[w];
+    }
+    bool swap(uint32_t &seen, uint32_t v)
+    {
+        std::lock_guard<std::mutex> lk(m.mu);
+        operation();
+        if (m.word[0] != seen) {
+            seen = m.word[0];
+            return false;
+        }
+        m.word[0] = v;
+        return true;
+    }
+    bool late() { return patience >= 0 && patience-- == 0; }
+    void pause()
+    {
+        if (rng() % 4 == 0) std::this_thread::yield();
+    }
+};
+
+// Sixteen workgroups, two on each XCD: all of them go, or none does.  Returns how many went.
+static int meeting(unsigned seed, bool ordered, bool impatient, int short_xcd)
+{
+    MeetMemory memory;
+    constexpr int kGroups = 16;
+    std::vector<char> went(kGroups, 2);
+    std::vector<std::thread> pool;
+    for (int k = 0; k < kGroups; ++k)
+        pool.emplace_back([&, k] {
+            std::mt19937 rng(seed * 100 + k);
+            const int patience = impatient && rng() % 3 == 0 ? (int)(rng() % 60) : -1;
+            MeetThread t{memory, rng, ordered, patience, {}, 0};
+            uint32_t slot;
+            const int xcc = k % 8 == short_xcd ? 0 : k % 8;
+            went[k] = meet(t, kGroups, 2u, (uint32_t)xcc, slot);
+        });
+    for (auto &t : pool) t.join();
+    int n = 0;
+    for (char w : went) {
+        CHECK(w == 0 || w == 1);
+        n += w;
+    }
+    return n;
+}
+
+static void meetings()
+{
+    int went = 0, unordered = 0;
+    for (unsigned s = 0; s < 200; ++s) {
+        CHECK(meeting(s, true, false, -1) == 16);
+        CHECK(meeting(s, true, false, 3) == 0);  // an XCD with too few
+        const int n = meeting(s, true, true, -1);
+        CHECK(n == 0 || n == 16);
+        went += n == 16;
+        unordered += meeting(s, false, false, -1) != 16;
+    }
+    std::printf("impatient meetings held: %d of 200\n", went);
+    CHECK(unordered > 0);  // the model does tell arrivals that order nothing
+}
+
 int main()
 {
     group_cursor();
     coupling_codes();
     exchange_octets();
+    meetings();
     std::printf("rules ok\n");
     return 0;
 }

@@ -140,3 +140,24 @@ def test_exchange_memory_costs_no_budget():
         seen.add(ok)
         assert not ok or sequence("5", budget), budget
     assert seen == {True, False}
+
+
+def test_workgroups_that_do_not_meet():
+    """A wait limit of zero: the workgroups leave before touching the spins, another kernel runs
+    the sweeps, and the next anneals do not try again."""
+    old = os.environ.get("PBIT_BQ_MEET_US")
+    os.environ["PBIT_BQ_MEET_US"] = "0"
+    try:
+        c = _forced_context("5")
+    finally:
+        if old is None:
+            del os.environ["PBIT_BQ_MEET_US"]
+        else:
+            os.environ["PBIT_BQ_MEET_US"] = old
+    try:
+        for na, nb, R, S in [(300, 200, 40, 20), (520, 600, 70, 18), (64, 32, 8, 5), (1100, 700, 33, 16)]:
+            inst = synth.biclique_instance(na, seed=na, nb=nb)
+            for _ in range(2):
+                assert _sampled(c.ctx, inst, synth.beta_linear(0.05, 2.0, S), R, seed=R) != CLUSTER
+    finally:
+        c.close()
