@@ -22,6 +22,7 @@
 #include "../../include/pbit.h"
 #include "batch.h"
 #include "bits.h"
+#include "bq_tune.h"
 #include "internal.h"
 #include "runtime_internal.h"
 
@@ -879,19 +880,23 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
         rt = run.second;
         float ms = 0.f;
         if (v == BqVariant::Slab || v == BqVariant::Cluster) {
-            float t1 = 0.f, t2 = 0.f;
-            time_it(v, 1, &t1);
-            if (v == BqVariant::Cluster && e == hipSuccess) {
+            double t1 = 0.0, t2 = 0.0;
+            auto pass = [&](int n) {
+                float t = 0.f;
+                time_it(v, n, &t);
+                return t;
+            };
+            auto ran = [&] {
                 int status = 0;
-                e = cluster_status(ds, st, &status);
-                if (status != 0) {  // not resident together: no candidate now
-                    ctx->bq_cluster_skip = kClusterSkip;
-                    cache = false;
-                    continue;
-                }
+                if (v == BqVariant::Cluster && e == hipSuccess) e = cluster_status(ds, st, &status);
+                return status == 0;
+            };
+            if (!time_runs(pass, ran, m, &t1, &t2)) {  // not resident together: no candidate now
+                ctx->bq_cluster_skip = kClusterSkip;
+                cache = false;
+                continue;
             }
-            if (m > 0) time_it(v, 1 + m, &t2);
-            const double per_sweep = m > 0 ? std::max(0.0, (double)(t2 - t1) / m) : t1;
+            const double per_sweep = m > 0 ? std::max(0.0, (t2 - t1) / m) : t1;
             const double load = m > 0 ? std::max(0.0, t1 - per_sweep) : 0.0;
             const int chunk = v == BqVariant::Slab ? kSlabChunk : kClusterChunk;
             const double total = (double)((S + chunk - 1) / chunk) * load + S * per_sweep;

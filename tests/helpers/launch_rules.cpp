@@ -10,6 +10,7 @@
 
 #include "bits.h"
 #include "bq.h"
+#include "bq_tune.h"
 #include "meet.h"
 
 using namespace pbit;
@@ -175,12 +176,26 @@ static void meetings()
     CHECK(unordered > 0);  // the model does tell arrivals that order nothing
 }
 
+// Timings of a kernel whose launches may not run: each has to have run.
+static void run_times()
+{
+    for (int lost = 0; lost < 4; ++lost) {  // the launch that does not run (3: none)
+        int launch = 0;
+        double one = 0.0, more = 0.0;
+        const bool ok = time_runs([&](int n) { return launch++ == lost ? 2.0 : 0.1 + 0.01 * n; },
+                                  [&] { return launch - 1 != lost; }, 32, &one, &more);
+        CHECK(ok == (lost > 1));
+        CHECK(!ok || (one < 0.2 && more < 0.5 && launch == 2));
+    }
+}
+
 int main()
 {
     group_cursor();
     coupling_codes();
     exchange_octets();
     meetings();
+    run_times();
     std::printf("rules ok\n");
     return 0;
 }
