@@ -2,7 +2,38 @@
 // device work so that the host can exercise it).
 #pragma once
 
+#include <vector>
+
+#include "bq.h"
+
 namespace pbit {
+
+// Timed cost of one kernel (with its replica tile or slice width rt) at a shape: of a launch
+// and of each sweep in it.
+struct BqCost {
+    BqVariant variant;
+    int rt;
+    double load_ms, sweep_ms;
+};
+
+// The timed kernel that costs least over `sweeps` sweeps, `chunk(variant)` of them per launch;
+// the cluster kernel only where this anneal can take it.  Null if none was timed.
+template <class Chunk>
+const BqCost *cheapest(const std::vector<BqCost> &costs, bool cluster_ok, int sweeps, Chunk chunk)
+{
+    const BqCost *best = nullptr;
+    double best_ms = 0.0;
+    for (const BqCost &c : costs) {
+        if (c.variant == BqVariant::Cluster && !cluster_ok) continue;
+        const int per = chunk(c.variant);
+        const double ms = (double)((sweeps + per - 1) / per) * c.load_ms + sweeps * c.sweep_ms;
+        if (!best || ms < best_ms) {
+            best = &c;
+            best_ms = ms;
+        }
+    }
+    return best;
+}
 
 // Times a kernel that runs any number of sweeps per launch over 1 and, if m > 0, 1 + m sweeps:
 // time(sweeps) gives milliseconds, ran() whether the launches just timed ran their sweeps.

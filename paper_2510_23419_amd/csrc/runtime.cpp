@@ -22,7 +22,6 @@
 #include "../../include/pbit.h"
 #include "batch.h"
 #include "bits.h"
-#include "bq_tune.h"
 #include "internal.h"
 #include "runtime_internal.h"
 
@@ -769,6 +768,22 @@ static hipError_t cluster_status(const DevState &ds, hipStream_t st, int *status
     return e == hipSuccess ? hipStreamSynchronize(st) : e;
 }
 
+static int bq_chunk(BqVariant v) { return v == BqVariant::Slab ? kSlabChunk : v == BqVariant::Cluster ? kClusterChunk : 1; }
+
+// Takes the cheapest kernel timed at this shape, if any was; the timings in *timed.
+static bool take_timed(pbit_ctx *ctx, const Problem &P, DevState &ds, bool slab_ok, bool cluster_ok, int n_sweeps,
+                       std::vector<BqCost> **timed)
+{
+    std::vector<BqCost> &costs = ctx->bq_tuned[{P.bq.na_p, P.bq.nb_p, ds.Rp, slab_ok ? 1 : 0}];
+    if (timed) *timed = &costs;
+    const BqCost *c = cheapest(costs, cluster_ok, std::max(1, n_sweeps), bq_chunk);
+    if (!c) return false;
+    ds.variant = c->variant;
+    if (c->variant == BqVariant::Bits) ds.bits_rt = c->rt;
+    if (c->variant == BqVariant::Slab) ds.slab_rs = c->rt;
+    return true;
+}
+
 // Pick the biclique kernel variant for this shape: the forced one, a cached
 // choice, or the fastest of the candidates timed here on the (not yet
 // initialised) spin buffers, whose contents do not affect the timing.
@@ -793,18 +808,17 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
         ds.variant = f;
         return PBIT_OK;
     }
-    const std::array<int, 4> shape{P.bq.na_p, P.bq.nb_p, ds.Rp, (slab_ok ? 1 : 0) + (cluster_ok ? 2 : 0)};
-    auto it = ctx->bq_tuned.find(shape);
-    if (it != ctx->bq_tuned.end()) {
-        ds.variant = it->second.first;
-        (ds.variant == BqVariant::Slab ? ds.slab_rs : ds.bits_rt) = it->second.second;
-        return PBIT_OK;
-    }
     if (!large && !slab_ok && !cluster_ok) {
         ds.variant = BqVariant::Small;
-        ctx->bq_tuned[shape] = {ds.variant, 0};
         return PBIT_OK;
     }
+    // timed before: all but the cluster kernel together, that one with the first anneal that can take it
+    std::vector<BqCost> *timed = nullptr;
+    const bool others = take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, &timed);
+    bool cluster = !cluster_ok;
+    for (const BqCost &c : *timed) cluster = cluster || c.variant == BqVariant::Cluster;
+    if (others && (cluster || ds.arena)) return PBIT_OK;
+    std::vector<BqCost> costs = *timed;
     if (ds.arena) {
         // no timing here (it would create events and wait for the stream): the kernel
         // the tuner keeps at the benchmark's shapes (the LDS-resident form where it
@@ -819,14 +833,9 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     if (e != hipSuccess) return device_fail(ctx, e, "hipEventCreate (tuning)");
     const Key key{0u, 0u};
     // the LDS-resident form loads its couplings once per launch of up to kSlabChunk sweeps:
-    // timed over 1 and 1 + m sweeps, and its cost for this call's sweeps set against the
-    // others' per half-sweep (table rows up to n_sweeps are read)
+    // timed over 1 and 1 + m sweeps (table rows up to n_sweeps are read)
     // (32 more sweeps: enough that a traced run's longer launches do not flip its slice choice)
     const int S = std::max(1, n_sweeps), m = std::min(32, S - 1);
-    float best_ms = 0.f;
-    BqVariant best = BqVariant::Small;
-    int best_rt = 0;
-    bool have = false, cache = true;
     int rt = 0;  // the bit kernel's replica tile or the LDS-resident kernel's slice being timed
     // one warm-up pass, then the best of three (a profiler's tracing stretches single launches;
     // of one for the cluster kernel, whose passes take the device to themselves)
@@ -863,8 +872,8 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     std::vector<std::pair<BqVariant, int>> runs;
     for (BqVariant v : cand) {
         if ((v == BqVariant::Dma && !large) || (v == BqVariant::Bits && !ds.MAb) || (v == BqVariant::Slab && !slab_ok) ||
-            (v == BqVariant::Cluster && !cluster_ok))
-            continue;  // the shape cannot take it
+            (v == BqVariant::Cluster ? cluster : others))
+            continue;  // the shape cannot take it, or it was timed
         if (v == BqVariant::Bits && ds.bits_rt == 0) {
             for (int w : {256, 128, 64})
                 if (ds.Rp % w == 0) runs.push_back({v, w});
@@ -878,7 +887,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     for (const auto &run : runs) {
         const BqVariant v = run.first;
         rt = run.second;
-        float ms = 0.f;
+        double load = 0.0, per_sweep = 0.0;
         if (v == BqVariant::Slab || v == BqVariant::Cluster) {
             double t1 = 0.0, t2 = 0.0;
             auto pass = [&](int n) {
@@ -893,32 +902,23 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
             };
             if (!time_runs(pass, ran, m, &t1, &t2)) {  // not resident together: no candidate now
                 ctx->bq_cluster_skip = kClusterSkip;
-                cache = false;
                 continue;
             }
-            const double per_sweep = m > 0 ? std::max(0.0, (t2 - t1) / m) : t1;
-            const double load = m > 0 ? std::max(0.0, t1 - per_sweep) : 0.0;
-            const int chunk = v == BqVariant::Slab ? kSlabChunk : kClusterChunk;
-            const double total = (double)((S + chunk - 1) / chunk) * load + S * per_sweep;
-            ms = (float)(total * 2.0 / S);  // per four half-sweeps, as the others
+            per_sweep = m > 0 ? std::max(0.0, (t2 - t1) / m) : t1;
+            load = m > 0 ? std::max(0.0, t1 - per_sweep) : 0.0;
         } else {
+            float ms = 0.f;  // four half-sweeps
             time_it(v, 0, &ms);
+            per_sweep = ms / 2.0;
         }
         if (e != hipSuccess) break;
-        if (!have || ms < best_ms) {
-            best_ms = ms;
-            best = v;
-            best_rt = rt;
-            have = true;
-        }
+        costs.push_back({v, rt, load, per_sweep});
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return device_fail(ctx, e, "biclique kernel tuning");
-    ds.variant = best;
-    if (best == BqVariant::Bits) ds.bits_rt = best_rt;
-    if (best == BqVariant::Slab) ds.slab_rs = best_rt;
-    if (cache) ctx->bq_tuned[shape] = {ds.variant, best == BqVariant::Slab ? ds.slab_rs : ds.bits_rt};
+    *timed = costs;
+    take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, nullptr);
     return PBIT_OK;
 }
 
@@ -1021,17 +1021,19 @@ static bool bits_preferred(const Problem &P, int R, int cus)
     return bit_sweep_us(P, Rp, bit_pick_rs(P, Rp, cus), cus) < 8.0 + 0.5e-6 * (double)P.N * R;
 }
 
-// The kernel that runs a biclique's sweeps when the cluster kernel's workgroups could not be
-// resident together (MA and MB hold the spins): as without timing.
-static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds, hipStream_t st)
+// The kernel that runs `n_sweeps` sweeps of a biclique when the cluster kernel's workgroups
+// could not be resident together (MA and MB hold the spins): the fastest timed one, or as without
+// timing.
+static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds, int n_sweeps, hipStream_t st)
 {
     ctx->bq_cluster_skip = kClusterSkip;
     const bool large = P.bq.na_p % 128 == 0 && P.bq.nb_p % 128 == 0;
-    ds.variant = bq_slab_supported(P.bq, ds.Rp, ds.width, 0) ? BqVariant::Slab
-                 : ds.MAb ? BqVariant::Bits : large ? BqVariant::Dma : BqVariant::Small;
+    const bool slab_ok = bq_slab_supported(P.bq, ds.Rp, ds.width, ctx->bq_slab_rs);
+    if (!take_timed(ctx, P, ds, slab_ok, false, n_sweeps, nullptr))
+        ds.variant = slab_ok ? BqVariant::Slab : ds.MAb ? BqVariant::Bits : large ? BqVariant::Dma : BqVariant::Small;
     ds.slab = ds.variant == BqVariant::Slab;
     ds.bits = ds.variant == BqVariant::Bits;
-    ds.chunk = ds.slab ? kSlabChunk : 1;
+    ds.chunk = bq_chunk(ds.variant);
     ctx->bq_last_variant = (int)ds.variant;
     return ds.bits ? bqb_pack(P.bq, ds.MA, ds.MB, ds.MAb, ds.MBb, ds.Rp, st) : hipSuccess;
 }
@@ -1154,7 +1156,7 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     ds.bits = P.kind == PBIT_BICLIQUE && ds.variant == BqVariant::Bits;
     // runs of sweeps per launch
     if (P.kind == PBIT_BICLIQUE) ds.slab = ds.variant == BqVariant::Slab || ds.variant == BqVariant::Cluster;
-    ds.chunk = !ds.slab ? 1 : ds.variant == BqVariant::Cluster ? kClusterChunk : kSlabChunk;
+    ds.chunk = P.kind == PBIT_BICLIQUE ? bq_chunk(ds.variant) : ds.slab ? kSlabChunk : 1;
     if (P.kind == PBIT_EA3D && d->n_sweeps > 0)
         ctx->ea_last_path = ds.slab && P.N <= kEaSlabMaxSites ? 2 : (ds.mfma ? 3 : 1);
     if (P.kind == PBIT_GRAPH && d->n_sweeps > 0) ctx->graph_last_path = ds.slab ? 2 : 1;
@@ -1232,7 +1234,7 @@ static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, 
         if (e == hipSuccess) e = cluster_status(ds, st, &status);
         if (e != hipSuccess || status == 0) return e;
         if (status != 1) return hipErrorLaunchFailure;
-        e = cluster_fallback(ctx, P, ds, st);
+        e = cluster_fallback(ctx, P, ds, s1 - s0, st);
         for (int s = s0; s < s1 && e == hipSuccess; s += ds.chunk)
             e = sweeps(ctx, P, ds, s, std::min(s1, s + ds.chunk), sweep0, rq0, key, st);
         return e;

@@ -11,6 +11,7 @@
 #include "../../include/pbit.h"
 #include "bits.h"
 #include "bq.h"
+#include "bq_tune.h"
 #include "host.h"
 
 namespace pbit {
@@ -95,7 +96,7 @@ struct pbit_ctx {
     int graph_slab_rs = 0;          // its tile width when forced (PBIT_GRAPH_SLAB=4, 8 or 16; 0: by the rule)
     // (na_p, nb_p, Rp, LDS form possible) -> fastest kernel and its replica tile (bit kernel) or
     // slice (LDS-resident kernel)
-    std::map<std::array<int, 4>, std::pair<pbit::BqVariant, int>> bq_tuned;
+    std::map<std::array<int, 4>, std::vector<pbit::BqCost>> bq_tuned;
 };
 
 namespace pbit {

@@ -189,6 +189,22 @@ static void run_times()
     }
 }
 
+// The cheapest of the timed kernels: the cluster kernel's place in the cache does not hide the
+// others from anneals that cannot take it (static scratch, graphs, short runs).
+static void timed_kernels()
+{
+    const std::vector<BqCost> costs = {{BqVariant::Small, 0, 0.0, 0.030}, {BqVariant::Bits, 256, 0.0, 0.021},
+                                       {BqVariant::Bits, 64, 0.0, 0.013}, {BqVariant::Cluster, 0, 0.040, 0.004}};
+    auto chunk = [](BqVariant v) { return v == BqVariant::Cluster ? 20000 : 1; };
+    const BqCost *c = cheapest(costs, true, 100, chunk);
+    CHECK(c && c->variant == BqVariant::Cluster);
+    c = cheapest(costs, false, 100, chunk);
+    CHECK(c && c->variant == BqVariant::Bits && c->rt == 64);
+    c = cheapest(costs, true, 2, chunk);
+    CHECK(c && c->variant == BqVariant::Bits);
+    CHECK(!cheapest(std::vector<BqCost>(), true, 100, chunk));
+}
+
 int main()
 {
     group_cursor();
@@ -196,6 +212,7 @@ int main()
     exchange_octets();
     meetings();
     run_times();
+    timed_kernels();
     std::printf("rules ok\n");
     return 0;
 }

@@ -161,3 +161,25 @@ def test_workgroups_that_do_not_meet():
                 assert _sampled(c.ctx, inst, synth.beta_linear(0.05, 2.0, S), R, seed=R) != CLUSTER
     finally:
         c.close()
+
+
+def test_static_scratch_takes_the_kernel_already_timed():
+    """pbit_anneal_dev_noalloc after an anneal that timed the shape, and chose the cluster kernel,
+    runs the fastest of the others, as an anneal too short for that kernel does."""
+    import torch
+    inst = synth.biclique_instance(1000, seed=11, nb=600)
+    c = pbit.Context(0)
+    try:
+        prob = pbit.load_instance(c.ctx, inst)
+        beta = synth.beta_linear(0.05, 2.0, 64)
+        pbit.pbit_anneal(c.ctx, prob, beta, 100, 3)
+        assert pbit.pbit_profile_variant(c.ctx) == CLUSTER
+        pbit.pbit_anneal(c.ctx, prob, beta[:8], 100, 3)
+        timed = pbit.pbit_profile_variant(c.ctx)
+        spins = torch.empty((100, 1600), dtype=torch.int8, device="cuda:0")
+        pbit.pbit_anneal_dev(c.ctx, prob, beta[:8], 100, 3, spins, noalloc=True)
+        assert pbit.pbit_profile_variant(c.ctx) == timed != CLUSTER
+        ref = oracle.anneal(graph_of(inst), beta[:8], 4, 3)
+        assert np.array_equal(spins[:4].cpu().numpy(), ref.spins)
+    finally:
+        c.close()
