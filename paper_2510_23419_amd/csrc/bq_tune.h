@@ -16,16 +16,17 @@ struct BqCost {
     double load_ms, sweep_ms;
 };
 
-// The timed kernel that costs least over `sweeps` sweeps, `chunk(variant)` of them per launch;
-// the cluster kernel only where this anneal can take it.  Null if none was timed.
+// The timed kernel that costs least over `sweeps` sweeps, up to `chunk(variant)` of them per
+// launch and no more than `run`, the sweeps from one energy check to the next; the cluster
+// kernel only where this anneal can take it.  Null if none was timed.
 template <class Chunk>
-const BqCost *cheapest(const std::vector<BqCost> &costs, bool cluster_ok, int sweeps, Chunk chunk)
+const BqCost *cheapest(const std::vector<BqCost> &costs, bool cluster_ok, int sweeps, int run, Chunk chunk)
 {
     const BqCost *best = nullptr;
     double best_ms = 0.0;
     for (const BqCost &c : costs) {
         if (c.variant == BqVariant::Cluster && !cluster_ok) continue;
-        const int per = chunk(c.variant);
+        const int most = chunk(c.variant), per = run < most ? run : most;
         const double ms = (double)((sweeps + per - 1) / per) * c.load_ms + sweeps * c.sweep_ms;
         if (!best || ms < best_ms) {
             best = &c;

@@ -735,6 +735,13 @@ constexpr int kClusterChunk = 20000;  // and of the biclique cluster kernel
 constexpr int kClusterSkip = 64;      // anneals that do not try it after it could not run
 constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
 
+// Sweeps of an anneal from one energy check to the next (at least 1).
+static int run_length(const pbit_anneal_desc *d)
+{
+    const int run = d->trace_every > 0 ? d->trace_every : d->has_target ? 1 : d->n_sweeps;
+    return std::max(1, std::min(run, d->n_sweeps));
+}
+
 // Whether the cluster kernel can run a biclique's sweeps.  It has to report back whether its
 // workgroups were resident together, so not from a graph or in static scratch, and not for the
 // next anneals after it once was not.  A launch starts by loading couplings and ends in that
@@ -745,10 +752,10 @@ constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph til
 // replicas it would make eight passes of what the bit tile does in one.
 static bool cluster_possible(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, bool slab_ok)
 {
-    const int run = d->trace_every > 0 ? d->trace_every : d->has_target ? 1 : d->n_sweeps;
+    const int run = run_length(d);
     const bool forced = ctx->bq_forced == BqVariant::Cluster;
     if (ds.arena || ctx->use_graph || (!forced && ctx->bq_forced != BqVariant::Auto) || ds.R > 8192 ||
-        (!forced && std::min(run, d->n_sweeps) < (slab_ok ? 64 : 16)) ||
+        (!forced && run < (slab_ok ? 64 : 16)) ||
         (!forced && slab_ok && (std::max(P.bq.na, P.bq.nb) <= 256 || ds.R > 1024)) || !bq_cluster_supported(P.bq, ds.width))
         return false;
     if (ctx->bq_cluster_skip > 0) {
@@ -772,11 +779,11 @@ static int bq_chunk(BqVariant v) { return v == BqVariant::Slab ? kSlabChunk : v 
 
 // Takes the cheapest kernel timed at this shape, if any was; the timings in *timed.
 static bool take_timed(pbit_ctx *ctx, const Problem &P, DevState &ds, bool slab_ok, bool cluster_ok, int n_sweeps,
-                       std::vector<BqCost> **timed)
+                       int run, std::vector<BqCost> **timed)
 {
     std::vector<BqCost> &costs = ctx->bq_tuned[{P.bq.na_p, P.bq.nb_p, ds.Rp, slab_ok ? 1 : 0}];
     if (timed) *timed = &costs;
-    const BqCost *c = cheapest(costs, cluster_ok, std::max(1, n_sweeps), bq_chunk);
+    const BqCost *c = cheapest(costs, cluster_ok, n_sweeps, run, bq_chunk);
     if (!c) return false;
     ds.variant = c->variant;
     if (c->variant == BqVariant::Bits) ds.bits_rt = c->rt;
@@ -789,7 +796,7 @@ static bool take_timed(pbit_ctx *ctx, const Problem &P, DevState &ds, bool slab_
 // initialised) spin buffers, whose contents do not affect the timing.
 static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, hipStream_t st)
 {
-    const int n_sweeps = d->n_sweeps;
+    const int n_sweeps = d->n_sweeps, run = run_length(d);
     // the DMA and bit tiles need sides padded to 128 (and the bit tiles a bit copy of
     // the spins, made where the replicas pad to 256); the LDS-resident form sides of
     // at most 512 and its decision words in LDS
@@ -814,7 +821,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     }
     // timed before: all but the cluster kernel together, that one with the first anneal that can take it
     std::vector<BqCost> *timed = nullptr;
-    const bool others = take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, &timed);
+    const bool others = take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, run, &timed);
     bool cluster = !cluster_ok;
     for (const BqCost &c : *timed) cluster = cluster || c.variant == BqVariant::Cluster;
     if (others && (cluster || ds.arena)) return PBIT_OK;
@@ -884,9 +891,9 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
             runs.push_back({v, v == BqVariant::Slab ? ds.slab_rs : ds.bits_rt});
         }
     }
-    for (const auto &run : runs) {
-        const BqVariant v = run.first;
-        rt = run.second;
+    for (const auto &c : runs) {
+        const BqVariant v = c.first;
+        rt = c.second;
         double load = 0.0, per_sweep = 0.0;
         if (v == BqVariant::Slab || v == BqVariant::Cluster) {
             double t1 = 0.0, t2 = 0.0;
@@ -918,7 +925,7 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return device_fail(ctx, e, "biclique kernel tuning");
     *timed = costs;
-    take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, nullptr);
+    take_timed(ctx, P, ds, slab_ok, cluster_ok, n_sweeps, run, nullptr);
     return PBIT_OK;
 }
 
@@ -1029,7 +1036,7 @@ static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds
     ctx->bq_cluster_skip = kClusterSkip;
     const bool large = P.bq.na_p % 128 == 0 && P.bq.nb_p % 128 == 0;
     const bool slab_ok = bq_slab_supported(P.bq, ds.Rp, ds.width, ctx->bq_slab_rs);
-    if (!take_timed(ctx, P, ds, slab_ok, false, n_sweeps, nullptr))
+    if (!take_timed(ctx, P, ds, slab_ok, false, n_sweeps, n_sweeps, nullptr))
         ds.variant = slab_ok ? BqVariant::Slab : ds.MAb ? BqVariant::Bits : large ? BqVariant::Dma : BqVariant::Small;
     ds.slab = ds.variant == BqVariant::Slab;
     ds.bits = ds.variant == BqVariant::Bits;

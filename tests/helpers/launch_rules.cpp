@@ -196,13 +196,18 @@ static void timed_kernels()
     const std::vector<BqCost> costs = {{BqVariant::Small, 0, 0.0, 0.030}, {BqVariant::Bits, 256, 0.0, 0.021},
                                        {BqVariant::Bits, 64, 0.0, 0.013}, {BqVariant::Cluster, 0, 0.040, 0.004}};
     auto chunk = [](BqVariant v) { return v == BqVariant::Cluster ? 20000 : 1; };
-    const BqCost *c = cheapest(costs, true, 100, chunk);
+    const BqCost *c = cheapest(costs, true, 100, 100, chunk);
     CHECK(c && c->variant == BqVariant::Cluster);
-    c = cheapest(costs, false, 100, chunk);
+    c = cheapest(costs, false, 100, 100, chunk);
     CHECK(c && c->variant == BqVariant::Bits && c->rt == 64);
-    c = cheapest(costs, true, 2, chunk);
+    c = cheapest(costs, true, 2, 2, chunk);
     CHECK(c && c->variant == BqVariant::Bits);
-    CHECK(!cheapest(std::vector<BqCost>(), true, 100, chunk));
+    // a launch for every energy check: 100 sweeps in runs of 3
+    c = cheapest(costs, true, 100, 3, chunk);
+    CHECK(c && c->variant == BqVariant::Bits);
+    c = cheapest(costs, true, 100, 10, chunk);
+    CHECK(c && c->variant == BqVariant::Cluster);
+    CHECK(!cheapest(std::vector<BqCost>(), true, 100, 100, chunk));
 }
 
 int main()
