@@ -31,6 +31,9 @@ int fail(int code, const char *fmt, ...)
     return code;
 }
 
+KeepError::KeepError() : saved(g_last_error) {}
+KeepError::~KeepError() { g_last_error = saved; }
+
 }  // namespace pbit
 
 extern "C" const char *pbit_last_error(void) { return g_last_error.c_str(); }

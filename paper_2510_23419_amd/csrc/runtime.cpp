@@ -45,27 +45,54 @@ namespace pbit {
 
 static std::atomic<uint32_t> g_ctx_serial{1};
 
-// The cluster kernel's exchange memory is the one buffer an anneal can do without: it is
-// given back, between anneals, before an allocation is refused.
-static bool give_back_work(pbit_ctx *ctx)
+// Buffers a call can do without (the cluster kernel's exchange memory, the rows a finished batch
+// job is transposed into): the context keeps them, and gives them back, between their uses,
+// before an allocation is refused.
+constexpr Slot kSpareSlots[] = {Slot::Work, Slot::Rows};
+
+bool give_back_spare(pbit_ctx *ctx)
 {
-    Scratch &w = ctx->scratch[(int)Slot::Work];
-    if (!w.ptr || ctx->work_busy) return false;
-    dev_free(ctx, w.ptr);
-    w = Scratch{};
-    return true;
+    bool any = false;
+    for (Slot k : kSpareSlots) {
+        Scratch &w = ctx->scratch[(int)k];
+        if (!w.ptr || (k == Slot::Work && ctx->work_busy)) continue;
+        dev_free(ctx, w.ptr);
+        w = Scratch{};
+        any = true;
+    }
+    return any;
+}
+
+static size_t spare_bytes(const pbit_ctx *ctx)
+{
+    size_t n = 0;
+    for (Slot k : kSpareSlots) n += ctx->scratch[(int)k].bytes;
+    return n;
+}
+
+// Scratch the call can do without: *out is null, and no error reported, where it does not fit.
+int spare_scratch(pbit_ctx *ctx, Slot slot, size_t bytes, void **out)
+{
+    *out = nullptr;
+    int rc;
+    {
+        const KeepError keep;
+        rc = scratch(ctx, slot, bytes, out);
+    }
+    if (rc == PBIT_E_DEVICE) return fail(rc, "device memory: HIP error; context poisoned");
+    return PBIT_OK;
 }
 
 int dev_alloc(pbit_ctx *ctx, size_t bytes, void **out)
 {
     *out = nullptr;
     if (bytes == 0) return PBIT_OK;
-    if (ctx->budget && ctx->in_use + bytes > ctx->budget) give_back_work(ctx);
+    if (ctx->budget && ctx->in_use + bytes > ctx->budget) give_back_spare(ctx);
     if (ctx->budget && ctx->in_use + bytes > ctx->budget)
         return fail(PBIT_E_NOMEM, "device budget exhausted: %llu in use + %llu requested > %llu",
                     (unsigned long long)ctx->in_use, (unsigned long long)bytes, (unsigned long long)ctx->budget);
     hipError_t e = hipMalloc(out, bytes);
-    if (e == hipErrorOutOfMemory && give_back_work(ctx)) {
+    if (e == hipErrorOutOfMemory && give_back_spare(ctx)) {
         (void)hipGetLastError();
         e = hipMalloc(out, bytes);
     }
@@ -750,23 +777,27 @@ static int run_length(const pbit_anneal_desc *d)
 // 2.0 us + 4.7 ns per site a sweep and this one 2.8 us + 1 ns for each 1024 replicas, so
 // beside it only sides over 256 with up to 1024 replicas are worth timing.  Above 8192
 // replicas it would make eight passes of what the bit tile does in one.
-static bool cluster_possible(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, bool slab_ok)
+static int cluster_possible(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, bool slab_ok,
+                            bool *possible)
 {
+    *possible = false;
     const int run = run_length(d);
     const bool forced = ctx->bq_forced == BqVariant::Cluster;
     if (ds.arena || ctx->use_graph || (!forced && ctx->bq_forced != BqVariant::Auto) || ds.R > 8192 ||
         (!forced && run < (slab_ok ? 64 : 16)) ||
         (!forced && slab_ok && (std::max(P.bq.na, P.bq.nb) <= 256 || ds.R > 1024)) || !bq_cluster_supported(P.bq, ds.width))
-        return false;
+        return PBIT_OK;
     if (ctx->bq_cluster_skip > 0) {
         --ctx->bq_cluster_skip;
-        return false;
+        return PBIT_OK;
     }
     // what the rest of the anneal may yet allocate (staged rows) comes first
     const size_t bytes = bq_cluster_bytes(P.bq, ds.R), rest = 2 * (size_t)ds.R * P.N + 65536;
-    if (ctx->budget && ctx->in_use + bytes + rest > ctx->budget) return false;
+    if (ctx->budget && ctx->in_use - spare_bytes(ctx) + bytes + rest > ctx->budget) return PBIT_OK;
     ctx->work_busy = true;
-    return scratch(ctx, Slot::Work, bytes, &ds.cluster_work) == PBIT_OK;
+    const int rc = spare_scratch(ctx, Slot::Work, bytes, &ds.cluster_work);
+    *possible = ds.cluster_work != nullptr;
+    return rc;
 }
 
 static hipError_t cluster_status(const DevState &ds, hipStream_t st, int *status)
@@ -810,7 +841,9 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
         ds.variant = f;  // a forced kernel the shape cannot take falls back to the tuned choice
         return PBIT_OK;
     }
-    const bool cluster_ok = cluster_possible(ctx, P, d, ds, slab_ok);
+    bool cluster_ok = false;
+    const int rc = cluster_possible(ctx, P, d, ds, slab_ok, &cluster_ok);
+    if (rc) return rc;
     if (cluster_ok && f == BqVariant::Cluster) {
         ds.variant = f;
         return PBIT_OK;

@@ -30,7 +30,7 @@ struct Problem {
     int jobs = 0;  // serving jobs that still reference the problem
 };
 
-enum class Slot : int { Spins = 0, Table, E32, Stage, Aux, Snap, Hit, Work, Count };
+enum class Slot : int { Spins = 0, Table, E32, Stage, Aux, Snap, Hit, Work, Rows, Count };
 
 struct Scratch {
     void *ptr = nullptr;
@@ -105,6 +105,8 @@ int device_fail(pbit_ctx *ctx, hipError_t e, const char *where);
 int dev_alloc(pbit_ctx *ctx, size_t bytes, void **out);
 void dev_free(pbit_ctx *ctx, void *p);
 int scratch(pbit_ctx *ctx, Slot slot, size_t bytes, void **out);
+int spare_scratch(pbit_ctx *ctx, Slot slot, size_t bytes, void **out);
+bool give_back_spare(pbit_ctx *ctx);
 Problem *find_problem(pbit_ctx *ctx, uint64_t handle);
 int check_desc(const pbit_anneal_desc *d, const char *who);
 void serve_shutdown(pbit_ctx *ctx);

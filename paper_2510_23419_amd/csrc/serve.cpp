@@ -768,6 +768,7 @@ struct ServeDevice {
     int harvest() { return pbit::harvest(ctx, s); }
     int admit(BJob *j)
     {
+        if (ctx->budget && ctx->in_use + j->bytes > ctx->budget) give_back_spare(ctx);
         if (ctx->budget && ctx->in_use + j->bytes > ctx->budget)
             return fail(PBIT_E_NOMEM, "job %llu needs %llu bytes; %llu of the %llu-byte budget are in use",
                         (unsigned long long)j->id, (unsigned long long)j->bytes, (unsigned long long)ctx->in_use,
@@ -824,17 +825,16 @@ static int new_job(pbit_ctx *ctx, ServeState &s, uint64_t problem, const pbit_an
 static int fill_result(pbit_ctx *ctx, BJob &j, pbit_result *res)
 {
     if (res && res->spins && j.d_state && j.bits) {
-        // transposed on the device where the staging rows fit the budget
+        // transposed on the device where the rows fit the budget
         void *rows = nullptr;
         const size_t bytes = (size_t)j.R * j.N;
-        const int rc = scratch(ctx, Slot::Stage, bytes, &rows);
-        if (rc == PBIT_OK) {
+        const int rc = spare_scratch(ctx, Slot::Rows, bytes, &rows);
+        if (rc) return rc;
+        if (rows) {
             hipError_t e = ea_to_rows(j.P->ea, (const int8_t *)j.d_state, bit_stride(j), (int8_t *)rows, j.R, ctx->stream);
             if (e == hipSuccess) e = hipMemcpyAsync(res->spins, rows, bytes, hipMemcpyDeviceToHost, ctx->stream);
             if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
             if (e != hipSuccess) return device_fail(ctx, e, "spin readback");
-        } else if (rc != PBIT_E_NOMEM) {
-            return rc;
         } else {
             std::vector<int8_t> tl(state_bytes(j));
             hipError_t e = hipMemcpy(tl.data(), j.d_state, tl.size(), hipMemcpyDeviceToHost);

@@ -371,3 +371,55 @@ def test_tuned_and_fixed_tile_sizes_give_the_same_results():
     finally:
         fixed.close()
         tuned.close()
+
+
+def test_batch_jobs_that_fit_one_after_the_other():
+    """Jobs of 40 and 70 % of what the budget leaves, in one batch and one by one: the second runs
+    when the first is read out, whose rows hold no budget."""
+    inst = synth.ea_instance(16, seed=3)  # 4096 sites
+    beta = synth.beta_linear(0.1, 1.0, 10)
+    refs = {R: oracle.anneal(graph_of(inst), beta, 4, R) for R in (160, 272)}
+    with pbit.Context(0) as probe:
+        pbit.load_instance(probe.ctx, inst)
+        held = pbit.pbit_bytes_in_use(probe.ctx)
+    with pbit.Context(0, hbm_budget_bytes=held + 1_600_000) as c:
+        p = pbit.load_instance(c.ctx, inst)
+        _say("batch under a budget of %d" % (held + 1_600_000))
+        jobs = [dict(problem=p, beta=beta, n_replicas=R, seed=R) for R in (160, 272)]
+        for out, R in zip(pbit.pbit_anneal_batch(c.ctx, jobs), (160, 272)):
+            assert np.array_equal(out.spins[:4], refs[R].spins)
+        for R in (160, 272, 160):
+            jid = pbit.pbit_submit(c.ctx, p, beta, R, R)
+            out = None
+            while out is None:
+                out = pbit.pbit_poll(c.ctx, jid, R, 4096, len(beta))
+            assert np.array_equal(out.spins[:4], refs[R].spins)
+
+
+def test_exchange_memory_leaves_room_for_jobs():
+    """A job as large as the budget left beside the problems runs after a biclique anneal whose
+    kernel keeps exchange memory."""
+    cube, bq = synth.ea_instance(8, seed=1), synth.biclique_instance(1000, seed=2, nb=600)
+    beta = synth.beta_linear(0.1, 1.0, 20)
+    with pbit.Context(0) as probe:
+        b = pbit.load_instance(probe.ctx, bq)
+        p = pbit.load_instance(probe.ctx, cube)
+        pbit.pbit_anneal(probe.ctx, b, synth.beta_linear(0.05, 2.0, 64), 256, 1)
+        assert pbit.pbit_profile_variant(probe.ctx) == 5
+        held = pbit.pbit_bytes_in_use(probe.ctx)
+        exchange = 4 * (16 + 2 * 8 * 64 + 8 * (4 + 3) * 256)  # 8 row tiles, 4 and 3 octets of blocks
+        pbit.pbit_unload_problem(probe.ctx, p)
+    # beside what the first anneal keeps but the exchange memory, and room for the staged rows it may
+    # yet want, a job's memory
+    budget = held + 2 * 256 * 1600 + 65536 + 1024
+    R = (budget - held + exchange - 40_000) // (512 + 4) // 16 * 16  # (the rest: thresholds, work lists)
+    assert R * 516 > budget - held
+    with pbit.Context(0, hbm_budget_bytes=budget) as c:
+        b = pbit.load_instance(c.ctx, bq)
+        p = pbit.load_instance(c.ctx, cube)
+        pbit.pbit_anneal(c.ctx, b, synth.beta_linear(0.05, 2.0, 64), 256, 1)
+        assert pbit.pbit_profile_variant(c.ctx) == 5
+        _say("job of %d replicas after the exchange memory" % R)
+        out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=2)])[0]
+        ref = oracle.anneal(graph_of(cube), beta, 4, 2)
+        assert np.array_equal(out.spins[:4], ref.spins)
