@@ -404,20 +404,20 @@ def test_exchange_memory_leaves_room_for_jobs():
     with pbit.Context(0) as probe:
         b = pbit.load_instance(probe.ctx, bq)
         p = pbit.load_instance(probe.ctx, cube)
-        pbit.pbit_anneal(probe.ctx, b, synth.beta_linear(0.05, 2.0, 64), 256, 1)
+        pbit.pbit_anneal(probe.ctx, b, synth.beta_linear(0.05, 2.0, 64), 1024, 1)
         assert pbit.pbit_profile_variant(probe.ctx) == 5
         held = pbit.pbit_bytes_in_use(probe.ctx)
-        exchange = 4 * (16 + 2 * 8 * 64 + 8 * (4 + 3) * 256)  # 8 row tiles, 4 and 3 octets of blocks
+        exchange = 4 * (16 + 2 * 32 * 64 + 32 * (4 + 3) * 256)  # 32 row tiles, 4 and 3 octets of blocks
         pbit.pbit_unload_problem(probe.ctx, p)
     # beside what the first anneal keeps but the exchange memory, and room for the staged rows it may
     # yet want, a job's memory
-    budget = held + 2 * 256 * 1600 + 65536 + 1024
-    R = (budget - held + exchange - 40_000) // (512 + 4) // 16 * 16  # (the rest: thresholds, work lists)
+    budget = held + 2 * 1024 * 1600 + 65536 + 1024
+    R = (budget - held + exchange - 100_000) // (512 + 4) // 16 * 16  # (the rest: thresholds, work lists)
     assert R * 516 > budget - held
     with pbit.Context(0, hbm_budget_bytes=budget) as c:
         b = pbit.load_instance(c.ctx, bq)
         p = pbit.load_instance(c.ctx, cube)
-        pbit.pbit_anneal(c.ctx, b, synth.beta_linear(0.05, 2.0, 64), 256, 1)
+        pbit.pbit_anneal(c.ctx, b, synth.beta_linear(0.05, 2.0, 64), 1024, 1)
         assert pbit.pbit_profile_variant(c.ctx) == 5
         _say("job of %d replicas after the exchange memory" % R)
         out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=2)])[0]
