@@ -186,8 +186,10 @@ static int tile_mode(const pbit_ctx *ctx)
     return kTileInt8;
 }
 
-// Replicas of a bit job's state, an [N][stride] matrix of bytes (the per-instance layout).
-static int bit_stride(const BJob &j) { return (j.tiles * j.rs + 15) / 16 * 16; }
+// Replicas of a bit job's state, an [N][stride] matrix of bytes (the per-instance layout): those
+// of its tiles, so that few replicas take no more memory than they fill (tiles read and write
+// four replicas at a time).
+static int bit_stride(const BJob &j) { return j.tiles * j.rs; }
 
 // Threads per workgroup of a bit job's tiles: for 16-replica tiles enough for the largest
 // group's pairs (the fewest instructions per update: such jobs share a full device), for

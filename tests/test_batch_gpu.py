@@ -423,3 +423,20 @@ def test_exchange_memory_leaves_room_for_jobs():
         out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=2)])[0]
         ref = oracle.anneal(graph_of(cube), beta, 4, 2)
         assert np.array_equal(out.spins[:4], ref.spins)
+
+
+@pytest.mark.parametrize("R", [3, 20])
+def test_few_replicas_take_their_own_memory(R):
+    """A job's spins take the replicas of its tiles (4 and 20 here), not sixteen at a time."""
+    inst = synth.ea_instance(32, seed=R)
+    beta = synth.beta_linear(0.1, 1.0, 5)
+    with pbit.Context(0) as probe:
+        pbit.load_instance(probe.ctx, inst)
+        held = pbit.pbit_bytes_in_use(probe.ctx)
+    with pbit.Context(0, hbm_budget_bytes=held + (R + 3) // 4 * 4 * 32**3 + 100_000) as c:
+        p = pbit.load_instance(c.ctx, inst)
+        _say("cube job of %d replicas under a budget" % R)
+        for init in (None, synth.random_spins(R, 32**3, seed=1)):
+            out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=2, init_spins=init)])[0]
+            ref = oracle.anneal(graph_of(inst), beta, R, 2, init_spins=init)
+            assert np.array_equal(out.spins, ref.spins) and np.array_equal(out.energies, ref.energies)
