@@ -110,6 +110,9 @@ typedef struct {
 } pbit_problem_desc;
 
 /* Validate and upload a problem; writes an opaque handle to *problem_out.
+ * A cube or graph also gets site records for the sweeps in LDS (26 to 34 bytes a site)
+ * where the budget holds them; without them it has its other paths, and a cube no place in
+ * a batch (E_NOMEM).
  * Errors: E_ARG, E_COLOURING (odd or zero EA side), E_RANGE, E_NOMEM, E_DEVICE. */
 int pbit_load_problem(pbit_ctx *ctx, const pbit_problem_desc *desc, uint64_t *problem_out);
 

@@ -254,15 +254,25 @@ static int upload(pbit_ctx *ctx, Problem &p, const void *host, size_t bytes, voi
     return PBIT_OK;
 }
 
-// Records of the bit-held sweep (bits.h), where the problem can take it.
+// Records of the bit-held sweep (bits.h), where the problem can take it: the last of its
+// arrays, which it does without where they do not fit (per-instance anneals have other paths).
 static int upload_bits(pbit_ctx *ctx, Problem &p, const BitHost &b, const int8_t *dev_h)
 {
     void *dg = nullptr, *dr = nullptr, *dw = nullptr, *dp = nullptr;
-    int rc = upload(ctx, p, b.groups.data(), sizeof(int32_t) * b.groups.size(), &dg);
-    if (rc == PBIT_OK) rc = upload(ctx, p, b.rec.data(), sizeof(uint32_t) * b.rec.size(), &dr);
-    if (rc == PBIT_OK && !b.wide.empty()) rc = upload(ctx, p, b.wide.data(), sizeof(uint32_t) * b.wide.size(), &dw);
-    if (rc == PBIT_OK) rc = upload(ctx, p, b.pos_site.data(), sizeof(uint16_t) * b.pos_site.size(), &dp);
-    if (rc != PBIT_OK) return rc;
+    const size_t before = p.allocs.size();
+    int rc;
+    {
+        const KeepError keep;
+        rc = upload(ctx, p, b.groups.data(), sizeof(int32_t) * b.groups.size(), &dg);
+        if (rc == PBIT_OK) rc = upload(ctx, p, b.rec.data(), sizeof(uint32_t) * b.rec.size(), &dr);
+        if (rc == PBIT_OK && !b.wide.empty()) rc = upload(ctx, p, b.wide.data(), sizeof(uint32_t) * b.wide.size(), &dw);
+        if (rc == PBIT_OK) rc = upload(ctx, p, b.pos_site.data(), sizeof(uint16_t) * b.pos_site.size(), &dp);
+    }
+    if (rc == PBIT_E_NOMEM) {
+        for (; p.allocs.size() > before; p.allocs.pop_back()) dev_free(ctx, p.allocs.back());
+        return PBIT_OK;
+    }
+    if (rc != PBIT_OK) return fail(rc, "site records: HIP error; context poisoned");
     p.bits = BitView{b.form, b.n, b.n_pos, b.n_groups, b.n_pairs, b.n_wide, b.max_pairs, (const int4 *)dg,
                      (const uint4 *)dr, (const uint4 *)dw, (const uint16_t *)dp, dev_h};
     return PBIT_OK;
@@ -314,6 +324,25 @@ static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
     if (rc == PBIT_OK && d->h) rc = upload(ctx, p, d->h, (size_t)N, &dh);
     EaView v{Lx, Ly, Lz, N, (const uint32_t *)dc, (const int8_t *)dJ, (const int8_t *)dh, dense,
              nullptr, nullptr, nullptr, 0, 0};
+    // the matrix-core half-sweep's tiles (about 24 bytes per site), where the shape
+    // allows them and the path may run: every cube with PBIT_EA_MFMA=1; by default the
+    // cubes too large for the LDS-resident path, up to 2^21 sites
+    const bool mfma_wanted = !ctx->ea_stream_forced && (ctx->ea_mfma == 1 ||
+                             (ctx->ea_mfma != 0 && N > kEaSlabMaxSites && N <= ((int64_t)1 << 21)));
+    if (rc == PBIT_OK && mfma_wanted) {
+        EaMfmaHost mh;
+        if (ea_mfma_build(Lx, Ly, Lz, d->J, d->h, mh)) {
+            void *dt = nullptr, *dp = nullptr, *df = nullptr;
+            rc = upload(ctx, p, mh.tiles.data(), sizeof(int32_t) * mh.tiles.size(), &dt);
+            if (rc == PBIT_OK) rc = upload(ctx, p, mh.pos.data(), sizeof(int32_t) * mh.pos.size(), &dp);
+            if (rc == PBIT_OK) rc = upload(ctx, p, mh.bonds.data(), sizeof(uint16_t) * mh.bonds.size(), &df);
+            v.mfma_tiles = (const int32_t *)dt;
+            v.mfma_pos = (const int2 *)dp;
+            v.mfma_bonds = df;
+            v.mfma_nb = mh.nb;
+            v.mfma_n_tiles = mh.n_tiles;
+        }
+    }
     BitHost bits;
     if (rc == PBIT_OK && N <= kBitMaxPositions) {
         std::vector<int32_t> start((size_t)N + 1), nbr((size_t)6 * N);
@@ -336,25 +365,6 @@ static int load_ea(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
         start[(size_t)N] = (int32_t)(6 * N);
         if (bit_build((int)N, start.data(), nbr.data(), Jn.data(), d->h, colour.data(), 2, Lx, bits))
             rc = upload_bits(ctx, p, bits, (const int8_t *)dh);
-    }
-    // the matrix-core half-sweep's tiles (about 24 bytes per site), where the shape
-    // allows them and the path may run: every cube with PBIT_EA_MFMA=1; by default the
-    // cubes too large for the LDS-resident path, up to 2^21 sites
-    const bool mfma_wanted = !ctx->ea_stream_forced && (ctx->ea_mfma == 1 ||
-                             (ctx->ea_mfma != 0 && N > kEaSlabMaxSites && N <= ((int64_t)1 << 21)));
-    if (rc == PBIT_OK && mfma_wanted) {
-        EaMfmaHost mh;
-        if (ea_mfma_build(Lx, Ly, Lz, d->J, d->h, mh)) {
-            void *dt = nullptr, *dp = nullptr, *df = nullptr;
-            rc = upload(ctx, p, mh.tiles.data(), sizeof(int32_t) * mh.tiles.size(), &dt);
-            if (rc == PBIT_OK) rc = upload(ctx, p, mh.pos.data(), sizeof(int32_t) * mh.pos.size(), &dp);
-            if (rc == PBIT_OK) rc = upload(ctx, p, mh.bonds.data(), sizeof(uint16_t) * mh.bonds.size(), &df);
-            v.mfma_tiles = (const int32_t *)dt;
-            v.mfma_pos = (const int2 *)dp;
-            v.mfma_bonds = df;
-            v.mfma_nb = mh.nb;
-            v.mfma_n_tiles = mh.n_tiles;
-        }
     }
     if (rc != PBIT_OK) return rc;
     p.kind = PBIT_EA3D;

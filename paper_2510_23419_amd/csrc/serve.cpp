@@ -236,6 +236,8 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
                     P.kind == PBIT_GRAPH ? "graph" : "cube", (long long)P.N);
     if (P.kind == PBIT_EA3D && (P.ea.Lx > 1024 || P.ea.Ly > 1024))
         return fail(PBIT_E_UNSUPPORTED, "cube of %lld sites is too large for a batched tile", (long long)P.N);
+    if (P.kind == PBIT_EA3D && !j.bits)
+        return fail(PBIT_E_NOMEM, "the site records of this cube did not fit the budget when it was loaded");
     if (P.kind == PBIT_GRAPH && j.width > kGraphMaxDegree + 2)
         return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
     if (j.bits) {

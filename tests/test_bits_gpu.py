@@ -131,3 +131,37 @@ def test_one_update_group(ctx, width_ctx, forced):
     ref = oracle.anneal(_graph(inst), beta, 4, 6)
     assert np.array_equal(out.spins[:4], ref.spins) and np.array_equal(out.energies[:4], ref.energies)
     pbit.pbit_unload_problem(c, prob)
+
+
+@pytest.mark.parametrize("kind", ["cube", "graph"])
+def test_problems_load_without_room_for_records(kind):
+    """Under every budget that a problem's other arrays and an anneal get by with, it loads and
+    anneals; a cube in a batch needs the records (E_NOMEM without)."""
+    inst = synth.ea_instance(16, seed=4) if kind == "cube" else _hub_graph(3000, [9] * 20, seed=4)
+    n = 4096 if kind == "cube" else 3000
+    beta = synth.beta_linear(0.1, 2.0, 6)
+    ref = oracle.anneal(_graph(inst), beta, 4, 1)
+    loaded, batched = [], []
+    # a cube's other arrays take 7 bytes a site and a graph's at least 16, before spins (16 + rows)
+    for budget in range(20_000, 400_000, 10_000):
+        with pbit.Context(0, hbm_budget_bytes=budget) as c:
+            try:
+                p = pbit.load_instance(c.ctx, inst)
+            except pbit.PbitError as err:
+                assert err.code == pbit.PBIT_E_NOMEM and not loaded
+                continue
+            held = pbit.pbit_bytes_in_use(c.ctx)
+            loaded.append(held)
+            if held + 34 * n < budget:
+                got = pbit.pbit_anneal(c.ctx, p, beta, 4, 1)
+                assert np.array_equal(got.spins, ref.spins) and np.array_equal(got.energies, ref.energies)
+            try:
+                out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=4, seed=1)])[0]
+                assert np.array_equal(out.spins, ref.spins)
+                batched.append(budget)
+            except pbit.PbitError as err:
+                assert err.code == pbit.PBIT_E_NOMEM
+    print(kind, "held without and with records", min(loaded), max(loaded), flush=True)
+    assert min(loaded) + 20 * n < max(loaded) and batched
+    if kind == "cube":
+        assert min(loaded) <= 7 * n + 1024
