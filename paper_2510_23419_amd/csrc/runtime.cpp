@@ -254,6 +254,8 @@ static int upload(pbit_ctx *ctx, Problem &p, const void *host, size_t bytes, voi
     return PBIT_OK;
 }
 
+constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
+
 // Records of the bit-held sweep (bits.h), where the problem can take it: the last of its
 // arrays, which it does without where they do not fit (per-instance anneals have other paths).
 static int upload_bits(pbit_ctx *ctx, Problem &p, const BitHost &b, const int8_t *dev_h)
@@ -557,15 +559,18 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
         meta[(size_t)4 * j + 3] = base[i];
     }
 
-    std::vector<int32_t> nbr(word.size());
-    std::vector<int8_t> Jn(word.size());
-    for (size_t e = 0; e < word.size(); ++e) {
-        nbr[e] = (int32_t)(word[e] >> 2);
-        Jn[e] = (int8_t)((word[e] & 1u) ? ((word[e] & 2u) ? -1 : 1) : 0);
-    }
+    // records of the bit-held sweep, for graphs whose spins the tiles' LDS takes
     BitHost bits;
-    const bool bits_ok = n <= kBitMaxPositions &&
-                         bit_build(n, start.data(), nbr.data(), Jn.data(), d->h, p.colour.data(), ncol, 0, bits);
+    bool bits_ok = graph_tile_lds(n, 4) <= kGraphSlabLds;
+    if (bits_ok) {
+        std::vector<int32_t> nbr(word.size());
+        std::vector<int8_t> Jn(word.size());
+        for (size_t e = 0; e < word.size(); ++e) {
+            nbr[e] = (int32_t)(word[e] >> 2);
+            Jn[e] = (int8_t)((word[e] & 1u) ? ((word[e] & 2u) ? -1 : 1) : 0);
+        }
+        bits_ok = bit_build(n, start.data(), nbr.data(), Jn.data(), d->h, p.colour.data(), ncol, 0, bits);
+    }
 
     void *dmeta = nullptr, *dadj = nullptr, *dbi = nullptr, *dbj = nullptr, *dbJ = nullptr, *dh = nullptr;
     int rc = upload(ctx, p, meta.data(), sizeof(int32_t) * meta.size(), &dmeta);
@@ -770,7 +775,6 @@ static int take(pbit_ctx *ctx, DevState &ds, Slot slot, size_t bytes, void **out
 constexpr int kSlabChunk = 1000;  // sweeps per launch of the LDS-resident cube, graph and biclique kernels
 constexpr int kClusterChunk = 20000;  // and of the biclique cluster kernel
 constexpr int kClusterSkip = 64;      // anneals that do not try it after it could not run
-constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
 
 // Sweeps of an anneal from one energy check to the next (at least 1).
 static int run_length(const pbit_anneal_desc *d)

@@ -165,3 +165,15 @@ def test_problems_load_without_room_for_records(kind):
     assert min(loaded) + 20 * n < max(loaded) and batched
     if kind == "cube":
         assert min(loaded) <= 7 * n + 1024
+
+
+@pytest.mark.parametrize("n,records", [(39_936, True), (39_937, False), (60_000, False)])
+def test_graphs_too_large_for_the_tiles_hold_no_records(ctx, n, records):
+    inst = synth.random_sparse_graph(n, 3, seed=1)
+    nb = len(inst["bond_J"])
+    before = pbit.pbit_bytes_in_use(ctx)
+    prob = pbit.load_instance(ctx, inst)
+    held = pbit.pbit_bytes_in_use(ctx) - before
+    # per vertex a class record of 16 bytes, per bond 8 + 9; the site records come to 34 a vertex
+    assert (held > 16 * n + 17 * nb + 30 * n) == records, (held, n, nb)
+    pbit.pbit_unload_problem(ctx, prob)
