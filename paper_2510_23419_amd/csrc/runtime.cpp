@@ -621,6 +621,7 @@ extern "C" int pbit_load_problem(pbit_ctx *ctx, const pbit_problem_desc *desc, u
             return rc;
         }
         const uint64_t h = ((uint64_t)ctx->serial << 40) | (++ctx->next_handle);
+        p.handle = h;
         ctx->problems.emplace(h, std::move(p));
         *problem_out = h;
         return PBIT_OK;
@@ -643,6 +644,7 @@ extern "C" int pbit_load_graph(pbit_ctx *ctx, const pbit_graph_desc *desc, uint6
             return rc;
         }
         const uint64_t h = ((uint64_t)ctx->serial << 40) | (++ctx->next_handle);
+        p.handle = h;
         auto it = ctx->problems.emplace(h, std::move(p)).first;
         it->second.graph.class_start = it->second.class_start.data();  // the vector moved
         *problem_out = h;
@@ -1510,11 +1512,12 @@ static uint64_t launch_key(const Problem &P, const pbit_anneal_desc *d, const De
         const unsigned char *b = (const unsigned char *)p;
         for (size_t k = 0; k < n; ++k) h = (h ^ b[k]) * 1099511628211ull;
     };
-    const void *ptrs[] = {&P, ds.spins, ds.MA, ds.MAb, ds.table, ds.E32, (void *)st};
+    const void *ptrs[] = {ds.spins, ds.MA, ds.MAb, ds.table, ds.E32, ds.graph_energy, (void *)st};
     mix(ptrs, sizeof ptrs);
     mix(d->beta, sizeof(double) * (size_t)d->n_sweeps);
-    const int64_t f[] = {d->n_sweeps, d->sweep_offset, d->n_replicas, d->replica_offset, (int64_t)d->seed,
-                         ds.Rp, ds.width, (int64_t)ds.variant, ds.slab, ds.bits, ds.mfma};
+    const int64_t f[] = {(int64_t)P.handle, d->n_sweeps, d->sweep_offset, d->n_replicas, d->replica_offset, (int64_t)d->seed,
+                         ds.Rp, ds.width, (int64_t)ds.variant, ds.slab, ds.bits, ds.mfma, ds.bit_tiles, ds.tile_rs,
+                         ds.bits_rt, ds.slab_rs};
     mix(f, sizeof f);
     return h;
 }

@@ -17,6 +17,7 @@
 namespace pbit {
 
 struct Problem {
+    uint64_t handle = 0;
     int kind = 0;
     int64_t N = 0;
     int amax = 0;  // largest possible |I|

@@ -76,3 +76,42 @@ def test_graph_replays_equal_the_eager_run(name, make, R, S, env):
     finally:
         eager.close()
         graph.close()
+
+
+def test_no_replay_with_other_buffers_or_another_problem():
+    """A graph is not replayed once the tiles' energy buffer was replaced (a larger biclique grew it),
+    nor for a problem loaded where an unloaded one was."""
+    import torch
+
+    small = synth.random_sparse_graph(700, 3, seed=4)  # byte tiles, whose launches write that buffer
+    R, beta = 512, synth.beta_linear(0.1, 3.0, 50)
+    graph, eager = _context(PBIT_GRAPH="1"), _context(PBIT_GRAPH="0")
+    try:
+        def run(c, prob, n):
+            s = torch.full((R, n), 3, dtype=torch.int8, device="cuda:0")
+            pbit.pbit_anneal_dev(c.ctx, prob, beta, R, 11, s)
+            return s.cpu().numpy()
+
+        pg, pe = pbit.load_instance(graph.ctx, small), pbit.load_instance(eager.ctx, small)
+        want = run(eager, pe, 700)
+        _say("replay beside a larger buffer")
+        assert np.array_equal(run(graph, pg, 700), want)
+        assert np.array_equal(run(graph, pg, 700), want)
+        assert pbit.pbit_profile_graph(graph.ctx)[0] == 1
+        # 512 x 512 at 256 replicas: less spin memory than the graph's, a larger auxiliary buffer
+        bq = pbit.load_instance(graph.ctx, synth.biclique_instance(512, seed=1, nb=512))
+        pbit.pbit_anneal(graph.ctx, bq, np.full(4, 2.0), 256, 1)
+        assert np.array_equal(run(graph, pg, 700), want)
+        assert pbit.pbit_profile_graph(graph.ctx)[0] == 2
+        pbit.pbit_unload_problem(graph.ctx, pg)
+        _say("replay for another problem")
+        for seed in (5, 6, 7):
+            other = dict(small, bond_J=-small["bond_J"], h=synth.random_spins(1, 700, seed=seed)[0])
+            pg, pe = pbit.load_instance(graph.ctx, other), pbit.load_instance(eager.ctx, other)
+            assert np.array_equal(run(graph, pg, 700), run(eager, pe, 700)), seed
+            pbit.pbit_unload_problem(graph.ctx, pg)
+            pbit.pbit_unload_problem(eager.ctx, pe)
+        assert pbit.pbit_profile_graph(graph.ctx)[0] == 5
+    finally:
+        graph.close()
+        eager.close()
