@@ -54,6 +54,7 @@ struct WorkItem {
 };
 
 constexpr int kGraphTileThreads = 512;
+constexpr int64_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
 constexpr int kBqTileThreads = 512;
 
 // Sweeps whose threshold rows a biclique tile holds at a time (16 KiB of them, or one).

@@ -254,8 +254,6 @@ static int upload(pbit_ctx *ctx, Problem &p, const void *host, size_t bytes, voi
     return PBIT_OK;
 }
 
-constexpr size_t kGraphSlabLds = 160 * 1024 - 4096;  // spin rows of a graph tile in LDS (beside its decision words)
-
 // Records of the bit-held sweep (bits.h), where the problem can take it: the last of its
 // arrays, which it does without where they do not fit (per-instance anneals have other paths).
 static int upload_bits(pbit_ctx *ctx, Problem &p, const BitHost &b, const int8_t *dev_h)
@@ -561,7 +559,7 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
 
     // records of the bit-held sweep, for graphs whose spins the tiles' LDS takes
     BitHost bits;
-    bool bits_ok = graph_tile_lds(n, 4) <= kGraphSlabLds;
+    bool bits_ok = (int64_t)n * 4 <= kGraphSlabLds;
     if (bits_ok) {
         std::vector<int32_t> nbr(word.size());
         std::vector<int8_t> Jn(word.size());
@@ -570,6 +568,27 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
             Jn[e] = (int8_t)((word[e] & 1u) ? ((word[e] & 2u) ? -1 : 1) : 0);
         }
         bits_ok = bit_build(n, start.data(), nbr.data(), Jn.data(), d->h, p.colour.data(), ncol, 0, bits);
+    }
+    if (bits_ok) {
+        GraphShape &g = p.shape;
+        g.groups = ncol;
+        for (int c = 0; c < ncol; ++c) g.wide_groups += bits.groups[(size_t)4 * c + 1] > 0;
+        g.sites = 2.0 * bits.n_pairs;
+        g.wide_sites = 2.0 * bits.n_wide;
+        g.n = n;
+        g.ends = 2.0 * nb;
+        for (int c = 0; c < ncol; ++c)
+            for (int j0 = p.class_start[c]; j0 < p.class_start[(size_t)c + 1]; j0 += kGraphTileThreads) {
+                const int j1 = std::min(j0 + kGraphTileThreads, p.class_start[(size_t)c + 1]);
+                int most = 0;
+                for (int j = j0; j < j1; ++j) {
+                    const int bonds = deg[cls[(size_t)j]];
+                    most = std::max(most, (bonds + 3) / 4);
+                    g.eights += j > p.class_start[c] && bonds == 8 && deg[cls[(size_t)j - 1]] == 8;
+                }
+                g.chunks += 1;
+                g.steps += most;
+            }
     }
 
     void *dmeta = nullptr, *dadj = nullptr, *dbi = nullptr, *dbj = nullptr, *dbJ = nullptr, *dh = nullptr;
@@ -1027,17 +1046,17 @@ int compute_units(const pbit_ctx *ctx)
     return cus;
 }
 
-// Microseconds per sweep of the bit-held tiles in the rounds the device needs for them:
+// Microseconds per sweep of the bit-held tiles in the rounds the device needs for them.  Cubes:
 // measured 0.58 ns per site and tile of 4 replicas (0.70 with fields or zero couplings), 1.6
 // and 2.7 times that with 8 and 16, at 12^3 to 36^3, and what an update group costs at least
-// (4^3 to 8^3 cubes; graphs of 64 to 500 sites).
+// (4^3 to 8^3).
 double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
 {
     const int tiles = (Rp + rs - 1) / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
+    if (P.kind == PBIT_GRAPH) return graph_bits_us(P.shape, P.bits, rs, Rp, cus);
     const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
-    const double group = P.bits.form == kBitGeneral && P.bits.n_groups != 2 ? 0.65 : 0.28;
     return ((tiles + slots - 1) / slots) *
-           (group * P.bits.n_groups + c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N);
+           (0.28 * P.bits.n_groups + c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N);
 }
 
 // Replicas per tile: the width whose rounds cost least (the narrowest among equals, which
@@ -1048,22 +1067,6 @@ int bit_pick_rs(const Problem &P, int Rp, int cus)
     for (int rs : {8, 16})
         if (bit_sweep_us(P, Rp, rs, cus) < bit_sweep_us(P, Rp, best, cus)) best = rs;
     return best;
-}
-
-// Whether a graph's sweeps are faster with its spins as bits than as bytes.  An update group
-// of the bit tiles costs 0.75 us at least (1.25 with a site of more than 7 terms), of the byte
-// tiles 0.35 us and 0.1 for every bond of a site, and 1 ns for every site: with about 4 bonds
-// a site the lines lie near 1000 sites (500: 3.1 against 2.6 us per sweep in bytes, 1500: 3.7
-// against 4.0), and with wide sites near 2500 (1500: 7.7 against 6.7, 2200: 8.9 against 8.8,
-// 4000: 8.5 against 12.1) or, with more replicas than one round of narrow tiles takes, 1000;
-// with 6 bonds bits win at any size (185: 4.3 against 4.9) or, with wide sites, from 400 on
-// (185: 7.6 against 6.4, 500: 7.5 against 7.3, 1500: 8.8 against 9.6).
-bool graph_bits_preferred(const Problem &P, int R)
-{
-    if (P.bits.n_groups == 2) return true;  // their records stay in registers
-    const bool sparse = 2 * (int64_t)P.graph.n_bonds <= 5 * P.N, wide = P.bits.n_wide > 0;
-    if (!sparse) return !wide || P.N >= 400;
-    return P.N >= (wide && R <= 1024 ? 2500 : 1000);
 }
 
 // Cubes too large for the tiles to win at any replica count: the faster of the two
@@ -1092,6 +1095,70 @@ static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds
     ds.chunk = bq_chunk(ds.variant);
     ctx->bq_last_variant = (int)ds.variant;
     return ds.bits ? bqb_pack(P.bq, ds.MA, ds.MB, ds.MAb, ds.MBb, ds.Rp, st) : hipSuccess;
+}
+
+static int byte_energies(pbit_ctx *ctx, DevState &ds)
+{
+    void *v = nullptr;
+    const int rc = take(ctx, ds, Slot::Aux, sizeof(int32_t) * (size_t)ds.Rp, &v);
+    ds.graph_energy = (int32_t *)v;
+    return rc;
+}
+
+static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, int s1, uint32_t sweep0,
+                         uint32_t rq0, Key key, hipStream_t st);
+
+// Between forms of a graph whose costs are close: the one that ran faster when the first anneal of
+// its shape and replica count timed one and nine sweeps of each (0.3 ms) on the spin buffer, whose
+// contents do not matter.  Anneals of less than 3 ms keep the estimate, and so does one in static
+// scratch before any was timed.
+static int tune_graph(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, int cus, hipStream_t st)
+{
+    const std::array<int, 4> shape{P.graph.n, P.graph.n_bonds, P.graph.n_colours, ds.Rp};
+    auto it = ctx->graph_tuned.find(shape);
+    if (it != ctx->graph_tuned.end()) {
+        ds.bit_tiles = it->second;
+        return PBIT_OK;
+    }
+    constexpr int m = 8;
+    const int bit_rs = bit_pick_rs(P, ds.Rp, cus);
+    if (ds.arena || d->n_sweeps <= m || d->n_sweeps * bit_sweep_us(P, ds.Rp, bit_rs, cus) < 3000.0) return PBIT_OK;
+    int rc = byte_energies(ctx, ds);
+    if (rc) return rc;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipError_t e = hipEventCreate(&e0);
+    if (e == hipSuccess) e = hipEventCreate(&e1);
+    const int prof = ctx->prof_every;
+    ctx->prof_every = 0;
+    double per_sweep[2] = {0.0, 0.0};
+    for (int bits = 0; bits < 2 && e == hipSuccess; ++bits) {
+        DevState t = ds;
+        t.slab = true;
+        t.bit_tiles = bits != 0;
+        if (bits) t.tile_rs = bit_rs;
+        auto pass = [&](int n) {
+            float best = 0.f;
+            for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // the first warms up
+                float ms = 0.f;
+                e = hipEventRecord(e0, st);
+                if (e == hipSuccess) e = sweeps(ctx, P, t, 0, n, 0u, 0u, Key{0u, 0u}, st);
+                if (e == hipSuccess) e = hipEventRecord(e1, st);
+                if (e == hipSuccess) e = hipEventSynchronize(e1);
+                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+                if (rep == 1 || (rep > 1 && ms < best)) best = ms;
+            }
+            return best;
+        };
+        double one = 0.0, more = 0.0;
+        time_runs(pass, [] { return true; }, m, &one, &more);
+        per_sweep[bits] = (more - one) / m;
+    }
+    ctx->prof_every = prof;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    if (e != hipSuccess) return device_fail(ctx, e, "graph kernel tuning");
+    ds.bit_tiles = ctx->graph_tuned[shape] = per_sweep[1] < per_sweep[0];
+    return PBIT_OK;
 }
 
 static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, hipStream_t st, DevState &ds,
@@ -1156,36 +1223,6 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
             if (e != hipSuccess) return device_fail(ctx, e, "spin bit buffer clear");
         }
     }
-    if (P.kind == PBIT_GRAPH && ctx->graph_slab && graph_tile_lds(P.N, 4) <= kGraphSlabLds) {
-        // the whole graph for a tile of replicas in LDS, runs of sweeps per launch
-        ds.bit_tiles = P.bits.n_pos > 0 && (ctx->graph_slab_rs != 0 || graph_bits_preferred(P, R));
-        ds.slab = true;
-        if (!ds.bit_tiles) {
-            // bytes: the narrowest tile (4, 8 or 16 replicas) that fits and leaves at most two
-            // workgroups per compute unit, else the widest that fits.  A workgroup's sweep
-            // costs about the same at any tile width up to two per CU, so narrow tiles
-            // spread small replica counts over more CUs, and past two per CU the wider
-            // tile wins.
-            const int cus = compute_units(ctx);
-            for (int rs : {4, 8, 16}) {
-                if (ds.Rp % rs != 0 || graph_tile_lds(P.N, rs) > kGraphSlabLds) continue;
-                if (ctx->graph_slab_rs && rs != ctx->graph_slab_rs) continue;
-                ds.tile_rs = rs;
-                if (ds.Rp / rs <= 2 * cus) break;
-            }
-            if (ds.tile_rs) {
-                rc = take(ctx, ds, Slot::Aux, sizeof(int32_t) * (size_t)ds.Rp, &v);
-                if (rc) return rc;
-                ds.graph_energy = (int32_t *)v;
-            }
-            ds.slab = ds.tile_rs != 0;
-        }
-    }
-    if (ds.bit_tiles) {
-        ds.slab = true;
-        ds.tile_rs = P.kind == PBIT_GRAPH && ctx->graph_slab_rs ? ctx->graph_slab_rs
-                                                                : bit_pick_rs(P, ds.Rp, compute_units(ctx));
-    }
     rc = take(ctx, ds, Slot::E32, sizeof(int32_t) * (size_t)ds.Rp, &v);
     if (rc) return rc;
     ds.E32 = (int32_t *)v;
@@ -1205,6 +1242,23 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
                                   hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return device_fail(ctx, e, "hipMemcpyAsync (table)");
 
+    if (P.kind == PBIT_GRAPH && ctx->graph_slab && P.N * 4 <= kGraphSlabLds) {
+        // the whole graph for a tile of replicas in LDS, runs of sweeps per launch
+        const int cus = compute_units(ctx);
+        ds.tile_rs = byte_pick_rs(P.N, ds.Rp, cus, ctx->graph_slab_rs);
+        if (P.bits.n_pos > 0) {
+            bool close = false;
+            ds.bit_tiles = ctx->graph_slab_rs != 0 || graph_bits_cheaper(P.shape, P.bits, R, cus, &close);
+            if (close && ctx->graph_slab_rs == 0 && S > 0 && (rc = tune_graph(ctx, P, d, ds, cus, st))) return rc;
+        }
+        if (!ds.bit_tiles && ds.tile_rs && (rc = byte_energies(ctx, ds))) return rc;
+        ds.slab = ds.bit_tiles || ds.tile_rs != 0;
+    }
+    if (ds.bit_tiles) {
+        ds.slab = true;
+        ds.tile_rs = P.kind == PBIT_GRAPH && ctx->graph_slab_rs ? ctx->graph_slab_rs
+                                                                : bit_pick_rs(P, ds.Rp, compute_units(ctx));
+    }
     if (P.kind == PBIT_BICLIQUE && d->n_sweeps > 0) {
         rc = tune_biclique(ctx, P, d, ds, st);
         if (rc) return rc;

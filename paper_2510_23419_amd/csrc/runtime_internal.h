@@ -12,6 +12,7 @@
 #include "bits.h"
 #include "bq.h"
 #include "bq_tune.h"
+#include "sweep_cost.h"
 #include "host.h"
 
 namespace pbit {
@@ -25,6 +26,7 @@ struct Problem {
     BqView bq{};
     GraphView graph{};
     BitView bits{};  // n_pos = 0: the problem cannot take the bit-held sweep
+    GraphShape shape;  // graphs with records: what their sweeps cost
     std::vector<int32_t> class_start;  // host copy behind graph.class_start
     std::vector<uint8_t> colour;       // colouring used (graph problems)
     std::vector<void *> allocs;
@@ -85,6 +87,7 @@ struct pbit_ctx {
     int ea_rows = 0;                // lattice rows per workgroup of the streaming stencil (PBIT_EA_ROWS; 0 = default)
     int ea_mfma = -1;  // matrix-core cube half-sweep: -1 timed against the stencil, 1 every cube, 0 none (PBIT_EA_MFMA)
     std::map<std::array<int, 4>, bool> ea_tuned;  // (Lx, Ly, Lz, replicas padded to 128) -> matrix cores faster
+    std::map<std::array<int, 4>, bool> graph_tuned;  // (spins, bonds, groups, replicas padded to 16) -> bits faster
     // pbit_anneal_dev's sweep launches as one HIP graph (PBIT_GRAPH=1), kept for replay
     bool use_graph = false;
     bool tile_tune = true;  // batched tile sizes timed per shape (PBIT_TILE_TUNE=0: the fixed rule)
@@ -122,7 +125,6 @@ int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_
 size_t anneal_dev_bytes(const pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d);
 int noalloc_setup(int device);
 int compute_units(const pbit_ctx *ctx);
-bool graph_bits_preferred(const Problem &P, int R);
 double bit_sweep_us(const Problem &P, int Rp, int rs, int cus);
 int bit_pick_rs(const Problem &P, int Rp, int cus);
 

@@ -230,7 +230,8 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
     j.mode = tile_mode(ctx);
     std::vector<int> cands;  // tile sizes the job can take (the autotuner times them)
     if (j.width > kMaxTableWidth) return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
-    j.bits = P.kind != PBIT_BICLIQUE && P.bits.n_pos > 0 && (P.kind != PBIT_GRAPH || graph_bits_preferred(P, j.R));
+    j.bits = P.kind != PBIT_BICLIQUE && P.bits.n_pos > 0 &&
+             (P.kind != PBIT_GRAPH || graph_bits_cheaper(P.shape, P.bits, j.R, compute_units(ctx), nullptr));
     if (P.kind != PBIT_BICLIQUE && P.N > kMaxTileSites)
         return fail(PBIT_E_UNSUPPORTED, "%s of %lld spins is too large for a batched tile",
                     P.kind == PBIT_GRAPH ? "graph" : "cube", (long long)P.N);

@@ -11,6 +11,7 @@
 #include "bits.h"
 #include "bq.h"
 #include "bq_tune.h"
+#include "sweep_cost.h"
 #include "meet.h"
 
 using namespace pbit;
@@ -210,6 +211,59 @@ static void timed_kernels()
     CHECK(!cheapest(std::vector<BqCost>(), true, 100, 100, chunk));
 }
 
+// Graphs as bits or as bytes: the faster form of shapes measured on the device (us per sweep in
+// bytes and in the best width of bits; random, regular, bipartite and dimerized graphs, and
+// graphs of some wide sites), and both estimates within a quarter of the measured times.
+static void graph_forms()
+{
+    struct Case {
+        GraphShape g;
+        int max_pairs, R;
+        double bytes, bits;
+    };
+    const Case cases[] = {
+        {{4, 0, 252, 0, 250, 744, 4, 4, 0}, 48, 16, 2.4, 2.9},  // reg3
+        {{5, 0, 502, 0, 500, 1992, 5, 5, 0}, 86, 1024, 3.2, 3.7},  // reg4
+        {{6, 0, 502, 0, 500, 2990, 6, 12, 0}, 69, 512, 4.6, 4.4},  // reg6
+        {{8, 8, 0, 506, 500, 4952, 8, 24, 0}, 54, 128, 8.1, 9.3},  // reg10
+        {{8, 8, 0, 1006, 1000, 9950, 8, 24, 0}, 105, 1024, 8.7, 9.9},  // reg10
+        {{8, 8, 0, 2006, 2000, 19964, 8, 24, 0}, 210, 4096, 16.3, 21.5},  // reg10
+        {{6, 6, 26, 476, 500, 3966, 6, 12, 443}, 63, 1024, 5.5, 7.5},  // reg8
+        {{7, 7, 40, 3962, 4000, 31954, 11, 22, 3909}, 485, 128, 18.6, 12.4},  // reg8
+        {{9, 9, 0, 4004, 4000, 51914, 14, 56, 0}, 357, 512, 21.4, 14.5},  // reg13
+        {{6, 5, 366, 136, 500, 2978, 6, 17, 3}, 75, 512, 5.8, 6.7},  // rnd6
+        {{7, 7, 2792, 1212, 4000, 23980, 13, 40, 45}, 602, 1024, 13.9, 11.4},  // rnd6
+        {{5, 5, 486, 16, 500, 1990, 5, 10, 0}, 95, 16, 4.2, 6.1},  // rnd4
+        {{5, 5, 3844, 158, 4000, 15984, 10, 25, 1}, 729, 4096, 17.4, 12.4},  // rnd4
+        {{4, 2, 250, 4, 250, 1004, 4, 8, 0}, 42, 128, 3.5, 4.0},  // hub0.01
+        {{6, 6, 3600, 402, 4000, 18786, 11, 43, 0}, 684, 1024, 13.5, 9.1},  // hub0.1
+        {{6, 6, 86, 36, 120, 694, 6, 21, 0}, 20, 4096, 8.4, 7.1},  // hub0.3
+        {{2, 2, 0, 500, 500, 6346, 2, 8, 0}, 125, 128, 3.3, 2.4},  // bip13
+        {{2, 2, 62, 1938, 2000, 15936, 4, 8, 1872}, 500, 1024, 8.1, 4.3},  // bip8
+        {{2, 0, 8000, 0, 8000, 23992, 16, 16, 0}, 2000, 4096, 21.0, 13.7},  // bip3
+        {{5, 2, 250, 4, 250, 1000, 5, 10, 0}, 49, 512, 4.0, 4.6},  // dimer
+        {{5, 5, 5478, 14, 5488, 21952, 14, 28, 0}, 1101, 4096, 21.3, 14.6},  // dimer
+        {{4, 0, 8002, 0, 8000, 23994, 17, 17, 0}, 1496, 16, 10.9, 7.2},  // reg3
+    };
+    for (const Case &c : cases) {
+        BitView v{};
+        v.form = kBitGeneral;
+        v.n = (int)c.g.n;
+        v.n_pos = (int)(c.g.sites + c.g.wide_sites);
+        v.n_groups = c.g.groups;
+        v.max_pairs = c.max_pairs;
+        bool close = false;
+        CHECK(graph_bits_cheaper(c.g, v, c.R, 256, &close) == (c.bits < c.bytes));
+        const int Rp = (c.R + 15) / 16 * 16, rs = byte_pick_rs(v.n, Rp, 256, 0);
+        double bits = 1e9;
+        for (int w : {4, 8, 16}) bits = std::min(bits, graph_bits_us(c.g, v, w, Rp, 256));
+        const double bytes = graph_bytes_us(c.g, rs, Rp, 256);
+        CHECK(bits < 1.25 * c.bits && c.bits < 1.25 * bits && bytes < 1.25 * c.bytes && c.bytes < 1.25 * bytes);
+    }
+    CHECK(byte_pick_rs(39936, 4096, 256, 0) == 4 && byte_pick_rs(39937, 4096, 256, 0) == 0);
+    CHECK(byte_pick_rs(5488, 4096, 256, 0) == 8 && byte_pick_rs(500, 16384, 256, 0) == 16 && byte_pick_rs(500, 64, 256, 16) == 16);
+}
+
 int main()
 {
     group_cursor();
@@ -218,6 +272,7 @@ int main()
     meetings();
     run_times();
     timed_kernels();
+    graph_forms();
     std::printf("rules ok\n");
     return 0;
 }

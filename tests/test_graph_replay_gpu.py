@@ -83,7 +83,11 @@ def test_no_replay_with_other_buffers_or_another_problem():
     nor for a problem loaded where an unloaded one was."""
     import torch
 
-    small = synth.random_sparse_graph(700, 3, seed=4)  # byte tiles, whose launches write that buffer
+    # a site of 30 bonds: byte tiles, whose launches write that buffer
+    hub = np.arange(1, 31, dtype=np.int32)
+    small = {"kind": "graph", "n": 700, "bond_i": np.concatenate([0 * hub, np.arange(40, 699, dtype=np.int32)]),
+             "bond_j": np.concatenate([hub, np.arange(41, 700, dtype=np.int32)]),
+             "bond_J": synth.random_spins(1, 689, seed=4)[0], "h": None}
     R, beta = 512, synth.beta_linear(0.1, 3.0, 50)
     graph, eager = _context(PBIT_GRAPH="1"), _context(PBIT_GRAPH="0")
     try:
