@@ -198,9 +198,10 @@ int pbit_anneal_dev(pbit_ctx *ctx, uint64_t problem, const pbit_anneal_desc *des
  * device array of PBIT_NOALLOC_SCRATCH_BYTES instead of the context's
  * allocations.  The call itself allocates nothing on the device and creates no
  * events; the biclique kernel is the one already timed for the shape on this
- * context, else the bit or DMA tile without timing, and a cube that both
- * one-launch-per-half-sweep kernels can take runs the matrix-core half-sweep for
- * at most 1024 replicas, else the streaming stencil.  Requests whose buffers
+ * context, else the LDS-resident, bit, DMA or 64 x 64 kernel without timing; a cube
+ * of more than 8192 sites runs the matrix-core half-sweep for at most 1024 replicas
+ * where it can take it, else, by their estimated costs, the sweep in LDS or the
+ * streaming stencil.  Requests whose buffers
  * exceed the array return E_UNSUPPORTED before any work is enqueued (the bytes
  * needed are about N x R for the cube and graphs, (na + nb) x R x 9/8 for the
  * biclique, plus 4 S x (max |I| + 1) for the table).  The array lives on every
@@ -333,12 +334,13 @@ int pbit_profile_graph(pbit_ctx *ctx, int64_t *captures, int64_t *launches);
  * replicas as int8 MFMAs over blocks of neighbour sites, one launch per half-sweep,
  * possible for cubes whose colour classes split into tiles of 32 sites with at most
  * 8 neighbour blocks each (every cube with Lx = 32, for one).  By default a cube of
- * more than 8192 and at most 61 950 sites is held in LDS where that is faster by the
- * measured costs of both forms; otherwise a cube of at most 2^21 sites that allows
- * path 3 takes whichever of the stencil and path 3 ran faster when the first anneal
- * of that shape and replica count (rounded up to 128) on this context timed four
- * half-sweeps of each; without allocation (pbit_anneal_dev_noalloc) there is no
- * timing and path 3 is taken for at most 1024 replicas.  When the context is
+ * more than 8192 and at most 61 950 sites is held in LDS where its estimated cost is
+ * far below that of the launch-per-half-sweep kernels, never where it is far above;
+ * in between, and for cubes of at most 2^21 sites that allow path 3, the first
+ * anneal of that shape and replica count on this context times the forms it can take
+ * and keeps the fastest (cubes that do not allow path 3 keep the estimate in anneals
+ * of less than 3 ms); without allocation (pbit_anneal_dev_noalloc) there is no timing:
+ * path 3 for at most 1024 replicas where possible, else by the estimate.  When the context is
  * created, PBIT_EA_STREAM=1 selects the stencil for every cube, PBIT_EA_MFMA=1 path 3
  * wherever it can run, PBIT_EA_MFMA=0 never path 3 and a negative value keeps the
  * default.  All give the same spins.

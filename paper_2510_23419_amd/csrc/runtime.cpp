@@ -997,48 +997,6 @@ static int tune_biclique(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc
     return PBIT_OK;
 }
 
-// Cube path for a shape that both one-launch-per-half-sweep kernels can take: the
-// streaming stencil or the matrix-core half-sweep, whichever ran faster when timed
-// here (four half-sweeps each, after a warm-up pass) on `spins`, zeroed first (zero
-// bytes are valid +1 spins for both kernels) and at least N x round_up(R, 128)
-// bytes.  The choice is cached per shape and replica count.
-static int tune_cube(pbit_ctx *ctx, const Problem &P, int R, int8_t *spins, hipStream_t st, bool *mfma)
-{
-    const int Rs = round_up(R, kEaRPad), Rm = round_up(R, kEaMfmaRPad);
-    const std::array<int, 4> shape{P.ea.Lx, P.ea.Ly, P.ea.Lz, Rm};
-    auto it = ctx->ea_tuned.find(shape);
-    if (it != ctx->ea_tuned.end()) {
-        *mfma = it->second;
-        return PBIT_OK;
-    }
-    hipError_t e = fill_i32((int32_t *)spins, (int64_t)((size_t)P.N * Rm / 4), 0, st);
-    if (e != hipSuccess) return device_fail(ctx, e, "spin buffer clear (tuning)");
-    hipEvent_t e0, e1;
-    e = hipEventCreate(&e0);
-    if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e != hipSuccess) return device_fail(ctx, e, "hipEventCreate (tuning)");
-    EaRow row;
-    for (uint64_t &v : row.s) v = (uint64_t)1 << 31;
-    const Key key{0u, 0u};
-    float ms[2] = {0.f, 0.f};
-    for (int m = 0; m < 2 && e == hipSuccess; ++m)
-        for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {  // the first pass warms up
-            e = hipEventRecord(e0, st);
-            for (int k = 0; k < 4 && e == hipSuccess; ++k)
-                e = m ? eam_halfsweep(P.ea, (uint8_t *)spins, Rm, k & 1, row, 0u, 0u, key, st)
-                      : ea_halfsweep(P.ea, spins, Rs, k & 1, row, 0u, 0u, key, st, ctx->ea_rows);
-            if (e == hipSuccess) e = hipEventRecord(e1, st);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms[m], e0, e1);
-        }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    if (e != hipSuccess) return device_fail(ctx, e, "cube kernel tuning");
-    *mfma = ms[1] < ms[0];
-    ctx->ea_tuned[shape] = *mfma;
-    return PBIT_OK;
-}
-
 int compute_units(const pbit_ctx *ctx)
 {
     int cus = 0;
@@ -1046,17 +1004,10 @@ int compute_units(const pbit_ctx *ctx)
     return cus;
 }
 
-// Microseconds per sweep of the bit-held tiles in the rounds the device needs for them.  Cubes:
-// measured 0.58 ns per site and tile of 4 replicas (0.70 with fields or zero couplings), 1.6
-// and 2.7 times that with 8 and 16, at 12^3 to 36^3, and what an update group costs at least
-// (4^3 to 8^3).
+// Microseconds per sweep of the bit-held tiles in the rounds the device needs for them.
 double bit_sweep_us(const Problem &P, int Rp, int rs, int cus)
 {
-    const int tiles = (Rp + rs - 1) / rs, slots = cus * bit_tiles_per_cu(P.bits, rs);
-    if (P.kind == PBIT_GRAPH) return graph_bits_us(P.shape, P.bits, rs, Rp, cus);
-    const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
-    return ((tiles + slots - 1) / slots) *
-           (0.28 * P.bits.n_groups + c * (P.bits.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)P.N);
+    return P.kind == PBIT_GRAPH ? graph_bits_us(P.shape, P.bits, rs, Rp, cus) : cube_bits_us(P.bits, rs, Rp, cus);
 }
 
 // Replicas per tile: the width whose rounds cost least (the narrowest among equals, which
@@ -1067,17 +1018,6 @@ int bit_pick_rs(const Problem &P, int Rp, int cus)
     for (int rs : {8, 16})
         if (bit_sweep_us(P, Rp, rs, cus) < bit_sweep_us(P, Rp, best, cus)) best = rs;
     return best;
-}
-
-// Cubes too large for the tiles to win at any replica count: the faster of the two
-// one-launch-per-half-sweep kernels takes about 8 us + 0.5 ps per spin and sweep at least
-// (measured 24^3 to 36^3, 64 to 4096 replicas: 8.0 to 101 us), against which the tiles'
-// time is set.  At 32^3 the line lies between 512 replicas (17.2 against 18.8 us per
-// sweep in tiles) and 1024 (27.8 against 19.2).
-static bool bits_preferred(const Problem &P, int R, int cus)
-{
-    const int Rp = round_up(R, kEaRPad);
-    return bit_sweep_us(P, Rp, bit_pick_rs(P, Rp, cus), cus) < 8.0 + 0.5e-6 * (double)P.N * R;
 }
 
 // The kernel that runs `n_sweeps` sweeps of a biclique when the cluster kernel's workgroups
@@ -1097,6 +1037,45 @@ static hipError_t cluster_fallback(pbit_ctx *ctx, const Problem &P, DevState &ds
     return ds.bits ? bqb_pack(P.bq, ds.MA, ds.MB, ds.MAb, ds.MBb, ds.Rp, st) : hipSuccess;
 }
 
+// (replicas padded to 128, or to 16 up to there: the stencil takes 9 us a sweep at 64 replicas of
+// 28^3 and 19 at 128; the records' form: with fields the tiles take 14.7 us there, without 12.4)
+static std::array<int, 5> cube_key(const Problem &P, int R)
+{
+    return {P.ea.Lx, P.ea.Ly, P.ea.Lz, round_up(R, R > kEaMfmaRPad ? kEaMfmaRPad : kEaRPad),
+            P.bits.n_pos ? P.bits.form : -1};
+}
+
+static bool cube_matrix_cores(const pbit_ctx *ctx, const Problem &P) { return P.ea.mfma_tiles && ctx->ea_mfma != 0; }
+
+static void take_cube_path(DevState &ds, int path)
+{
+    ds.bit_tiles = path == 2;
+    ds.mfma = path == 3;
+}
+
+// The path of a cube too large to stay in LDS always, by an earlier timing or by cost; true where
+// tune_cube is to time it.
+static bool choose_cube(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds)
+{
+    const int R = ds.R, cus = compute_units(ctx), Rp = round_up(R, kEaRPad);
+    const bool matrix = cube_matrix_cores(ctx, P);
+    const double bits = P.bits.n_pos ? bit_sweep_us(P, Rp, bit_pick_rs(P, Rp, cus), cus) : 1e30;
+    if (ds.arena) {
+        // no timing without allocation: the measured default, not cached
+        ds.mfma = matrix && R <= 1024;
+        ds.bit_tiles = !ds.mfma && bits < cube_launch_us(P.N, R);
+        return false;
+    }
+    auto it = ctx->ea_tuned.find(cube_key(P, R));
+    if (it != ctx->ea_tuned.end()) {
+        take_cube_path(ds, it->second);
+        return false;
+    }
+    const CubeForm form = cube_form(bits, P.N, R, d->n_sweeps, matrix);
+    ds.bit_tiles = form == CubeForm::Tiles;
+    return d->n_sweeps > 0 && (form == CubeForm::Time || (form == CubeForm::Launches && matrix));
+}
+
 static int byte_energies(pbit_ctx *ctx, DevState &ds)
 {
     void *v = nullptr;
@@ -1107,6 +1086,80 @@ static int byte_energies(pbit_ctx *ctx, DevState &ds)
 
 static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, int s1, uint32_t sweep0,
                          uint32_t rq0, Key key, hipStream_t st);
+
+// Times the paths a cube can take on its spin buffer, zeroed first (zero bytes are valid +1 spins
+// for all) and at least N x round_up(R, 128) bytes: one and nine sweeps of each (the difference leaves
+// out what the first launch after an event costs, which the launch kernels pay once an anneal and
+// not every other sweep), the tiles in LDS where their cost is not far above the others'.  The fastest
+// is cached per shape and replica count.
+static int tune_cube(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, DevState &ds, hipStream_t st)
+{
+    const int R = ds.R, cus = compute_units(ctx), Rs = round_up(R, kEaRPad), Rm = round_up(R, kEaMfmaRPad);
+    int8_t *spins = ds.spins;
+    hipError_t e = fill_i32((int32_t *)spins, (int64_t)((size_t)P.N * Rm / 4), 0, st);
+    if (e != hipSuccess) return device_fail(ctx, e, "spin buffer clear (tuning)");
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    e = hipEventCreate(&e0);
+    if (e == hipSuccess) e = hipEventCreate(&e1);
+    const Key key{0u, 0u};
+    const int prof = ctx->prof_every;
+    ctx->prof_every = 0;
+    auto pass = [&](auto launch) {
+        float best = 0.f;
+        for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // the first warms up
+            float ms = 0.f;
+            e = hipEventRecord(e0, st);
+            if (e == hipSuccess) e = launch();
+            if (e == hipSuccess) e = hipEventRecord(e1, st);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+            if (rep == 1 || (rep > 1 && ms < best)) best = ms;
+        }
+        return (double)best;
+    };
+    EaRow row;
+    for (uint64_t &v : row.s) v = (uint64_t)1 << 31;
+    double best = 0.0;
+    int path = 0;
+    auto offer = [&](int p, double per_sweep) {
+        if (path && per_sweep >= best) return;
+        path = p;
+        best = per_sweep;
+    };
+    auto time_sweeps = [&](int p, int m, auto run) {
+        double one = 0.0, more = 0.0;
+        time_runs([&](int n) { return pass([&] { return run(n); }); }, [] { return true; }, m, &one, &more);
+        offer(p, m > 0 ? (more - one) / m : one);
+    };
+    auto half_sweeps = [&](int n, auto half) {
+        hipError_t x = hipSuccess;
+        for (int k = 0; k < 2 * n && x == hipSuccess; ++k) x = half(k & 1);
+        return x;
+    };
+    time_sweeps(1, 8, [&](int n) {
+        return half_sweeps(n, [&](int c) { return ea_halfsweep(P.ea, spins, Rs, c, row, 0u, 0u, key, st, ctx->ea_rows); });
+    });
+    if (cube_matrix_cores(ctx, P))
+        time_sweeps(3, 8, [&](int n) {
+            return half_sweeps(n, [&](int c) { return eam_halfsweep(P.ea, (uint8_t *)spins, Rm, c, row, 0u, 0u, key, st); });
+        });
+    if (P.bits.n_pos) {
+        DevState t = ds;
+        t.slab = t.bit_tiles = true;
+        t.Rp = Rs;
+        t.tile_rs = bit_pick_rs(P, Rs, cus);
+        if (cube_form(bit_sweep_us(P, Rs, t.tile_rs, cus), P.N, R, d->n_sweeps, true) == CubeForm::Time)
+            time_sweeps(2, std::min(8, d->n_sweeps - 1), [&](int n) { return sweeps(ctx, P, t, 0, n, 0u, 0u, key, st); });
+    }
+    ctx->prof_every = prof;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    if (e != hipSuccess) return device_fail(ctx, e, "cube kernel tuning");
+    ctx->ea_tuned[cube_key(P, R)] = path;
+    take_cube_path(ds, path);
+    ds.Rp = round_up(R, ds.mfma ? kEaMfmaRPad : kEaRPad);
+    return PBIT_OK;
+}
 
 // Between forms of a graph whose costs are close: the one that ran faster when the first anneal of
 // its shape and replica count timed one and nine sweeps of each (0.3 ms) on the spin buffer, whose
@@ -1168,37 +1221,30 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     ds.R = R;
     void *v = nullptr;
     int rc;
+    bool tune = false;
     if (P.kind == PBIT_EA3D || P.kind == PBIT_GRAPH) {
         // the stencil and the gather address the spin matrix with 32-bit byte offsets
         if ((uint64_t)P.N * (((uint64_t)R + kEaRPad - 1) / kEaRPad * kEaRPad) >= ((uint64_t)1 << 32))
             return fail(PBIT_E_UNSUPPORTED, "%lld spins x %d replicas exceed 4 GiB of int8 spins",
                         (long long)P.N, R);
         // cube paths: PBIT_EA_STREAM=1 takes the stencil; PBIT_EA_MFMA=1 the matrix cores
-        // wherever built; by default cubes of at most kEaSlabMaxSites sites, and larger ones
-        // with enough replicas, stay in LDS as bits, and for the others the stencil and the
-        // matrix cores (where built) are timed against each other (PBIT_EA_MFMA=0: the stencil)
-        const bool cube = P.kind == PBIT_EA3D, tiles = cube && P.ea.mfma_tiles;
-        bool tune = false;
+        // wherever built; by default cubes of at most kEaSlabMaxSites sites stay in LDS as bits,
+        // and larger ones take what costs least of that, the stencil and the matrix cores (where
+        // built, not with PBIT_EA_MFMA=0)
+        const bool cube = P.kind == PBIT_EA3D;
         if (cube && !ctx->ea_stream_forced) {
-            ds.mfma = tiles && ctx->ea_mfma == 1;
-            // (without allocation, large cubes keep the matrix cores at up to 1024 replicas)
-            ds.bit_tiles = !ds.mfma && P.bits.n_pos &&
-                           (P.N <= kEaSlabMaxSites || (!(ds.arena && tiles && R <= 1024) &&
-                                                       bits_preferred(P, R, compute_units(ctx))));
-            tune = !ds.mfma && !ds.bit_tiles && tiles && ctx->ea_mfma != 0 && d->n_sweeps > 0;
+            ds.mfma = P.ea.mfma_tiles && ctx->ea_mfma == 1;
+            if (!ds.mfma && P.bits.n_pos && P.N <= kEaSlabMaxSites)
+                ds.bit_tiles = true;
+            else if (!ds.mfma)
+                tune = choose_cube(ctx, P, d, ds);
         }
         // the tuner times both layouts in one buffer: spins for replicas padded to 128
         ds.Rp = round_up(R, ds.mfma || tune ? kEaMfmaRPad : kEaRPad);
         rc = take(ctx, ds, Slot::Spins, (size_t)P.N * ds.Rp, &v);
         if (rc) return rc;
         ds.spins = (int8_t *)v;
-        if (tune) {
-            if (ds.arena)
-                ds.mfma = R <= 1024;  // no timing without allocation: the measured default, not cached
-            else if ((rc = tune_cube(ctx, P, R, ds.spins, st, &ds.mfma)))
-                return rc;
-            ds.Rp = round_up(R, ds.mfma ? kEaMfmaRPad : kEaRPad);
-        }
+        ds.Rp = round_up(R, ds.mfma ? kEaMfmaRPad : kEaRPad);
     } else {
         // int8 spins, plus a bit copy where the sides are padded to 128 and the replicas to 256
         // (the tuner then times the bit kernel, whose tiles hold 256 replicas: a forced bit
@@ -1223,10 +1269,6 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
             if (e != hipSuccess) return device_fail(ctx, e, "spin bit buffer clear");
         }
     }
-    rc = take(ctx, ds, Slot::E32, sizeof(int32_t) * (size_t)ds.Rp, &v);
-    if (rc) return rc;
-    ds.E32 = (int32_t *)v;
-
     // threshold table for this call's sweeps (built on the host in FP64)
     const int S = d->n_sweeps;
     ds.width = S > 0 ? table_width(d->beta, S, P.amax) : 1;
@@ -1241,6 +1283,11 @@ static int prepare(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, h
     hipError_t e = hipMemcpyAsync(ds.table, ctx->host_table.data(), sizeof(uint32_t) * ctx->host_table.size(),
                                   hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return device_fail(ctx, e, "hipMemcpyAsync (table)");
+
+    if (tune && (rc = tune_cube(ctx, P, d, ds, st))) return rc;
+    rc = take(ctx, ds, Slot::E32, sizeof(int32_t) * (size_t)ds.Rp, &v);
+    if (rc) return rc;
+    ds.E32 = (int32_t *)v;
 
     if (P.kind == PBIT_GRAPH && ctx->graph_slab && P.N * 4 <= kGraphSlabLds) {
         // the whole graph for a tile of replicas in LDS, runs of sweeps per launch

@@ -86,7 +86,7 @@ struct pbit_ctx {
     bool ea_stream_forced = false;  // cubes always take the streaming stencil (PBIT_EA_STREAM=1)
     int ea_rows = 0;                // lattice rows per workgroup of the streaming stencil (PBIT_EA_ROWS; 0 = default)
     int ea_mfma = -1;  // matrix-core cube half-sweep: -1 timed against the stencil, 1 every cube, 0 none (PBIT_EA_MFMA)
-    std::map<std::array<int, 4>, bool> ea_tuned;  // (Lx, Ly, Lz, replicas padded to 128) -> matrix cores faster
+    std::map<std::array<int, 5>, int> ea_tuned;  // (Lx, Ly, Lz, replicas, record form) -> 1 stencil, 2 tiles in LDS, 3 matrix cores
     std::map<std::array<int, 4>, bool> graph_tuned;  // (spins, bonds, groups, replicas padded to 16) -> bits faster
     // pbit_anneal_dev's sweep launches as one HIP graph (PBIT_GRAPH=1), kept for replay
     bool use_graph = false;

@@ -1,7 +1,8 @@
-// sweep_cost.h — what a general graph's sweep costs in the tiles that hold its spins as bits
-// (bit_tile.h) and as bytes (graph_tile_item), in microseconds on MI355X (host only).
+// sweep_cost.h — what a sweep costs in the forms a cube or general graph can take, in
+// microseconds on MI355X (host only).
 //
-// Both forms were timed over 835 shapes: 60 to 8000 spins, 3 to 15 terms a site (regular, random,
+// Graphs, in tiles that hold their spins as bits (bit_tile.h) or as bytes (graph_tile_item): both
+// were timed over 835 shapes: 60 to 8000 spins, 3 to 15 terms a site (regular, random,
 // bipartite, dimerized, and with 1 to 30 % of sites of 8 to 15 terms among sites of four), 2 to 9
 // update groups, 16 to 4096 replicas, bits in each tile width.  The formulas below, fitted to
 // that, are within 6 % (one standard deviation) of either form.  A sweep is a serial chain per
@@ -83,6 +84,36 @@ inline bool graph_bits_cheaper(const GraphShape &g, const BitView &v, int R, int
     const double bytes = rs ? graph_bytes_us(g, rs, Rp, cus) : 2.0 * bits;
     if (close) *close = bits < 1.15 * bytes && bytes < 1.15 * bits;
     return bits < bytes;
+}
+
+// A cube's sweep in tiles of rs replicas: measured 0.58 ns per site and tile of 4 replicas (0.70
+// with fields or zero couplings), 1.6 and 2.7 times that with 8 and 16, at 12^3 to 36^3, and what an
+// update group costs at least (4^3 to 8^3).
+inline double cube_bits_us(const BitView &v, int rs, int Rp, int cus)
+{
+    const int tiles = (Rp + rs - 1) / rs, slots = cus * bit_tiles_per_cu(v, rs);
+    const double c = rs == 4 ? 1.0 : rs == 8 ? 1.62 : 2.7;
+    return ((tiles + slots - 1) / slots) *
+           (0.28 * v.n_groups + c * (v.form == kBitGeneral ? 0.70e-3 : 0.58e-3) * (double)v.n);
+}
+
+// How a cube of more sites than always stay in LDS runs, given the cost of its best tiles: in
+// tiles, by the launch-per-half-sweep kernels, or as a timing of all of them says.  Those take 8 us +
+// 0.5 ps per spin and sweep at least and up to 2.2 times that (8.4 to 132 us from 8320 to 61 952
+// sites and 16 to 4096 replicas: the stencil's launches of 128 replicas and more, and shapes without
+// matrix-core tiles, are far above the line), so the estimate decides only where the tiles need
+// less than 0.6 of that least or more than 2.5 times it.  Without matrix-core tiles, where no anneal
+// was timed before, it also decides for anneals of less than 3 ms.
+enum class CubeForm { Tiles, Launches, Time };
+inline double cube_launch_us(int64_t n, int R) { return 8.0 + 0.5e-6 * (double)n * R; }
+inline CubeForm cube_form(double tiles_us, int64_t n, int R, int sweeps, bool matrix_tiles)
+{
+    const double launches = cube_launch_us(n, R);
+    if (tiles_us < 0.6 * launches) return CubeForm::Tiles;
+    if (tiles_us > 2.5 * launches) return CubeForm::Launches;
+    if (!matrix_tiles && sweeps * std::min(tiles_us, launches) < 3000.0)
+        return tiles_us < launches ? CubeForm::Tiles : CubeForm::Launches;
+    return CubeForm::Time;
 }
 
 }  // namespace pbit

@@ -264,6 +264,60 @@ static void graph_forms()
     CHECK(byte_pick_rs(5488, 4096, 256, 0) == 8 && byte_pick_rs(500, 16384, 256, 0) == 16 && byte_pick_rs(500, 64, 256, 16) == 16);
 }
 
+// Cubes of more than 8192 sites, in tiles or by a launch per half-sweep (us per sweep of the faster of
+// the two launch kernels, and of the best tiles, measured): what the estimate decides is the faster
+// form, or within 5 % of it, and the rest is timed.
+static void cube_forms()
+{
+    struct Case {
+        int n;
+        bool fields;
+        int R;
+        double launches, tiles;
+    };
+    const Case cases[] = {
+        {8712, false, 16, 9.3, 5.7},  // 22x22x18
+        {8712, true, 128, 12.8, 6.2},  // 22x22x18
+        {10240, true, 64, 8.8, 6.7},  // 64x16x10
+        {11520, true, 16, 9.2, 8.3},  // 32x20x18
+        {13824, false, 16, 10.0, 7.8},  // 24x24x24
+        {13824, true, 128, 16.2, 9.4},  // 24x24x24
+        {17576, false, 64, 9.2, 11.2},  // 26x26x26
+        {17576, false, 256, 19.0, 11.2},  // 26x26x26
+        {17576, true, 512, 17.3, 12.0},  // 26x26x26
+        {18432, false, 256, 12.3, 10.2},  // 32x24x24
+        {21952, true, 16, 10.1, 14.7},  // 28x28x28
+        {21952, true, 512, 17.2, 14.7},  // 28x28x28
+        {27000, false, 64, 9.5, 16.6},  // 30x30x30
+        {27000, false, 256, 22.5, 16.7},  // 30x30x30
+        {32768, false, 512, 16.2, 18.6},  // 32x32x32
+        {32768, false, 1024, 26.3, 18.5},  // 32x32x32
+        {32768, false, 4096, 69.6, 49.5},  // 32x32x32
+        {46080, false, 16, 9.2, 25.8},  // 48x32x30
+        {46080, true, 128, 21.4, 30.5},  // 48x32x30
+        {46080, true, 1024, 34.7, 30.6},  // 48x32x30
+        {46080, false, 4096, 95.7, 70.0},  // 48x32x30
+        {38880, false, 64, 11.5, 21.6},  // 36x36x30
+        {38880, false, 512, 29.6, 21.8},  // 36x36x30
+    };
+    int timed = 0;
+    for (const Case &c : cases) {
+        BitView v{};
+        v.form = c.fields ? kBitGeneral : kBitCube4;
+        v.n = v.n_pos = c.n;
+        v.n_groups = 2;
+        v.max_pairs = c.n / 4;
+        double tiles = 1e9;
+        for (int rs : {4, 8, 16}) tiles = std::min(tiles, cube_bits_us(v, rs, (c.R + 15) / 16 * 16, 256));
+        const CubeForm f = cube_form(tiles, c.n, c.R, 1000, true);
+        CHECK(f != CubeForm::Tiles || c.tiles < 1.05 * c.launches);
+        CHECK(f != CubeForm::Launches || c.launches < 1.05 * c.tiles);
+        timed += f == CubeForm::Time;
+        CHECK(cube_form(tiles, c.n, c.R, 2, false) != CubeForm::Time);
+    }
+    CHECK(timed >= 10);
+}
+
 int main()
 {
     group_cursor();
@@ -273,6 +327,7 @@ int main()
     run_times();
     timed_kernels();
     graph_forms();
+    cube_forms();
     std::printf("rules ok\n");
     return 0;
 }

@@ -177,3 +177,33 @@ def test_graphs_too_large_for_the_tiles_hold_no_records(ctx, n, records):
     # per vertex a class record of 16 bytes, per bond 8 + 9; the site records come to 34 a vertex
     assert (held > 16 * n + 17 * nb + 30 * n) == records, (held, n, nb)
     pbit.pbit_unload_problem(ctx, prob)
+
+
+@pytest.mark.parametrize("dims,R,S", [((22, 22, 18), 24, 600), ((26, 26, 26), 130, 300), ((24, 24, 24), 64, 40),
+                                      ((32, 32, 30), 20, 400), ((32, 32, 32), 512, 20)])
+def test_cubes_whose_path_is_timed(ctx, dims, R, S):
+    """Between the tiles and the launches by a timing; again from the cache, in part and at another
+    replica count."""
+    inst = synth.ea_instance(dims, seed=R)
+    beta = synth.beta_geometric(0.1, 5.0, S)
+    _sampled(ctx, inst, beta, R, 2)
+    path = pbit.pbit_profile_ea_path(ctx)
+    _sampled(ctx, inst, beta[:5], R, 3)
+    assert pbit.pbit_profile_ea_path(ctx) == path
+    _sampled(ctx, inst, beta[:20], R + 130, 4)
+
+
+def test_large_cubes_run_in_tiles(ctx):
+    """Runs of sweeps in LDS are one timed launch counted as its half-sweeps; of launches per half-sweep
+    a window of eight is timed."""
+    S = 40
+    for dims, R, tiles in [((24, 24, 24), 4096, True), ((32, 32, 32), 4096, True), ((36, 36, 48), 16, False)]:
+        prob = pbit.load_instance(ctx, synth.ea_instance(dims, seed=1))
+        pbit.pbit_anneal(ctx, prob, synth.beta_linear(0.1, 1.0, S), R, 1, want_spins=False)
+        pbit.pbit_profile_read(ctx, pbit.PBIT_EA3D, reset=True)
+        pbit.pbit_profile_enable(ctx, 1000)
+        pbit.pbit_anneal(ctx, prob, synth.beta_linear(0.1, 1.0, S), R, 1, want_spins=False)
+        pbit.pbit_profile_enable(ctx, 0)
+        launches = pbit.pbit_profile_read(ctx, pbit.PBIT_EA3D, reset=True)[1]
+        assert launches == (2 * S if tiles else 8), (dims, R, launches)
+        pbit.pbit_unload_problem(ctx, prob)
