@@ -238,9 +238,9 @@ typedef struct {
     pbit_result *result;      /* filled as by pbit_anneal (spin_trace is not supported) */
 } pbit_batch_job;
 
-/* Tile sizes of batched jobs.  Cube and graph tiles that hold their spins as bits take
- * 4, 8 or 16 replicas, by the cost of each width (and, in pbit_anneal_batch, so that the
- * longest tile and the work of the whole batch end together).  Where another job's shape
+/* Tile sizes of batched jobs.  Cubes and graphs that hold their spins as bits (every one
+ * whose spins have at most 15 nonzero couplings and fields each) take 4, 8 or 16 replicas
+ * by the cost of each width.  Where another job's shape
  * can take more than one tile size, the library times one tile of each (a couple of the job's sweeps on
  * scratch memory) when the shape is first seen and no round is in flight, and
  * keeps the size whose tiles cost the least device time per job; the choice is

@@ -569,27 +569,27 @@ static int load_graph(pbit_ctx *ctx, const pbit_graph_desc *d, Problem &p)
         }
         bits_ok = bit_build(n, start.data(), nbr.data(), Jn.data(), d->h, p.colour.data(), ncol, 0, bits);
     }
+    GraphShape &g = p.shape;
+    g.groups = ncol;
     if (bits_ok) {
-        GraphShape &g = p.shape;
-        g.groups = ncol;
         for (int c = 0; c < ncol; ++c) g.wide_groups += bits.groups[(size_t)4 * c + 1] > 0;
         g.sites = 2.0 * bits.n_pairs;
         g.wide_sites = 2.0 * bits.n_wide;
-        g.n = n;
-        g.ends = 2.0 * nb;
-        for (int c = 0; c < ncol; ++c)
-            for (int j0 = p.class_start[c]; j0 < p.class_start[(size_t)c + 1]; j0 += kGraphTileThreads) {
-                const int j1 = std::min(j0 + kGraphTileThreads, p.class_start[(size_t)c + 1]);
-                int most = 0;
-                for (int j = j0; j < j1; ++j) {
-                    const int bonds = deg[cls[(size_t)j]];
-                    most = std::max(most, (bonds + 3) / 4);
-                    g.eights += j > p.class_start[c] && bonds == 8 && deg[cls[(size_t)j - 1]] == 8;
-                }
-                g.chunks += 1;
-                g.steps += most;
-            }
     }
+    g.n = n;
+    g.ends = 2.0 * nb;
+    for (int c = 0; c < ncol; ++c)
+        for (int j0 = p.class_start[c]; j0 < p.class_start[(size_t)c + 1]; j0 += kGraphTileThreads) {
+            const int j1 = std::min(j0 + kGraphTileThreads, p.class_start[(size_t)c + 1]);
+            int most = 0;
+            for (int j = j0; j < j1; ++j) {
+                const int bonds = deg[cls[(size_t)j]];
+                most = std::max(most, (bonds + 3) / 4);
+                g.eights += j > p.class_start[c] && bonds == 8 && deg[cls[(size_t)j - 1]] == 8;
+            }
+            g.chunks += 1;
+            g.steps += most;
+        }
 
     void *dmeta = nullptr, *dadj = nullptr, *dbi = nullptr, *dbj = nullptr, *dbJ = nullptr, *dh = nullptr;
     int rc = upload(ctx, p, meta.data(), sizeof(int32_t) * meta.size(), &dmeta);

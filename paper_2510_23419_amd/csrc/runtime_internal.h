@@ -26,7 +26,7 @@ struct Problem {
     BqView bq{};
     GraphView graph{};
     BitView bits{};  // n_pos = 0: the problem cannot take the bit-held sweep
-    GraphShape shape;  // graphs with records: what their sweeps cost
+    GraphShape shape;  // graphs: what their sweeps cost
     std::vector<int32_t> class_start;  // host copy behind graph.class_start
     std::vector<uint8_t> colour;       // colouring used (graph problems)
     std::vector<void *> allocs;

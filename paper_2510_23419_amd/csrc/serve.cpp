@@ -230,8 +230,11 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
     j.mode = tile_mode(ctx);
     std::vector<int> cands;  // tile sizes the job can take (the autotuner times them)
     if (j.width > kMaxTableWidth) return fail(PBIT_E_UNSUPPORTED, "threshold rows of %d entries are too wide", j.width);
-    j.bits = P.kind != PBIT_BICLIQUE && P.bits.n_pos > 0 &&
-             (P.kind != PBIT_GRAPH || graph_bits_cheaper(P.shape, P.bits, j.R, compute_units(ctx), nullptr));
+    // cubes and graphs as bits wherever they have records: beside other tiles a group's latency
+    // costs a graph nothing, and its rows are read out without the host's transposition (1 to 40 jobs
+    // of 60 to 6000 spins, 64 to 512 replicas: 0.19 to 0.98 of the time in bytes, also where every
+    // site has more than seven terms)
+    j.bits = P.kind != PBIT_BICLIQUE && P.bits.n_pos > 0;
     if (P.kind != PBIT_BICLIQUE && P.N > kMaxTileSites)
         return fail(PBIT_E_UNSUPPORTED, "%s of %lld spins is too large for a batched tile",
                     P.kind == PBIT_GRAPH ? "graph" : "cube", (long long)P.N);
@@ -464,6 +467,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     std::vector<BqJobDev> bq[3];
     std::vector<WorkItem> items[kKinds];
     std::vector<double> cost[kKinds];  // microseconds
+    double graph_work[kKinds] = {}, other_work[kKinds] = {};  // compute-unit time of graph tiles; time of the others
     size_t lds[kKinds] = {};
     for (BJob *j : running) {
         if (j->finished) continue;
@@ -485,6 +489,11 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
                 cost[k].push_back((s1 - s0) * us);
             }
+            const int beside = 1024 / threads_of_kind(k);
+            if (j->kind == PBIT_GRAPH)
+                graph_work[k] += (double)j->tiles * (s1 - s0) * graph_bit_tile_us(j->P->shape, j->rs, beside) / beside;
+            else
+                other_work[k] += (double)j->tiles * (s1 - s0) * us;
             lds[k] = std::max(lds[k], bit_lds(v.n_pos));
         } else if (j->kind == PBIT_GRAPH) {
             const GraphView &v = j->P->graph;
@@ -499,6 +508,8 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
                 cost[k].push_back((s1 - s0) * us);
             }
+            const int beside = byte_tiles_per_cu(j->N, j->rs, kByteTilesPerCu);
+            graph_work[k] += (double)j->tiles * (s1 - s0) * graph_byte_tile_us(j->P->shape, j->rs, beside) / beside;
             lds[k] = std::max(lds[k], graph_tile_lds(j->N, j->rs));
         } else {
             const BqView &v = j->P->bq;
@@ -513,6 +524,7 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
                 items[k].push_back(WorkItem{idx, t, s0, s1, j->started ? 0 : 1, {0, 0, 0}});
                 cost[k].push_back((s1 - s0) * us);
             }
+            other_work[k] += (double)j->tiles * (s1 - s0) * us;
             lds[k] = std::max(lds[k], bq_tile_lds(j->rs, v.na_p, v.nb_p, j->width, j->mode));
         }
     }
@@ -569,14 +581,13 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     double work[kQueues] = {}, want[kQueues] = {}, all_work = 0.0, all_want = 0.0;
     for (int q = 0; q < kKinds; ++q) {
         const int k = kinds[q], i = std::min(q, kQueues - 1);
-        const int by_threads = bit_kind(k) ? 1024 / threads_of_kind(k) : k == kGraphKind ? 2 : 1;
+        const int by_threads = bit_kind(k) ? 1024 / threads_of_kind(k) : k == kGraphKind ? kByteTilesPerCu : 1;
         per_cu[k] = std::max(1, std::min(by_threads, (int)((160 * 1024) / (lds[k] + 2048))));
-        double sum = 0.0;
-        for (double c : cost[k]) sum += c;
-        // tiles of fewer threads lie beside 1024-thread ones and run at a third of their pace
+        // graph tiles by what one takes of a full compute unit (sweep_cost.h);
+        // cube tiles of fewer threads lie beside 1024-thread ones and run at a third of their pace
         // there (256 mixed jobs: 350 ms of the others' tiles, and 633 and 698 ms of the 512- and
         // 256-thread tiles with shares by their time alone)
-        work[i] += bit_kind(k) && per_cu[k] > 1 ? 1.5 * sum : sum / per_cu[k];
+        work[i] += graph_work[k] + (bit_kind(k) && per_cu[k] > 1 ? 1.5 * other_work[k] : other_work[k] / per_cu[k]);
         want[i] = std::max(want[i], (double)items[k].size() / per_cu[k]);
     }
     for (int i = 0; i < kQueues; ++i) {
@@ -995,7 +1006,10 @@ static double tile_us(const BJob &j, int rs, int *per_cu)
         *per_cu = bit_tiles_per_cu(j.P->bits, rs);
         return bit_sweep_us(*j.P, rs, rs, 1);
     }
-    if (j.kind != PBIT_BICLIQUE) return 2.5e-4 * j.N * rs;
+    if (j.kind != PBIT_BICLIQUE) {
+        *per_cu = byte_tiles_per_cu(j.N, rs, kByteTilesPerCu);
+        return graph_byte_tile_us(j.P->shape, rs, *per_cu);
+    }
     const double n = j.P->bq.na + j.P->bq.nb;
     return (1.0 + n / 128.0 * (0.47 + 1.8e-4 * n)) * (rs == 32 ? 1.0 : rs / 36.0);
 }
@@ -1005,7 +1019,8 @@ static double tile_us(const BJob &j, int rs, int *per_cu)
 // tile is sought: with each job in its widest tiles within the limit, the larger of that
 // limit and the work spread over the device is to be least.  For an eighth of the mixed bag
 // (32 jobs) that is 46 ms in tiles of 8 replicas for its 24^3 cubes, which alone took 78 ms
-// in tiles of 16. 
+// in tiles of 16.  A batch of 64 random graphs of 8 bonds a site, 40 % of them in byte tiles for a
+// site of more than 15 terms, takes 31 ms so, 38 with byte tiles of 16 replicas only.
 // Bicliques take tiles of 32 replicas: those of 64 need a tenth less work, but a launch of
 // their own beside three others ended later (101 against 79 ms).
 static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
@@ -1026,6 +1041,9 @@ static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
         if (j.bits) {
             for (int rs : {16, 8, 4})
                 if (rs == 4 || j.R > rs / 2) add(rs);
+        } else if (j.kind == PBIT_GRAPH) {
+            for (int rs : {16, 8, 4})
+                if (rs <= j.rs) add(rs);
         } else {
             add(j.kind == PBIT_BICLIQUE && j.mode == kTileInt8 ? 32 : j.rs);
         }

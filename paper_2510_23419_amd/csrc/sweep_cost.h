@@ -34,17 +34,37 @@ inline double chain_and_work(double chain, double work, double norm)
     return std::pow(std::pow(chain, norm) + std::pow(work, norm), 1.0 / norm);
 }
 
-// Microseconds of a sweep of Rp replicas in tiles of rs on `cus` compute units.
-inline double graph_bits_us(const GraphShape &g, const BitView &v, int rs, int Rp, int cus)
+// Microseconds of a sweep of one tile of rs replicas with `beside` of them on its compute unit.
+inline double graph_bit_tile_us(const GraphShape &g, int rs, int beside)
 {
     const int i = rs == 4 ? 0 : rs == 8 ? 1 : 2;
     static const double many[3] = {0.72, 0.845, 0.95}, two[3] = {0.46, 0.50, 0.54}, wide[3] = {0.48, 0.26, 0.24};
     static const double site[3] = {0.61e-3, 1.0e-3, 1.64e-3}, wide_site[3] = {1.33e-3, 2.95e-3, 6.2e-3};
-    const int tiles = (Rp + rs - 1) / rs, per_cu = bit_tiles_per_cu(v, rs);
-    const int rounds = (tiles + cus * per_cu - 1) / (cus * per_cu), beside = std::min(per_cu, (tiles + cus - 1) / cus);
     const double chain = g.groups * (g.groups == 2 ? two : many)[i] + g.wide_groups * wide[i];
     const double work = g.sites * site[i] + g.wide_sites * wide_site[i];
-    return rounds * chain_and_work(chain, work * (1 + 0.96 * (beside - 1)), 1.09);
+    return chain_and_work(chain, work * (1 + 0.96 * (beside - 1)), 1.09);
+}
+
+inline double graph_byte_tile_us(const GraphShape &g, int rs, int beside)
+{
+    const double chain = 0.41 * g.groups + (rs == 4 ? 0.0 : 0.166) * g.chunks + (rs == 4 ? 0.196 : 0.24) * g.steps;
+    const double work = (0.59e-3 * g.n + 0.112e-3 * g.ends + 1.72e-3 * g.eights) * (rs / 4);
+    return chain_and_work(chain, work * (1 + 0.064 * (beside - 1)), 1.21);
+}
+
+// Byte tiles a compute unit holds, of eight waves each: `most` by registers, and their rows' LDS.
+constexpr int kByteSlabsPerCu = 4, kByteTilesPerCu = 3;  // per-instance kernels (up to 49), batched kernel (71)
+inline int byte_tiles_per_cu(double n, int rs, int most)
+{
+    return std::max(1, std::min(most, (int)(160 * 1024 / (n * rs + 2304))));
+}
+
+// Microseconds of a sweep of Rp replicas in tiles of rs on `cus` compute units.
+inline double graph_bits_us(const GraphShape &g, const BitView &v, int rs, int Rp, int cus)
+{
+    const int tiles = (Rp + rs - 1) / rs, per_cu = bit_tiles_per_cu(v, rs);
+    const int rounds = (tiles + cus * per_cu - 1) / (cus * per_cu), beside = std::min(per_cu, (tiles + cus - 1) / cus);
+    return rounds * graph_bit_tile_us(g, rs, beside);
 }
 
 // Replicas per byte tile: the narrowest of 4, 8 and 16 that fits LDS and leaves at most two
@@ -64,11 +84,9 @@ inline int byte_pick_rs(int64_t n, int Rp, int cus, int forced)
 
 inline double graph_bytes_us(const GraphShape &g, int rs, int Rp, int cus)
 {
-    const int tiles = Rp / rs, per_cu = std::max(1, std::min(4, (int)(160 * 1024 / (g.n * rs + 2304))));
+    const int tiles = Rp / rs, per_cu = byte_tiles_per_cu(g.n, rs, kByteSlabsPerCu);
     const int rounds = (tiles + cus * per_cu - 1) / (cus * per_cu), beside = std::min(per_cu, (tiles + cus - 1) / cus);
-    const double chain = 0.41 * g.groups + (rs == 4 ? 0.0 : 0.166) * g.chunks + (rs == 4 ? 0.196 : 0.24) * g.steps;
-    const double work = (0.59e-3 * g.n + 0.112e-3 * g.ends + 1.72e-3 * g.eights) * (rs / 4);
-    return rounds * chain_and_work(chain, work * (1 + 0.064 * (beside - 1)), 1.21);
+    return rounds * graph_byte_tile_us(g, rs, beside);
 }
 
 // Whether a graph's sweeps are faster with its spins as bits than as bytes.  Over the shapes the

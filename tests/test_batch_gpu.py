@@ -440,3 +440,33 @@ def test_few_replicas_take_their_own_memory(R):
             out = pbit.pbit_anneal_batch(c.ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=2, init_spins=init)])[0]
             ref = oracle.anneal(graph_of(inst), beta, R, 2, init_spins=init)
             assert np.array_equal(out.spins, ref.spins) and np.array_equal(out.energies, ref.energies)
+
+
+@pytest.mark.parametrize("mix", [False, True])
+def test_byte_graphs_at_every_width_of_a_batch(ctx, mix):
+    """Graphs with a site of more than 15 terms (byte tiles), whose batches take narrower tiles where
+    the longest would end last, alone and beside graphs and cubes held as bits."""
+    jobs = []
+    for n, R, seed in [(300, 5, 1), (300, 100, 2), (2500, 300, 3), (9000, 40, 4), (30000, 9, 5)]:
+        rng = np.random.default_rng(seed)
+        hub, i = np.arange(1, 21, dtype=np.int32), np.arange(30, n - 1, dtype=np.int32)
+        inst = {"kind": "graph", "n": n, "bond_i": np.concatenate([0 * hub, i]), "bond_j": np.concatenate([hub, i + 1]),
+                "bond_J": rng.choice(np.array([-1, 1], np.int8), size=20 + i.size), "h": None}
+        jobs.append((inst, oracle.graph_from_bonds(n, inst["bond_i"], inst["bond_j"], inst["bond_J"], None), R, seed))
+    if mix:
+        inst = synth.random_sparse_graph(1500, 6, seed=6)
+        jobs.append((inst, oracle.graph_from_bonds(1500, inst["bond_i"], inst["bond_j"], inst["bond_J"], inst["h"]), 150, 6))
+        inst = synth.ea_instance(12, seed=7)
+        jobs.append((inst, graph_of(inst), 200, 7))
+    beta = synth.beta_geometric(0.1, 4.0, 25)
+    probs = [pbit.load_instance(ctx, j[0]) for j in jobs]
+    _say("byte graphs in a batch%s" % (", mixed" if mix else ""))
+    outs = pbit.pbit_anneal_batch(ctx, [dict(problem=p, beta=beta, n_replicas=R, seed=s)
+                                        for p, (_, _, R, s) in zip(probs, jobs)])
+    for p, (inst, g, R, s), out in zip(probs, jobs, outs):
+        for q in sorted({0, (R - 1) // 4}):
+            cnt = min(4, R - 4 * q)
+            ref = oracle.anneal(g, beta, cnt, s, replica_offset=4 * q)
+            assert np.array_equal(out.spins[4 * q:4 * q + cnt], ref.spins), (inst["kind"], R, q)
+            assert np.array_equal(out.energies[4 * q:4 * q + cnt], ref.energies)
+        pbit.pbit_unload_problem(ctx, p)
