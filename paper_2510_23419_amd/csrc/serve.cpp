@@ -301,6 +301,12 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
             s.tile_tuned[key] = pick;
         }
     }
+    // a job whose narrow tiles all fit its share of the device ends sooner in them: 300 x 300 with
+    // 100 replicas, served alone, takes 5.7 us a sweep in tiles of 32 and 11.5 in tiles of 64
+    if (P.kind == PBIT_BICLIQUE && j.mode == kTileInt8 && j.rs > 32) {
+        const int active = (int)(s.q.queue.size() + s.q.running.size());
+        if ((j.R + 31) / 32 <= compute_units(ctx) / (active + 1)) j.rs = 32;
+    }
     size_job(j);
     const bool check = j.d.has_target || j.d.trace_every > 0;
     j.chunk = check ? (j.d.trace_every > 0 ? j.d.trace_every : PBIT_CHECK_SWEEPS) : std::max(j.S, 1);
