@@ -1391,6 +1391,7 @@ static hipError_t sweeps(pbit_ctx *ctx, const Problem &P, DevState &ds, int s0, 
         if (e == hipSuccess) e = cluster_status(ds, st, &status);
         if (e != hipSuccess || status == 0) return e;
         if (status != 1) return hipErrorLaunchFailure;
+        if (timed) prof_drop(ctx);
         e = cluster_fallback(ctx, P, ds, s1 - s0, st);
         for (int s = s0; s < s1 && e == hipSuccess; s += ds.chunk)
             e = sweeps(ctx, P, ds, s, std::min(s1, s + ds.chunk), sweep0, rq0, key, st);
@@ -1822,6 +1823,14 @@ hipError_t prof_close(pbit_ctx *ctx, hipStream_t st)
     const int k = ctx->prof_open;
     ctx->prof_open = -1;
     return hipEventRecord(ctx->prof_pool[k + 1], st);
+}
+
+// Forgets the last window, closed: its launch ran no sweeps.
+void prof_drop(pbit_ctx *ctx)
+{
+    ctx->prof_kind.pop_back();
+    ctx->prof_launches.pop_back();
+    ctx->prof_used -= 2;
 }
 
 hipError_t prof_harvest(pbit_ctx *ctx)

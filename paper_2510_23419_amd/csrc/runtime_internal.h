@@ -118,6 +118,7 @@ int spins_in_range(const int8_t *s, size_t n);
 hipError_t prof_begin(pbit_ctx *ctx, int kind, hipStream_t st);
 hipError_t prof_count_launch(pbit_ctx *ctx, hipStream_t st);
 hipError_t prof_close(pbit_ctx *ctx, hipStream_t st);
+void prof_drop(pbit_ctx *ctx);
 hipError_t prof_harvest(pbit_ctx *ctx);
 void prof_release(pbit_ctx *ctx);
 int run_device(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d, int8_t *d_spins, bool spins_in,

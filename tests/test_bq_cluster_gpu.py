@@ -142,9 +142,7 @@ def test_exchange_memory_costs_no_budget():
     assert seen == {True, False}
 
 
-def test_workgroups_that_do_not_meet():
-    """A wait limit of zero: the workgroups leave before touching the spins, another kernel runs
-    the sweeps, and the next anneals do not try again."""
+def _impatient_context():
     old = os.environ.get("PBIT_BQ_MEET_US")
     os.environ["PBIT_BQ_MEET_US"] = "0"
     try:
@@ -154,6 +152,13 @@ def test_workgroups_that_do_not_meet():
             del os.environ["PBIT_BQ_MEET_US"]
         else:
             os.environ["PBIT_BQ_MEET_US"] = old
+    return c
+
+
+def test_workgroups_that_do_not_meet():
+    """A wait limit of zero: the workgroups leave before touching the spins, another kernel runs
+    the sweeps, and the next anneals do not try again."""
+    c = _impatient_context()
     try:
         for na, nb, R, S in [(300, 200, 40, 20), (520, 600, 70, 18), (64, 32, 8, 5), (1100, 700, 33, 16)]:
             inst = synth.biclique_instance(na, seed=na, nb=nb)
@@ -181,5 +186,19 @@ def test_static_scratch_takes_the_kernel_already_timed():
         assert pbit.pbit_profile_variant(c.ctx) == timed != CLUSTER
         ref = oracle.anneal(graph_of(inst), beta[:8], 4, 3)
         assert np.array_equal(spins[:4].cpu().numpy(), ref.spins)
+    finally:
+        c.close()
+
+
+def test_profile_counts_the_sweeps_that_ran():
+    """The window of a launch whose workgroups did not meet is no half-sweep's time."""
+    c = _impatient_context()
+    try:
+        prob = pbit.load_instance(c.ctx, synth.biclique_instance(300, seed=1, nb=200))
+        pbit.pbit_profile_enable(c.ctx, 1)
+        pbit.pbit_anneal(c.ctx, prob, synth.beta_linear(0.05, 2.0, 20), 40, 1)
+        assert pbit.pbit_profile_variant(c.ctx) == 4  # sweeps in LDS, one launch
+        ms, launches = pbit.pbit_profile_read(c.ctx, pbit.PBIT_BICLIQUE)
+        assert launches == 40 and ms > 0
     finally:
         c.close()
