@@ -1063,7 +1063,7 @@ static bool choose_cube(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc 
     if (ds.arena) {
         // no timing without allocation: the measured default, not cached
         ds.mfma = matrix && R <= 1024;
-        ds.bit_tiles = !ds.mfma && bits < cube_launch_us(P.N, R);
+        ds.bit_tiles = !ds.mfma && bits < cube_launch_us(P.N, R, matrix);
         return false;
     }
     auto it = ctx->ea_tuned.find(cube_key(P, R));
@@ -1104,18 +1104,16 @@ static int tune_cube(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d,
     const Key key{0u, 0u};
     const int prof = ctx->prof_every;
     ctx->prof_every = 0;
-    auto pass = [&](auto launch) {
-        float best = 0.f;
-        for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // the first warms up
-            float ms = 0.f;
+    auto pass = [&](int n, auto launch) {
+        float ms = 0.f;
+        for (int rep = n > 1 ? 1 : 0; rep < 2 && e == hipSuccess; ++rep) {  // one sweep first warms up
             e = hipEventRecord(e0, st);
-            if (e == hipSuccess) e = launch();
+            if (e == hipSuccess) e = launch(n);
             if (e == hipSuccess) e = hipEventRecord(e1, st);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-            if (rep == 1 || (rep > 1 && ms < best)) best = ms;
         }
-        return (double)best;
+        return (double)ms;
     };
     EaRow row;
     for (uint64_t &v : row.s) v = (uint64_t)1 << 31;
@@ -1128,7 +1126,7 @@ static int tune_cube(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d,
     };
     auto time_sweeps = [&](int p, int m, auto run) {
         double one = 0.0, more = 0.0;
-        time_runs([&](int n) { return pass([&] { return run(n); }); }, [] { return true; }, m, &one, &more);
+        time_runs([&](int n) { return pass(n, run); }, [] { return true; }, m, &one, &more);
         offer(p, m > 0 ? (more - one) / m : one);
     };
     auto half_sweeps = [&](int n, auto half) {
@@ -1175,7 +1173,8 @@ static int tune_graph(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d
     }
     constexpr int m = 8;
     const int bit_rs = bit_pick_rs(P, ds.Rp, cus);
-    if (ds.arena || d->n_sweeps <= m || d->n_sweeps * bit_sweep_us(P, ds.Rp, bit_rs, cus) < 3000.0) return PBIT_OK;
+    if (ds.arena || d->n_sweeps <= m || d->n_sweeps * bit_sweep_us(P, ds.Rp, bit_rs, cus) < kTimedAnnealUs)
+        return PBIT_OK;
     int rc = byte_energies(ctx, ds);
     if (rc) return rc;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1191,7 +1190,7 @@ static int tune_graph(pbit_ctx *ctx, const Problem &P, const pbit_anneal_desc *d
         if (bits) t.tile_rs = bit_rs;
         auto pass = [&](int n) {
             float best = 0.f;
-            for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // the first warms up
+            for (int rep = n > 1 ? 1 : 0; rep < 3 && e == hipSuccess; ++rep) {  // one sweep first warms up
                 float ms = 0.f;
                 e = hipEventRecord(e0, st);
                 if (e == hipSuccess) e = sweeps(ctx, P, t, 0, n, 0u, 0u, Key{0u, 0u}, st);

@@ -29,6 +29,10 @@ struct GraphShape {
     double n = 0, ends = 0, chunks = 0, steps = 0, eights = 0;
 };
 
+// Anneals shorter than this keep an estimate where longer ones time the forms (0.3 ms, once a
+// shape and context).
+constexpr double kTimedAnnealUs = 3000.0;
+
 inline double chain_and_work(double chain, double work, double norm)
 {
     return std::pow(std::pow(chain, norm) + std::pow(work, norm), 1.0 / norm);
@@ -116,20 +120,24 @@ inline double cube_bits_us(const BitView &v, int rs, int Rp, int cus)
 }
 
 // How a cube of more sites than always stay in LDS runs, given the cost of its best tiles: in
-// tiles, by the launch-per-half-sweep kernels, or as a timing of all of them says.  Those take 8 us +
-// 0.5 ps per spin and sweep at least and up to 2.2 times that (8.4 to 132 us from 8320 to 61 952
+// tiles, by the launch-per-half-sweep kernels, or as a timing of all of them says.  Those were
+// measured at 0.93 to 2.4 times 8 us + 0.5 ps per spin and sweep (8.4 to 132 us from 8320 to 61 952
 // sites and 16 to 4096 replicas: the stencil's launches of 128 replicas and more, and shapes without
 // matrix-core tiles, are far above the line), so the estimate decides only where the tiles need
-// less than 0.6 of that least or more than 2.5 times it.  Without matrix-core tiles, where no anneal
-// was timed before, it also decides for anneals of less than 3 ms.
+// less than 0.8 of that or more than 2.5 times it.  Without matrix-core tiles, where no anneal
+// was timed before, it also decides for short anneals.
 enum class CubeForm { Tiles, Launches, Time };
-inline double cube_launch_us(int64_t n, int R) { return 8.0 + 0.5e-6 * (double)n * R; }
+inline double cube_launch_us(int64_t n, int R, bool matrix_tiles)
+{
+    const double least = 8.0 + 0.5e-6 * (double)n * R;
+    return matrix_tiles || R < 128 ? least : std::max(least, 10.0 + 0.4e-3 * (double)n);
+}
 inline CubeForm cube_form(double tiles_us, int64_t n, int R, int sweeps, bool matrix_tiles)
 {
-    const double launches = cube_launch_us(n, R);
-    if (tiles_us < 0.6 * launches) return CubeForm::Tiles;
+    const double launches = cube_launch_us(n, R, matrix_tiles);
+    if (tiles_us < 0.8 * launches) return CubeForm::Tiles;
     if (tiles_us > 2.5 * launches) return CubeForm::Launches;
-    if (!matrix_tiles && sweeps * std::min(tiles_us, launches) < 3000.0)
+    if (!matrix_tiles && sweeps * std::min(tiles_us, launches) < kTimedAnnealUs)
         return tiles_us < launches ? CubeForm::Tiles : CubeForm::Launches;
     return CubeForm::Time;
 }

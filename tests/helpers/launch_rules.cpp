@@ -316,6 +316,9 @@ static void cube_forms()
         CHECK(cube_form(tiles, c.n, c.R, 2, false) != CubeForm::Time);
     }
     CHECK(timed >= 10);
+    // without matrix-core tiles and too short to time: the stencil takes 17.4 and 9.2 us a sweep of 26^3
+    CHECK(cube_form(11.2, 17576, 128, 100, false) == CubeForm::Tiles);
+    CHECK(cube_form(11.2, 17576, 64, 100, false) == CubeForm::Launches);
 }
 
 int main()
