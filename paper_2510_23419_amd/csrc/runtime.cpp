@@ -422,10 +422,15 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
             const size_t words = (size_t)bq_row_bytes(cols) / 4;
             out.assign((size_t)rows * words, 0u);
             for (int r = 0; r < rows; ++r)
-                for (int c = 0; c < cols; ++c) {
-                    const int v = M[(size_t)r * cols + c], j = c % 4;
-                    if (v != 0)
-                        out[r * words + (size_t)(c / 32) * 4 + j] |= (size[j] | (v < 0 ? 8u : 0u)) << (4 * (c % 32 / 4));
+                for (int c = 0; c < cols; c += 32) {
+                    const int8_t *m = &M[(size_t)r * cols + c];
+                    uint32_t w[4] = {0u, 0u, 0u, 0u};
+                    for (int i = 0; i < 8; ++i)
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t v = (uint32_t)(int32_t)m[4 * i + j];  // set and negative: bits 0 and 31
+                            w[j] |= ((size[j] & (0u - (v & 1u))) | (v >> 28 & 8u)) << (4 * i);
+                        }
+                    std::copy(w, w + 4, &out[r * words + (size_t)(c / 32) * 4]);
                 }
         };
         std::vector<uint32_t> J4, JT4;
@@ -457,11 +462,18 @@ static int load_biclique(pbit_ctx *ctx, const pbit_problem_desc *d, Problem &p)
         auto pack2 = [](const std::vector<int8_t> &M, int rows, int cols, uint32_t *out) {
             const int nku = cols / 64;
             for (int r = 0; r < rows; ++r)
-                for (int c = 0; c < cols; ++c) {
-                    const int v = M[(size_t)r * cols + c];
-                    const int blk = r / 32, l = r % 32, u = c / 64, g = (c / 32) % 2, i = (c / 4) % 8, j = c % 4;
-                    const uint32_t code = v == 0 ? 0u : v > 0 ? 2u : 10u;
-                    out[((((size_t)blk * nku + u) * 2 + g) * 32 + l) * 2 + j / 2] |= (code >> (j % 2)) << (4 * i);
+                for (int c = 0; c < cols; c += 32) {
+                    const int8_t *m = &M[(size_t)r * cols + c];
+                    uint32_t w[4] = {0u, 0u, 0u, 0u};
+                    for (int i = 0; i < 8; ++i)
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t v = (uint32_t)(int32_t)m[4 * i + j];
+                            w[j] |= ((v & 1u) << 1 | (v >> 28 & 8u)) << (4 * i);
+                        }
+                    const int blk = r / 32, l = r % 32, u = c / 64, g = (c / 32) % 2;
+                    uint32_t *to = out + ((((size_t)blk * nku + u) * 2 + g) * 32 + l) * 2;
+                    to[0] = w[0] | w[1] >> 1;
+                    to[1] = w[2] | w[3] >> 1;
                 }
         };
         pack2(J, na_p, nb_p, J2.data());
