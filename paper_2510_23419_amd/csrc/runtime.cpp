@@ -258,23 +258,30 @@ static int upload(pbit_ctx *ctx, Problem &p, const void *host, size_t bytes, voi
 // arrays, which it does without where they do not fit (per-instance anneals have other paths).
 static int upload_bits(pbit_ctx *ctx, Problem &p, const BitHost &b, const int8_t *dev_h)
 {
-    void *dg = nullptr, *dr = nullptr, *dw = nullptr, *dp = nullptr;
+    // groups, records, wide records and sites in one array, each from a multiple of 16 bytes on
+    size_t at[5] = {0};
+    const size_t sizes[4] = {sizeof(int32_t) * b.groups.size(), sizeof(uint32_t) * b.rec.size(),
+                             sizeof(uint32_t) * b.wide.size(), sizeof(uint16_t) * b.pos_site.size()};
+    for (int k = 0; k < 4; ++k) at[k + 1] = at[k] + (sizes[k] + 15) / 16 * 16;
+    std::vector<uint8_t> all(at[4]);
+    const void *from[4] = {b.groups.data(), b.rec.data(), b.wide.data(), b.pos_site.data()};
+    for (int k = 0; k < 4; ++k)
+        if (sizes[k]) std::memcpy(all.data() + at[k], from[k], sizes[k]);
+    void *dev = nullptr;
     const size_t before = p.allocs.size();
     int rc;
     {
         const KeepError keep;
-        rc = upload(ctx, p, b.groups.data(), sizeof(int32_t) * b.groups.size(), &dg);
-        if (rc == PBIT_OK) rc = upload(ctx, p, b.rec.data(), sizeof(uint32_t) * b.rec.size(), &dr);
-        if (rc == PBIT_OK && !b.wide.empty()) rc = upload(ctx, p, b.wide.data(), sizeof(uint32_t) * b.wide.size(), &dw);
-        if (rc == PBIT_OK) rc = upload(ctx, p, b.pos_site.data(), sizeof(uint16_t) * b.pos_site.size(), &dp);
+        rc = upload(ctx, p, all.data(), all.size(), &dev);
     }
     if (rc == PBIT_E_NOMEM) {
         for (; p.allocs.size() > before; p.allocs.pop_back()) dev_free(ctx, p.allocs.back());
         return PBIT_OK;
     }
     if (rc != PBIT_OK) return fail(rc, "site records: HIP error; context poisoned");
-    p.bits = BitView{b.form, b.n, b.n_pos, b.n_groups, b.n_pairs, b.n_wide, b.max_pairs, (const int4 *)dg,
-                     (const uint4 *)dr, (const uint4 *)dw, (const uint16_t *)dp, dev_h};
+    const uint8_t *d = (const uint8_t *)dev;
+    p.bits = BitView{b.form, b.n, b.n_pos, b.n_groups, b.n_pairs, b.n_wide, b.max_pairs, (const int4 *)(d + at[0]),
+                     (const uint4 *)(d + at[1]), (const uint4 *)(d + at[2]), (const uint16_t *)(d + at[3]), dev_h};
     return PBIT_OK;
 }
 

@@ -2,6 +2,8 @@
 loops end: K steps of 64 sites in every remainder of a ring of four, site blocks that fill no
 wave and more than the 16 waves, ragged sides, replicas past one tile, threshold rows past the
 16 held at a time, given spins, and fields at their largest."""
+import os
+
 import numpy as np
 import pytest
 
@@ -57,3 +59,36 @@ def test_largest_fields_are_exact(ctx, n):
     pbit.pbit_unload_problem(ctx, prob)
     for got in outs:
         assert np.array_equal(got.spins, ref.spins) and np.array_equal(got.energies, ref.energies)
+
+
+def test_longest_side_of_the_bit_kernel_is_exact():
+    """128 x 524160, the longest side the FP4 bit kernel takes.  Partial sums reach 524160, the most that
+    can cancel to a field whose decision is open (the float accumulators are exact to 2^20), and the
+    fields of some hundreds that are left have to decide as in the int8 kernel with int32 sums."""
+    na, nb, R = 128, 524160, 8
+    rng = np.random.default_rng(1)
+    J = np.ones((na, nb), np.int8)
+    J[:, nb // 2:] = -1
+    J[rng.random((na, nb), dtype=np.float32) < 2e-4] = 0
+    spins = np.full((R, na + nb), -1, np.int8)
+    spins[rng.random((R, na + nb), dtype=np.float32) < 5e-4] = 1
+    inst = {"kind": "biclique", "dims": (na, nb), "J": J, "h": None}
+    got = {}
+    for variant in ("3", "2"):
+        old = os.environ.get("PBIT_BQ_VARIANT")
+        os.environ["PBIT_BQ_VARIANT"] = variant
+        try:
+            c = pbit.Context(0)
+        finally:
+            if old is None:
+                del os.environ["PBIT_BQ_VARIANT"]
+            else:
+                os.environ["PBIT_BQ_VARIANT"] = old
+        print("longest side, kernel", variant, flush=True)
+        with c:
+            out = pbit.pbit_anneal(c.ctx, pbit.load_instance(c.ctx, inst), [0.006, 0.006], R, 3, init_spins=spins)
+            assert pbit.pbit_profile_variant(c.ctx) == int(variant)
+            got[variant] = (out.spins, out.energies)
+    field = J.sum(1, dtype=np.int64)  # of spins +1; the fields that decide are far below the partial sums
+    assert np.abs(field).max() < 2000
+    assert np.array_equal(got["3"][0], got["2"][0]) and np.array_equal(got["3"][1], got["2"][1])
