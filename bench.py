@@ -196,9 +196,9 @@ def measured_traffic(workload, kernel=None):
 
 
 def _bag_dtype():
-    """Data of the batched tiles: int8 spins and couplings (cubes as bits, biclique fields
-    as exact FP4 MFMA products)."""
-    return "int8"
+    """Arithmetic of the batched tiles: cube fields counted on spin bits, biclique fields as FP4
+    MFMA products of spins and couplings in {-1, 0, 1}; both exact."""
+    return "bits (cubes), fp4 (bicliques), exact"
 
 
 def mixed_bag_bench(args, pbit, torch):

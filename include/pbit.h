@@ -224,7 +224,7 @@ int pbit_energy(pbit_ctx *ctx, uint64_t problem, const int8_t *spins, int32_t R,
  * need each other, and every workgroup keeps taking (job, tile, sweep range)
  * items from a device queue with its tile's spins held in LDS.  Results are
  * identical to pbit_anneal for the same job, whatever it is batched with.
- * Batched jobs need a cube or a general graph of at most 38,912 spins (a
+ * Batched jobs need a cube or a general graph of at most 39,936 spins (a
  * 4-replica tile in LDS) or a biclique with na_p + nb_p <= 4,096 padded sites
  * (E_UNSUPPORTED otherwise).  When a job
  * has a target or a trace, its energies are checked every trace_every sweeps,
@@ -246,8 +246,11 @@ typedef struct {
  * keeps the size whose tiles cost the least device time per job; the choice is
  * cached per (problem kind, sides or spins, threshold width, replicas rounded up
  * to a power of two, operand mode).  PBIT_TILE_TUNE=0 at context creation keeps
- * the fixed rule (the widest tile the replicas fill).  Results do not depend on
- * the tile size.  Writes the number of timings run and of cached shapes. */
+ * the fixed rule (the widest tile the replicas fill).  pbit_anneal_batch then sizes the
+ * tiles for the batch: cubes and graphs so that the longest tile and the work of the
+ * whole batch end together, bicliques in 32 replicas (a launch of wider tiles beside
+ * the others ended later), and a served biclique takes 32 where all its tiles fit its
+ * share of the device.  Results do not depend on the tile size.  Writes the number of timings run and of cached shapes. */
 int pbit_profile_tiles(pbit_ctx *ctx, int64_t *tunings, int32_t *shapes);
 
 /* Run all jobs and wait for them.  A job whose device memory does not fit the
@@ -351,10 +354,11 @@ int pbit_profile_ea_path(pbit_ctx *ctx, int32_t *path);
  * any): 1 = one launch per colour class (every site of the class, 16 replicas per
  * thread); 2 = the whole graph for a tile of 16, 8 or 4 replicas held in one
  * workgroup's LDS for runs of up to 1000 sweeps per launch, taken for graphs of at
- * most 39 936 spins: as bits where every spin has at most 15 nonzero couplings and
- * fields, with the tile width of least measured cost, else as bytes, with the
+ * most 39 936 spins: as bits, with the tile width of least cost, or as bytes, with the
  * narrowest tile that fits and leaves at most two workgroups per compute unit (else
- * the widest that fits).  When the context is created, PBIT_GRAPH_SLAB=0 keeps path 1
+ * the widest that fits).  Bits need every spin to have at most 15 nonzero couplings and
+ * fields, and are taken by the estimated cost of both forms, which the first anneal of
+ * 3 ms or more of a shape times where they are close.  When the context is created, PBIT_GRAPH_SLAB=0 keeps path 1
  * and PBIT_GRAPH_SLAB=4, 8 or 16 forces that tile width where it fits.  Both paths
  * give the same spins.  *path is written on success only. */
 int pbit_profile_graph_path(pbit_ctx *ctx, int32_t *path);

@@ -66,7 +66,7 @@ constexpr int bq_tile_rows(int width) { return width >= 4096 ? 1 : width <= 256 
 hipError_t bit_tiles(const BitJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter,
                      int grid, int threads, size_t lds_bytes, hipStream_t st);
 // operand modes of the biclique tiles
-constexpr int kTileInt8 = 0, kTileBits = 2;
+constexpr int kTileFp4 = 0, kTileBits = 2;
 hipError_t bq_tiles(const BqJobDev *jobs, const WorkItem *items, const int32_t *n_items, int32_t *counter,
                     int rs, int mode, int grid, size_t lds_bytes, hipStream_t st);
 

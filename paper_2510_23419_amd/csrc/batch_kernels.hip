@@ -692,7 +692,7 @@ hipError_t bq_tiles(const BqJobDev *jobs, const WorkItem *items, const int32_t *
 #define PBIT_BQ_TILES(K, THREADS, ...)                                                                             \
     hipLaunchKernelGGL(K, dim3((unsigned)grid), dim3(THREADS), lds_bytes, st, jobs, items, n_items, counter, ##__VA_ARGS__)
     const int rb = rs == 128 ? 4 : rs == 64 ? 2 : rs == 32 ? 1 : 0;
-    if (rb == 0 || (mode != kTileInt8 && mode != kTileBits)) return hipErrorInvalidValue;
+    if (rb == 0 || (mode != kTileFp4 && mode != kTileBits)) return hipErrorInvalidValue;
     if (mode == kTileBits) {
         if (rb == 4) PBIT_BQ_TILES((k_bq_tiles_bits<4>), kBqTileThreads, 1u);
         else if (rb == 2) PBIT_BQ_TILES((k_bq_tiles_bits<2>), kBqTileThreads, 1u);

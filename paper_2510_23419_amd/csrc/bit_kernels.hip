@@ -3,8 +3,9 @@
 //
 // Bound: the vector ALU.  A pair of a dense cube costs 413 vector instructions for its 32
 // updates (12.9 per update: 8.6 of them Philox, 2 the decision and its storing, the rest
-// the field, the table index and addresses; the byte rows this replaces took 16.4), and
-// at 32^3 x 4096 replicas they issue at 90 % of the 2.4 GHz peak.  Two bytes per site
+// the field, the table index and addresses) and 13.8 with what a sweep does beside them, by the
+// counters (the byte rows this replaces took 16.4), and at 32^3 x 4096 replicas they issue at 94 %
+// of the 2.4 GHz peak.  Two bytes per site
 // hold 16 replicas of 32^3 in 64 KiB, so that cube runs without a launch or any memory
 // traffic per sweep.  Small problems are bound by the latency of a half-sweep (about
 // 0.45 us: one Philox block, two dependent LDS reads and a barrier), which is why groups

@@ -91,7 +91,8 @@ hipError_t bq_halfsweep(const BqView &p, int side, int8_t *MA, int8_t *MB, int R
 hipError_t bq_energy(const BqView &p, const int8_t *MA, const int8_t *MB, int R, int Rp, int32_t *E, hipStream_t st);
 
 // ---- the same with spins held as bits (set = -1), 32 sites per word, by blocks of 128 sites:
-// word w of replica r at ((w / 4) Rp + r) 4 + w % 4 of MAb (na_p / 32 words per replica) or MBb
+// word w of replica r at ((w / 4) Rp + r) 4 + (w % 2) 2 + (w / 2) % 2 of MAb (na_p / 32 words per
+// replica) or MBb
 bool bqb_supported(const BqView &p, int Rp);
 hipError_t bqb_pack(const BqView &p, const int8_t *MA, const int8_t *MB, uint32_t *MAb, uint32_t *MBb, int Rp,
                     hipStream_t st);

@@ -24,8 +24,10 @@
 //   1024 x 1024, 1024 replicas   13.3 ->  3.8 (4.4 with int8 operands)
 //   1024 x 1024, 16 replicas     21.5 ->  3.7
 //    512 x 512, 1024 replicas     4.5 ->  3.3; below 256 sites the LDS-resident form wins
-// Stores with agent scope, which the protocol does not need inside one L2, made 1024 x 1024
-// 9.2 us; threshold rows loaded every sweep instead of 16 at a time, and a table of carry
+// Words and flags are stored at workgroup scope and read, by other workgroups of the XCD, at agent
+// scope.  That is this machine's guarantee, not the language's: a gfx950 compute unit writes stores
+// of that scope through to the L2 that the whole XCD shares (vmcnt counts them there), and the
+// loads bypass the reader's own cache.  Stores with agent scope made 1024 x 1024 9.2 us; threshold rows loaded every sweep instead of 16 at a time, and a table of carry
 // words rebuilt every sweep instead of the rows themselves, cost 0.5 and 0.3 us.
 //
 // The workgroups have to be resident together, and spread evenly over the XCDs: they

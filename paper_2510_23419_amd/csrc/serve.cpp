@@ -60,7 +60,7 @@ struct BJob : SchedJob {
     std::vector<uint32_t> table;  // threshold rows built ahead of admission (batch calls), else empty
     int kind = 0, N = 0, R = 0, S = 0;
     int rs = 4, tiles = 0, width = 1, chunk = 1;
-    int mode = kTileInt8;  // biclique tile states: int8 spins (default) or spin bits
+    int mode = kTileFp4;  // biclique tiles: int8 spins in HBM, four bits in LDS (default), or spin bits
     bool bits = false;     // cube or graph tiles hold their spins as bits
     // device memory (released when the job finishes)
     void *d_table = nullptr, *d_state = nullptr, *d_energy = nullptr;
@@ -177,13 +177,13 @@ static int bq_row_bytes(const BJob &j)
     return j.mode == kTileBits ? n / 8 : n;
 }
 
-// Mode of a context's biclique tiles: int8 spins, run on the FP4 matrix cores, unless the
-// bit variant is forced (int8 MFMAs on widened bits, up to 128 replicas a tile): half the
-// matrix time and a quarter of the coupling bytes make the first the faster one.
+// Mode of a context's biclique tiles: spins as four-bit numbers in LDS (int8 in HBM) against
+// two-bit couplings, unless the bit variant is forced (bits in both, up to 128 replicas a tile, against
+// four-bit couplings): half the coupling bytes and smaller tiles make the first the faster one.
 static int tile_mode(const pbit_ctx *ctx)
 {
     if (ctx->bq_forced == BqVariant::Bits) return kTileBits;
-    return kTileInt8;
+    return kTileFp4;
 }
 
 // Replicas of a bit job's state, an [N][stride] matrix of bytes (the per-instance layout): those
@@ -303,7 +303,7 @@ static int plan_job(pbit_ctx *ctx, ServeState &s, BJob &j)
     }
     // a job whose narrow tiles all fit its share of the device ends sooner in them: 300 x 300 with
     // 100 replicas, served alone, takes 5.7 us a sweep in tiles of 32 and 11.5 in tiles of 64
-    if (P.kind == PBIT_BICLIQUE && j.mode == kTileInt8 && j.rs > 32) {
+    if (P.kind == PBIT_BICLIQUE && j.mode == kTileFp4 && j.rs > 32) {
         const int active = (int)(s.q.queue.size() + s.q.running.size());
         if ((j.R + 31) / 32 <= compute_units(ctx) / (active + 1)) j.rs = 32;
     }
@@ -605,7 +605,8 @@ static int launch_round(pbit_ctx *ctx, ServeState &s, const std::vector<BJob *> 
     if (all_want > cus) {
         // streams that want an eighth or less get it all (their tiles share compute units with
         // others and run at half speed or less there, so a small share would end last), the
-        // rest share what is left
+        // rest share what is left (a fifth to a sixteenth makes no difference beyond the noise on those
+        // bags, nor do 1.0 to 2.2 for the 1.5 above; 256 mixed jobs took 758 ms with 1.0)
         double left = cus;
         bool full[kQueues] = {};
         for (int i = 0; i < kQueues; ++i)
@@ -1051,7 +1052,7 @@ static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
             for (int rs : {16, 8, 4})
                 if (rs <= j.rs) add(rs);
         } else {
-            add(j.kind == PBIT_BICLIQUE && j.mode == kTileInt8 ? 32 : j.rs);
+            add(j.kind == PBIT_BICLIQUE && j.mode == kTileFp4 ? 32 : j.rs);
         }
         longest = std::max(longest, options[q][0].us);
     }
@@ -1069,7 +1070,9 @@ static void share_device(pbit_ctx *ctx, const std::vector<BJob *> &js)
             load += o.load;
             last = std::max(last, o.us);
         }
-        const double ends = std::max(last, load / (0.8 * cus));  // tiles of several lengths do not pack fully
+        // tiles of several lengths do not pack fully (0.65 to 1.0 here end within 5 % of each other on
+        // eleven bags of cubes, bicliques, graphs and all three)
+        const double ends = std::max(last, load / (0.8 * cus));
         if (best == 0.0 || ends < best) {
             best = ends;
             best_limit = limit;
